@@ -84,9 +84,10 @@ int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K, int32_t *
                     void *ws, size_t ws_bytes, int32_t *dev_status, void *stream);
 
 /* knn_graph_build_plan -- how knn_graph_build divides the linear search of Section 3.2.2 when it computes every
- * similarity once and uses it for both rows of the pair (large C; D = 128, 256 or 512; K <= 64).  Host-only, no GPU
- * work; for tests and tools.
- *   n_workgroups [1]   out (host): workgroups of that pass, 0 when this problem takes the plain pass
+ * similarity once and uses it for both rows of the pair (C >= 6,144; D = 128, 256 or 512; K <= 64).  Host-only, no GPU
+ * work; for tests and tools.  (Problems of less than 15 million elements of W have such a division too, but the build
+ * passes all rows by all blocks there, which is faster; a large share may be carried out by several workgroups.)
+ *   n_workgroups [1]   out (host): shares of that pass, 0 when this problem has no such division
  *   out          [12]  out (host), may be NULL: for `workgroup` in [0, *n_workgroups):
  *                      [0] its block of 256 resident rows (rows 256 b .. 256 b + 255), or -1: none;
  *                      [1 + 2 p], [2 + 2 p], p = 0..4: streamed rows [first, end) of its five ranges (end <= first:

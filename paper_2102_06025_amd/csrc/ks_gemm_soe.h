@@ -27,8 +27,12 @@
 #include <type_traits>
 #include "ks_gemm_async.h"
 
-template <int KT_, int CH_, int STAGES_, int KSUB_ = 1> struct KsSoe {
+// RAGGED: the depth is 64 * KT - 32 (D an odd multiple of 32).  The second half of the last k-tile is then no data: the
+// lanes that would fetch it fetch the first half of the same rows again (in bounds, finite), and the resident fragments
+// of those k-steps are zero.
+template <int KT_, int CH_, int STAGES_, int KSUB_ = 1, bool RAGGED_ = false> struct KsSoe {
     static constexpr int KT = KT_, STAGES = STAGES_, KSUB = KSUB_;
+    static constexpr bool RAGGED = RAGGED_;
     static constexpr int NW = 8, NT = 512, CH = CH_, RES = 256;
     static constexpr int FM = CH / 32;
     static constexpr int LW = 4;       // wavefronts that issue the stream loads: 0..3, one per SIMD (see the sweep)
@@ -92,6 +96,17 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
         static_assert(CFG::LDS_ELEMS >= 2 * CFG::RES * 64, "the stream stages double as staging for the resident block");
         KsARows<CFG::RES, CFG::NW> rr;
         rr.init(R, ldr, nullptr, r_row0, r_limit);
+        // the last k-tile of a ragged depth: chunks 4..7 of its rows are redirected to chunks 0..3
+        auto res_issue = [&](int kt, uint16_t *dst) __attribute__((always_inline)) {
+            if (CFG::RAGGED && kt == KT - 1) {
+#pragma unroll
+                for (int j = 0; j < KsARows<CFG::RES, CFG::NW>::NI; ++j) {
+                    const int row = (j * CFG::NW + wave) * 8 + (lane >> 3);
+                    if (((lane & 7) ^ ((row >> 1) & 7)) >= 4) rr.ptr[j] -= 32;
+                }
+            }
+            rr.issue(kt * 64, dst);
+        };
         const int r31 = lane & 31, khalf = lane >> 5, swz = (lane >> 1) & 7;
         // up to four k-tiles in flight (the stream stages hold that many 256-row tiles): one memory round trip for the
         // first four instead of one per k-tile
@@ -99,7 +114,7 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
         constexpr int RNI = KsARows<CFG::RES, CFG::NW>::NI;
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            if (s < KT) rr.issue(s * 64, lds + s * CFG::RES * 64);
+            if (s < KT) res_issue(s, lds + s * CFG::RES * 64);
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) {
             const int issued_tiles = (NS + (kt > 0 ? kt - 1 : 0)) < KT ? (NS + (kt > 0 ? kt - 1 : 0)) : KT;
@@ -110,11 +125,13 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
             else ks_wait_vmcnt<0>();
             __builtin_amdgcn_s_waitcnt(0xC07F); // the fragment reads of k-tile kt-1 have returned: its slot may be reused
             ks_barrier_nofence();               // k-tile kt is in LDS
-            if (kt > 0 && kt - 1 + NS < KT) rr.issue((kt - 1 + NS) * 64, lds + ((kt - 1) % NS) * CFG::RES * 64);
+            if (kt > 0 && kt - 1 + NS < KT) res_issue(kt - 1 + NS, lds + ((kt - 1) % NS) * CFG::RES * 64);
             const uint16_t *st = lds + (kt % NS) * CFG::RES * 64;
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                bres[kt * 4 + kk] = *(const bf16x8_t *)(st + (wave * 32 + r31) * 64 + (((kk * 2 + khalf) ^ swz) * 8));
+            for (int kk = 0; kk < 4; ++kk) {
+                if (CFG::RAGGED && kt == KT - 1 && kk >= 2) bres[kt * 4 + kk] = bf16x8_t{};
+                else bres[kt * 4 + kk] = *(const bf16x8_t *)(st + (wave * 32 + r31) * 64 + (((kk * 2 + khalf) ^ swz) * 8));
+            }
         }
     }
 
@@ -137,6 +154,9 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
     __builtin_amdgcn_s_waitcnt(0xC07F); // the fragment reads have returned before the stages are reused
     __syncthreads();                    // (also publishes the gather list)
     const bool loader = wave < CFG::LW;
+    // (the chunk of a row that a lane fetches is the same for all its rows: they lie 32 apart)
+    static_assert(CFG::LW == 4, "rows of a lane 32 apart");
+    const int tail_back = (CFG::RAGGED && ((lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7)) >= 4) ? 32 : 0;
     const uint16_t *ptr[NI]; // row pointers (k = 0, swizzled chunk) of the chunk being issued (loading wavefronts)
     // (table entries are read one chunk before they are needed, on the issue side and on the compute side: the wait for
     // a scalar load at the point of use would sit in the middle of the stream)
@@ -164,11 +184,14 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
         uint16_t *st = lds + is_stage * CFG::STAGE_ELEMS;
         if (loader) {
 #pragma unroll
-            for (int u = 0; u < CFG::KSUB; ++u)
+            for (int u = 0; u < CFG::KSUB; ++u) {
+                int koff = (is_kt + u) * 64;
+                if (CFG::RAGGED && is_kt + u == KT - 1) koff -= tail_back;
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
-                    __builtin_amdgcn_global_load_lds(KS_GPTR(ptr[j] + (is_kt + u) * 64),
+                    __builtin_amdgcn_global_load_lds(KS_GPTR(ptr[j] + koff),
                                                      KS_LPTR(st + u * CFG::CH * 64 + (j * CFG::LW + wave) * 8 * 64), 16, 0, 0);
+            }
         }
         ++issued;
         if (++is_stage == ST) is_stage = 0;

@@ -1,17 +1,19 @@
 // Exact KNN graph of the class-weight rows (paper Section 3.2.2: linear search with inner-product
 // similarity; 16-bit matrix-core pass that recalls k' > K candidates, then an exact re-rank).
 //
-//   prepare   bf16 copy of W when the input is fp32; row norms and their maximum (for the error bound)
-//   recall    each workgroup owns a block of rows (256 in the sweep kernel) and passes all rows of W by them: bf16
-//             MFMA tiles of similarities; an element that beats its row's threshold is appended to that row's candidate
-//             buffer; a full buffer is cut back to its k' best by a wavefront (a bitwise search for the
-//             k'-th largest key), which also raises the threshold.  The C x C similarities are never stored.
-//             Large problems (D = 128, 256, 512, K <= 64) take the variant that computes every similarity once and
-//             uses it for both rows of the pair, with thresholds fixed beforehand from a sample of the rows (gr_sym_*).
-//   re-rank   one wavefront per row: canonical fp64 similarity of the k' candidates, exact order
-//             (similarity descending, id ascending), first K written out.  The row is certified when
-//             the K-th exact similarity exceeds the recall threshold by more than the error bound of the
-//             matrix-core pass; otherwise the row goes to the exhaustive list.
+//   prepare   bf16 copy of W when the input is fp32; row norms and their maximum (for the error bound); the sampled rows
+//   threshold (K <= 64, D <= 512) per row the 8th, 10th or 12th largest similarity to a sample of one in 32 of the searched rows: what lies below
+//             it is not recalled.  Some 256 to 384 rows lie above it, whatever the data (an order statistic).
+//   recall    each workgroup keeps a block of 256 rows resident and streams rows of W by them: bf16 MFMA tiles of
+//             similarities; an element above its row's threshold is appended to one of the row's candidate segments.
+//             The C x C similarities are never stored.  Small problems cut the streamed rows into parts so that every
+//             compute unit has work.  Large problems (D = 128, 256, 512) take the variant that computes every similarity
+//             once and uses it for both rows of the pair (gr_sym_*).  K > 64 or D > 512: a running threshold per row
+//             instead of the sample's (a full candidate buffer is cut back to its k' best).
+//   rank      one wavefront per row: the candidates that can be among the K best by the error bound (a bitwise search for
+//             the K-th key), their canonical fp64 similarities, exact order (similarity descending, id ascending), first K written out.  The row is
+//             certified when the K-th exact similarity exceeds the largest dropped one by more than the error bound of
+//             the matrix-core pass; otherwise it is ranked again over all its candidates, and failing that goes to
 //   exhaustive  uncertified rows are searched over all C columns in canonical fp64 arithmetic.
 // Every decision that reaches the output is taken on the canonical fp64 similarity, so the lists are
 // exact and do not depend on scheduling.
@@ -75,48 +77,125 @@ template <> struct GrElem<float> {
     static __device__ __forceinline__ float f(float v) { return v; }
 };
 
-// one wavefront per row: squared norm in fp32 (only used for the error bound, with slack), optional bf16 copy
+// One pass over the rows of up to two matrices (a hop has two): norms in fp32 (only used for the error bound, with
+// slack), their maximum per workgroup, the bf16 copy of fp32 rows, the copy of the sampled rows; and the counters of the
+// later kernels are cleared.  HBM-bound.  A row is read by as many lanes as it has 16-byte pieces (a wavefront reads four
+// rows of 128 bf16 at once), four row groups in flight per wavefront.  The maximum goes to memory once per workgroup: an
+// atomic per row on one address serialised in the L2 (10,000 x 128 fp32: 53 us; 390,625 x 512 bf16: 232 us).
+#define GR_PREP_BLOCKS 1024
+struct GrPrepJob {
+    const void *W;
+    int64_t C;
+    uint16_t *Wb;    // bf16 copy, or nullptr
+    float *norms;    // [C], or nullptr
+    float *blockmax; // largest norm seen by each of this job's workgroups
+    uint16_t *Ws;    // [n_sample, D] rows picked by gr_sample_row, or nullptr
+    int64_t n_sample;
+    int blocks;
+};
+struct GrClear {
+    int32_t *fb_count, *second_count, *logcnt;
+    int nlog;
+    float *thf; // thresholds of the padding rows [pad0, pad1): nothing passes
+    int64_t pad0, pad1;
+};
+#define GR_SYM_RATIO 32          /* rows of W per sampled row */
+// rows sampled: one of every 32 consecutive rows, at a position that varies from one run of 32 rows to the next
+__device__ __forceinline__ int64_t gr_sample_row(int64_t s) {
+    return s * GR_SYM_RATIO + (int64_t)(((uint32_t)s * 2654435761u) >> 16) % GR_SYM_RATIO;
+}
 template <typename IN>
 __global__ void __launch_bounds__(GR_NT)
-gr_prepare_kernel(const IN *__restrict__ W, int64_t C, int D, uint16_t *__restrict__ Wb, float *__restrict__ norms,
-                  uint32_t *maxnorm_bits) {
-    const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + (threadIdx.x >> 6);
-    if (i >= C) return;
-    const int lane = threadIdx.x & 63;
-    float s = 0.f;
-    if (sizeof(IN) == 2 && D % 8 == 0) { // 16-byte loads (the sum is only used for the error bound, with slack)
-        for (int d = lane * 8; d < D; d += 512) {
-            const uint4 v = *(const uint4 *)((const uint16_t *)W + i * D + d);
-            const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float lo = __uint_as_float(w4[e] << 16), hi = __uint_as_float(w4[e] & 0xFFFF0000u);
-                s = fmaf(lo, lo, s);
-                s = fmaf(hi, hi, s);
-            }
-            if (Wb) *(uint4 *)(Wb + i * D + d) = v;
+gr_prepare_kernel(GrPrepJob job0, GrPrepJob job1, int D, GrClear clr) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            *clr.fb_count = 0;
+            if (clr.second_count) *clr.second_count = 0;
         }
-    } else {
-        for (int d = lane; d < D; d += 64) {
-            float v = GrElem<IN>::f(W[i * D + d]);
-            s += v * v;
-            if (Wb) Wb[i * D + d] = (uint16_t)ks_f2bf(v);
+        for (int q = threadIdx.x; q < clr.nlog; q += GR_NT) clr.logcnt[q] = 0;
+        for (int64_t q = clr.pad0 + threadIdx.x; q < clr.pad1; q += GR_NT) clr.thf[q] = INFINITY;
+    }
+    const bool second = (int)blockIdx.x >= job0.blocks;
+    const GrPrepJob job = second ? job1 : job0;
+    const int bid = second ? (int)blockIdx.x - job0.blocks : (int)blockIdx.x;
+    constexpr int EPL = 16 / sizeof(IN), U = 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int lpr = 64; // lanes per row
+    while (lpr > 4 && (lpr >> 1) * EPL >= D) lpr >>= 1;
+    const int l = lane & (lpr - 1), rpw = 64 / lpr;
+    const int64_t stride = (int64_t)job.blocks * (GR_NT / 64) * rpw;
+    const IN *__restrict__ W = (const IN *)job.W;
+    float mx = 0.f;
+    for (int64_t i0 = ((int64_t)bid * (GR_NT / 64) + wave) * rpw + lane / lpr; i0 < job.C; i0 += U * stride) {
+        float s[U];
+        bool pick[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + u * stride;
+            s[u] = 0.f;
+            const int64_t sm = i / GR_SYM_RATIO;
+            pick[u] = job.Ws && sm < job.n_sample && gr_sample_row(sm) == i;
+        }
+        for (int d = l * EPL; d < D; d += lpr * EPL) {
+            uint4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = i0 + u * stride;
+                v[u] = i < job.C ? *(const uint4 *)(W + i * D + d) : make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = i0 + u * stride;
+                if (i >= job.C) continue;
+                const uint32_t w4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                if (sizeof(IN) == 2) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float lo = __uint_as_float(w4[e] << 16), hi = __uint_as_float(w4[e] & 0xFFFF0000u);
+                        s[u] = fmaf(lo, lo, s[u]);
+                        s[u] = fmaf(hi, hi, s[u]);
+                    }
+                    if (pick[u]) *(uint4 *)(job.Ws + (i / GR_SYM_RATIO) * D + d) = v[u];
+                } else {
+                    float f[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        f[e] = __uint_as_float(w4[e]);
+                        s[u] = fmaf(f[e], f[e], s[u]);
+                    }
+                    const uint2 b = make_uint2(ks_pack_bf2(f[0], f[1]), ks_pack_bf2(f[2], f[3]));
+                    *(uint2 *)(job.Wb + i * D + d) = b;
+                    if (pick[u]) *(uint2 *)(job.Ws + (i / GR_SYM_RATIO) * D + d) = b;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + u * stride;
+            for (int o = 1; o < lpr; o <<= 1) s[u] += __shfl_xor(s[u], o, 64);
+            const float nrm = sqrtf(s[u]);
+            mx = fmaxf(mx, nrm);
+            if (i < job.C && l == 0 && job.norms) job.norms[i] = nrm;
         }
     }
-    s = ks_wave_sum(s);
-    if (lane == 0) {
-        float nrm = sqrtf(s);
-        norms[i] = nrm;
-        // non-negative floats order like their bit patterns.  The running maximum is read first: one atomic
-        // per row on a single address would serialise the whole kernel in the L2
-        const uint32_t bits = __float_as_uint(nrm);
-        if (bits > __atomic_load_n(maxnorm_bits, __ATOMIC_RELAXED)) atomicMax(maxnorm_bits, bits);
+    __shared__ float s_mx[GR_NT / 64];
+    mx = ks_wave_max(mx);
+    if (lane == 0) s_mx[wave] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < GR_NT / 64; ++w) mx = fmaxf(mx, s_mx[w]);
+        job.blockmax[bid] = mx;
     }
 }
-
-__global__ void gr_zero_kernel(uint32_t *maxnorm_bits, int32_t *fb_count) {
-    *maxnorm_bits = 0u;
-    *fb_count = 0;
+// largest row norm from the workgroups' maxima; every lane of a wavefront gets it
+__device__ __forceinline__ float gr_max_norm(const float *__restrict__ blockmax, int n) {
+    float mx = 0.f;
+    for (int q = threadIdx.x & 63; q < n; q += 64) mx = fmaxf(mx, blockmax[q]);
+    return ks_wave_max(mx);
+}
+__global__ void __launch_bounds__(64) gr_maxnorm_kernel(const float *__restrict__ blockmax, int n, float *maxnorm) {
+    const float mx = gr_max_norm(blockmax, n);
+    if (threadIdx.x == 0) *maxnorm = mx;
 }
 
 // Cut the candidate buffer of one row back to its kprime best (in no particular order: the exact stage ranks them
@@ -459,54 +538,254 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// recall pass that computes every similarity ONCE (W searched in W, D = 128, 256 or 512, k' <= 64).
+// Recall with thresholds fixed beforehand (K <= 64, D <= 512).
+//
+// A first sweep (gr_threshold_kernel) finds for every row its r-th largest similarity to a sample of one in 32 of the
+// searched rows; r = 8 for K <= 16, 10 for K <= 32, 12 for K <= 64.  The number of searched rows at or above it is
+// 32 * Gamma(r) whatever their distribution (an order statistic of a uniform sample): 256, 320 or 384 on average, beyond
+// 1,100 or at most K (then r of the row's K + 1 best would have to be in the sample) for less than one row in a million.
+// The candidate segments are sized for those counts and nothing is cut back during the sweep, so that
+//   * a row's candidates may come from several workgroups: gr_recall_fix_kernel cuts the searched rows into `parts`, one
+//     workgroup per (256 resident rows, part).  10,000 rows are 40 blocks; with one workgroup each, 216 compute units idle.
+//   * a similarity may serve both of its rows: gr_recall_sym_kernel.
+// A row that does end up with too many or too few candidates is caught by the certificate like any other uncertain row.
+// ------------------------------------------------------------------------------------------------
+#define GR_SYM_Q 512             /* slots of a candidate segment (one lane's hits) */
+#define GR_SYM_SCAP 1024         /* slots of the stream-side segment */
+#define GR_MAX_CAND 2048         /* candidates of a row that the ranking takes */
+#define GR_SYM_RANK 12           /* places of the sorted list that finds a row's threshold */
+#define GR_MAX_PARTS 24
+#define GR_CUS 256               /* compute units that the parts are planned for */
+
+// A row's candidate segments: 2 * parts of q slots (the two lanes of a part that hold the row), then `stream` slots.
+struct GrSegs {
+    int parts, q, stream;
+    __host__ __device__ int cap() const { return 2 * parts * q + stream; }
+};
+// stage shape of the sweeps for a depth of KT k-tiles: twelve k-tiles in flight, two per stage where KT is even (a barrier
+// per stage); a single k-tile per chunk (KT = 1): six, so that at most seven chunks are in flight
+template <int KT, bool RAGGED> using GrSoe = KsSoe<KT, 96, (KT % 2 == 0 || KT == 1) ? 6 : 12, KT % 2 == 0 ? 2 : 1, RAGGED>;
+
+// One hop of the distributed build: a row whose list is full needs no visiting row whose similarity cannot reach the
+// list's last entry: its threshold is at least that entry's similarity, lowered by more than twice the recall's error
+// bound (a visiting row that ties the entry exactly is still recalled, and the certificate of the merge -- new K-th
+// similarity above threshold + bound -- holds when nothing new comes in).  graph == nullptr: no lists.
+struct GrHop {
+    const int32_t *graph;
+    const double *sims;
+    const float *norms;
+    int K;
+    float gamma;
+};
+__device__ __forceinline__ uint32_t gr_hop_threshold(const GrHop &hop, int64_t i, float maxnorm) {
+    if (!hop.graph || hop.graph[i * hop.K + hop.K - 1] < 0) return 0u;
+    const double eps = (double)hop.gamma * (double)hop.norms[i] * (double)maxnorm;
+    const double want = hop.sims[i * hop.K + hop.K - 1] - 2.5 * eps;
+    float f = (float)want;
+    if ((double)f > want) f = nextafterf(f, -INFINITY); // rounded down
+    return (f == f && f > -INFINITY) ? gr_orderable(f) : 0u;
+}
+
+// thf[i]: a similarity of row i passes if it is above this; tbits[i]: the key of thf[i], so that "key value <= tbits"
+// holds for everything that fails.  (thf is the float below the sample's r-th largest: that one passes.)
+// A lane keeps the GR_SYM_RANK largest similarities of its row that it has seen, sorted, in registers: an insertion is one
+// median-of-three per place.  (The first version appended to candidate buffers in memory and cut them back: every cut is
+// 32 rows in turn per wavefront, 199 us for 10,000 rows of 128 against a sample of 312.)
+template <class CFG>
+__global__ void __launch_bounds__(512)
+gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *__restrict__ Ws, int n_sample, int D,
+                    int r, const float *__restrict__ blockmax, int n_blockmax, float *maxnorm, GrHop hop, float *__restrict__ thf,
+                    uint32_t *__restrict__ tbits) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
+    constexpr int RANK = GR_SYM_RANK;
+    const int64_t row0 = (int64_t)blockIdx.x * CFG::RES;
+    float top[RANK]; // descending
+#pragma unroll
+    for (int k = 0; k < RANK; ++k) top[k] = -INFINITY;
+    auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
+        (void)c0;
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int fm = 0; fm < CFG::FM; ++fm)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = acc[fm][4 * q + e];
+                if (rows_here < CFG::CH) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (ks_soe_row(fm, 4 * q + e, lane) >= rows_here) v[e] = -INFINITY;
+                }
+                if (fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > top[RANK - 1]) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                        for (int k = RANK - 1; k > 0; --k) top[k] = __builtin_amdgcn_fmed3f(top[k - 1], top[k], v[e]);
+                        top[0] = fmaxf(top[0], v[e]);
+                    }
+                }
+            }
+    };
+    ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, 0, n_sample, n_sample, lds, epi);
+    // The two lanes of a row hold disjoint sampled rows: the r-th largest of both sorted lists together is the r-th largest
+    // of the 2 RANK values.  (Of a pair of places k, RANK - 1 - k the larger value is one of the RANK largest; what is left
+    // is sorted by inserting it again.)
+    float u[RANK];
+#pragma unroll
+    for (int k = 0; k < RANK; ++k) u[k] = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < RANK; ++k) {
+        const float v = fmaxf(top[k], __shfl_xor(top[RANK - 1 - k], 32, 64));
+#pragma unroll
+        for (int j = RANK - 1; j > 0; --j) u[j] = __builtin_amdgcn_fmed3f(u[j - 1], u[j], v);
+        u[0] = fmaxf(u[0], v);
+    }
+    float t = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < RANK; ++k) t = k + 1 == r ? u[k] : t;
+    const float mx = (hop.graph || blockIdx.x == 0) ? gr_max_norm(blockmax, n_blockmax) : 0.f;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *maxnorm = mx;
+    const int64_t i = row0 + ks_soe_col();
+    if ((threadIdx.x & 63) < 32 && i < Cr) {
+        const uint32_t lowest = gr_orderable(-INFINITY), tb = gr_orderable(t);
+        uint32_t bits = tb > lowest + 1u ? tb - 1u : lowest;
+        const uint32_t hb = gr_hop_threshold(hop, i, mx);
+        if (hb > bits) bits = hb;
+        thf[i] = gr_unorder(bits);
+        tbits[i] = bits;
+    }
+}
+
+// Element r (0 .. 15, different from lane to lane) of a lane's 16 accumulator values: a binary tree of selects on the
+// bits of r.  (As assembly: written as conditional expressions the compiler turns the tree into a table in scratch
+// memory that it indexes with r.  The s_nop after each compare: a select must not read a mask that one of the two
+// instructions before it has written.)
+__device__ __forceinline__ float gr_sym_pick16(const f32x16_t &a, int r) {
+    float b0, b1, b2, b3, b4, b5, b6, b7, c0, c1, c2, c3, d0, d1, v;
+    asm("v_and_b32 %8, 1, %25\n\tv_cmp_ne_u32 vcc, 0, %8\n\ts_nop 1\n\t"
+        "v_cndmask_b32 %0, %9, %10, vcc\n\tv_cndmask_b32 %1, %11, %12, vcc\n\t"
+        "v_cndmask_b32 %2, %13, %14, vcc\n\tv_cndmask_b32 %3, %15, %16, vcc\n\t"
+        "v_cndmask_b32 %4, %17, %18, vcc\n\tv_cndmask_b32 %5, %19, %20, vcc\n\t"
+        "v_cndmask_b32 %6, %21, %22, vcc\n\tv_cndmask_b32 %7, %23, %24, vcc"
+        : "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3), "=&v"(b4), "=&v"(b5), "=&v"(b6), "=&v"(b7), "=&v"(v)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]),
+          "v"(a[10]), "v"(a[11]), "v"(a[12]), "v"(a[13]), "v"(a[14]), "v"(a[15]), "v"(r)
+        : "vcc");
+    asm("v_and_b32 %4, 2, %13\n\tv_cmp_ne_u32 vcc, 0, %4\n\ts_nop 1\n\t"
+        "v_cndmask_b32 %0, %5, %6, vcc\n\tv_cndmask_b32 %1, %7, %8, vcc\n\t"
+        "v_cndmask_b32 %2, %9, %10, vcc\n\tv_cndmask_b32 %3, %11, %12, vcc"
+        : "=&v"(c0), "=&v"(c1), "=&v"(c2), "=&v"(c3), "=&v"(v)
+        : "v"(b0), "v"(b1), "v"(b2), "v"(b3), "v"(b4), "v"(b5), "v"(b6), "v"(b7), "v"(r)
+        : "vcc");
+    asm("v_and_b32 %2, 4, %7\n\tv_cmp_ne_u32 vcc, 0, %2\n\ts_nop 1\n\t"
+        "v_cndmask_b32 %0, %3, %4, vcc\n\tv_cndmask_b32 %1, %5, %6, vcc"
+        : "=&v"(d0), "=&v"(d1), "=&v"(v)
+        : "v"(c0), "v"(c1), "v"(c2), "v"(c3), "v"(r)
+        : "vcc");
+    asm("v_and_b32 %0, 8, %3\n\tv_cmp_ne_u32 vcc, 0, %0\n\ts_nop 1\n\tv_cndmask_b32 %0, %1, %2, vcc"
+        : "=&v"(v)
+        : "v"(d0), "v"(d1), "v"(r)
+        : "vcc");
+    return v;
+}
+
+// The lane's hits among its 16 values as a bit mask, bit 15 - r for value r > t[r / 4][r % 4]: a compare and an
+// add-with-carry per value.  (The four compares first: a vector instruction must not read a mask that one of the two
+// instructions before it has written.)
+__device__ __forceinline__ uint32_t gr_hit_mask4(uint32_t hm, float t0, float t1, float t2, float t3, float a0, float a1, float a2, float a3) {
+    uint64_t k0, k1, k2, k3;
+    asm("v_cmp_lt_f32 %1, %5, %9\n\tv_cmp_lt_f32 %2, %6, %10\n\tv_cmp_lt_f32 %3, %7, %11\n\t"
+        "v_cmp_lt_f32 %4, %8, %12\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %3\n\tv_addc_co_u32 %0, vcc, %0, %0, %4"
+        : "+v"(hm), "=&s"(k0), "=&s"(k1), "=&s"(k2), "=&s"(k3)
+        : "v"(t0), "v"(t1), "v"(t2), "v"(t3), "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+        : "vcc");
+    return hm;
+}
+__device__ __forceinline__ uint32_t gr_hit_mask(float t, const f32x16_t &a) {
+    uint32_t hm = 0u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hm = gr_hit_mask4(hm, t, t, t, t, a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+    return hm;
+}
+
+// Resident rows against one part of the searched rows.  Lane (row, half) appends to segment (part, half) of the row and
+// counts in a register: an append is a store and an increment.  In the problems that come here one value in 30 to 1,000
+// passes, so that of 64 lanes x 16 values nearly always some do: the hits of a lane become a bit mask and are taken one by
+// one (testing value by value costs a branch around the append for each of them).
+template <class CFG>
+__global__ void __launch_bounds__(512)
+gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const float *__restrict__ thf_row,
+                     uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
+    const int id = ks_xcd_remap(blockIdx.x, gridDim.x); // the workgroups of an XCD stream the same parts
+    const int part = id / nb;
+    const int row0 = id % nb * CFG::RES;
+    const int s0 = part * part_rows, s1 = (int64_t)s0 + part_rows < pr.Cs ? s0 + part_rows : (int)pr.Cs;
+    const int Cr = (int)pr.Cr;
+    const int cap = seg.cap(), Q = seg.q;
+    const int64_t self0 = row0 + pr.self; // streamed rows [self0, self0 + RES) are this workgroup's own rows
+    const float thf = row0 + ks_soe_col() < Cr ? thf_row[row0 + ks_soe_col()] : INFINITY;
+    uint64_t *const wg_cand = cand + (int64_t)row0 * cap;
+    const uint32_t my_base = (uint32_t)(ks_soe_col() * cap + (2 * part + ((threadIdx.x & 63) >> 5)) * Q);
+    int my_cnt = 0;
+    auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
+        const int lane = threadIdx.x & 63;
+        const bool special = rows_here < CFG::CH || ((int64_t)c0 < self0 + CFG::RES && (int64_t)c0 + CFG::CH > self0);
+#pragma unroll
+        for (int fm = 0; fm < CFG::FM; ++fm) {
+            uint32_t hm = gr_hit_mask(thf, acc[fm]);
+            while (__ballot(hm != 0u) != 0ull) { // as often as the lane with the most hits has some
+                if (hm != 0u) {
+                    const int r = 15 - __builtin_ctz(hm);
+                    hm &= hm - 1u;
+                    const float v = gr_sym_pick16(acc[fm], r);
+                    const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), j = c0 + lr;
+                    if (!special || (lr < rows_here && (int64_t)j != (int64_t)row0 + ks_soe_col() + pr.self)) {
+                        // (the mask keeps the store inside the segment; a count beyond Q marks the row as overflowed)
+                        wg_cand[my_base + ((uint32_t)my_cnt & (uint32_t)(Q - 1))] =
+                            ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
+                        ++my_cnt;
+                    }
+                }
+            }
+        }
+    };
+    ks_soe_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, nullptr, s0, s1, (int)pr.Cs, lds, epi);
+    const int i = row0 + ks_soe_col();
+    if (i < Cr) cnt_res[(int64_t)i * 2 * seg.parts + 2 * part + ((threadIdx.x & 63) >> 5)] = my_cnt;
+}
+
+// ------------------------------------------------------------------------------------------------
+// recall pass that computes every similarity ONCE (W searched in W, D = 128, 256 or 512, K <= 64).
 //
 // The similarity matrix is symmetric, so the tile of a workgroup's 256 resident rows against a streamed row j holds,
 // for every resident row i, a candidate for BOTH lists: j for row i (the "resident side", a lane's own row, as in the
 // kernel above) and i for row j (the "stream side").  Each unordered pair of 256-row blocks is given to exactly one
-// workgroup, which halves the MFMA work of the pass.  What it takes:
+// share of the work, which halves the MFMA work of the pass.  What it takes beyond the fixed thresholds:
 //
-//  * thresholds known in advance.  A row that is streamed past hundreds of workgroups cannot keep a running
-//    threshold, so a first pass (the kernel above, on every 32nd row of W only) finds for each row the 12th largest
-//    similarity to that sample.  The number of rows of all of W at or above it is 32 times a Gamma(12) variable
-//    whatever the distribution of the rows (it is an order statistic of a uniform sample): 384 on average, beyond
-//    1,100 or below k' (then 12 of the row's k' best would have to be in the sample) for less than one row in a
-//    million.  Both sides test against these fixed thresholds and the buffers are sized for those counts; nothing is
-//    cut back during the sweep.  A row that does end up with too many or too few candidates is caught by the
-//    re-rank's certificate like any other uncertain row.
-//  * who takes which pair.  Rows are cut into blocks of 256 (a workgroup's resident rows), super-blocks of 768 rows
+//  * who takes which pair.  Rows are cut into blocks of 256 (a share's resident rows), super-blocks of 768 rows
 //    (three blocks = eight 96-row chunks, so that every streamed range starts on a chunk boundary) and groups of up
 //    to 10 super-blocks.  On each level the members form a ring and a member takes the following half of the ring
-//    (gr_sym_succ): a workgroup streams its own super-block (its own block for the resident side only, the blocks it
+//    (gr_sym_succ): a share streams its own super-block (its own block for the resident side only, the blocks it
 //    takes there for both sides), then the super-blocks it takes inside its group, then all rows of the groups its
-//    group takes.  The 30 workgroups of a group sit on one XCD and stream the same long ranges at the same pace, so
-//    a streamed row is fetched from memory once per group.
+//    group takes.  A share's chunks are cut into `parts` runs, one workgroup each (one part per share in problems that
+//    fill the chip without it).  The shares of a group run on one XCD (or two neighbouring ones) and stream the same long
+//    ranges at the same pace, so a streamed row is fetched from memory about once per group.
 //  * the stream side's candidates.  A hit for streamed row j is a record (j, i, similarity): a wavefront collects them
-//    in LDS and appends them, with one atomic per batch, to the log of j's super-block; gr_sym_scatter_kernel (one
-//    workgroup per super-block, row counters in LDS) then moves them into the rows' buffers.  In the sweep the
-//    thresholds of the streamed rows are scalar registers (an accumulator register holds one streamed row across the
-//    lanes); the two halves of a wavefront hold different rows (j and j + 4), so the test is against the smaller of
-//    the two thresholds (gr_sym_prep_kernel stores these minima) and the scatter kernel applies the row's own.
-//  * gr_sym_select_kernel cuts every row's candidates (two resident-side halves and the stream side) to the k' best,
-//    in the layout the re-rank expects.  A row whose buffers or log overflowed gets a threshold no similarity
-//    exceeds: its certificate fails and the exhaustive pass computes it.
+//    in LDS and appends them, with one atomic per batch, to the log of j's run of `log_rows` rows (a super-block in a
+//    large problem; as little as a chunk in a small one, whose chunks have a batch's worth of hits each);
+//    gr_sym_scatter_kernel (one workgroup per log, row counters in LDS) then moves them into the rows' stream segments.
+//  * A row whose segments or log overflowed gets a threshold no similarity exceeds: its certificate fails and the
+//    exhaustive pass computes it.
 // ------------------------------------------------------------------------------------------------
-#define GR_SYM_CAP 2048          /* candidate slots per row: two resident-side halves, then the stream side */
-#define GR_SYM_Q 512             /* slots of each resident-side half */
-#define GR_SYM_SCAP 1024         /* slots of the stream side */
 #define GR_SYM_SB 768            /* rows of a super-block */
-#define GR_SYM_LOGCAP (768 * 384) /* records per super-block log (expected: 768 rows * 192 stream-side hits, plus a tenth) */
+#define GR_SYM_LOG_PER_ROW 384   /* log records per row (expected: 192 stream-side hits, plus a tenth) */
 #define GR_SYM_STAGE 192         /* records a wavefront collects in LDS between two appends to a log */
-#define GR_SYM_RATIO 32          /* rows of W per sampled row */
-#define GR_SYM_RANK 12           /* the threshold of a row: its GR_SYM_RANK-th largest similarity to the sample */
-#define GR_SYM_MAX_GROUP 10      /* super-blocks per group at most: 30 workgroups, about the compute units of an XCD */
+#define GR_SYM_MAX_GROUP 10      /* super-blocks per group at most: 30 shares, about the compute units of an XCD */
 
-// rows of W sampled by the first pass: one of every `ratio` consecutive rows, at a position that varies from one run
-// of `ratio` rows to the next
-__device__ __forceinline__ int64_t gr_sym_sample_row(int64_t s, int ratio, int64_t C) {
-    const int64_t r = s * ratio + (int64_t)(((uint32_t)s * 2654435761u) >> 16) % ratio;
-    return r < C ? r : C - 1;
-}
 // members of a ring of n that member x takes: the next gr_sym_succ(n, x) ones.  Every unordered pair is taken once:
 // for even n the opposite member is taken by the lower of the two.
 __host__ __device__ __forceinline__ int gr_sym_succ(int n, int x) {
@@ -516,37 +795,6 @@ __host__ __device__ __forceinline__ int gr_sym_group_sbs(int64_t C) { // super-b
     const int nsb = (int)((C + GR_SYM_SB - 1) / GR_SYM_SB);
     const int gs = nsb / 16;
     return gs < 1 ? 1 : (gs > GR_SYM_MAX_GROUP ? GR_SYM_MAX_GROUP : gs);
-}
-
-__global__ void __launch_bounds__(GR_NT)
-gr_sym_sample_kernel(const uint16_t *__restrict__ W, int64_t C, int D, int ratio, int64_t n_sample,
-                     uint16_t *__restrict__ Ws) {
-    const int64_t s = (int64_t)blockIdx.x * (GR_NT / 64) + (threadIdx.x >> 6);
-    if (s >= n_sample) return;
-    const uint4 *src = (const uint4 *)(W + gr_sym_sample_row(s, ratio, C) * D);
-    uint4 *dst = (uint4 *)(Ws + s * D);
-    for (int q = threadIdx.x & 63; q < D / 8; q += 64) dst[q] = src[q];
-}
-
-// thr_sample[i]: value bits of the GR_SYM_RANK-th largest similarity of row i to the sample (0: the sample had fewer rows).
-// Row i takes every similarity at or above it: thf[i] is the next float below, and tbits[i] its key, so that "v > thf"
-// is the test and "key value <= tbits" holds for everything that fails it.  Rows at and beyond C never pass.  Also
-// clears the counters of the logs and of the second-chance list.
-__global__ void __launch_bounds__(GR_NT)
-gr_sym_prep_kernel(const uint32_t *__restrict__ thr_sample, int64_t C, int64_t Cpad, float *__restrict__ thf,
-                   uint32_t *__restrict__ tbits, int32_t *__restrict__ logcnt, int nsb, int32_t *second_count) {
-    const int64_t i = (int64_t)blockIdx.x * GR_NT + threadIdx.x;
-    if (i < nsb) logcnt[i] = 0;
-    if (i == 0) *second_count = 0;
-    if (i >= Cpad) return;
-    if (i >= C) {
-        thf[i] = INFINITY;
-        return;
-    }
-    const uint32_t lowest = gr_orderable(-INFINITY), t = thr_sample[i];
-    const uint32_t bits = t > lowest + 1u ? t - 1u : lowest;
-    thf[i] = gr_unorder(bits);
-    tbits[i] = bits;
 }
 
 // The plan of the sweep, made by a small kernel beforehand (the sweep kernel has no registers to spare for the
@@ -560,17 +808,14 @@ struct GrSymRanges {
     int ring;           // place | members << 4 | members taken << 8 in the ring of its super-block's blocks
     int first[5], end[5]; // streamed rows [first, end) of the five ranges; empty: end <= first
 };
-__host__ __device__ inline GrSymRanges gr_sym_ranges(int wg, int C, int GS) {
+__host__ __device__ inline GrSymRanges gr_sym_ranges(int block, int C, int GS) {
     GrSymRanges out;
     const int NB = (C + 255) / 256, NSB = (C + GR_SYM_SB - 1) / GR_SYM_SB, NG = (NSB + GS - 1) / GS;
-    const int BPG = GS * (GR_SYM_SB / 256); // blocks per group
-    // the workgroups of a group are those that one XCD receives in a row (workgroups are dealt to the eight XCDs in turn)
-    const int g = (wg >> 3) / BPG * 8 + (wg & 7);
-    const int block = g * BPG + (wg >> 3) % BPG;
+    const int g = block / (GS * (GR_SYM_SB / 256));
     out.block = -1;
     out.ring = 0;
     for (int part = 0; part < 5; ++part) out.first[part] = out.end[part] = 0;
-    if (g >= NG || block >= NB) return out;
+    if (block >= NB) return out;
     const int sb = block * 256 / GR_SYM_SB, own0 = sb * GR_SYM_SB, own1 = own0 + GR_SYM_SB < C ? own0 + GR_SYM_SB : C;
     const int kb = (block * 256 - own0) / 256, n_b = (own1 - own0 + 255) / 256;
     const int gsb0 = g * GS, n_sb = (gsb0 + GS < NSB ? gsb0 + GS : NSB) - gsb0, s_loc = sb - gsb0;
@@ -615,99 +860,70 @@ gr_sym_plan_kernel(int C, int GS, int32_t *__restrict__ plan, int2 *__restrict__
     }
 }
 
-// Element r (0 .. 15, different from lane to lane) of a lane's 16 accumulator values: a binary tree of selects on the
-// bits of r.  (As assembly: written as conditional expressions the compiler turns the tree into a table in scratch
-// memory that it indexes with r.  The s_nop after each compare: a select must not read a mask that one of the two
-// instructions before it has written.)
-__device__ __forceinline__ float gr_sym_pick16(const f32x16_t &a, int r) {
-    float b0, b1, b2, b3, b4, b5, b6, b7, c0, c1, c2, c3, d0, d1, v;
-    asm("v_and_b32 %8, 1, %25\n\tv_cmp_ne_u32 vcc, 0, %8\n\ts_nop 1\n\t"
-        "v_cndmask_b32 %0, %9, %10, vcc\n\tv_cndmask_b32 %1, %11, %12, vcc\n\t"
-        "v_cndmask_b32 %2, %13, %14, vcc\n\tv_cndmask_b32 %3, %15, %16, vcc\n\t"
-        "v_cndmask_b32 %4, %17, %18, vcc\n\tv_cndmask_b32 %5, %19, %20, vcc\n\t"
-        "v_cndmask_b32 %6, %21, %22, vcc\n\tv_cndmask_b32 %7, %23, %24, vcc"
-        : "=&v"(b0), "=&v"(b1), "=&v"(b2), "=&v"(b3), "=&v"(b4), "=&v"(b5), "=&v"(b6), "=&v"(b7), "=&v"(v)
-        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]),
-          "v"(a[10]), "v"(a[11]), "v"(a[12]), "v"(a[13]), "v"(a[14]), "v"(a[15]), "v"(r)
-        : "vcc");
-    asm("v_and_b32 %4, 2, %13\n\tv_cmp_ne_u32 vcc, 0, %4\n\ts_nop 1\n\t"
-        "v_cndmask_b32 %0, %5, %6, vcc\n\tv_cndmask_b32 %1, %7, %8, vcc\n\t"
-        "v_cndmask_b32 %2, %9, %10, vcc\n\tv_cndmask_b32 %3, %11, %12, vcc"
-        : "=&v"(c0), "=&v"(c1), "=&v"(c2), "=&v"(c3), "=&v"(v)
-        : "v"(b0), "v"(b1), "v"(b2), "v"(b3), "v"(b4), "v"(b5), "v"(b6), "v"(b7), "v"(r)
-        : "vcc");
-    asm("v_and_b32 %2, 4, %7\n\tv_cmp_ne_u32 vcc, 0, %2\n\ts_nop 1\n\t"
-        "v_cndmask_b32 %0, %3, %4, vcc\n\tv_cndmask_b32 %1, %5, %6, vcc"
-        : "=&v"(d0), "=&v"(d1), "=&v"(v)
-        : "v"(c0), "v"(c1), "v"(c2), "v"(c3), "v"(r)
-        : "vcc");
-    asm("v_and_b32 %0, 8, %3\n\tv_cmp_ne_u32 vcc, 0, %0\n\ts_nop 1\n\tv_cndmask_b32 %0, %1, %2, vcc"
-        : "=&v"(v)
-        : "v"(d0), "v"(d1), "v"(r)
-        : "vcc");
-    return v;
-}
-
 // a stream-side hit: similarity v of a streamed row (given by its place in its super-block) with resident row `other`
 __device__ __forceinline__ uint2 gr_sym_record(int j_in_sb, int other, float v) {
     return make_uint2(gr_orderable(v), ((uint32_t)other << 10) | (uint32_t)j_in_sb);
 }
 
-template <int KT>
+// SPLIT: shares are cut into parts and the logs are finer than a super-block (the addresses are then arithmetic on two
+// more registers; compiled apart, the sweep over 390,625 rows of 512 takes 84 ms instead of 88).
+template <int KT, bool SPLIT>
 __global__ void __launch_bounds__(512)
 gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t *__restrict__ plan,
-                     const int2 *__restrict__ chunks, int chunks_stride, const float *__restrict__ thf_row,
-                     uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res,
+                     const int2 *__restrict__ chunks, int chunks_stride, int split_parts, int split_log_rows,
+                     const float *__restrict__ thf_row, uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res,
                      uint2 *__restrict__ log, int32_t *logcnt) {
-    typedef KsSoe<KT, 96, GR_SOE_STAGES, 2> CFG;
-    constexpr int CAP = GR_SYM_CAP, Q = GR_SYM_Q, SB = GR_SYM_SB;
+    typedef GrSoe<KT, false> CFG;
+    constexpr int Q = GR_SYM_Q, SB = GR_SYM_SB;
+    const int parts = SPLIT ? split_parts : 1, log_rows = SPLIT ? split_log_rows : SB;
     static_assert(SB % CFG::CH == 0 && SB % CFG::RES == 0 && CFG::RES == 256, "super-blocks are whole chunks and whole blocks");
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
     __shared__ uint2 s_stage[CFG::NW][GR_SYM_STAGE];
     __shared__ __attribute__((aligned(16))) float s_thr[8][CFG::CH]; // the streamed rows' thresholds of the chunks in flight
     const int lane = threadIdx.x & 63;
-    const int32_t *my_plan = plan + (int64_t)blockIdx.x * GR_SYM_PLAN;
+    // Share and part.  Every XCD gets the same number of workgroups, for consecutive blocks: the 32 that it runs at a time
+    // belong to one group and the next.  (Whole groups dealt to XCDs: at 390,625 rows three XCDs had seven groups of 30
+    // and five had six, seven rounds of workgroups instead of six, 87 ms instead of 75.)
+    const int id = ks_xcd_remap(blockIdx.x, gridDim.x), shares = (int)gridDim.x / parts, share = id % shares, part = id / shares;
+    const int32_t *my_plan = plan + (int64_t)share * GR_SYM_PLAN;
     const int block = my_plan[0];
     if (block < 0) return;
+    const int chunk0 = (int)((int64_t)my_plan[2] * part / parts), chunk1 = (int)((int64_t)my_plan[2] * (part + 1) / parts);
     const int row0 = block * CFG::RES;
     const int sb_own = row0 / SB;
     const int ring = my_plan[1];
     const float thf = row0 + ks_soe_col() < C ? thf_row[row0 + ks_soe_col()] : INFINITY;
-    uint64_t *const wg_cand = cand + (int64_t)row0 * CAP;
+    const int cap = 2 * Q * parts + GR_SYM_SCAP;
+    uint64_t *const wg_cand = cand + (int64_t)row0 * cap;
     int my_cnt = 0;
-    // stream side: records collected by this wavefront, and the super-block they belong to
-    int staged = 0, cur_sb = sb_own;
+    // stream side: records collected by this wavefront, and the log they belong to (log_rows is a multiple of the chunk
+    // and divides the super-block)
+    int staged = 0, cur_log = -1;
     auto my_stage = [&]() __attribute__((always_inline)) { return s_stage[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]; };
     auto flush = [&]() {
         if (staged > 0) {
             int base = 0;
-            if (lane == 0) base = atomicAdd(&logcnt[cur_sb], staged);
+            if (lane == 0) base = atomicAdd(&logcnt[cur_log], staged);
             base = __builtin_amdgcn_readfirstlane(base);
-            uint2 *dst = log + (int64_t)cur_sb * GR_SYM_LOGCAP;
+            const int logcap = log_rows * GR_SYM_LOG_PER_ROW;
+            uint2 *dst = log + (int64_t)cur_log * logcap;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the records written by the other lanes are in LDS
             for (int q = lane; q < staged; q += 64)
-                if (base + q < GR_SYM_LOGCAP) dst[base + q] = my_stage()[q];
+                if (base + q < logcap) dst[base + q] = my_stage()[q];
             asm volatile("" ::: "memory");
             staged = 0;
         }
     };
-    // all lanes call it together with the ballot m of `hit`; the lanes that hit add the record (j, own row, v)
-    auto push = [&](uint64_t m, bool hit, int j, float v) __attribute__((always_inline)) {
-        const int n = __popcll(m);
-        if (staged + n > GR_SYM_STAGE) flush();
-        if (hit) my_stage()[staged + __popcll(m & ((1ull << lane) - 1ull))] = gr_sym_record(j - cur_sb * SB, row0 + ks_soe_col(), v);
-        staged = __builtin_amdgcn_readfirstlane(staged + n);
-    };
     auto append_res = [&](int j, float v) __attribute__((always_inline)) {
         // (the mask keeps the store inside the lane's half; a count beyond Q marks the row as overflowed)
-        const uint32_t my_base = (uint32_t)(ks_soe_col() * CAP + (lane >> 5) * Q);
+        const uint32_t my_base = (uint32_t)(ks_soe_col() * cap + (2 * part + (lane >> 5)) * Q);
         wg_cand[my_base + ((uint32_t)my_cnt & (uint32_t)(Q - 1))] = ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
         ++my_cnt;
     };
     // The thresholds of a chunk's rows travel to LDS beside its rows: requested by wavefront 0 when the chunk's loads begin.
     // The loads run up to STAGES - 1 pipeline stages ahead of the MFMAs and a chunk of D = 128 is a single stage, so up to
     // seven chunks lie between the request and the epilogue that reads it: eight slots.
-    static_assert(GR_SOE_STAGES - 1 + 2 <= 8, "slots for the chunks in flight");
+    static_assert((CFG::STAGES - 1) * CFG::KSUB / KT + 2 <= 8, "slots for the chunks in flight");
     auto side = [&](int first, int c) __attribute__((always_inline)) {
         static_assert(CFG::CH == 96, "64 + 32 lanes");
         __builtin_amdgcn_global_load_lds(KS_GPTR(thf_row + first + lane), KS_LPTR(&s_thr[c & 7][0]), 4, 0, 0);
@@ -717,24 +933,55 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
         const float *thr_chunk = s_thr[epi_chunk & 7];
         ++epi_chunk;
-        const int sb = c0 / SB; // uniform; a chunk lies in one super-block
-        if (sb != cur_sb) { flush(); cur_sb = sb; }
-        if (rows_here == CFG::CH && sb != sb_own) {
-            // plain chunk: all rows real, both sides wanted for every element
-            const bool real_row = row0 + ks_soe_col() < C;
+        const int sb = c0 / SB; // uniform; a chunk lies in one super-block and in one log
+        if (c0 < cur_log * log_rows || c0 >= (cur_log + 1) * log_rows) { flush(); cur_log = c0 / log_rows; }
+        // Which sides are wanted is the same for 32 streamed rows at a time (block boundaries are multiples of 32 rows):
+        // both, except in the workgroup's own super-block, where its own block is searched for the resident side only and
+        // the other blocks as the ring says.
+        const bool own_sb = sb == sb_own, ragged = rows_here < CFG::CH; // (ragged: the last chunk of W)
+        const bool real_row = row0 + ks_soe_col() < C;
 #pragma unroll
-            for (int fm = 0; fm < CFG::FM; ++fm) {
+        for (int fm = 0; fm < CFG::FM; ++fm) {
+            bool res_side = true, str_side = true, diag = false;
+            if (own_sb) {
+                const int kb = ring & 15, n_b = (ring >> 4) & 15, succ_b = ring >> 8;
+                int dd = (c0 + fm * 32 - sb_own * SB) / CFG::RES - kb; // ring distance from this block to the streamed rows' block
+                if (dd < 0) dd += n_b;
+                diag = dd == 0;
+                str_side = dd >= 1 && dd <= succ_b;
+                res_side = diag || str_side;
+            }
+            if (res_side) {
+                const bool check = diag || ragged;
+                if (SPLIT) {
+                    uint32_t hr = gr_hit_mask(thf, acc[fm]);
+                    while (__ballot(hr != 0u) != 0ull) {
+                        if (hr != 0u) {
+                            const int r = 15 - __builtin_ctz(hr);
+                            hr &= hr - 1u;
+                            const float v = gr_sym_pick16(acc[fm], r);
+                            const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                            if (!check || (lr < rows_here && c0 + lr != row0 + ks_soe_col())) append_res(c0 + lr, v);
+                        }
+                    }
+                } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float a0 = acc[fm][4 * q], a1 = acc[fm][4 * q + 1], a2 = acc[fm][4 * q + 2], a3 = acc[fm][4 * q + 3];
-                    if (fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)) > thf) {
+                    for (int q = 0; q < 4; ++q) { // four values at a time: most groups have none that passes
+                        const float a0 = acc[fm][4 * q], a1 = acc[fm][4 * q + 1], a2 = acc[fm][4 * q + 2], a3 = acc[fm][4 * q + 3];
+                        if (fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)) > thf) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float v = acc[fm][4 * q + e];
-                            if (v > thf) append_res(c0 + ks_soe_row(fm, 4 * q + e, lane), v);
+                            for (int e = 0; e < 4; ++e) {
+                                const float v = acc[fm][4 * q + e];
+                                if (v > thf) {
+                                    const int lr = ks_soe_row(fm, 4 * q + e, lane);
+                                    if (!check || (lr < rows_here && c0 + lr != row0 + ks_soe_col())) append_res(c0 + lr, v);
+                                }
+                            }
                         }
                     }
                 }
+            }
+            if (str_side) {
                 // Stream side.  An accumulator register holds ONE streamed row in the lanes 0..31 and the row four further
                 // on in the lanes 32..63.  (Testing against the smaller of the two thresholds, held in a scalar register,
                 // and sorting out the surplus later was tried: the number of records then depends on how well
@@ -742,207 +989,72 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
                 // overflowed and every row went to the exhaustive pass.  With the exact test the counts depend on
                 // nothing but the sample.)
                 // Every instruction here runs once per chunk and fragment, so there are few: a lane's hits become a bit
-                // mask with a compare and an add-with-carry per element and half (bit 15 - r for element r); nearly always
-                // no lane has more than one hit, and then a lane picks its element with a binary tree of selects and the
-                // slots come from one ballot.
+                // mask (bit 15 - r for element r); while any lane has a hit left, every lane that has picks one with a
+                // binary tree of selects and the slots come from one ballot.
                 // (a lane reads the four thresholds of its own rows from LDS: rows 8 q + e in the lanes 0..31, 8 q + 4 + e
                 // in the lanes 32..63)
                 uint32_t hm = 0u;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x4_t t4 = *(const f32x4_t *)(thr_chunk + fm * 32 + 8 * q + 4 * (lane >> 5));
-                    // (the four compares first: a vector instruction must not read a mask that one of the two
-                    // instructions before it has written)
-                    uint64_t k0, k1, k2, k3;
-                    asm("v_cmp_lt_f32 %1, %5, %9\n\tv_cmp_lt_f32 %2, %6, %10\n\tv_cmp_lt_f32 %3, %7, %11\n\t"
-                        "v_cmp_lt_f32 %4, %8, %12\n\t"
-                        "v_addc_co_u32 %0, vcc, %0, %0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
-                        "v_addc_co_u32 %0, vcc, %0, %0, %3\n\tv_addc_co_u32 %0, vcc, %0, %0, %4"
-                        : "+v"(hm), "=&s"(k0), "=&s"(k1), "=&s"(k2), "=&s"(k3)
-                        : "v"(t4[0]), "v"(t4[1]), "v"(t4[2]), "v"(t4[3]), "v"(acc[fm][4 * q]), "v"(acc[fm][4 * q + 1]),
-                          "v"(acc[fm][4 * q + 2]), "v"(acc[fm][4 * q + 3])
-                        : "vcc");
+                    hm = gr_hit_mask4(hm, t4[0], t4[1], t4[2], t4[3], acc[fm][4 * q], acc[fm][4 * q + 1], acc[fm][4 * q + 2],
+                                      acc[fm][4 * q + 3]);
                 }
-                if (!real_row) hm = 0u;
-                const uint64_t any = __ballot(hm != 0u);
-                if (any != 0ull) {
-                    if (__ballot((hm & (hm - 1u)) != 0u) == 0ull) {
-                        const int n = __popcll(any);
-                        if (staged + n > GR_SYM_STAGE) flush();
-                        if (hm != 0u) {
-                            const int r = 15 - __builtin_ctz(hm);
-                            const float v = gr_sym_pick16(acc[fm], r);
-                            const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                            my_stage()[staged + __popcll(any & ((1ull << lane) - 1ull))] = gr_sym_record(c0 - sb * SB + lr, row0 + ks_soe_col(), v);
-                        }
-                        staged = __builtin_amdgcn_readfirstlane(staged + n);
-                    } else { // a lane with several hits: row by row
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const bool hit = (hm >> (15 - r)) & 1u;
-                            const uint64_t m = __ballot(hit);
-                            if (m != 0ull) push(m, hit, c0 + ks_soe_row(fm, r, lane), acc[fm][r]);
-                        }
+                if (!real_row) hm = 0u; // (streamed rows beyond W have a threshold that nothing exceeds)
+                uint64_t any = __ballot(hm != 0u);
+                while (any != 0ull) {
+                    const int n = __popcll(any);
+                    if (staged + n > GR_SYM_STAGE) flush();
+                    if (hm != 0u) {
+                        const int r = 15 - __builtin_ctz(hm);
+                        hm &= hm - 1u;
+                        const float v = gr_sym_pick16(acc[fm], r);
+                        const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                        my_stage()[staged + __popcll(any & ((1ull << lane) - 1ull))] = gr_sym_record(c0 - cur_log * log_rows + lr, row0 + ks_soe_col(), v);
                     }
-                }
-            }
-        } else {
-            // the workgroup's own super-block (which side is wanted depends on the streamed row's block) or a ragged end
-            // (the lane number goes through an opaque copy: otherwise the compiler computes the 48 row numbers and what
-            // follows from them once, before the sweep, and keeps them in registers that the sweep does not have)
-            int lane_here = lane;
-            asm volatile("" : "+v"(lane_here));
-            const int gi = row0 + (threadIdx.x >> 6) * 32 + (lane_here & 31);
-            const int own0 = sb_own * SB, kb = ring & 15, n_b = (ring >> 4) & 15, succ_b = ring >> 8;
-#pragma unroll
-            for (int fm = 0; fm < CFG::FM; ++fm) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int lr = ks_soe_row(fm, 4 * q + e, lane_here);
-                        const int j = c0 + lr;
-                        const float v = acc[fm][4 * q + e];
-                        bool res_side = lr < rows_here, str_side = lr < rows_here;
-                        if (sb == sb_own) {
-                            int dd = (j - own0) / CFG::RES - kb; // ring distance from this block to the streamed row's block
-                            if (dd < 0) dd += n_b;
-                            const bool taken = dd >= 1 && dd <= succ_b;
-                            res_side = res_side && ((dd == 0 && j != gi) || taken);
-                            str_side = str_side && taken;
-                        }
-                        if (res_side && v > thf) append_res(j, v);
-                        float t = INFINITY;
-                        if (str_side && gi < C) t = thf_row[j];
-                        const uint64_t m = __ballot(v > t);
-                        if (m != 0ull) push(m, v > t, j, v);
-                    }
-                    asm volatile("" ::: "memory"); // one group at a time: no pile of threshold loads in flight
+                    staged = __builtin_amdgcn_readfirstlane(staged + n);
+                    any = __ballot(hm != 0u);
                 }
             }
         }
     };
     ks_soe_sweep<CFG>(W, D, row0, C, W, D, nullptr, 0, 0, C, lds, epi, nullptr, 0, KsSoeNoPost(),
-                      chunks + (int64_t)blockIdx.x * chunks_stride, my_plan[2], side);
+                      chunks + (int64_t)share * chunks_stride + chunk0, chunk1 - chunk0, side);
     flush();
-    if (row0 + ks_soe_col() < C) cnt_res[2 * (row0 + ks_soe_col()) + (lane >> 5)] = my_cnt;
+    if (row0 + ks_soe_col() < C)
+        cnt_res[(int64_t)(row0 + ks_soe_col()) * 2 * parts + 2 * part + (lane >> 5)] = my_cnt;
 }
 
-// the stream-side records of a super-block go to the rows they belong to; one workgroup per super-block
+// the stream-side records of a log go to the rows they belong to; one workgroup per log
 __global__ void __launch_bounds__(1024)
-gr_sym_scatter_kernel(const uint2 *__restrict__ log, const int32_t *__restrict__ logcnt, int C, const uint32_t *__restrict__ tbits,
+gr_sym_scatter_kernel(const uint2 *__restrict__ log, const int32_t *__restrict__ logcnt, int C, int log_rows, GrSegs seg,
                       uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_str) {
     __shared__ int s_cnt[GR_SYM_SB];
-    __shared__ uint32_t s_tb[GR_SYM_SB];
-    const int sb = blockIdx.x, row0 = sb * GR_SYM_SB;
-    for (int r = threadIdx.x; r < GR_SYM_SB; r += 1024) {
-        s_cnt[r] = 0;
-        s_tb[r] = row0 + r < C ? tbits[row0 + r] : 0xFFFFFFFFu;
-    }
+    const int row0 = blockIdx.x * log_rows, logcap = log_rows * GR_SYM_LOG_PER_ROW, cap = seg.cap();
+    for (int r = threadIdx.x; r < log_rows; r += 1024) s_cnt[r] = 0;
     __syncthreads();
-    const int n_raw = logcnt[sb], n = n_raw < GR_SYM_LOGCAP ? n_raw : GR_SYM_LOGCAP;
-    const uint2 *src = log + (int64_t)sb * GR_SYM_LOGCAP;
+    const int n_raw = logcnt[blockIdx.x], n = n_raw < logcap ? n_raw : logcap;
+    const uint2 *src = log + (int64_t)blockIdx.x * logcap;
     for (int q0 = 0; q0 < n; q0 += 4 * 1024) { // four records per thread in flight
         uint2 rec[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int q = q0 + u * 1024 + (int)threadIdx.x;
-            rec[u] = q < n ? src[q] : make_uint2(0u, 0xFFFFFFFFu); // (place 1023 of a super-block: dropped below)
+            rec[u] = q < n ? src[q] : make_uint2(0u, 0xFFFFFFFFu); // (place 1023 of a log: dropped below)
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int jl = (int)(rec[u].y & 1023u); // (checked all the same: it becomes an address)
             const uint32_t other = rec[u].y >> 10;
-            if (jl >= GR_SYM_SB || row0 + jl >= C || other >= (uint32_t)C) continue;
-            if (rec[u].x <= s_tb[jl]) continue;  // passed its neighbour's threshold in the sweep's test, not its own
+            if (jl >= log_rows || row0 + jl >= C || other >= (uint32_t)C) continue;
             const int slot = atomicAdd(&s_cnt[jl], 1);
-            if (slot < GR_SYM_SCAP)
-                cand[(int64_t)(row0 + jl) * GR_SYM_CAP + 2 * GR_SYM_Q + slot] = ((uint64_t)rec[u].x << 32) | (uint32_t)(0xFFFFFFFFu - other);
+            if (slot < seg.stream)
+                cand[(int64_t)(row0 + jl) * cap + 2 * seg.parts * seg.q + slot] = ((uint64_t)rec[u].x << 32) | (uint32_t)(0xFFFFFFFFu - other);
         }
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < GR_SYM_SB; r += 1024)
-        if (row0 + r < C) cnt_str[row0 + r] = n_raw > GR_SYM_LOGCAP ? 0x7FFFFFFF : s_cnt[r]; // a lost record: all rows overflow
-}
-
-// k' best of a row's candidates to the front of its buffer; one wavefront per row
-__global__ void __launch_bounds__(GR_NT)
-gr_sym_select_kernel(int64_t C, int kprime, uint64_t *__restrict__ cand, const int32_t *__restrict__ cnt_res,
-                     const int32_t *__restrict__ cnt_str, const uint32_t *__restrict__ tbits, int32_t *__restrict__ cnt_out,
-                     uint32_t *__restrict__ thr_out, int32_t *__restrict__ cnt_all) {
-    constexpr int E = GR_SYM_CAP / 64, Q = GR_SYM_Q;
-    const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + (threadIdx.x >> 6);
-    if (i >= C) return;
-    const int lane = threadIdx.x & 63;
-    uint64_t *row = cand + i * GR_SYM_CAP;
-    const int r0 = cnt_res[2 * i], r1 = cnt_res[2 * i + 1], rs = cnt_str[i];
-    const bool overflow = r0 > Q || r1 > Q || rs > GR_SYM_SCAP;
-    const int n0 = r0 < Q ? r0 : Q, n1 = r1 < Q ? r1 : Q, ns = rs < GR_SYM_SCAP ? rs : GR_SYM_SCAP;
-    const int n = n0 + n1 + ns, nreg = (n + 63) >> 6;
-    uint64_t val[E];
-#pragma unroll
-    for (int r = 0; r < E; ++r) {
-        val[r] = 0ull; // below every real key
-        if (r < nreg) {
-            const int idx = r * 64 + lane;
-            if (idx < n) val[r] = row[idx < n0 ? idx : (idx < n0 + n1 ? Q + (idx - n0) : 2 * Q + (idx - n0 - n1))];
-        }
-    }
-    auto count_hi = [&](uint32_t t) {
-        int c = 0;
-#pragma unroll
-        for (int r = 0; r < E; ++r)
-            if (r < nreg) c += __popcll(__ballot((uint32_t)(val[r] >> 32) >= t));
-        return c;
-    };
-    auto count_lo = [&](uint32_t hi, uint32_t t) {
-        int c = 0;
-#pragma unroll
-        for (int r = 0; r < E; ++r)
-            if (r < nreg) c += __popcll(__ballot((uint32_t)(val[r] >> 32) == hi && (uint32_t)val[r] >= t));
-        return c;
-    };
-    uint64_t t = 1ull; // keeps every real key
-    if (n > kprime) {
-        uint32_t t_hi = 0;
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t c = t_hi | (1u << bit);
-            if (count_hi(c) >= kprime) t_hi = c;
-        }
-        t = (uint64_t)t_hi << 32;
-        if (count_hi(t_hi) != kprime) { // keys of equal value straddle the cut: the ids decide
-            const int need = kprime - (t_hi == 0xFFFFFFFFu ? 0 : count_hi(t_hi + 1u));
-            uint32_t t_lo = 0;
-            for (int bit = 31; bit >= 0; --bit) {
-                const uint32_t c = t_lo | (1u << bit);
-                if (count_lo(t_hi, c) >= need) t_lo = c;
-            }
-            t |= t_lo;
-        }
-    }
-    // the k' best to the front, the other candidates behind them (gr_sym_second_kernel may need them: a row whose k'
-    // best do not certify its K-th neighbour is ranked again over everything the sweep found for it)
-    const int kept = n > kprime ? kprime : n;
-    int base = 0, rest = kept;
-#pragma unroll
-    for (int r = 0; r < E; ++r) {
-        if (r < nreg) {
-            const bool real = r * 64 + lane < n, keep = real && val[r] >= t;
-            const uint64_t m = __ballot(keep), m2 = __ballot(real && !keep);
-            const uint64_t below = (1ull << lane) - 1ull;
-            if (keep) row[base + __popcll(m & below)] = val[r];
-            else if (real) row[rest + __popcll(m2 & below)] = val[r];
-            base += __popcll(m);
-            rest += __popcll(m2);
-        }
-    }
-    if (lane == 0) {
-        cnt_all[i] = n;
-        cnt_out[i] = kept;
-        // what was left out is at or below the k'-th key if the cut dropped something, else at or below the row's
-        // fixed threshold; after an overflow nothing is known about it
-        thr_out[i] = overflow ? 0xFFFFFFFFu : (n > kprime ? (uint32_t)(t >> 32) : tbits[i]);
-    }
+    for (int r = threadIdx.x; r < log_rows; r += 1024)
+        if (row0 + r < C) cnt_str[row0 + r] = n_raw > logcap ? 0x7FFFFFFF : s_cnt[r]; // a lost record: all rows overflow
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -984,12 +1096,18 @@ __device__ __forceinline__ double gr_canon(const uint16_t *__restrict__ a, const
 }
 __device__ __forceinline__ double gr_canon(const float *__restrict__ a, const float *__restrict__ b, int D) {
     double acc = 0.0;
-    for (int d = 0; d < D; d += 4) {
-        float4 va = *(const float4 *)(a + d), vb = *(const float4 *)(b + d);
-        acc = __builtin_fma((double)va.x, (double)vb.x, acc);
-        acc = __builtin_fma((double)va.y, (double)vb.y, acc);
-        acc = __builtin_fma((double)va.z, (double)vb.z, acc);
-        acc = __builtin_fma((double)va.w, (double)vb.w, acc);
+    for (int d = 0; d < D; d += 32) { // whole 128-byte lines of b at a time, as above (D % 32 == 0)
+        float4 vb[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) vb[q] = *(const float4 *)(b + d + q * 4);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float4 va = *(const float4 *)(a + d + q * 4);
+            acc = __builtin_fma((double)va.x, (double)vb[q].x, acc);
+            acc = __builtin_fma((double)va.y, (double)vb[q].y, acc);
+            acc = __builtin_fma((double)va.z, (double)vb[q].z, acc);
+            acc = __builtin_fma((double)va.w, (double)vb[q].w, acc);
+        }
     }
     return acc;
 }
@@ -997,17 +1115,252 @@ __device__ __forceinline__ double gr_canon(const float *__restrict__ a, const fl
 __device__ __forceinline__ bool gr_ranks_before(double s, int32_t j, double t, int32_t k) {
     return s > t || (s == t && j < k);
 }
+// the value that lane `src` (uniform) holds, in scalar registers
+__device__ __forceinline__ double gr_readlane(double v, int src) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+#define GR_NO_ID 0x7FFFFFFF
+// rank[t] += the number of the first n (<= 64) lanes' entries (s2, id2) that rank before the lane's entry t
+template <int S>
+__device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, const double (&s)[S], const int32_t (&id)[S], int (&rank)[S]) {
+    for (int src = 0; src < n; ++src) {
+        const double os = gr_readlane(s2, src);
+        const int32_t oid = __builtin_amdgcn_readlane(id2, src);
+#pragma unroll
+        for (int t = 0; t < S; ++t) rank[t] += gr_ranks_before(os, oid, s[t], id[t]) ? 1 : 0;
+    }
+}
 
 // ------------------------------------------------------------------------------------------------
-// exact re-rank of the recalled candidates; one wavefront per row; kprime <= 256 (4 slots per lane)
+// exact ranking of the candidates; one wavefront per row, at most 64 * KP candidates ranked
+//
+// Build (HOP false): first K of the row's candidates.  Hop (HOP true): best K of candidates and list so far (ids of the
+// whole problem = visit_offset + row); a candidate that is in the list already is dropped.
+//
+// Ranked are the candidates whose 16-bit similarity lies no more than 2.5 error bounds below the K-th largest: K of them
+// are at least (K-th largest - bound) exactly, and what is left out is at most (that - 1.5 bounds).  That is K and a few
+// for bf16 rows (K and 16 or more were ranked before: 19.7 GB of gathered rows at 390,625 x 512, K = 32).  Where more than
+// 64 * KP lie that close, the best 64 * KP are ranked, and the certificate decides.
+// One kernel does what were three passes over the candidates (cut, re-rank, and before them a gather of the
+// segments): the keys are read once, and the row's own data and the other lanes' entries come through scalar registers
+// (the ranking by shuffles cost three LDS permutes and 24 instructions per entry, now three lane reads and 6).
+// ------------------------------------------------------------------------------------------------
+template <typename IN, int KP, bool HOP>
+__global__ void __launch_bounds__(GR_NT)
+gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, int64_t Cv, int D, int K, GrSegs seg,
+               const uint64_t *__restrict__ cand, const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str,
+               const uint32_t *__restrict__ tbits, const float *__restrict__ norms, const float *__restrict__ maxnorm, float gamma,
+               int64_t visit_offset, int32_t *__restrict__ graph, void *__restrict__ sims_, int32_t *list_count,
+               int32_t *__restrict__ list_rows) {
+    __shared__ uint64_t s_key[GR_NT / 64][KP * 64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + wave;
+    if (i >= C) return;
+    // the row's segments: lane s looks at segment s
+    const int nres = 2 * seg.parts, nseg = nres + (seg.stream > 0 ? 1 : 0);
+    int c = 0, c_max = seg.q;
+    if (lane < nres) c = cnt_res[i * nres + lane];
+    else if (lane < nseg) { c = cnt_str[i]; c_max = seg.stream; }
+    bool overflow = __ballot(c > c_max) != 0ull;
+    if (c > c_max) c = c_max;
+    const int incl = ks_wave_iscan(c), excl = incl - c;
+    int n = __builtin_amdgcn_readlane(incl, 63);
+    if (n > GR_MAX_CAND) { n = GR_MAX_CAND; overflow = true; }
+    const uint32_t tb = tbits[i];
+    const uint64_t *__restrict__ row = cand + i * seg.cap();
+    const double eps = (double)gamma * (double)norms[i] * (double)*maxnorm; // error bound of the 16-bit similarities
+    uint32_t thr = tb; // nothing above this value (as a key) was dropped
+    int kept = n;
+    // The keys to rank to LDS.  E: registers for the keys.  The m-th largest value by a bitwise search ("how many keys are
+    // >= this prefix": a compare, a ballot and a population count per register and round) below the bits that threshold
+    // and largest key share; it ends as soon as exactly m keys are left (a bound below the m-th and above the next).
+    auto select = [&](auto e_) __attribute__((always_inline)) {
+        constexpr int E = decltype(e_)::value;
+        uint64_t val[E];
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            val[r] = 0ull; // below every real key
+            if (r * 64 < n) {
+                const int idx = r * 64 + lane;
+                int adj = 0;
+                for (int sg = 1; sg < nseg; ++sg) {
+                    const int st = __builtin_amdgcn_readlane(excl, sg);
+                    if (idx >= st) adj = sg * seg.q - st;
+                }
+                if (idx < n) val[r] = row[idx + adj];
+            }
+        }
+        uint64_t t = 1ull; // keeps every real key
+        if (n > K) {
+            auto count_hi = [&](uint32_t v) __attribute__((always_inline)) {
+                int k = 0;
+#pragma unroll
+                for (int r = 0; r < E; ++r)
+                    if (E <= 8 || r * 64 < n) k += __popcll(__ballot((uint32_t)(val[r] >> 32) >= v));
+                return k;
+            };
+            uint32_t mx = 0u;
+#pragma unroll
+            for (int r = 0; r < E; ++r) mx = (uint32_t)(val[r] >> 32) > mx ? (uint32_t)(val[r] >> 32) : mx;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                const uint32_t other = (uint32_t)__shfl_xor((int)mx, o, 64);
+                mx = other > mx ? other : mx;
+            }
+            mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)mx);
+            const int top_bit = mx > tb ? 31 - __builtin_clz(mx ^ tb) : -1; // (always above: only such keys are appended)
+            const uint32_t prefix = top_bit >= 31 ? 0u : (top_bit < 0 ? mx : mx >> (top_bit + 1) << (top_bit + 1));
+            auto search = [&](int m, bool &exact) __attribute__((always_inline)) {
+                uint32_t v = prefix;
+                exact = false;
+                for (int bit = top_bit; bit >= 0 && !exact; --bit) {
+                    const int k = count_hi(v | (1u << bit));
+                    if (k >= m) v |= 1u << bit;
+                    exact = k == m;
+                }
+                return v;
+            };
+            bool exact;
+            const double low = (double)gr_unorder(search(K, exact)) - 2.5 * eps;
+            float f = (float)low;
+            if ((double)f > low) f = nextafterf(f, -INFINITY); // rounded down
+            uint32_t cut = f == f ? gr_orderable(f) : 0u;
+            if (cut > tb) {
+                kept = count_hi(cut);
+                t = (uint64_t)cut << 32;
+                thr = cut; // what was left out is below this
+            }
+            if (kept > KP * 64) {
+                cut = search(KP * 64, exact);
+                t = (uint64_t)cut << 32;
+                if (!exact) { // keys of equal value straddle the cut: the ids (the lower half of the keys) decide
+                    auto count_lo = [&](uint32_t v) __attribute__((always_inline)) {
+                        int k = 0;
+#pragma unroll
+                        for (int r = 0; r < E; ++r)
+                            if (E <= 8 || r * 64 < n) k += __popcll(__ballot((uint32_t)(val[r] >> 32) == cut && (uint32_t)val[r] >= v));
+                        return k;
+                    };
+                    const int need = KP * 64 - (cut == 0xFFFFFFFFu ? 0 : count_hi(cut + 1u));
+                    uint32_t t_lo = 0;
+                    for (int bit = 31; bit >= 0; --bit) {
+                        const uint32_t v = t_lo | (1u << bit);
+                        if (count_lo(v) >= need) t_lo = v;
+                    }
+                    t |= t_lo;
+                }
+                thr = cut; // what was left out is at or below this
+                kept = KP * 64;
+            }
+        }
+        int base = 0;
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            if (r * 64 < n) {
+                const bool keep = r * 64 + lane < n && val[r] >= t;
+                const uint64_t m = __ballot(keep);
+                const int q = base + __popcll(m & ((1ull << lane) - 1ull));
+                if (keep && q < KP * 64) s_key[wave][q] = val[r]; // (q < kept always)
+                base += __popcll(m);
+            }
+        }
+    };
+    if (n <= 512) select(std::integral_constant<int, 8>());
+    else select(std::integral_constant<int, GR_MAX_CAND / 64>());
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the keys written by the other lanes are in LDS
+    if (overflow) thr = 0xFFFFFFFFu; // nothing is known about what was left out
+
+    constexpr int S = KP + (HOP ? 1 : 0); // the last slot of a hop holds the list so far (K <= 64)
+    double s[S];
+    int32_t id[S];
+#pragma unroll
+    for (int t = 0; t < KP; ++t) {
+        const int q = t * 64 + lane;
+        s[t] = -INFINITY;
+        id[t] = GR_NO_ID;
+        if (q < kept) {
+            const uint32_t j = 0xFFFFFFFFu - (uint32_t)s_key[wave][q];
+            if (j < (uint64_t)Cv) { // always true for keys written by the recall pass
+                id[t] = (int32_t)(visit_offset + j);
+                s[t] = gr_canon(Wl + i * D, Wv + (int64_t)j * D, D);
+            }
+        }
+    }
+    if (HOP) {
+        s[KP] = -INFINITY;
+        id[KP] = GR_NO_ID;
+        if (lane < K) {
+            const int32_t g = graph[i * K + lane];
+            if (g >= 0) {
+                id[KP] = g;
+                s[KP] = ((const double *)sims_)[i * K + lane];
+            }
+        }
+        // a visiting row that is in the list already (a shard seen twice) is not a new candidate
+        for (int src = 0; src < K; ++src) {
+            const int32_t oid = __builtin_amdgcn_readlane(id[S - 1], src);
+            if (oid == GR_NO_ID) continue;
+#pragma unroll
+            for (int t = 0; t < KP; ++t)
+                if (id[t] == oid) {
+                    id[t] = GR_NO_ID;
+                    s[t] = -INFINITY;
+                }
+        }
+    }
+    // (entries without an id have similarity -inf and the largest id: they rank behind every real one)
+    int rank[S];
+#pragma unroll
+    for (int t = 0; t < S; ++t) rank[t] = 0;
+    int n_valid = 0;
+#pragma unroll
+    for (int t = 0; t < KP; ++t) {
+        const int here = kept - t * 64 < 64 ? kept - t * 64 : 64;
+        gr_count_before<S>(s[t], id[t], here, s, id, rank);
+        n_valid += __popcll(__ballot(id[t] != GR_NO_ID));
+    }
+    if (HOP) {
+        gr_count_before<S>(s[S - 1], id[S - 1], K, s, id, rank);
+        n_valid += __popcll(__ballot(id[S - 1] != GR_NO_ID));
+    }
+    bool certified = true;
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+        if (id[t] != GR_NO_ID && rank[t] < K) {
+            graph[i * K + rank[t]] = id[t];
+            if (HOP) ((double *)sims_)[i * K + rank[t]] = s[t];
+            else if (sims_) ((float *)sims_)[i * K + rank[t]] = (float)s[t];
+            if (rank[t] == K - 1) { // certificate: nothing that was dropped can reach the K-th exact similarity
+                certified = s[t] > (double)gr_unorder(thr) + eps;
+            }
+        }
+    }
+    // A threshold of -infinity dropped nothing (a sample of fewer rows than its rank: every row passed).
+    if (thr == gr_orderable(-INFINITY)) certified = true;
+    else if (n_valid < K) certified = false; // no K-th candidate to certify
+    if (HOP) {
+        for (int e = n_valid + lane; e < K; e += 64) { // fewer than K known so far: empty slots
+            graph[i * K + e] = -1;
+            ((double *)sims_)[i * K + e] = -INFINITY;
+        }
+    } else if (n_valid < K) {
+        certified = false;
+    }
+    if (__ballot(!certified) != 0ull && lane == 0) list_rows[atomicAdd(list_count, 1)] = (int32_t)i;
+}
+
+// ------------------------------------------------------------------------------------------------
+// the same for the passes with running thresholds (K > 64 or D > 512), whose candidates are cut to k' <= 256 already
 // ------------------------------------------------------------------------------------------------
 template <typename IN>
 __global__ void __launch_bounds__(GR_NT)
 gr_rerank_kernel(const IN *__restrict__ W, int64_t C, int D, int K, int cap, const uint64_t *__restrict__ cand,
                  const int32_t *__restrict__ cnt, const uint32_t *__restrict__ thr, const float *__restrict__ norms,
-                 const uint32_t *__restrict__ maxnorm_bits, float gamma, int32_t *__restrict__ graph,
+                 const float *__restrict__ maxnorm, float gamma, int32_t *__restrict__ graph,
                  float *__restrict__ sims, int32_t *fb_count, int32_t *__restrict__ fb_rows) {
-    const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + (threadIdx.x >> 6);
+    const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (i >= C) return;
     const int lane = threadIdx.x & 63;
     const int n = cnt[i];
@@ -1018,7 +1371,7 @@ gr_rerank_kernel(const IN *__restrict__ W, int64_t C, int D, int K, int cap, con
     for (int t = 0; t < 4; ++t) {
         const int q = t * 64 + lane;
         s[t] = -INFINITY;
-        id[t] = 0x7FFFFFFF;
+        id[t] = GR_NO_ID;
         if (q < n) {
             const uint32_t j = 0xFFFFFFFFu - (uint32_t)cand[i * cap + q];
             if (j < (uint32_t)C) { // always true for keys written by the recall pass
@@ -1028,19 +1381,8 @@ gr_rerank_kernel(const IN *__restrict__ W, int64_t C, int D, int K, int cap, con
         }
     }
     int rank[4] = {0, 0, 0, 0};
-    const int slots = (n + 63) >> 6;
-    for (int t2 = 0; t2 < slots; ++t2) {
-        double s2 = t2 == 0 ? s[0] : (t2 == 1 ? s[1] : (t2 == 2 ? s[2] : s[3]));
-        int32_t id2 = t2 == 0 ? id[0] : (t2 == 1 ? id[1] : (t2 == 2 ? id[2] : id[3]));
-        for (int src = 0; src < 64; ++src) {
-            const double os = __shfl(s2, src, 64);
-            const int32_t oid = __shfl(id2, src, 64);
-            if (t2 * 64 + src < n) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) rank[t] += gr_ranks_before(os, oid, s[t], id[t]) ? 1 : 0;
-            }
-        }
-    }
+    for (int t = 0; t < 4; ++t) gr_count_before<4>(s[t], id[t], n - t * 64 < 64 ? n - t * 64 : 64, s, id, rank);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const int q = t * 64 + lane;
@@ -1052,7 +1394,7 @@ gr_rerank_kernel(const IN *__restrict__ W, int64_t C, int D, int K, int cap, con
                 const uint32_t th = thr[i];
                 bool certified = (th == 0u); // nothing was ever dropped
                 if (!certified) {
-                    const double eps = (double)gamma * (double)norms[i] * (double)__uint_as_float(*maxnorm_bits);
+                    const double eps = (double)gamma * (double)norms[i] * (double)*maxnorm;
                     certified = s[t] > (double)gr_unorder(th) + eps;
                 }
                 if (!certified) fb_rows[atomicAdd(fb_count, 1)] = (int32_t)i;
@@ -1118,60 +1460,65 @@ gr_exhaustive_kernel(const IN *__restrict__ W, int64_t C, int D, int K, const in
 }
 
 // ------------------------------------------------------------------------------------------------
-// Second chance for rows that the re-rank could not certify, after the pass that computes every similarity once: that pass
-// leaves ALL rows above the row's fixed threshold in its buffer (some 400), not only the k' best, so the row is ranked
-// again over all of them, and the certificate is taken against the fixed threshold, which lies far below the K-th
-// neighbour.  It is what keeps tight clusters cheap: with hundreds of neighbours 2e-6 apart no k' of a few dozen
-// spans the error bound, and the exhaustive search costs such a row 30 ms.  One wavefront per row; rows that still
-// fail (a buffer overflowed; ties at the fixed threshold) go to the exhaustive list.
+// Second chance for rows that the ranking of the k' best could not certify: the segments hold ALL rows above the row's
+// fixed threshold (some 400), so the row is ranked again over all of them, and the certificate is taken against the fixed
+// threshold, which lies far below the K-th neighbour.  It is what keeps tight clusters cheap: with hundreds of neighbours
+// 2e-6 apart no k' of a few dozen spans the error bound, and the exhaustive search costs such a row 30 ms.  One wavefront
+// per row; rows that still fail (a segment overflowed; ties at the fixed threshold) go to the exhaustive list.
 // ------------------------------------------------------------------------------------------------
 template <typename IN>
 __global__ void __launch_bounds__(GR_NT)
-gr_sym_second_kernel(const IN *__restrict__ W, int64_t C, int D, int K, const uint64_t *__restrict__ cand,
-                     const int32_t *__restrict__ cnt_all, const uint32_t *__restrict__ thr, const uint32_t *__restrict__ tbits,
-                     const float *__restrict__ norms, const uint32_t *__restrict__ maxnorm_bits, float gamma,
-                     const int32_t *__restrict__ list_count, const int32_t *__restrict__ list_rows, int32_t *__restrict__ graph,
-                     float *__restrict__ sims, int32_t *fb_count, int32_t *__restrict__ fb_rows) {
-    __shared__ double s_s[GR_NT / 64][GR_SYM_CAP];
-    __shared__ int32_t s_id[GR_NT / 64][GR_SYM_CAP];
+gr_second_kernel(const IN *__restrict__ W, int64_t C, int D, int K, GrSegs seg, const uint64_t *__restrict__ cand,
+                 const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str, const uint32_t *__restrict__ tbits,
+                 const float *__restrict__ norms, const float *__restrict__ maxnorm, float gamma,
+                 const int32_t *__restrict__ list_count, const int32_t *__restrict__ list_rows, int32_t *__restrict__ graph,
+                 float *__restrict__ sims, int32_t *fb_count, int32_t *__restrict__ fb_rows) {
+    __shared__ double s_s[GR_NT / 64][GR_MAX_CAND];
+    __shared__ int32_t s_id[GR_NT / 64][GR_MAX_CAND];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nres = 2 * seg.parts, nseg = nres + (seg.stream > 0 ? 1 : 0);
     int64_t n_list = *list_count;
     if (n_list > C) n_list = C;
     for (int64_t e0 = (int64_t)blockIdx.x * (GR_NT / 64); e0 < n_list; e0 += (int64_t)gridDim.x * (GR_NT / 64)) {
         const int64_t e = e0 + wave;
         const int64_t i = e < n_list ? list_rows[e] : -1;
-        const bool usable = i >= 0 && thr[i] != 0xFFFFFFFFu; // (an overflowed buffer does not hold everything above the threshold)
-        const int n = usable ? (cnt_all[i] < GR_SYM_CAP ? cnt_all[i] : GR_SYM_CAP) : 0;
-        int n_valid = 0;
-        for (int q0 = 0; q0 < n; q0 += 64) {
-            const int q = q0 + lane;
-            double sv = -INFINITY;
-            int32_t id = 0x7FFFFFFF;
-            if (q < n) {
-                const uint32_t j = 0xFFFFFFFFu - (uint32_t)cand[i * GR_SYM_CAP + q];
+        bool usable = i >= 0; // (an overflowed segment does not hold everything above the threshold)
+        int n = 0, n_valid = 0;
+        for (int sg = 0; sg < nseg && usable; ++sg) {
+            const int c = sg < nres ? cnt_res[i * nres + sg] : cnt_str[i];
+            if (c > (sg < nres ? seg.q : seg.stream) || n + c > GR_MAX_CAND) {
+                usable = false;
+                break;
+            }
+            for (int q = lane; q < c; q += 64) {
+                double sv = -INFINITY;
+                int32_t id = GR_NO_ID;
+                const uint32_t j = 0xFFFFFFFFu - (uint32_t)cand[i * seg.cap() + sg * seg.q + q];
                 if (j < (uint32_t)C && (int64_t)j != i) { // always true for keys written by the recall pass
                     id = (int32_t)j;
                     sv = gr_canon(W + i * D, W + (int64_t)j * D, D);
+                    ++n_valid;
                 }
-                s_s[wave][q] = sv;
-                s_id[wave][q] = id;
+                s_s[wave][n + q] = sv;
+                s_id[wave][n + q] = id;
             }
-            n_valid += __popcll(__ballot(id != 0x7FFFFFFF));
+            n += c;
         }
+        n_valid = ks_wave_sum_i(n_valid);
         __syncthreads();
         bool certified = usable && n_valid >= K;
         if (certified) {
             for (int q = lane; q < n; q += 64) {
                 const double sv = s_s[wave][q];
                 const int32_t id = s_id[wave][q];
-                if (id == 0x7FFFFFFF) continue;
+                if (id == GR_NO_ID) continue;
                 int rank = 0;
                 for (int p = 0; p < n && rank < K; ++p) rank += gr_ranks_before(s_s[wave][p], s_id[wave][p], sv, id) ? 1 : 0;
                 if (rank < K) {
                     graph[i * K + rank] = id;
                     if (sims) sims[i * K + rank] = (float)sv;
                     if (rank == K - 1) {
-                        const double eps = (double)gamma * (double)norms[i] * (double)__uint_as_float(*maxnorm_bits);
+                        const double eps = (double)gamma * (double)norms[i] * (double)*maxnorm;
                         if (!(sv > (double)gr_unorder(tbits[i]) + eps)) certified = false;
                     }
                 }
@@ -1185,72 +1532,125 @@ gr_sym_second_kernel(const IN *__restrict__ W, int64_t C, int D, int K, const ui
 // ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
+static unsigned gr_sym_shares(int64_t C) { return (unsigned)ks_ceil_div(C, 256); } // a share per block of resident rows
+static int gr_sym_chunks_stride(int64_t C) { // chunks of a share at most: half of all groups, half of its own, a spare
+    const int64_t nsb = ks_ceil_div(C, GR_SYM_SB), GS = gr_sym_group_sbs(C), NG = ks_ceil_div(nsb, GS);
+    return (int)(((NG / 2) * GS + GS / 2 + 2) * (GR_SYM_SB / 96));
+}
+// Fixed thresholds serve K <= 64 (a row with few candidates keeps them all and is certified against its fixed threshold).
+// The resident rows' fragments of a depth beyond
+// 512 do not fit in registers.  A row id has 22 bits in the stream side's records; beyond them (and for lists that no
+// device memory holds twice) the running thresholds stay.
+static bool gr_use_fixed(int64_t Cr, int64_t Cs, int D, int K) {
+    return K <= 64 && D <= 512 && Cr <= ((int64_t)1 << 22) && Cs <= ((int64_t)1 << 22);
+}
+// The division of the symmetric sweep exists from 6,144 rows on; it is used from C * D = 15 million on.  Below, the passes
+// over both halves of the pairs (gr_recall_fix_kernel) are faster: the matrix cores idle anyway, and what costs is the
+// epilogue's work per hit, of which the stream side's is the dearer one (10,000 x 128: 148 against 170 us; 30,000 x 512:
+// 1.17 against 1.03 ms; 65,000 x 256: 2.47 against 2.43; 100,000 x 128: 4.13 against 4.29).
+static bool gr_has_sym(int64_t C, int D, int K) {
+    return (D == 128 || D == 256 || D == 512) && gr_use_fixed(C, C, D, K) && C >= 6144;
+}
+static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && C * D >= 15000000; }
+// Parts that the streamed chunks of each of nb blocks are cut into: the number with the least estimated time on the
+// chip's compute units (rounds of workgroups x (set-up + chunks of a part); set-up 6 us and a chunk of 96 rows 1.2 us,
+// 0.5 and 0.4 us more per k-tile: measured on the sweeps).  Bounded by memory: a part costs every row two segments.
+static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
+    const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 1.2 + 0.4 * kt;
+    int64_t most = ((int64_t)1 << 19) / C; // 4 GiB of segments
+    if (most > GR_MAX_PARTS) most = GR_MAX_PARTS;
+    if (most > chunks) most = chunks;
+    int best = 1;
+    double best_t = 0.0;
+    for (int p = 1; p <= most || p == 1; ++p) {
+        const double t = (double)ks_ceil_div(nb * p, GR_CUS) * (setup + (double)ks_ceil_div(chunks, p) * per_chunk);
+        if (p == 1 || t < 0.98 * best_t) { best = p; best_t = t; }
+    }
+    return best;
+}
+static int gr_rank_of(int K) { return K <= 16 ? 8 : (K <= 32 ? 10 : GR_SYM_RANK); }
+
+// how a pass with fixed thresholds divides its work and a row's segments
+struct GrFixPlan {
+    GrSegs seg;
+    int part_rows;        // streamed rows per part (not the symmetric sweep)
+    int log_rows, logs;   // symmetric sweep: rows per log, number of logs
+};
+static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, bool sym) {
+    GrFixPlan f;
+    const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(Cs, 96);
+    f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
+    f.seg.q = GR_SYM_Q;
+    f.seg.stream = sym ? GR_SYM_SCAP : 0;
+    f.part_rows = (int)ks_ceil_div(chunks, f.seg.parts) * 96;
+    if (!sym) f.seg.parts = (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
+    while (!sym && f.seg.q > 64 && f.seg.q / 2 >= f.part_rows / 2) f.seg.q /= 2; // a lane sees half of the part's rows
+    f.log_rows = GR_SYM_SB;
+    f.logs = 0;
+    if (sym) {
+        // a wavefront finds about 96 * 32 * 384 / C stream-side hits per chunk: logs of as few chunks as still give it a
+        // batch's worth, so that small problems have a log for every compute unit in the scatter kernel
+        while (f.log_rows > 96 && (double)(f.log_rows / 2) * 32.0 * 384.0 / (double)Cs >= 96.0) f.log_rows /= 2;
+        f.logs = (int)ks_ceil_div(Cr, f.log_rows);
+    }
+    return f;
+}
+
 struct GrWs {
     uint16_t *Wb;
-    float *norms;
-    uint32_t *maxnorm;
+    float *norms, *blockmax, *maxnorm;
     uint64_t *cand;
-    int32_t *cnt;
-    uint32_t *thr;
     int32_t *fb_count;
     int32_t *fb_rows;
     double *scratch;
-    // the pass that computes every similarity once (gr_sym_*), when it is used
+    // running thresholds
+    int32_t *cnt;
+    uint32_t *thr;
+    // fixed thresholds
     uint16_t *Ws;      // sampled rows
-    float *thf;        // fixed thresholds
+    float *thf;
     uint32_t *tbits;
-    int32_t *cnt_res, *cnt_str, *cnt_all, *logcnt, *plan;
-    int32_t *second_count, *second_rows; // rows for gr_sym_second_kernel
+    int32_t *cnt_res, *cnt_str;
+    int32_t *second_count, *second_rows; // rows for gr_second_kernel
+    // every similarity computed once
+    int32_t *logcnt, *plan;
     int2 *chunks;
     uint2 *log;
 };
 
-static unsigned gr_sym_grid(int64_t C) { // workgroups of the sweep: whole groups, dealt to the eight XCDs
-    const int nsb = (int)ks_ceil_div(C, GR_SYM_SB), GS = gr_sym_group_sbs(C), NG = (nsb + GS - 1) / GS;
-    return (unsigned)((NG + 7) / 8) * (unsigned)(GS * 3) * 8u;
-}
-static int gr_sym_chunks_stride(int64_t C) { // chunks a workgroup streams at most: half of all groups, half of its own, a spare
-    const int64_t nsb = ks_ceil_div(C, GR_SYM_SB), GS = gr_sym_group_sbs(C), NG = ks_ceil_div(nsb, GS);
-    return (int)(((NG / 2) * GS + GS / 2 + 2) * (GR_SYM_SB / 96));
-}
-// The pass that computes every similarity once pays off for problems of more than a few thousand rows.  A row's fixed
-// threshold leaves 32 * Gamma(12) candidates (384 on average, fewer than 64 for one row in 10^7), which serves K <= 64:
-// a row with fewer than k' candidates keeps them all and is certified against its fixed threshold.  A row id has 22
-// bits in the stream side's records.
-static bool gr_use_sym(int64_t C, int D, const GrParams &p) {
-    return (D == 128 || D == 256 || D == 512) && p.kprime <= 128 && C >= 6144 && C <= ((int64_t)1 << 22);
-}
-
 static GrWs gr_carve(void *ws, int64_t C, int D, int K, int dtype, size_t *total) {
     KsArena ar(ws);
     GrParams p = gr_params(K, D);
-    const GrParams pd = gr_params(K, D, dtype);
-    const bool sym = gr_use_sym(C, D, pd);
-    GrWs w;
+    const bool fixed = gr_use_fixed(C, C, D, K), sym = gr_use_sym(C, D, K);
+    GrWs w = GrWs();
     w.Wb = dtype == KS_DTYPE_FP32 ? ar.take<uint16_t>((size_t)C * D) : nullptr;
     w.norms = ar.take<float>((size_t)C);
-    w.maxnorm = ar.take<uint32_t>(1);
-    w.cand = ar.take<uint64_t>((size_t)C * (sym ? GR_SYM_CAP : p.cap));
-    w.cnt = ar.take<int32_t>((size_t)C);
-    w.thr = ar.take<uint32_t>((size_t)C);
+    w.blockmax = ar.take<float>(GR_PREP_BLOCKS);
+    w.maxnorm = ar.take<float>(1);
     w.fb_count = ar.take<int32_t>(1);
     w.fb_rows = ar.take<int32_t>((size_t)C);
     w.scratch = ar.take<double>((size_t)GR_FB_BLOCKS * C);
-    w.Ws = nullptr; w.thf = nullptr; w.tbits = nullptr; w.cnt_res = w.cnt_str = w.cnt_all = w.logcnt = w.plan = w.second_count = w.second_rows = nullptr; w.chunks = nullptr; w.log = nullptr;
-    if (sym) {
-        const int64_t nsb = ks_ceil_div(C, GR_SYM_SB), Cpad = nsb * GR_SYM_SB + 96;
+    if (!fixed) {
+        w.cand = ar.take<uint64_t>((size_t)C * p.cap);
+        w.cnt = ar.take<int32_t>((size_t)C);
+        w.thr = ar.take<uint32_t>((size_t)C);
+    } else {
+        const GrFixPlan f = gr_fix_plan(C, C, D, K, sym);
+        const int64_t Cpad = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
+        w.cand = ar.take<uint64_t>((size_t)C * f.seg.cap());
         w.Ws = ar.take<uint16_t>((size_t)(C / GR_SYM_RATIO) * D);
         w.thf = ar.take<float>((size_t)Cpad);
         w.tbits = ar.take<uint32_t>((size_t)C);
-        w.cnt_res = ar.take<int32_t>((size_t)C * 2);
-        w.cnt_str = ar.take<int32_t>((size_t)C);
-        w.cnt_all = ar.take<int32_t>((size_t)C);
+        w.cnt_res = ar.take<int32_t>((size_t)C * 2 * f.seg.parts);
         w.second_count = ar.take<int32_t>(1);
         w.second_rows = ar.take<int32_t>((size_t)C);
-        w.logcnt = ar.take<int32_t>((size_t)nsb);
-        w.plan = ar.take<int32_t>((size_t)gr_sym_grid(C) * GR_SYM_PLAN);
-        w.chunks = ar.take<int2>((size_t)gr_sym_grid(C) * gr_sym_chunks_stride(C));
-        w.log = ar.take<uint2>((size_t)nsb * GR_SYM_LOGCAP);
+        if (sym) {
+            w.cnt_str = ar.take<int32_t>((size_t)C);
+            w.logcnt = ar.take<int32_t>((size_t)f.logs);
+            w.plan = ar.take<int32_t>((size_t)gr_sym_shares(C) * GR_SYM_PLAN);
+            w.chunks = ar.take<int2>((size_t)gr_sym_shares(C) * gr_sym_chunks_stride(C));
+            w.log = ar.take<uint2>((size_t)f.logs * f.log_rows * GR_SYM_LOG_PER_ROW);
+        }
     }
     if (total) *total = ar.off;
     return w;
@@ -1268,8 +1668,8 @@ extern "C" int knn_graph_build_plan(int64_t C, int D, int K, int dtype, int work
     int rc = gr_check(C, D, K, dtype);
     if (rc != KS_OK) return rc;
     *n_workgroups = 0;
-    if (!gr_use_sym(C, D, gr_params(K, D, dtype))) return KS_OK;
-    *n_workgroups = (int32_t)gr_sym_grid(C);
+    if (!gr_has_sym(C, D, K)) return KS_OK;
+    *n_workgroups = (int32_t)gr_sym_shares(C);
     if (!out) return KS_OK;
     if (workgroup < 0 || workgroup >= *n_workgroups) return KS_INVALID_ARG;
     const GrSymRanges r = gr_sym_ranges(workgroup, (int)C, gr_sym_group_sbs(C));
@@ -1295,18 +1695,63 @@ extern "C" size_t knn_graph_build_workspace(int64_t C, int D, int K, int dtype) 
     return total;
 }
 
-template <typename IN>
-static void gr_launch_exact(const IN *W, int64_t C, int D, int K, const GrParams &p, const GrWs &w, float gamma,
-                            int32_t *graph, float *sims, hipStream_t st, bool second_chance) {
-    // (after the pass that computes every similarity once, uncertified rows get a second chance before the exhaustive list)
-    hipLaunchKernelGGL(gr_rerank_kernel<IN>, dim3((unsigned)ks_ceil_div(C, GR_NT / 64)), dim3(GR_NT), 0, st, W, C, D, K, p.cap,
-                       w.cand, w.cnt, w.thr, w.norms, w.maxnorm, gamma, graph, sims, second_chance ? w.second_count : w.fb_count,
-                       second_chance ? w.second_rows : w.fb_rows);
-    if (second_chance)
-        hipLaunchKernelGGL(gr_sym_second_kernel<IN>, dim3(1024), dim3(GR_NT), 0, st, W, C, D, K, w.cand, w.cnt_all, w.thr, w.tbits,
-                           w.norms, w.maxnorm, gamma, w.second_count, w.second_rows, graph, sims, w.fb_count, w.fb_rows);
-    hipLaunchKernelGGL(gr_exhaustive_kernel<IN>, dim3(GR_FB_BLOCKS), dim3(GR_NT), 0, st, W, C, D, K, w.fb_count, w.fb_rows,
-                       w.scratch, graph, sims);
+static GrPrepJob gr_prep_job(const void *W, int64_t C, int D, int dtype, uint16_t *Wb, float *norms, float *blockmax, uint16_t *Ws) {
+    GrPrepJob j;
+    j.W = W;
+    j.C = C;
+    j.Wb = Wb;
+    j.norms = norms;
+    j.blockmax = blockmax;
+    j.Ws = Ws;
+    j.n_sample = Ws ? C / GR_SYM_RATIO : 0;
+    // four row groups per wavefront: a wavefront takes 64 / (lanes per row) rows at a time
+    const int pieces = D * (dtype == KS_DTYPE_BF16 ? 2 : 4) / 16;
+    int64_t rows = 64 / (pieces > 32 ? 64 : (pieces > 16 ? 32 : (pieces > 8 ? 16 : (pieces > 4 ? 8 : 4)))) * (GR_NT / 64) * 2;
+    const int64_t b = ks_ceil_div(C, rows);
+    j.blocks = (int)(b < GR_PREP_BLOCKS ? b : GR_PREP_BLOCKS);
+    return j;
+}
+static void gr_launch_prepare(const GrPrepJob &j0, const GrPrepJob &j1, int D, int dtype, const GrClear &clr, hipStream_t st) {
+    const dim3 grid((unsigned)(j0.blocks + j1.blocks));
+    if (dtype == KS_DTYPE_FP32) hipLaunchKernelGGL(gr_prepare_kernel<float>, grid, dim3(GR_NT), 0, st, j0, j1, D, clr);
+    else hipLaunchKernelGGL(gr_prepare_kernel<uint16_t>, grid, dim3(GR_NT), 0, st, j0, j1, D, clr);
+}
+
+// Sweeps of a depth of KT k-tiles (D <= 512, D % 32 == 0): F(CFG) is instantiated for the depth's stage shape
+#define GR_FOR_DEPTH(F)                                                                                     \
+    do {                                                                                                    \
+        const int kt = (D + 63) / 64;                                                                       \
+        if (D % 64 == 0) {                                                                                  \
+            if (kt == 1) F(GrSoe<1 COMMA false>); else if (kt == 2) F(GrSoe<2 COMMA false>);                \
+            else if (kt == 3) F(GrSoe<3 COMMA false>); else if (kt == 4) F(GrSoe<4 COMMA false>);           \
+            else if (kt == 5) F(GrSoe<5 COMMA false>); else if (kt == 6) F(GrSoe<6 COMMA false>);           \
+            else if (kt == 7) F(GrSoe<7 COMMA false>); else F(GrSoe<8 COMMA false>);                        \
+        } else {                                                                                            \
+            if (kt == 1) F(GrSoe<1 COMMA true>); else if (kt == 2) F(GrSoe<2 COMMA true>);                  \
+            else if (kt == 3) F(GrSoe<3 COMMA true>); else if (kt == 4) F(GrSoe<4 COMMA true>);             \
+            else if (kt == 5) F(GrSoe<5 COMMA true>); else if (kt == 6) F(GrSoe<6 COMMA true>);             \
+            else if (kt == 7) F(GrSoe<7 COMMA true>); else F(GrSoe<8 COMMA true>);                          \
+        }                                                                                                   \
+    } while (0)
+#define COMMA ,
+
+static void gr_launch_threshold(const uint16_t *R, int64_t Cr, const uint16_t *Ws, int64_t n_sample, int D, int K, const float *blockmax,
+                                int n_blockmax, float *maxnorm, const GrHop &hop, float *thf, uint32_t *tbits, hipStream_t st) {
+    const dim3 grid((unsigned)ks_ceil_div(Cr, 256));
+#define GR_THR_LAUNCH(CFG)                                                                                                    \
+    hipLaunchKernelGGL((gr_threshold_kernel<CFG>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, gr_rank_of(K), blockmax, \
+                       n_blockmax, maxnorm, hop, thf, tbits)
+    GR_FOR_DEPTH(GR_THR_LAUNCH);
+#undef GR_THR_LAUNCH
+}
+static void gr_launch_recall_fix(const GrPair &pr, int D, const GrFixPlan &f, const float *thf, uint64_t *cand, int32_t *cnt_res,
+                                 hipStream_t st) {
+    const int nb = (int)ks_ceil_div(pr.Cr, 256);
+    const dim3 grid((unsigned)(nb * f.seg.parts));
+#define GR_FIX_LAUNCH(CFG) \
+    hipLaunchKernelGGL((gr_recall_fix_kernel<CFG>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, thf, cand, cnt_res)
+    GR_FOR_DEPTH(GR_FIX_LAUNCH);
+#undef GR_FIX_LAUNCH
 }
 
 // thr_init (optional, honoured by the sweep kernel only, may be `thr`): per row the value bits of a similarity at or below
@@ -1343,44 +1788,27 @@ static void gr_launch_recall(const GrPair &pr, int D, const GrParams &p, uint64_
     }
 }
 
-// W searched in W with every similarity computed once: thresholds from a sample, the sweep, the stream side's records
-// to their rows, the cut to k'
-static void gr_launch_recall_sym(const uint16_t *Wb, int64_t C, int D, int K, const GrParams &p, const GrWs &w, hipStream_t st) {
-    const int ratio = GR_SYM_RATIO;
-    const int64_t n_sample = C / ratio;
-    const int nsb = (int)ks_ceil_div(C, GR_SYM_SB);
-    const int64_t Cpad = (int64_t)nsb * GR_SYM_SB + 96;
-    hipLaunchKernelGGL(gr_sym_sample_kernel, dim3((unsigned)ks_ceil_div(n_sample, GR_NT / 64)), dim3(GR_NT), 0, st, Wb, C, D, ratio,
-                       n_sample, w.Ws);
-    // the sample is searched with the kernel of the plain pass: GR_SYM_RANK kept, no row is "the row itself" (the
-    // sample may hold it; it counts like any other row)
-    GrParams ps = p;
-    ps.kprime = GR_SYM_RANK;
-    ps.cap = 256;
-    const GrPair pr{Wb, C, w.Ws, n_sample, -((int64_t)1 << 40)};
-    gr_launch_recall(pr, D, ps, w.cand, w.cnt, w.thr, st);
-    hipLaunchKernelGGL(gr_sym_prep_kernel, dim3((unsigned)ks_ceil_div(Cpad, GR_NT)), dim3(GR_NT), 0, st, w.thr, C, Cpad, w.thf,
-                       w.tbits, w.logcnt, nsb, w.second_count);
-    const unsigned grid = gr_sym_grid(C);
+// W searched in W with every similarity computed once: the sweep, the stream side's records to their rows
+static void gr_launch_recall_sym(const uint16_t *Wb, int64_t C, int D, const GrFixPlan &f, const GrWs &w, hipStream_t st) {
+    const unsigned shares = gr_sym_shares(C), grid = shares * (unsigned)f.seg.parts;
     const int stride = gr_sym_chunks_stride(C);
-    hipLaunchKernelGGL(gr_sym_plan_kernel, dim3(grid), dim3(GR_NT), 0, st, (int)C, gr_sym_group_sbs(C), w.plan, w.chunks, stride);
-    if (D == 512)
-        hipLaunchKernelGGL((gr_recall_sym_kernel<8>), dim3(grid), dim3(512), 0, st, Wb, (int)C, D, w.plan, w.chunks, stride, w.thf, w.cand,
-                           w.cnt_res, w.log, w.logcnt);
-    else if (D == 256)
-        hipLaunchKernelGGL((gr_recall_sym_kernel<4>), dim3(grid), dim3(512), 0, st, Wb, (int)C, D, w.plan, w.chunks, stride, w.thf, w.cand,
-                           w.cnt_res, w.log, w.logcnt);
-    else
-        hipLaunchKernelGGL((gr_recall_sym_kernel<2>), dim3(grid), dim3(512), 0, st, Wb, (int)C, D, w.plan, w.chunks, stride, w.thf, w.cand,
-                           w.cnt_res, w.log, w.logcnt);
-    hipLaunchKernelGGL(gr_sym_scatter_kernel, dim3((unsigned)nsb), dim3(1024), 0, st, w.log, w.logcnt, (int)C, w.tbits, w.cand,
-                       w.cnt_str);
-    // (Handing the re-rank only K + 8 candidates of bf16 rows saves it 0.6 of 5.2 ms at the headline size, and costs rows
-    // of tight clusters their certificate: with neighbours 2e-5 apart, eight of them span less than the error bound for
-    // four rows in ten, and an uncertified row costs a millisecond.)
-    const int kept = p.kprime;
-    hipLaunchKernelGGL(gr_sym_select_kernel, dim3((unsigned)ks_ceil_div(C, GR_NT / 64)), dim3(GR_NT), 0, st, C, kept, w.cand,
-                       w.cnt_res, w.cnt_str, w.tbits, w.cnt, w.thr, w.cnt_all);
+    hipLaunchKernelGGL(gr_sym_plan_kernel, dim3(shares), dim3(GR_NT), 0, st, (int)C, gr_sym_group_sbs(C), w.plan, w.chunks, stride);
+    const bool split = f.seg.parts > 1 || f.log_rows != GR_SYM_SB;
+#define GR_SYM_LAUNCH2(KT, SPLIT)                                                                                              \
+    hipLaunchKernelGGL((gr_recall_sym_kernel<KT, SPLIT>), dim3(grid), dim3(512), 0, st, Wb, (int)C, D, w.plan, w.chunks, stride, \
+                       f.seg.parts, f.log_rows, w.thf, w.cand, w.cnt_res, w.log, w.logcnt)
+#define GR_SYM_LAUNCH(KT)                        \
+    do {                                         \
+        if (split) GR_SYM_LAUNCH2(KT, true);     \
+        else GR_SYM_LAUNCH2(KT, false);          \
+    } while (0)
+    if (D == 512) GR_SYM_LAUNCH(8);
+    else if (D == 256) GR_SYM_LAUNCH(4);
+    else GR_SYM_LAUNCH(2);
+#undef GR_SYM_LAUNCH
+#undef GR_SYM_LAUNCH2
+    hipLaunchKernelGGL(gr_sym_scatter_kernel, dim3((unsigned)f.logs), dim3(1024), 0, st, w.log, w.logcnt, (int)C, f.log_rows, f.seg,
+                       w.cand, w.cnt_str);
 }
 
 // error bound of the recall pass relative to |w_i||w_j|: fp32 accumulation of D exact bf16 products
@@ -1390,6 +1818,22 @@ static float gr_gamma(int D, int dtype) {
     float gamma = (float)D * 1.1920929e-7f * 1.01f;
     if (dtype == KS_DTYPE_FP32) gamma += 0.0042f;
     return gamma;
+}
+
+// ranking of the candidates, and the second chance of the rows that it could not certify
+template <typename IN>
+static void gr_launch_rank(const IN *W, int64_t C, int D, int K, const GrFixPlan &f, const GrWs &w, float gamma,
+                           int32_t *graph, float *sims, hipStream_t st) {
+    const dim3 grid((unsigned)ks_ceil_div(C, GR_NT / 64));
+#define GR_RANK_LAUNCH(KP)                                                                                                     \
+    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, false>), grid, dim3(GR_NT), 0, st, W, C, W, C, D, K, f.seg, w.cand,               \
+                       w.cnt_res, w.cnt_str, w.tbits, w.norms, w.maxnorm, gamma, (int64_t)0, graph, (void *)sims, w.second_count, \
+                       w.second_rows)
+    if (K <= 32) GR_RANK_LAUNCH(1);
+    else GR_RANK_LAUNCH(2);
+#undef GR_RANK_LAUNCH
+    hipLaunchKernelGGL(gr_second_kernel<IN>, dim3(1024), dim3(GR_NT), 0, st, W, C, D, K, f.seg, w.cand, w.cnt_res, w.cnt_str, w.tbits,
+                       w.norms, w.maxnorm, gamma, w.second_count, w.second_rows, graph, sims, w.fb_count, w.fb_rows);
 }
 
 extern "C" int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K, int32_t *graph, float *sims, void *ws,
@@ -1403,31 +1847,46 @@ extern "C" int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K
     if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
     const GrParams p = gr_params(K, D, dtype);
     hipStream_t st = (hipStream_t)stream;
-
-    hipLaunchKernelGGL(gr_zero_kernel, dim3(1), dim3(1), 0, st, w.maxnorm, w.fb_count);
-    const unsigned row_blocks = (unsigned)ks_ceil_div(C, GR_NT / 64);
-    const uint16_t *Wb;
-    if (dtype == KS_DTYPE_FP32) {
-        hipLaunchKernelGGL(gr_prepare_kernel<float>, dim3(row_blocks), dim3(GR_NT), 0, st, (const float *)W, C, D, w.Wb,
-                           w.norms, w.maxnorm);
-        Wb = w.Wb;
-    } else {
-        hipLaunchKernelGGL(gr_prepare_kernel<uint16_t>, dim3(row_blocks), dim3(GR_NT), 0, st, (const uint16_t *)W, C, D,
-                           (uint16_t *)nullptr, w.norms, w.maxnorm);
-        Wb = (const uint16_t *)W;
-    }
-    GrParams pe = p; // what the exact stage reads
-    const bool sym = gr_use_sym(C, D, p);
+    const bool fixed = gr_use_fixed(C, C, D, K), sym = gr_use_sym(C, D, K);
+    const GrFixPlan f = gr_fix_plan(C, C, D, K, sym);
+    GrClear clr = GrClear();
+    clr.fb_count = w.fb_count;
+    if (fixed) clr.second_count = w.second_count;
     if (sym) {
-        gr_launch_recall_sym(Wb, C, D, K, p, w, st);
-        pe.cap = GR_SYM_CAP;
-    } else {
-        const GrPair pr{Wb, C, Wb, C, 0};
-        gr_launch_recall(pr, D, p, w.cand, w.cnt, w.thr, st);
+        clr.logcnt = w.logcnt;
+        clr.nlog = f.logs;
+        clr.thf = w.thf;
+        clr.pad0 = C;
+        clr.pad1 = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
     }
+    const GrPrepJob job = gr_prep_job(W, C, D, dtype, w.Wb, w.norms, w.blockmax, fixed ? w.Ws : nullptr);
+    gr_launch_prepare(job, GrPrepJob(), D, dtype, clr, st);
+    const uint16_t *Wb = dtype == KS_DTYPE_FP32 ? w.Wb : (const uint16_t *)W;
+    const GrPair pr{Wb, C, Wb, C, 0};
     const float gamma = gr_gamma(D, dtype);
-    if (dtype == KS_DTYPE_FP32) gr_launch_exact<float>((const float *)W, C, D, K, pe, w, gamma, graph, sims, st, sym);
-    else gr_launch_exact<uint16_t>((const uint16_t *)W, C, D, K, pe, w, gamma, graph, sims, st, sym);
+    if (fixed) {
+        gr_launch_threshold(Wb, C, w.Ws, job.n_sample, D, K, w.blockmax, job.blocks, w.maxnorm, GrHop(), w.thf, w.tbits, st);
+        if (sym) gr_launch_recall_sym(Wb, C, D, f, w, st);
+        else gr_launch_recall_fix(pr, D, f, w.thf, w.cand, w.cnt_res, st);
+        if (dtype == KS_DTYPE_FP32) gr_launch_rank<float>((const float *)W, C, D, K, f, w, gamma, graph, sims, st);
+        else gr_launch_rank<uint16_t>((const uint16_t *)W, C, D, K, f, w, gamma, graph, sims, st);
+    } else {
+        hipLaunchKernelGGL(gr_maxnorm_kernel, dim3(1), dim3(64), 0, st, w.blockmax, job.blocks, w.maxnorm);
+        gr_launch_recall(pr, D, p, w.cand, w.cnt, w.thr, st);
+        const dim3 grid((unsigned)ks_ceil_div(C, GR_NT / 64));
+        if (dtype == KS_DTYPE_FP32)
+            hipLaunchKernelGGL(gr_rerank_kernel<float>, grid, dim3(GR_NT), 0, st, (const float *)W, C, D, K, p.cap, w.cand, w.cnt, w.thr,
+                               w.norms, w.maxnorm, gamma, graph, sims, w.fb_count, w.fb_rows);
+        else
+            hipLaunchKernelGGL(gr_rerank_kernel<uint16_t>, grid, dim3(GR_NT), 0, st, (const uint16_t *)W, C, D, K, p.cap, w.cand, w.cnt,
+                               w.thr, w.norms, w.maxnorm, gamma, graph, sims, w.fb_count, w.fb_rows);
+    }
+    if (dtype == KS_DTYPE_FP32)
+        hipLaunchKernelGGL(gr_exhaustive_kernel<float>, dim3(GR_FB_BLOCKS), dim3(GR_NT), 0, st, (const float *)W, C, D, K, w.fb_count,
+                           w.fb_rows, w.scratch, graph, sims);
+    else
+        hipLaunchKernelGGL(gr_exhaustive_kernel<uint16_t>, dim3(GR_FB_BLOCKS), dim3(GR_NT), 0, st, (const uint16_t *)W, C, D, K,
+                           w.fb_count, w.fb_rows, w.scratch, graph, sims);
     KS_LAUNCH_CHECK();
     return KS_OK;
 }
@@ -1439,14 +1898,12 @@ extern "C" int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K
 // (canonical fp64 similarity descending, id of the whole problem ascending), with the same certificate; rows
 // that fail it are merged against every visiting row.
 // ------------------------------------------------------------------------------------------------
-#define GR_NO_ID 0x7FFFFFFF
-
-// one wavefront per row; k' <= 256 candidates (slots 0..3) + K <= 128 list entries (slots 4, 5) per lane
+// Running thresholds (K > 64 or D > 512): one wavefront per row; k' <= 256 candidates (slots 0..3) + K <= 128 list entries (slots 4, 5) per lane
 template <typename IN>
 __global__ void __launch_bounds__(GR_NT)
 gr_merge_kernel(const IN *__restrict__ Wl, int64_t C_loc, const IN *__restrict__ Wv, int64_t C_vis, int D, int K, int cap,
                 const uint64_t *__restrict__ cand, const int32_t *__restrict__ cnt, const uint32_t *__restrict__ thr,
-                const float *__restrict__ norms, const uint32_t *__restrict__ maxnorm_bits, float gamma, int64_t local_offset,
+                const float *__restrict__ norms, const float *__restrict__ maxnorm, float gamma, int64_t local_offset,
                 int64_t visit_offset, int32_t *__restrict__ graph, double *__restrict__ sims, int32_t *fb_count,
                 int32_t *__restrict__ fb_rows) {
     const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + (threadIdx.x >> 6);
@@ -1521,7 +1978,7 @@ gr_merge_kernel(const IN *__restrict__ Wl, int64_t C_loc, const IN *__restrict__
                 // certificate: no visiting row that the recall pass dropped can reach the K-th exact similarity
                 const uint32_t th = thr[i];
                 if (th != 0u) {
-                    const double eps = (double)gamma * (double)norms[i] * (double)__uint_as_float(*maxnorm_bits);
+                    const double eps = (double)gamma * (double)norms[i] * (double)*maxnorm;
                     certified = s[t] > (double)gr_unorder(th) + eps;
                 }
             }
@@ -1535,25 +1992,10 @@ gr_merge_kernel(const IN *__restrict__ Wl, int64_t C_loc, const IN *__restrict__
     if (__ballot(!certified) != 0ull && lane == 0) fb_rows[atomicAdd(fb_count, 1)] = (int32_t)i;
 }
 
-// A row whose list is full needs no visiting row whose similarity cannot reach the list's last entry: the recall pass
-// starts from that entry's similarity, lowered by more than twice the recall's error bound (a visiting row that ties
-// the entry exactly is still recalled, and the certificate of the merge -- new K-th similarity above threshold + bound
-// -- holds when nothing new comes in).  0: no threshold (the list has empty slots).
 __global__ void __launch_bounds__(GR_NT)
-gr_hop_threshold_kernel(int64_t C_loc, int K, const int32_t *__restrict__ graph, const double *__restrict__ sims,
-                        const float *__restrict__ norms, const uint32_t *__restrict__ maxnorm_bits, float gamma,
-                        uint32_t *__restrict__ thr) {
+gr_hop_threshold_kernel(int64_t C_loc, GrHop hop, const float *__restrict__ maxnorm, uint32_t *__restrict__ thr) {
     const int64_t i = (int64_t)blockIdx.x * GR_NT + threadIdx.x;
-    if (i >= C_loc) return;
-    uint32_t t = 0u;
-    if (graph[i * K + K - 1] >= 0) {
-        const double eps = (double)gamma * (double)norms[i] * (double)__uint_as_float(*maxnorm_bits);
-        const double want = sims[i * K + K - 1] - 2.5 * eps;
-        float f = (float)want;
-        if ((double)f > want) f = nextafterf(f, -INFINITY); // rounded down
-        if (f == f && f > -INFINITY) t = gr_orderable(f);
-    }
-    thr[i] = t;
+    if (i < C_loc) thr[i] = gr_hop_threshold(hop, i, *maxnorm);
 }
 
 // rows on the list: every visiting row in canonical fp64 arithmetic, merged with the row's list
@@ -1648,31 +2090,43 @@ gr_exhaustive_merge_kernel(const IN *__restrict__ Wl, int64_t C_loc, const IN *_
 
 struct GrUpWs {
     uint16_t *Wlb, *Wvb;
-    float *norms_l, *norms_v;
-    uint32_t *maxnorm_l, *maxnorm_v;
+    float *norms_l, *blockmax_l, *blockmax_v, *maxnorm_v;
     uint64_t *cand;
-    int32_t *cnt;
-    uint32_t *thr;
     int32_t *fb_count;
     int32_t *fb_rows;
     double *scratch;
+    int32_t *cnt;  // running thresholds
+    uint32_t *thr;
+    uint16_t *Ws;  // fixed thresholds
+    float *thf;
+    uint32_t *tbits;
+    int32_t *cnt_res;
 };
 static GrUpWs gr_up_carve(void *ws, int64_t C_loc, int64_t C_vis, int D, int K, int dtype, size_t *total) {
     KsArena ar(ws);
     GrParams p = gr_params(K, D);
-    GrUpWs w;
+    GrUpWs w = GrUpWs();
     w.Wlb = dtype == KS_DTYPE_FP32 ? ar.take<uint16_t>((size_t)C_loc * D) : nullptr;
     w.Wvb = dtype == KS_DTYPE_FP32 ? ar.take<uint16_t>((size_t)C_vis * D) : nullptr;
     w.norms_l = ar.take<float>((size_t)C_loc);
-    w.norms_v = ar.take<float>((size_t)C_vis);
-    w.maxnorm_l = ar.take<uint32_t>(1);
-    w.maxnorm_v = ar.take<uint32_t>(1);
-    w.cand = ar.take<uint64_t>((size_t)C_loc * p.cap);
-    w.cnt = ar.take<int32_t>((size_t)C_loc);
-    w.thr = ar.take<uint32_t>((size_t)C_loc);
+    w.blockmax_l = ar.take<float>(GR_PREP_BLOCKS);
+    w.blockmax_v = ar.take<float>(GR_PREP_BLOCKS);
+    w.maxnorm_v = ar.take<float>(1);
     w.fb_count = ar.take<int32_t>(1);
     w.fb_rows = ar.take<int32_t>((size_t)C_loc);
     w.scratch = ar.take<double>((size_t)GR_FB_BLOCKS * C_vis);
+    if (gr_use_fixed(C_loc, C_vis, D, K)) {
+        const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, false);
+        w.cand = ar.take<uint64_t>((size_t)C_loc * f.seg.cap());
+        w.Ws = ar.take<uint16_t>((size_t)(C_vis / GR_SYM_RATIO) * D);
+        w.thf = ar.take<float>((size_t)C_loc);
+        w.tbits = ar.take<uint32_t>((size_t)C_loc);
+        w.cnt_res = ar.take<int32_t>((size_t)C_loc * 2 * f.seg.parts);
+    } else {
+        w.cand = ar.take<uint64_t>((size_t)C_loc * p.cap);
+        w.cnt = ar.take<int32_t>((size_t)C_loc);
+        w.thr = ar.take<uint32_t>((size_t)C_loc);
+    }
     if (total) *total = ar.off;
     return w;
 }
@@ -1692,16 +2146,19 @@ extern "C" size_t knn_graph_update_workspace(int64_t C_loc, int64_t C_vis, int D
 }
 
 template <typename IN>
-static void gr_up_prepare(const IN *W, int64_t C, int D, uint16_t *Wb, float *norms, uint32_t *maxnorm, hipStream_t st) {
-    hipLaunchKernelGGL(gr_prepare_kernel<IN>, dim3((unsigned)ks_ceil_div(C, GR_NT / 64)), dim3(GR_NT), 0, st, W, C, D, Wb, norms,
-                       maxnorm);
-}
-template <typename IN>
-static void gr_up_exact(const IN *Wl, int64_t C_loc, const IN *Wv, int64_t C_vis, int D, int K, const GrParams &p,
+static void gr_up_exact(const IN *Wl, int64_t C_loc, const IN *Wv, int64_t C_vis, int D, int K, const GrParams &p, const GrFixPlan *f,
                         const GrUpWs &w, float gamma, int64_t lo, int64_t vo, int32_t *graph, double *sims, hipStream_t st) {
-    hipLaunchKernelGGL(gr_merge_kernel<IN>, dim3((unsigned)ks_ceil_div(C_loc, GR_NT / 64)), dim3(GR_NT), 0, st, Wl, C_loc, Wv,
-                       C_vis, D, K, p.cap, w.cand, w.cnt, w.thr, w.norms_l, w.maxnorm_v, gamma, lo, vo, graph, sims, w.fb_count,
-                       w.fb_rows);
+    const dim3 grid((unsigned)ks_ceil_div(C_loc, GR_NT / 64));
+#define GR_HOP_RANK_LAUNCH(KP)                                                                                                 \
+    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, true>), grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, f->seg,             \
+                       w.cand, w.cnt_res, (const int32_t *)nullptr, w.tbits, w.norms_l, w.maxnorm_v, gamma, vo, graph, (void *)sims, \
+                       w.fb_count, w.fb_rows)
+    if (f && K <= 32) GR_HOP_RANK_LAUNCH(1);
+    else if (f) GR_HOP_RANK_LAUNCH(2);
+    else
+        hipLaunchKernelGGL(gr_merge_kernel<IN>, grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, p.cap, w.cand, w.cnt, w.thr,
+                           w.norms_l, w.maxnorm_v, gamma, lo, vo, graph, sims, w.fb_count, w.fb_rows);
+#undef GR_HOP_RANK_LAUNCH
     hipLaunchKernelGGL(gr_exhaustive_merge_kernel<IN>, dim3(GR_FB_BLOCKS), dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, lo, vo,
                        w.fb_count, w.fb_rows, w.scratch, graph, sims);
 }
@@ -1718,30 +2175,33 @@ extern "C" int knn_graph_update(const void *W_local, const void *W_visit, int dt
     if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
     const GrParams p = gr_params(K, D, dtype);
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(gr_zero_kernel, dim3(1), dim3(1), 0, st, w.maxnorm_l, w.fb_count);
-    hipLaunchKernelGGL(gr_zero_kernel, dim3(1), dim3(1), 0, st, w.maxnorm_v, w.fb_count);
-    const uint16_t *Rl, *Sv;
-    if (dtype == KS_DTYPE_FP32) {
-        gr_up_prepare<float>((const float *)W_local, C_loc, D, w.Wlb, w.norms_l, w.maxnorm_l, st);
-        gr_up_prepare<float>((const float *)W_visit, C_vis, D, w.Wvb, w.norms_v, w.maxnorm_v, st);
-        Rl = w.Wlb;
-        Sv = w.Wvb;
-    } else {
-        gr_up_prepare<uint16_t>((const uint16_t *)W_local, C_loc, D, nullptr, w.norms_l, w.maxnorm_l, st);
-        gr_up_prepare<uint16_t>((const uint16_t *)W_visit, C_vis, D, nullptr, w.norms_v, w.maxnorm_v, st);
-        Rl = (const uint16_t *)W_local;
-        Sv = (const uint16_t *)W_visit;
-    }
+    const bool fixed = gr_use_fixed(C_loc, C_vis, D, K);
+    const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, false);
+    GrClear clr = GrClear();
+    clr.fb_count = w.fb_count;
+    const GrPrepJob jl = gr_prep_job(W_local, C_loc, D, dtype, w.Wlb, w.norms_l, w.blockmax_l, nullptr);
+    const GrPrepJob jv = gr_prep_job(W_visit, C_vis, D, dtype, w.Wvb, nullptr, w.blockmax_v, fixed ? w.Ws : nullptr);
+    gr_launch_prepare(jl, jv, D, dtype, clr, st);
+    const uint16_t *Rl = dtype == KS_DTYPE_FP32 ? w.Wlb : (const uint16_t *)W_local;
+    const uint16_t *Sv = dtype == KS_DTYPE_FP32 ? w.Wvb : (const uint16_t *)W_visit;
     const GrPair pr{Rl, C_loc, Sv, C_vis, local_offset - visit_offset};
     const float gamma = gr_gamma(D, dtype);
-    hipLaunchKernelGGL(gr_hop_threshold_kernel, dim3((unsigned)ks_ceil_div(C_loc, GR_NT)), dim3(GR_NT), 0, st, C_loc, K, graph, sims,
-                       w.norms_l, w.maxnorm_v, gamma, w.thr);
-    gr_launch_recall(pr, D, p, w.cand, w.cnt, w.thr, st, w.thr);
+    const GrHop hop{graph, sims, w.norms_l, K, gamma};
+    if (fixed) {
+        gr_launch_threshold(Rl, C_loc, w.Ws, jv.n_sample, D, K, w.blockmax_v, jv.blocks, w.maxnorm_v, hop, w.thf, w.tbits, st);
+        gr_launch_recall_fix(pr, D, f, w.thf, w.cand, w.cnt_res, st);
+    } else {
+        hipLaunchKernelGGL(gr_maxnorm_kernel, dim3(1), dim3(64), 0, st, w.blockmax_v, jv.blocks, w.maxnorm_v);
+        hipLaunchKernelGGL(gr_hop_threshold_kernel, dim3((unsigned)ks_ceil_div(C_loc, GR_NT)), dim3(GR_NT), 0, st, C_loc, hop,
+                           w.maxnorm_v, w.thr);
+        gr_launch_recall(pr, D, p, w.cand, w.cnt, w.thr, st, w.thr);
+    }
+    const GrFixPlan *fp = fixed ? &f : nullptr;
     if (dtype == KS_DTYPE_FP32)
-        gr_up_exact<float>((const float *)W_local, C_loc, (const float *)W_visit, C_vis, D, K, p, w, gamma, local_offset,
+        gr_up_exact<float>((const float *)W_local, C_loc, (const float *)W_visit, C_vis, D, K, p, fp, w, gamma, local_offset,
                            visit_offset, graph, sims, st);
     else
-        gr_up_exact<uint16_t>((const uint16_t *)W_local, C_loc, (const uint16_t *)W_visit, C_vis, D, K, p, w, gamma,
+        gr_up_exact<uint16_t>((const uint16_t *)W_local, C_loc, (const uint16_t *)W_visit, C_vis, D, K, p, fp, w, gamma,
                               local_offset, visit_offset, graph, sims, st);
     KS_LAUNCH_CHECK();
     return KS_OK;

@@ -1,0 +1,65 @@
+"""Problem depths and sizes at the edges of the kernels' dispatch: row lengths that are odd multiples of 32 or not a power of
+two, searches cut into parts, and the sizes on both sides of the line between the two recall passes."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ks():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2102_06025_amd as ks
+    ks.lib()
+    return ks
+
+
+def dev(a, bf16=False):
+    import torch
+    t = torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    return t.to(torch.bfloat16) if bf16 else t
+
+
+@pytest.mark.parametrize("C,D,K,bf16", [
+    (31, 32, 5, True), (97, 64, 64, False), (300, 96, 33, True), (2049, 160, 16, False), (6143, 224, 32, True), (2500, 288, 17, True),
+    (7001, 320, 64, True), (4097, 384, 8, False), (3001, 416, 32, True), (3500, 448, 16, True), (2300, 480, 48, False), (12_289, 192, 24, True),
+    (29_296, 512, 32, True), (29_297, 512, 16, True), (58_594, 256, 8, True), (117_188, 128, 32, True)])
+def test_graph_at_every_depth_and_around_the_symmetric_pass(ks, orc, C, D, K, bf16):
+    """Fixed-threshold recall: depths of 1 to 8 k-tiles, whole and ragged; fewer rows than one sample, than one chunk, than one
+    block; the last sizes before and the first sizes of the pass that computes every similarity once (C * D = 15 million)."""
+    import torch
+    print(f"[depths] graph C={C} D={D} K={K} bf16={bf16}", flush=True)
+    W = synth.unit_rows(21, synth.TID_W, C, D, bf16=bf16)
+    W[C - 1] = W[C // 3]                                          # an exact twin
+    rows = np.unique(np.concatenate([synth.class_permutation(21, C)[:120], [0, C // 3, C - 1], np.arange(max(0, C - 3), C)])).astype(np.int32)
+    g, s = ks.knn_graph_build(dev(W, bf16), K, want_sims=True)
+    torch.cuda.synchronize()
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("C_loc,C_vis,D,K,bf16", [(300, 20_011, 320, 16, True), (257, 9_000, 96, 64, False), (5000, 40, 512, 32, True),
+                                                  (1, 6_001, 64, 32, True)])
+def test_hop_cut_into_parts(ks, orc, C_loc, C_vis, D, K, bf16):
+    """One hop of few local rows against many visiting ones (many parts), and the reverse; the shard visits twice (the second
+    visit starts from full lists, or from short ones where the shard is smaller than K, and changes nothing)."""
+    import torch
+    print(f"[depths] hop {C_loc} x {C_vis} D={D} K={K} bf16={bf16}", flush=True)
+    W = synth.unit_rows(22, synth.TID_W, C_loc + C_vis, D, bf16=bf16)
+    Wl, Wv = dev(W[:C_loc], bf16), dev(W[C_loc:], bf16)
+    graph = torch.full((C_loc, K), -1, dtype=torch.int32, device="cuda")
+    sims = torch.full((C_loc, K), -np.inf, dtype=torch.float64, device="cuda")
+    for _ in range(2):
+        ks.knn_graph_update(Wl, Wv, 0, C_loc, graph, sims)
+        torch.cuda.synchronize()
+        S = W[:C_loc].astype(np.float64) @ W[C_loc:].astype(np.float64).T
+        for i in (0, C_loc // 2, C_loc - 1):
+            n = min(K, C_vis)
+            best = np.argsort(-S[i], kind="stable")[:n] + C_loc
+            got = graph[i].cpu().numpy()
+            assert (got[:n] == best).all() and (got[n:] == -1).all()
+            assert np.allclose(sims[i].cpu().numpy()[:n], S[i][best - C_loc], rtol=0, atol=1e-12)
