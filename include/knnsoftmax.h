@@ -295,7 +295,7 @@ int apply_weight_grad(float *W_master, uint16_t *W_bf16, const int32_t *idx, con
  *   knn_select_active or knn_select_active_csr: local ids, target_pos = -1 for a sample whose class another node
  *   owns) and per sample
  *     row_max [B], row_sumexp [B]:  a pair with  sum_a exp(z_ia - row_max_i) = row_sumexp_i, not necessarily
- *                  the maximum itself: where the one-sweep softmax runs (KS_FLAG_UNIT_ROWS, D = 128, 256 or 512,
+ *                  the maximum itself: where the one-sweep softmax runs (KS_FLAG_UNIT_ROWS, D <= 512,
  *                  scale <= 40) row_max = scale for every sample on every node, so that combining the nodes
  *                  comes down to ADDING their sums; otherwise the pair is normalised to row_sumexp = 1.  A node
  *                  without active classes gives (-infinity, 0)

@@ -23,6 +23,10 @@
 //
 // After every chunk (all KT k-tiles of CH streamed rows) the caller's epilogue functor gets the
 // accumulators; the loads of the next chunk are already in flight at that point.
+//
+// A kernel that calls the sweep keeps ALL its LDS in one __shared__ array.  With several, the compiler tracks the
+// asynchronous loads per array and puts s_waitcnt vmcnt(0) before the fragment reads of every stage, which serialises the
+// loads in flight with the MFMAs (it did in the two-sweep softmax and in the graph's symmetric sweep).
 #pragma once
 #include <type_traits>
 #include "ks_gemm_async.h"
@@ -61,30 +65,21 @@ __device__ __forceinline__ int ks_soe_col() { return (threadIdx.x >> 6) * 32 + (
 // ctab / ctab_n: optional table of chunks (first streamed row, rows) that replaces the single range [s_begin, s_end):
 // the sweep then visits ctab_n chunks that may lie anywhere (the same table for all threads; no gather list with it).
 //
-// post(chunk_first_row, rows_in_chunk): optional second half of a chunk's epilogue, for global stores.  The
-// sweep tells that a stage has landed by counting outstanding vector-memory instructions, and stores count
-// too: stores issued at the end of a chunk make the very next wait sit out their round trip.  post() for
-// chunk c is therefore called inside chunk c+1, right after the loads that follow its first barrier have been
-// issued: the next wait comes a whole stage of MFMAs later, when most of the stores have completed.  (Letting
-// that wait tolerate the stores as well, and sparing the wavefronts that load nothing the wait altogether, was
-// measured and gains nothing.)  The last chunk's post() runs after the sweep.  epi() leaves what post() needs
-// in LDS of the caller's.
-struct KsSoeNoPost {
-    __device__ __forceinline__ void operator()(int, int) const {}
-};
+// NSTORE: vector-memory stores that epi() issues per full chunk and wavefront.  The sweep tells that a stage has landed by
+// counting outstanding vector-memory instructions, and stores count too; they are younger than the loads of the STAGES - 1
+// stages that are in flight when they are issued, so the waits for those stages let NSTORE more instructions be outstanding
+// instead of sitting out the stores' round trip.
 // side(chunk_first_row, chunk_index): optional, called by wavefront 0 when the loads of a chunk begin to be requested (up
 // to two chunks before its epilogue): the place for a small asynchronous load of per-row data that the epilogue will
 // want in LDS (global_load_lds; it is older than the chunk's stream loads, so the waits that cover those cover it).
 struct KsSoeNoSide {
     __device__ __forceinline__ void operator()(int, int) const {}
 };
-template <class P> struct KsSoeHasPost { static constexpr bool value = true; };
-template <> struct KsSoeHasPost<KsSoeNoPost> { static constexpr bool value = false; };
-template <class CFG, class Epi, class Post = KsSoeNoPost, class Side = KsSoeNoSide>
+template <class CFG, int NSTORE = 0, class Epi, class Side = KsSoeNoSide>
 __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int64_t ldr, int r_row0, int r_limit,
                                               const uint16_t *__restrict__ S, int64_t lds_ld, const int32_t *__restrict__ gidx,
                                               int s_begin, int s_end, int s_clamp, uint16_t *lds, Epi &epi,
-                                              int32_t *lidx = nullptr, int lidx_cap = 0, Post post = Post(),
+                                              int32_t *lidx = nullptr, int lidx_cap = 0,
                                               const int2 *__restrict__ ctab = nullptr, int ctab_n = 0, Side side = Side()) {
     constexpr int KT = CFG::KT, ST = CFG::STAGES, NI = CFG::NI, FM = CFG::FM;
     const int lane = threadIdx.x & 63;
@@ -170,7 +165,8 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
             const int row = (j * CFG::LW + wave) * 8 + (lane >> 3);
             int64_t src;
             if (use_lidx) {
-                src = lidx[c * CFG::CH + row];
+                // (as an LDS access by type: merged with the list in memory it would be a flat load, which waits for everything)
+                src = ((const int32_t __attribute__((address_space(3))) *)lidx)[c * CFG::CH + row];
             } else {
                 int g = first + row;
                 if (g >= s_clamp) g = s_clamp - 1;
@@ -233,10 +229,12 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
             for (int kt0 = 0; kt0 < KT; kt0 += CFG::KSUB) {
                 // stage `done` must have landed; the stages issued after it may still be in flight.  (Wavefronts that
                 // load nothing only have the stores of their epilogues outstanding, which this wait also covers.)
-                if (issued - done - 1 >= ST - 2) ks_wait_vmcnt<(ST - 2) * NI * CFG::KSUB>();
-                else ks_wait_vmcnt<0>();
+                constexpr int YOUNGER = (ST - 2) * NI * CFG::KSUB;
+                static_assert(YOUNGER + NSTORE <= 63, "vmcnt range");
+                if (issued - done - 1 < ST - 2) ks_wait_vmcnt<0>();
+                else if (NSTORE > 0 && kt0 / CFG::KSUB < ST - 1 && c > 0) ks_wait_vmcnt<YOUNGER + NSTORE>();
+                else ks_wait_vmcnt<YOUNGER>();
                 ks_barrier_nofence();
-                if (kt0 == 0 && c > 0 && KsSoeHasPost<Post>::value) post(chunk_first(c - 1), chunk_rows(c - 1));
 #pragma unroll
                 for (int u = 0; u < CFG::KSUB; ++u) {
                     const int kt = kt0 + u;
@@ -285,11 +283,7 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
         };
         if (rows_here == CFG::CH) chunk(std::true_type());
         else chunk(std::false_type());
-        // a chunk of a single stage has no barrier between post() of the previous chunk (which reads what epi() left
-        // in LDS) and this chunk's epi(): a wavefront that runs ahead must not overwrite what another still reads
-        if (KT / CFG::KSUB < 2 && KsSoeHasPost<Post>::value) ks_barrier_nofence();
         epi(ctab ? ct.x : chunk_first(c), rows_here, acc);
     }
     ks_barrier_nofence();
-    if (n_chunks > 0 && KsSoeHasPost<Post>::value) post(chunk_first(n_chunks - 1), chunk_rows(n_chunks - 1));
 }

@@ -877,9 +877,11 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
     constexpr int Q = GR_SYM_Q, SB = GR_SYM_SB;
     const int parts = SPLIT ? split_parts : 1, log_rows = SPLIT ? split_log_rows : SB;
     static_assert(SB % CFG::CH == 0 && SB % CFG::RES == 0 && CFG::RES == 256, "super-blocks are whole chunks and whole blocks");
-    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
-    __shared__ uint2 s_stage[CFG::NW][GR_SYM_STAGE];
-    __shared__ __attribute__((aligned(16))) float s_thr[8][CFG::CH]; // the streamed rows' thresholds of the chunks in flight
+    // one LDS array (see ks_gemm_soe.h): the stream stages, the streamed rows' thresholds of the chunks in flight, the
+    // records that the wavefronts collect
+    constexpr int THR_ELEMS = 2 * 8 * CFG::CH, STAGE_ELEMS = 4 * GR_SYM_STAGE;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS + THR_ELEMS + CFG::NW * STAGE_ELEMS];
+    float(*const s_thr)[CFG::CH] = (float(*)[CFG::CH])(lds + CFG::LDS_ELEMS);
     const int lane = threadIdx.x & 63;
     // Share and part.  Every XCD gets the same number of workgroups, for consecutive blocks: the 32 that it runs at a time
     // belong to one group and the next.  (Whole groups dealt to XCDs: at 390,625 rows three XCDs had seven groups of 30
@@ -899,7 +901,9 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
     // stream side: records collected by this wavefront, and the log they belong to (log_rows is a multiple of the chunk
     // and divides the super-block)
     int staged = 0, cur_log = -1;
-    auto my_stage = [&]() __attribute__((always_inline)) { return s_stage[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]; };
+    auto my_stage = [&]() __attribute__((always_inline)) {
+        return (uint2 *)(lds + CFG::LDS_ELEMS + THR_ELEMS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * STAGE_ELEMS);
+    };
     auto flush = [&]() {
         if (staged > 0) {
             int base = 0;
@@ -1018,7 +1022,7 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
             }
         }
     };
-    ks_soe_sweep<CFG>(W, D, row0, C, W, D, nullptr, 0, 0, C, lds, epi, nullptr, 0, KsSoeNoPost(),
+    ks_soe_sweep<CFG>(W, D, row0, C, W, D, nullptr, 0, 0, C, lds, epi, nullptr, 0,
                       chunks + (int64_t)share * chunks_stride + chunk0, chunk1 - chunk0, side);
     flush();
     if (row0 + ks_soe_col() < C)

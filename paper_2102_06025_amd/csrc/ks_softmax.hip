@@ -14,24 +14,15 @@
 #include "ks_gemm_soe.h"
 #include "ks_select.h"
 
-#ifndef KS_DX_IL
-#define KS_DX_IL 0
-#endif
-#ifndef KS_DW_IL
-#define KS_DW_IL 1
-#endif
-#ifndef KS_IL_SPREAD
-#define KS_IL_SPREAD 2
-#endif
 typedef KsTile<128, 128, 64, 2, 2> TileG;      // generic path (any D % 32 == 0)
 typedef KsATile<256, 256, 2, 4, 2> TileSm;     // fast path (D % 64 == 0): tile = 256 classes x 256 samples
-typedef KsATile<128, 128, 2, 2, 2> TileDx;
+typedef KsATile<128, 128, 2, 2, 2, KS_K8> TileDx;
 #define DX_IDX_CACHE 4096 /* gather indices of one workgroup's share of the active dimension, staged in LDS */
 // dW tiles: 256 columns of D, and 256, 192 or 128 active rows -- chosen inside the kernel from the number of active
 // rows, which only the device knows (see dw_tile_rows)
-typedef KsATile<256, 256, 2, 4, 2> TileDw;
-typedef KsATile<192, 256, 2, 4, 2> TileDw192;
-typedef KsATile<128, 256, 2, 4, 2> TileDw128;
+typedef KsATile<256, 256, 2, 4, 2, KS_M8> TileDw;
+typedef KsATile<192, 256, 2, 4, 2, KS_M8> TileDw192;
+typedef KsATile<128, 256, 2, 4, 2, KS_M8> TileDw128;
 #define KS_BP_ALIGN 256
 #define SM_LIDX_CAP 1536 // gather-list entries a sweep keeps in LDS (longer slabs read the list from memory)
 #define SM_SOE_GRID 256 /* workgroups of the stationary-operand softmax passes (one per compute unit) */
@@ -240,36 +231,40 @@ dw_kernel(const uint16_t *__restrict__ dZ, int64_t ldz, const uint16_t *__restri
 }
 
 // ================================================================================================
-// Fast path (D % 64 == 0).  All contractions run on the asynchronous engine and the logits are recomputed
-// instead of stored (see below).  The logit gradient is stored once, transposed (dZT[a][i]); it is the
-// k-contiguous operand of the dW contraction and a k-major operand of the dX contraction.  Weight rows (gathered through the index list) and X enter as
-// k-major operands where k is their row index, so no transposed copies of them are made.
+// Fast path (D <= 512, or D % 64 == 0).  The contractions run on the asynchronous and the stationary-operand engine and the
+// logits are recomputed instead of stored (see below).  The logit gradient is stored once, in blocks of eight classes:
+//     dZ8[(a / 8) * Bp + i][a % 8]        (Bp: samples rounded up to whole tiles)
+// In the accumulators of the sweeps a lane holds four consecutive classes of one sample, so a block's 16 bytes come together
+// by exchanging halves between two lanes (v_permlane32_swap) and leave as full 512-byte rows straight from registers: no
+// transposition through LDS.  For the dX contraction (over classes) such a block is a ready MFMA fragment; the dW contraction
+// (over samples) reads the same array through the transposing LDS read.  Weight rows (gathered through the index list) and
+// X enter as k-major operands where k is their row index, so no transposed copies of them are made.
 // ================================================================================================
 
-// 8x8 transpose of 16-bit elements held as 8 rows of uint4 (row k, elements n=0..7) -> out[n] = 8 k's
-__device__ __forceinline__ void sm_transpose8x8(const uint4 (&in)[8], uint4 (&out)[8]) {
+// element (class position a, sample i) of dZ8
+__device__ __forceinline__ int64_t sm_dz_at(int a, int i, int Bp) { return (((int64_t)(a >> 3) * Bp) + i) * 8 + (a & 7); }
+
+// Stores the values of one 32 x 32 accumulator block as bf16: pk[g] = the lane's classes 8 g + 4 (lane / 32) .. + 3 of its
+// sample, packed in pairs.  p: the lane's sample in the block of eight classes (lane / 32) of the accumulator block.
+// After the exchange a lane holds all eight classes of its sample for block 0 or 2 (lanes 0..31) or 1 or 3 (lanes 32..63).
+__device__ __forceinline__ void sm_store_block(uint32_t (&pk)[4][2], uint16_t *p, int Bp) {
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
-        uint32_t o[4];
+    for (int g = 0; g < 4; g += 2) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint4 &ra = in[2 * j], &rb = in[2 * j + 1];
-            uint32_t a = (n >> 1) == 0 ? ra.x : ((n >> 1) == 1 ? ra.y : ((n >> 1) == 2 ? ra.z : ra.w));
-            uint32_t b = (n >> 1) == 0 ? rb.x : ((n >> 1) == 1 ? rb.y : ((n >> 1) == 2 ? rb.z : rb.w));
-            o[j] = (n & 1) ? ((a >> 16) | (b & 0xFFFF0000u)) : ((a & 0xFFFFu) | (b << 16));
+        for (int w = 0; w < 2; ++w) {
+            const auto x = __builtin_amdgcn_permlane32_swap(pk[g][w], pk[g + 1][w], false, false);
+            pk[g][w] = x[0];
+            pk[g + 1][w] = x[1];
         }
-        out[n] = make_uint4(o[0], o[1], o[2], o[3]);
+        *(uint4 *)(p + (int64_t)g * Bp * 8) = make_uint4(pk[g][0], pk[g][1], pk[g + 1][0], pk[g + 1][1]);
     }
 }
-
-#define TR_TILE 128
-#define TR_LD (TR_TILE + 8)
 
 // The logits are never stored on the fast path.  Two passes over the same tile product
 //     Zt[a][i] = scale * <W[active[a]], X[i]>            (classes = MFMA rows, samples = MFMA columns)
 // First pass: per-sample running max / sum of exponentials of each class tile, and the target logit.
 // Second pass (after the per-sample log-sum-exp is known): the same product again, turned into the logit
-// gradient in registers and stored transposed, dZT[a][i].  In this orientation a lane owns one sample
+// gradient in registers and stored transposed, dZ8[a][i].  In this orientation a lane owns one sample
 // column of the accumulator tile, so the per-sample reductions are lane-local.
 
 // accumulator element (fm, r) of a lane: class row inside the wave's part of the tile
@@ -380,17 +375,14 @@ sm_combine_kernel(const float *__restrict__ pm, const float *__restrict__ pl, co
     }
 }
 
-// second pass: logit gradient, stored transposed.  dZT[a][i] = g (exp(Zt[a][i] - lse_i) - [a == target_pos[i]]),
-// zero for a >= n_active (up to the end of the class tile) and for i >= B (up to Bp).
+// second pass: logit gradient g (exp(Zt[a][i] - lse_i) - [a == target_pos[i]]), zero for a >= n_active (up to the end of the
+// class tile) and for i >= B (up to Bp).
 template <class T>
 __global__ void __launch_bounds__(T::NT)
 sm_grad_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const int32_t *__restrict__ active_idx,
                const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, const float *__restrict__ lse,
-               int B, int Bp, int D, int M, float scale, float g, uint16_t *__restrict__ dZT) {
-    constexpr int STAGE_LD = T::BN + 8;
-    constexpr int STAGE_ELEMS = T::BM * STAGE_LD;
-    constexpr int LDS_N = STAGE_ELEMS > T::LDS_ELEMS ? STAGE_ELEMS : T::LDS_ELEMS;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[LDS_N];
+               int B, int Bp, int D, int M, float scale, float g, uint16_t *__restrict__ dZ8) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[T::LDS_ELEMS];
     const int n_active = sm_clamp_n(n_active_p, M);
     const int tiles_s = (B + T::BN - 1) / T::BN;
     const int n_tiles = tiles_s * ((n_active + T::BM - 1) / T::BM);
@@ -398,56 +390,43 @@ sm_grad_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, c
     const int t = ks_xcd_remap(blockIdx.x, n_tiles);
     const int ts = t % tiles_s, tc = t / tiles_s;
     f32x16_t acc[T::FM][T::FN];
-    sm_logits_tile<T>(X, W, active_idx, n_active, B, D, tc, ts, lds, acc); // ends with a barrier: LDS is free
+    sm_logits_tile<T>(X, W, active_idx, n_active, B, D, tc, ts, lds, acc);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / T::WAVES_N, wn = wave % T::WAVES_N;
-    const int r0 = wm * T::WM;         // first class row of this wave inside the tile
-    const int c0 = tc * T::BM + r0;
-    const bool odd = lane & 1;
+    const int c0 = tc * T::BM + wm * T::WM; // first class row of this wave
 #pragma unroll
     for (int fn = 0; fn < T::FN; ++fn) {
-        const int col = wn * T::WN + fn * 32 + (lane & 31); // sample column inside the tile
-        const int i = ts * T::BN + col;
+        const int i = ts * T::BN + wn * T::WN + fn * 32 + (lane & 31);
         const bool i_ok = i < B;
         const float ls = i_ok ? lse[i] : 0.f;
         const int tp = i_ok ? target_pos[i] : -1;
 #pragma unroll
-        for (int fm = 0; fm < T::FM; ++fm)
+        for (int fm = 0; fm < T::FM; ++fm) {
+            uint32_t pk[4][2];
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
+            for (int q = 0; q < 8; ++q) {
                 float d[2];
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    const int c = c0 + sm_tile_row(fm, r + e, lane);
-                    d[e] = (i_ok && c < n_active) ? g * (__expf(scale * acc[fm][fn][r + e] - ls) - (c == tp ? 1.f : 0.f)) : 0.f;
+                    const int c = c0 + sm_tile_row(fm, 2 * q + e, lane);
+                    d[e] = (i_ok && c < n_active) ? g * (__expf(scale * acc[fm][fn][2 * q + e] - ls) - (c == tp ? 1.f : 0.f)) : 0.f;
                 }
-                // neighbouring lanes (samples 2j, 2j+1) trade so that each holds two adjacent samples of one class
-                // row: the even lane ends up with row r, the odd lane with row r+1
-                const float send = odd ? d[0] : d[1];
-                const float recv =
-                    __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(send), 0xB1, 0xF, 0xF, true));
-                const uint32_t packed = odd ? ks_pack_bf2(recv, d[1]) : ks_pack_bf2(d[0], recv);
-                const int row = r0 + sm_tile_row(fm, r + (odd ? 1 : 0), lane);
-                *(uint32_t *)(lds + row * STAGE_LD + (col & ~1)) = packed;
+                pk[q >> 1][q & 1] = ks_pack_bf2(d[0], d[1]);
             }
-    }
-    __syncthreads();
-    // coalesced store of the staged tile: 16 bytes per lane along the sample index
-    constexpr int CHUNKS = T::BM * (T::BN / 8);
-    for (int q = threadIdx.x; q < CHUNKS; q += T::NT) {
-        const int row = q / (T::BN / 8), ch = q % (T::BN / 8);
-        *(uint4 *)(dZT + (int64_t)(tc * T::BM + row) * Bp + ts * T::BN + ch * 8) = *(const uint4 *)(lds + row * STAGE_LD + ch * 8);
+            sm_store_block(pk, dZ8 + sm_dz_at(c0 + fm * 32 + 8 * (lane >> 5), i, Bp), Bp);
+        }
     }
 }
 
 // ================================================================================================
-// Stationary-operand versions of the two softmax passes (D = 128, 256 or 512): a workgroup keeps the MFMA
+// Stationary-operand versions of the two softmax passes (D <= 512): a workgroup keeps the MFMA
 // fragments of 256 samples in registers and streams its share ("slab") of the active classes past them.
 // The active classes are cut into G / tiles_s equal slabs (multiples of 32 rows), so the chip is loaded
 // evenly whatever the active count; per-sample softmax statistics are carried in registers along the slab.
 // ================================================================================================
-#define SOE_STAGES 3
+// stage shape of the sweeps for a depth of KT k-tiles: two per stage where KT is even (half the barriers), twelve in flight
+template <int KT, bool RAGGED> using SmSoe = KsSoe<KT, 96, KT % 2 == 0 ? 6 : 12, KT % 2 == 0 ? 2 : 1, RAGGED>;
 #define KS_FUSED_MAX_SCALE 40.f // exp(-2 * scale) must stay a normal fp32 / bf16 number
 
 // rows per slab for n64 = round_up(n_active, 64) rows and `slabs` slabs
@@ -457,14 +436,13 @@ __host__ __device__ __forceinline__ int sm_slab_rows(int n64, int slabs) {
     return h < 32 ? 32 : h;
 }
 
-template <int KT>
+template <class CFG>
 __global__ void __launch_bounds__(512)
 sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const int32_t *__restrict__ active_idx,
                     const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, int B, int Bp, int D, int M,
                     int tiles_s, float scale, float *__restrict__ pm, float *__restrict__ pl, float *__restrict__ zt) {
-    typedef KsSoe<KT, 96, SOE_STAGES, 2> CFG;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
-    __shared__ int32_t s_lidx[SM_LIDX_CAP];
+    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS + 2 * SM_LIDX_CAP]; // one array: see ks_gemm_soe.h
+    int32_t *const s_lidx = (int32_t *)(lds + CFG::LDS_ELEMS);
     const int n = sm_clamp_n(n_active_p, M);
     const int n64 = (n + 63) & ~63;
     const int slabs = gridDim.x / tiles_s;
@@ -545,17 +523,14 @@ sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     }
 }
 
-template <int KT>
+template <class CFG>
 __global__ void __launch_bounds__(512)
 sm_grad_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const int32_t *__restrict__ active_idx,
                    const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos,
                    const float *__restrict__ lse, int B, int Bp, int D, int M, int tiles_s, float scale, float g,
-                   uint16_t *__restrict__ dZT) {
-    typedef KsSoe<KT, 96, SOE_STAGES, 2> CFG;
-    constexpr int STAGE_LD = CFG::RES + 8;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
-    __shared__ int32_t s_lidx[SM_LIDX_CAP];
-    __shared__ __attribute__((aligned(16))) uint16_t stage[CFG::CH * STAGE_LD];
+                   uint16_t *__restrict__ dZ8) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS + 2 * SM_LIDX_CAP]; // one array: see ks_gemm_soe.h
+    int32_t *const s_lidx = (int32_t *)(lds + CFG::LDS_ELEMS);
     const int n = sm_clamp_n(n_active_p, M);
     const int n64 = (n + 63) & ~63;
     const int slabs = gridDim.x / tiles_s;
@@ -564,63 +539,48 @@ sm_grad_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
     const int ts = id % tiles_s, slab = id / tiles_s;
     const int s0 = slab * h, s1 = (s0 + h < n64) ? s0 + h : n64;
     if (slab >= slabs || s0 >= s1) return;
-    const int i0 = ts * CFG::RES + ks_soe_col();
-    const float ls = i0 < B ? lse[i0] : 0.f;
-    const int tp = i0 < B ? target_pos[i0] : -1;
+    const int i = ts * CFG::RES + ks_soe_col();
+    const bool ok = i < B;
+    const float ls = ok ? lse[i] : 0.f;
+    const int tp = ok ? target_pos[i] : -1;
     // scale > 0 and g > 0 (checked by the host): g * exp(scale * acc - lse) = exp2(fma(acc, k1, k2)) with
     // k2 = log2(g) - lse * log2(e): one fused multiply-add and one exponential per element
     const float k1 = scale * 1.4426950408889634f;
     const float k2 = __log2f(g) - ls * 1.4426950408889634f;
     const bool samples_ok = (ts + 1) * CFG::RES <= B;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
+        const int lane = threadIdx.x & 63;
         const bool plain = samples_ok && c0 + CFG::CH <= n; // no row or column of this chunk needs masking
-        // Everything derived from the thread index is derived afresh here, from a copy the compiler cannot see
-        // through: otherwise it hoists the dozens of LDS addresses below out of the sweep, runs out of
-        // registers and spills them -- and every reload of a spilled value is a vector-memory load whose wait
-        // also waits for the stream loads in flight.
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        const int lane = tid & 63;
-        const bool odd = lane & 1;
-        const int col = (tid >> 6) * 32 + (tid & 31);
-        const bool ok = ts * CFG::RES + col < B;
-        // does any sample of this wavefront have its label inside the chunk?
-        const bool mine = tp >= c0 && tp < c0 + CFG::CH;
-        const bool any_target = __builtin_amdgcn_ballot_w64(mine) != 0;
+        const int tq = tp - c0 - 4 * (lane >> 5);           // the own class's accumulator element: fm * 32 + 8 * (r >> 2) + (r & 3) == tq
+        const int lq = ok ? n - c0 - 4 * (lane >> 5) : 0;           // the first of its elements to mask
+        const bool any_target = __any(tp >= c0 && tp < c0 + CFG::CH);
+        if (!plain) {
 #pragma unroll
-        for (int fm = 0; fm < CFG::FM; ++fm)
+            for (int fm = 0; fm < CFG::FM; ++fm)
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
+                for (int r = 0; r < 16; ++r)
+                    if (fm * 32 + 8 * (r >> 2) + (r & 3) >= lq) acc[fm][r] = -INFINITY; // its exponential is 0
+        }
+        uint16_t *p = dZ8 + sm_dz_at(c0 + 8 * (lane >> 5), i, Bp);
+#pragma unroll
+        for (int fm = 0; fm < CFG::FM; ++fm) {
+            uint32_t pk[4][2];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
                 float d[2];
 #pragma unroll
-                for (int e = 0; e < 2; ++e) d[e] = __builtin_amdgcn_exp2f(fmaf(acc[fm][r + e], k1, k2));
+                for (int e = 0; e < 2; ++e) d[e] = __builtin_amdgcn_exp2f(fmaf(acc[fm][2 * q + e], k1, k2));
                 if (any_target) {
 #pragma unroll
                     for (int e = 0; e < 2; ++e)
-                        if (c0 + ks_soe_row(fm, r + e, lane) == tp) d[e] -= g;
+                        if (fm * 32 + 8 * (q >> 1) + 2 * (q & 1) + e == tq) d[e] -= g;
                 }
-                if (!plain) {
-#pragma unroll
-                    for (int e = 0; e < 2; ++e)
-                        if (!ok || c0 + ks_soe_row(fm, r + e, lane) >= n) d[e] = 0.f;
-                }
-                // neighbouring lanes (samples 2j, 2j+1) trade so that each holds two adjacent samples of one
-                // class row: the even lane ends up with row r, the odd lane with row r+1
-                const float send = odd ? d[0] : d[1];
-                const float recv = __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(send), 0xB1, 0xF, 0xF, true));
-                const uint32_t packed = odd ? ks_pack_bf2(recv, d[1]) : ks_pack_bf2(d[0], recv);
-                const int row = ks_soe_row(fm, r + (odd ? 1 : 0), lane);
-                *(uint32_t *)(stage + row * STAGE_LD + (col & ~1)) = packed;
+                pk[q >> 1][q & 1] = ks_pack_bf2(d[0], d[1]);
             }
-        __builtin_amdgcn_s_waitcnt(0xC07F); // LDS writes done (lgkmcnt 0); loads in flight are left alone
-        ks_barrier_nofence();
-        const int chunks = rows_here * (CFG::RES / 8);
-        for (int q = tid; q < chunks; q += CFG::NT) {
-            const int row = q / (CFG::RES / 8), ch = q % (CFG::RES / 8);
-            *(uint4 *)(dZT + (int64_t)(c0 + row) * Bp + ts * CFG::RES + ch * 8) = *(const uint4 *)(stage + row * STAGE_LD + ch * 8);
+            if (fm * 32 < rows_here) sm_store_block(pk, p + (int64_t)fm * 4 * Bp * 8, Bp);
         }
     };
-    ks_soe_sweep<CFG>(X, D, ts * CFG::RES, B, W, D, active_idx, s0, s1, n, lds, epi, s_lidx, SM_LIDX_CAP);
+    ks_soe_sweep<CFG, 2 * CFG::FM>(X, D, ts * CFG::RES, B, W, D, active_idx, s0, s1, n, lds, epi, s_lidx, SM_LIDX_CAP);
 }
 
 
@@ -636,19 +596,15 @@ sm_grad_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
 // exponential overflows and not all of a sample's vanish, which the combine kernel checks.
 // ------------------------------------------------------------------------------------------------
 // The sweep runs on the eight-wavefront engine (ks_gemm_soe.h): wavefront w owns samples [32 w, 32 w + 32) of the
-// tile and two wavefronts share a SIMD, so the exponentials, the LDS writes and the copy-out of one overlap with
-// the MFMAs of the other (measured on the headline shape: 34 us against 40 us with four wavefronts of 64 samples).
-template <int KT>
+// tile and two wavefronts share a SIMD, so the exponentials and stores of one overlap with the MFMAs of the other.
+// The sums of the stored (rounded) values come from the matrix pipe: a product with a block of ones on the packed values.
+template <class CFG>
 __global__ void __launch_bounds__(512)
 sm_fused_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const int32_t *__restrict__ active_idx,
                      const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, int B, int Bp, int D, int M,
-                     int tiles_s, float scale, float *__restrict__ pl, float *__restrict__ pl_others, uint16_t *__restrict__ dZT) {
-    typedef KsSoe<KT, 96, SOE_STAGES, 2> CFG;
-    constexpr int STAGE_LD = CFG::RES + 8;
-    constexpr int NT = CFG::NT;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
-    __shared__ int32_t s_lidx[SM_LIDX_CAP];
-    __shared__ __attribute__((aligned(16))) uint16_t stage[CFG::CH * STAGE_LD];
+                     int tiles_s, float scale, float *__restrict__ pl, float *__restrict__ pl_others, uint16_t *__restrict__ dZ8) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS + 2 * SM_LIDX_CAP]; // one array: see ks_gemm_soe.h
+    int32_t *const s_lidx = (int32_t *)(lds + CFG::LDS_ELEMS);
     const int n = sm_clamp_n(n_active_p, M);
     const int n64 = (n + 63) & ~63;
     const int slabs = gridDim.x / tiles_s;
@@ -658,129 +614,64 @@ sm_fused_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     const int s0 = slab * h, s1 = (s0 + h < n64) ? s0 + h : n64;
     if (slab >= slabs || s0 >= s1) return;
     const int lim = n < s1 ? n : s1; // rows of this slab that are real classes
-    __shared__ float s_sum[8 * NT];  // thread t: running sums of its eight samples over its rows, at [c * NT + t]
-#pragma unroll
-    for (int c = 0; c < 8; ++c) s_sum[c * NT + threadIdx.x] = 0.f;
     const float k1 = scale * 1.4426950408889634f; // exp(scale * acc - scale) = exp2(fma(acc, k1, -k1))
     const bool samples_ok = (ts + 1) * CFG::RES <= B;
+    const int i = ts * CFG::RES + ks_soe_col();
+    const bool ok = i < B;
+    const int my_tp = ok ? target_pos[i] : -1; // position of this lane's sample's class in the active list
     // For the loss: this lane's sum of the UNROUNDED exponentials of its sample over its rows, the sample's own class
     // left out (the combine step adds that one from an fp32 dot product).  The sums of the stored, rounded values
     // (`pl`) are what the gradient columns must add up to; for the loss of a confident sample they would carry the
-    // bf16 rounding of its strongest competitor, 2^-9 relative.
+    // bf16 rounding of its strongest competitor, 2^-9 relative.  The own class is left out of those too, and stored as 0:
+    // the combine step writes its place.
     float others = 0.f;
-    int my_tp = -1; // position of this lane's sample's class in the active list
-    {
-        const int i = ts * CFG::RES + ks_soe_col();
-        if (i < B) my_tp = target_pos[i];
-    }
+    f32x4_t rounded = {0.f, 0.f, 0.f, 0.f}; // every element: the sum of the values that this lane has stored
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
+        const int lane = threadIdx.x & 63;
         const bool plain = samples_ok && c0 + CFG::CH <= lim; // no row or column of this chunk needs masking
         const int tl = my_tp - c0;                             // the own class's row in this chunk, if in [0, CH)
-        const bool own_here = __any(tl >= 0 && tl < CFG::CH);  // uniform: some sample of this wavefront has its class here
-        float csum = 0.f;
-        // thread-index arithmetic is redone here behind a copy the compiler cannot see through, so that it does not
-        // hoist the LDS addresses out of the sweep and spill them
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        const int lane = tid & 63;
-        const bool odd = lane & 1;
-        const int col = (tid >> 6) * 32 + (tid & 31);
-        const bool ok = ts * CFG::RES + col < B;
-        const int tq = tl - 4 * (lane >> 5); // the own class's accumulator element: fm * 32 + 8 * (r >> 2) + (r & 3) == tq
-        // the element loop, compiled three times: plain chunks with and without the test for the own class, and chunks
-        // with rows or samples to mask (no branch inside the loop)
-        auto elements = [&](auto own, auto is_plain) __attribute__((always_inline)) {
-            constexpr bool OWN = decltype(own)::value, PLAIN = decltype(is_plain)::value;
+        uint16_t *p = dZ8 + sm_dz_at(c0 + 8 * (lane >> 5), i, Bp); // (i < Bp: whole tiles exist)
+        typedef short s16x4_t __attribute__((ext_vector_type(4)));
+        const s16x4_t ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80}; // bf16
+        float c4[4] = {0.f, 0.f, 0.f, 0.f}; // four chains: the additions do not wait on one sum
+        if (!plain || __any(tl >= 0 && tl < CFG::CH)) { // rows or samples to mask, or some sample of this wavefront has its class here
+            // accumulator element (fm, r) is row fm * 32 + 8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)
+            const int tq = tl - 4 * (lane >> 5), lq = ok ? lim - c0 - 4 * (lane >> 5) : 0;
 #pragma unroll
             for (int fm = 0; fm < CFG::FM; ++fm)
 #pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    float d[2];
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) d[e] = __builtin_amdgcn_exp2f(fmaf(acc[fm][r + e], k1, -k1));
-                    if (!PLAIN) {
-#pragma unroll
-                        for (int e = 0; e < 2; ++e)
-                            if (!ok || c0 + ks_soe_row(fm, r + e, lane) >= lim) d[e] = 0.f;
-                    }
-                    if (OWN) {
-                        csum += (fm * 32 + 8 * (r >> 2) + (r & 3)) == tq ? 0.f : d[0];
-                        csum += (fm * 32 + 8 * ((r + 1) >> 2) + ((r + 1) & 3)) == tq ? 0.f : d[1];
-                    } else {
-                        csum += d[0] + d[1];
-                    }
-                    // neighbouring lanes (samples 2j, 2j+1) trade so that each holds two adjacent samples of one class
-                    // row: the even lane ends up with row r, the odd lane with row r+1
-                    const float send = odd ? d[0] : d[1];
-                    const float recv = __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(send), 0xB1, 0xF, 0xF, true));
-                    const uint32_t packed = odd ? ks_pack_bf2(recv, d[1]) : ks_pack_bf2(d[0], recv);
-                    const int row = ks_soe_row(fm, r + (odd ? 1 : 0), lane);
-                    *(uint32_t *)(stage + row * STAGE_LD + (col & ~1)) = packed;
+                for (int r = 0; r < 16; ++r) {
+                    const int e = fm * 32 + 8 * (r >> 2) + (r & 3);
+                    if (e == tq || e >= lq) acc[fm][r] = -INFINITY; // its exponential is 0
                 }
-        };
-        if (plain) {
-            if (own_here) elements(std::true_type(), std::true_type());
-            else elements(std::false_type(), std::true_type());
-        } else {
-            elements(std::true_type(), std::false_type()); // (rare: the test for the own class is harmless where it is not needed)
-        }
-        others += csum;
-        __builtin_amdgcn_s_waitcnt(0xC07F); // LDS writes done (lgkmcnt 0); loads in flight are left alone
-    };
-    // second half, one stage into the next chunk: copy the chunk out in 16-byte pieces; thread t always takes the
-    // same eight samples (piece t % 32 of a row) of rows t / 32, t / 32 + 16, ..., and carries their sums
-    auto post = [&](int c0, int rows_here) {
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        constexpr int PPR = CFG::RES / 8, RPP = NT / PPR; // pieces per row, rows per pass
-        const int ch = tid % PPR;
-        float l[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) l[c] = s_sum[c * NT + tid];
-        for (int r0 = tid / PPR; r0 < rows_here; r0 += 3 * RPP) {
-            uint4 v[3];
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int row = r0 + u * RPP;
-                v[u] = (row < rows_here) ? *(const uint4 *)(stage + row * STAGE_LD + ch * 8) : make_uint4(0u, 0u, 0u, 0u);
-            }
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int row = r0 + u * RPP;
-                if (row < rows_here) *(uint4 *)(dZT + (int64_t)(c0 + row) * Bp + ts * CFG::RES + ch * 8) = v[u];
-                const uint32_t w4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    l[2 * c] += ks_bf2f(w4[c] & 0xFFFFu);
-                    l[2 * c + 1] += ks_bf2f(w4[c] >> 16);
-                }
-            }
         }
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s_sum[c * NT + tid] = l[c];
+        for (int fm = 0; fm < CFG::FM; ++fm) {
+            uint32_t pk[4][2];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                float d[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    d[e] = __builtin_amdgcn_exp2f(fmaf(acc[fm][2 * q + e], k1, -k1));
+                    c4[2 * (q & 1) + e] += d[e];
+                }
+                pk[q >> 1][q & 1] = ks_pack_bf2(d[0], d[1]);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) // (sixteen 4 x 4 products side by side: a lane's four k's of its own column)
+                rounded = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4_t, (ks_u32x2){pk[g][0], pk[g][1]}), rounded, 0, 0, 0);
+            if (fm * 32 < rows_here) sm_store_block(pk, p + (int64_t)fm * 4 * Bp * 8, Bp);
+            __builtin_amdgcn_sched_barrier(0); // one block's values at a time: the sweep leaves few registers
+        }
+        others += (c4[0] + c4[1]) + (c4[2] + c4[3]);
     };
-    ks_soe_sweep<CFG>(X, D, ts * CFG::RES, B, W, D, active_idx, s0, s1, n, lds, epi, s_lidx, SM_LIDX_CAP, post);
-    __syncthreads();
-    // the sixteen row groups of a sample meet through LDS (the stream stages are free now): red[group][sample]
-    float *red = (float *)lds;
-    static_assert(CFG::LDS_ELEMS * 2 >= (NT / (CFG::RES / 8)) * CFG::RES * 4, "reduction buffer");
-    {
-        const int grp = threadIdx.x / (CFG::RES / 8), ch = threadIdx.x % (CFG::RES / 8);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) red[grp * CFG::RES + ch * 8 + c] = s_sum[c * NT + threadIdx.x];
-    }
-    __syncthreads();
-    if (threadIdx.x < CFG::RES) {
-        const int i = ts * CFG::RES + threadIdx.x;
-        float sum = 0.f;
-#pragma unroll
-        for (int grp = 0; grp < NT / (CFG::RES / 8); ++grp) sum += red[grp * CFG::RES + threadIdx.x];
-        if (i < B) pl[(int64_t)slab * Bp + i] = sum;
-    }
+    ks_soe_sweep<CFG, 2 * CFG::FM>(X, D, ts * CFG::RES, B, W, D, active_idx, s0, s1, n, lds, epi, s_lidx, SM_LIDX_CAP);
     others += __shfl_xor(others, 32, 64); // the two lanes of a sample hold different rows
-    if ((threadIdx.x & 63) < 32) {
-        const int i = ts * CFG::RES + ks_soe_col();
-        if (i < B) pl_others[(int64_t)slab * Bp + i] = others;
+    const float stored = rounded[0] + __shfl_xor(rounded[0], 32, 64);
+    if ((threadIdx.x & 63) < 32 && ok) {
+        pl[(int64_t)slab * Bp + i] = stored;
+        pl_others[(int64_t)slab * Bp + i] = others;
     }
 }
 
@@ -807,7 +698,7 @@ __global__ void __launch_bounds__(SM_CF_NT)
 sm_combine_fused_kernel(const float *__restrict__ pl, const float *__restrict__ pl_others, const int32_t *__restrict__ n_active_p,
                         const int32_t *__restrict__ active_idx, const int32_t *__restrict__ target_pos,
                         const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, int M, int slabs, int B, int Bp, int D,
-                        float scale, float *__restrict__ inv_sum, float *__restrict__ loss_i, uint16_t *__restrict__ dZT,
+                        float scale, float *__restrict__ inv_sum, float *__restrict__ loss_i, uint16_t *__restrict__ dZ8,
                         uint16_t *__restrict__ X2, int32_t *dev_status, int mode, SmSplitIO io) {
     // SM_CF_SPB samples per workgroup, SM_CF_PARTS threads per sample (each takes a share of the slab sums and of
     // the dot product): the kernel is a chain of dependent round trips, so it is spread over many compute units
@@ -844,27 +735,22 @@ sm_combine_fused_kernel(const float *__restrict__ pl, const float *__restrict__ 
                     oth += u[q];
                 }
             }
-            // this thread's share of the dot product: D / PARTS elements, in 8-byte pieces (D is 128, 256 or 512)
-            const int per = D / PARTS;
-            const uint16_t *xr = X + (int64_t)i * D + gq * per;
-            const uint16_t *wr = W + (int64_t)cls * D + gq * per;
+            // this thread's share of the dot product: pieces gq, gq + PARTS, ... of four elements (D <= 512, D % 4 == 0)
+            const uint16_t *xr = X + (int64_t)i * D, *wr = W + (int64_t)cls * D;
             constexpr int MAXP = 512 / PARTS / 4;
             uint2 xv[MAXP], wv[MAXP];
 #pragma unroll
             for (int q = 0; q < MAXP; ++q) {
-                if (q * 4 < per) {
-                    xv[q] = *(const uint2 *)(xr + q * 4);
-                    wv[q] = *(const uint2 *)(wr + q * 4);
-                }
+                const int e = (gq + q * PARTS) * 4;
+                xv[q] = e < D ? *(const uint2 *)(xr + e) : make_uint2(0u, 0u);
+                wv[q] = e < D ? *(const uint2 *)(wr + e) : make_uint2(0u, 0u);
             }
 #pragma unroll
             for (int q = 0; q < MAXP; ++q) {
-                if (q * 4 < per) {
-                    dot = fmaf(ks_bf2f(xv[q].x & 0xFFFFu), ks_bf2f(wv[q].x & 0xFFFFu), dot);
-                    dot = fmaf(ks_bf2f(xv[q].x >> 16), ks_bf2f(wv[q].x >> 16), dot);
-                    dot = fmaf(ks_bf2f(xv[q].y & 0xFFFFu), ks_bf2f(wv[q].y & 0xFFFFu), dot);
-                    dot = fmaf(ks_bf2f(xv[q].y >> 16), ks_bf2f(wv[q].y >> 16), dot);
-                }
+                dot = fmaf(ks_bf2f(xv[q].x & 0xFFFFu), ks_bf2f(wv[q].x & 0xFFFFu), dot);
+                dot = fmaf(ks_bf2f(xv[q].x >> 16), ks_bf2f(wv[q].x >> 16), dot);
+                dot = fmaf(ks_bf2f(xv[q].y & 0xFFFFu), ks_bf2f(wv[q].y & 0xFFFFu), dot);
+                dot = fmaf(ks_bf2f(xv[q].y >> 16), ks_bf2f(wv[q].y >> 16), dot);
             }
         }
         sh[threadIdx.x] = part;
@@ -883,7 +769,7 @@ sm_combine_fused_kernel(const float *__restrict__ pl, const float *__restrict__ 
             }
             const float z_t = scale * dot;
             const float e_t = __expf(z_t - scale);
-            uint16_t *cell = dZT + (int64_t)tp * Bp + i;
+            uint16_t *cell = dZ8 + sm_dz_at(tp, i, Bp);
             if (mode == SM_IMPORT) {
                 // the sum over the classes of all nodes, brought to this kernel's reference `scale`
                 const float S = io.gsum[i] * __expf(io.gmax[i] - scale);
@@ -895,8 +781,7 @@ sm_combine_fused_kernel(const float *__restrict__ pl, const float *__restrict__ 
             } else {
                 float others = sum;
                 if (owned) {
-                    others = sum - ks_bf2f(*cell); // sum of the exponentials of the other classes
-                    sum = others + e_t;
+                    sum = others + e_t; // (the sweep leaves the sample's own class out)
                 }
                 if (mode == SM_EXPORT) {
                     io.row_max[i] = scale;
@@ -971,11 +856,11 @@ sm_combine_soe_kernel(const float *__restrict__ pm, const float *__restrict__ pl
     }
 }
 
-// dX partials on the asynchronous engine: P[s][i][d] = sum_{a in share s} dZT[a][i] * W[active[a]][d].
-// Both operands are k-major (k = a): dZT as stored, the weight rows fetched through the index list.
+// dX partials on the asynchronous engine: P[s][i][d] = sum_{a in share s} dZ[a][i] * W[active[a]][d].
+// dZ8 as stored is the operand in blocks of eight k's (k = a); the weight rows, fetched through the index list, are k-major.
 template <class T>
 __global__ void __launch_bounds__(T::NT)
-dx_partial_async_kernel(const uint16_t *__restrict__ dZT, int Bp, int64_t Mp, const uint16_t *__restrict__ W,
+dx_partial_async_kernel(const uint16_t *__restrict__ dZ8, int Bp, const uint16_t *__restrict__ W,
                         const int32_t *__restrict__ active_idx, const int32_t *__restrict__ n_active_p, int B, int D, int M,
                         int S, float *__restrict__ part, KsSelNext next) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[T::LDS_ELEMS];
@@ -997,22 +882,18 @@ dx_partial_async_kernel(const uint16_t *__restrict__ dZT, int Bp, int64_t Mp, co
     ks_a_clear<T>(acc);
     if (kt0 < kt1) {
         // gather list of this share, staged in LDS (the host sizes S so that a share fits), clamped at the end:
-        // rows at or beyond n_active meet zeros of dZT
+        // rows at or beyond n_active meet zeros of dZ8
         for (int e = threadIdx.x; e < (kt1 - kt0) * 64 && e < DX_IDX_CACHE; e += T::NT) {
             int k = kt0 * 64 + e;
             if (k >= n_active) k = n_active - 1;
             s_idx[e] = active_idx[k];
         }
         __syncthreads();
-        KsAKmaj<T::BM, T::NW> ar;
+        KsAK8<T::BM, T::NW> ar;
         KsAKmaj<T::BN, T::NW> br;
-        ar.init(dZT, Bp, nullptr, tm * T::BM, Bp, (int)Mp, kt0 * 64);
+        ar.init(dZ8, Bp, tm * T::BM); // (Bp is a multiple of the tile)
         br.init(W, D, s_idx, tn * T::BN, D, kt1 * 64, kt0 * 64);
-#if KS_DX_IL
-        ks_a_mainloop_il<T, true, true, KS_IL_SPREAD>(ar, br, kt0, kt1, lds, acc);
-#else
-        ks_a_mainloop<T, true, true>(ar, br, kt0, kt1, lds, acc);
-#endif
+        ks_a_mainloop<T, KS_K8, KS_KMAJ>(ar, br, kt0, kt1, lds, acc);
     }
     // row-wise through LDS (the main loop has ended with a barrier): 16-byte pieces of whole rows, a quarter of the
     // store instructions of an element-wise hand-out
@@ -1035,7 +916,7 @@ dx_partial_async_kernel(const uint16_t *__restrict__ dZT, int Bp, int64_t Mp, co
     }
 }
 
-// dW_active[a][d] = scale * sum_i dZT[a][i] * X[i][d] on the asynchronous engine (X k-major, k = i).
+// dW_active[a][d] = scale * sum_i dZ[a][i] * X[i][d] on the asynchronous engine (X k-major, k = i).
 // The grid is sized for M rows, so with fewer active rows part of the chip would idle; the last
 // DW_REDUCE_BLOCKS blocks of the grid therefore do a job that is due anyway and does not depend on this
 // kernel: the sum of the dX partial products of the kernel before (with the per-sample factor, if any) and
@@ -1078,12 +959,12 @@ __device__ __forceinline__ int dw_tile_rows(int n_active, int tiles_n, int n_cu)
 }
 
 template <class T>
-__device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZT, const uint16_t *__restrict__ X, int B,
+__device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
                                         const DwUpdate &up);
 
 __global__ void __launch_bounds__(TileDw::NT)
-dw_async_kernel(const uint16_t *__restrict__ dZT, const uint16_t *__restrict__ X, int B, int Bp,
+dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B, int Bp,
                 const int32_t *__restrict__ n_active_p, int D, int M, int64_t Mp, float scale, float *__restrict__ dW,
                 int tiles_max, int n_cu, DxReduceJob job, DwUpdate up, KsSelNext next) {
     typedef TileDw T;
@@ -1125,13 +1006,13 @@ dw_async_kernel(const uint16_t *__restrict__ dZT, const uint16_t *__restrict__ X
     }
     const int n_active = sm_clamp_n(n_active_p, M);
     const int rows = dw_tile_rows(n_active, (D + T::BN - 1) / T::BN, n_cu);
-    if (rows == 256) dw_tile<TileDw>(bid, lds, dZT, X, B, Bp, n_active, D, Mp, scale, dW, up);
-    else if (rows == 192) dw_tile<TileDw192>(bid, lds, dZT, X, B, Bp, n_active, D, Mp, scale, dW, up);
-    else dw_tile<TileDw128>(bid, lds, dZT, X, B, Bp, n_active, D, Mp, scale, dW, up);
+    if (rows == 256) dw_tile<TileDw>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up);
+    else if (rows == 192) dw_tile<TileDw192>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up);
+    else dw_tile<TileDw128>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up);
 }
 
 template <class T>
-__device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZT, const uint16_t *__restrict__ X, int B,
+__device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
                                         const DwUpdate &up) {
     const int tiles_n = (D + T::BN - 1) / T::BN;
@@ -1139,17 +1020,14 @@ __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *
     if (bid >= n_tiles) return;
     const int t = ks_xcd_remap(bid, n_tiles);
     const int tn = t % tiles_n, tm = t / tiles_n;
-    KsARows<T::BM, T::NW> ar;
+    KsAM8<T::BM, T::NW> ar;
     KsAKmaj<T::BN, T::NW> br;
-    ar.init(dZT, Bp, nullptr, tm * T::BM, (int)Mp);
+    ar.init(dZ8, Bp, tm * T::BM, (int)Mp);
     br.init(X, D, nullptr, tn * T::BN, D, B, 0);
     f32x16_t acc[T::FM][T::FN];
     ks_a_clear<T>(acc);
-#if KS_DW_IL
-    ks_a_mainloop_il<T, false, true, KS_IL_SPREAD>(ar, br, 0, Bp / 64, lds, acc);
-#else
-    ks_a_mainloop<T, false, true>(ar, br, 0, Bp / 64, lds, acc);
-#endif
+    // (samples B .. of the last k-tile: zeros of dZ8 meet the last row of X)
+    ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, (B + 63) / 64, lds, acc);
     // epilogue, row-wise through LDS: gradient rows out (if wanted) and, if asked for, the update of the master
     // rows and of their 16-bit copy.  Four rows per thread are in flight at a time.
     typedef KsASlab<T> SL;
@@ -1305,13 +1183,16 @@ static int ks_n_cu() {
     return n;
 }
 
+// depths that the stationary-operand engine takes, or the tile engine
+static bool sm_fast(int D) { return D <= 512 || D % 64 == 0; }
+
 struct SmWs {
     void *select;
     float *Z;
     uint16_t *dZ;
     float *lse;
     float *part;
-    uint16_t *dZT; // fast path: the logit gradient is kept transposed only
+    uint16_t *dZ8; // fast path: the logit gradient is kept transposed only
     float *pm, *pl, *zt; // fast path: per class-tile softmax statistics, target logits
     float *inv;          // one-sweep softmax: 1 / sum_a exp(z_ia - scale) per sample
     uint16_t *X2;        // one-sweep softmax: rows of X scaled by that
@@ -1339,7 +1220,7 @@ static int sm_splits(int B, int D, int64_t M, bool fast) {
 static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool with_select, size_t *total) {
     KsArena ar(ws);
     SmWs w;
-    w.fast = (D % 64 == 0);
+    w.fast = sm_fast(D);
     w.Mp = sm_mp(M);
     w.Bp = (int)ks_align_up((size_t)B, KS_BP_ALIGN);
     w.S = sm_splits(B, D, M, w.fast);
@@ -1347,11 +1228,11 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
     w.lse = ar.take<float>((size_t)B);
     w.part = ar.take<float>((size_t)w.S * B * D);
     w.Z = nullptr;
-    w.dZ = w.dZT = nullptr;
+    w.dZ = w.dZ8 = nullptr;
     w.pm = w.pl = w.zt = w.inv = nullptr;
     w.X2 = nullptr;
     if (w.fast) {
-        w.dZT = ar.take<uint16_t>((size_t)w.Mp * w.Bp);
+        w.dZ8 = ar.take<uint16_t>((size_t)w.Mp * w.Bp);
         size_t nt = (size_t)(w.Mp / TileSm::BM);
         if (nt < (size_t)SM_SOE_GRID) nt = SM_SOE_GRID; // per-slab statistics of the stationary-operand kernels
         w.pm = ar.take<float>(nt * w.Bp);
@@ -1366,6 +1247,24 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
     if (total) *total = ar.off;
     return w;
 }
+
+// Sweeps of a depth of up to eight k-tiles (D <= 512, D % 32 == 0): F(CFG) is instantiated for the depth's stage shape
+#define SM_COMMA ,
+#define SM_FOR_DEPTH(F)                                                                                   \
+    do {                                                                                                  \
+        const int kt = (D + 63) / 64;                                                                     \
+        if (D % 64 == 0) {                                                                                \
+            if (kt == 1) F(SmSoe<1 SM_COMMA false>); else if (kt == 2) F(SmSoe<2 SM_COMMA false>);        \
+            else if (kt == 3) F(SmSoe<3 SM_COMMA false>); else if (kt == 4) F(SmSoe<4 SM_COMMA false>);   \
+            else if (kt == 5) F(SmSoe<5 SM_COMMA false>); else if (kt == 6) F(SmSoe<6 SM_COMMA false>);   \
+            else if (kt == 7) F(SmSoe<7 SM_COMMA false>); else F(SmSoe<8 SM_COMMA false>);                \
+        } else {                                                                                          \
+            if (kt == 1) F(SmSoe<1 SM_COMMA true>); else if (kt == 2) F(SmSoe<2 SM_COMMA true>);          \
+            else if (kt == 3) F(SmSoe<3 SM_COMMA true>); else if (kt == 4) F(SmSoe<4 SM_COMMA true>);     \
+            else if (kt == 5) F(SmSoe<5 SM_COMMA true>); else if (kt == 6) F(SmSoe<6 SM_COMMA true>);     \
+            else if (kt == 7) F(SmSoe<7 SM_COMMA true>); else F(SmSoe<8 SM_COMMA true>);                  \
+        }                                                                                                 \
+    } while (0)
 
 // everything after the selection; active_idx / n_active / target_pos are device-resident inputs here
 static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M, float scale, float grad_scale,
@@ -1383,52 +1282,47 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
     bool fused = false;
     if (w.fast) {
         const int tiles_s = (int)ks_ceil_div(B, 256);
-        const bool soe = (D == 128 || D == 256 || D == 512) && tiles_s <= SM_SOE_GRID && scale > 0.f && g > 0.f;
+        const bool soe = D <= 512 && tiles_s <= SM_SOE_GRID && scale > 0.f && g > 0.f;
         // unit rows: |logit| <= scale, and exp(-2 scale) must stay a normal number
         fused = soe && (flags & KS_FLAG_UNIT_ROWS) && scale <= KS_FUSED_MAX_SCALE;
+        const int grid = soe ? SM_SOE_GRID / tiles_s * tiles_s : 0, slabs = soe ? grid / tiles_s : 0;
         if (fused) {
-            const int grid = SM_SOE_GRID / tiles_s * tiles_s, slabs = grid / tiles_s;
-#define SM_FUSED_LAUNCH(KT)                                                                                               \
-    hipLaunchKernelGGL(sm_fused_soe_kernel<KT>, dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, B,   \
-                       w.Bp, D, Mi, tiles_s, scale, w.pl, w.pm, w.dZT)
-            if (mode != SM_IMPORT) { // the first call of a split has left the exponentials in the workspace
-                if (D == 512) SM_FUSED_LAUNCH(8);
-                else if (D == 256) SM_FUSED_LAUNCH(4);
-                else SM_FUSED_LAUNCH(2);
-            }
+#define SM_FUSED_LAUNCH(CFG)                                                                                              \
+    hipLaunchKernelGGL((sm_fused_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, B, \
+                       w.Bp, D, Mi, tiles_s, scale, w.pl, w.pm, w.dZ8)
+            if (mode != SM_IMPORT) SM_FOR_DEPTH(SM_FUSED_LAUNCH); // the first call of a split has left the exponentials in the workspace
 #undef SM_FUSED_LAUNCH
             mark(2);
             hipLaunchKernelGGL(sm_combine_fused_kernel, dim3((unsigned)ks_ceil_div(B, SM_CF_SPB)), dim3(SM_CF_NT), 0, st, w.pl,
                                w.pm, n_active, active_idx, target_pos, X, W, Mi, slabs, B, w.Bp, D, scale, w.inv, loss_per_sample,
-                               w.dZT, w.X2, dev_status, mode, io);
+                               w.dZ8, w.X2, dev_status, mode, io);
             mark(3);
             if (mode == SM_EXPORT) {
                 KS_LAUNCH_CHECK();
                 return KS_OK;
             }
         } else if (soe) {
-            const int grid = SM_SOE_GRID / tiles_s * tiles_s, slabs = grid / tiles_s;
-#define SM_SOE_LAUNCH(KT)                                                                                                 \
-    do {                                                                                                                  \
-        if (mode != SM_IMPORT) {                                                                                          \
-            hipLaunchKernelGGL(sm_stats_soe_kernel<KT>, dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active,         \
-                               target_pos, B, w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt);                              \
-            mark(2);                                                                                                      \
-            hipLaunchKernelGGL(sm_combine_soe_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT / 64)), dim3(SM_NT), 0, st,     \
-                               w.pm, w.pl, w.zt, n_active, Mi, slabs, B, w.Bp, w.lse, loss_per_sample);                    \
-            mark(3);                                                                                                      \
-        }                                                                                                                 \
-        if (mode != SM_EXPORT)                                                                                            \
-            hipLaunchKernelGGL(sm_grad_soe_kernel<KT>, dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active,          \
-                               target_pos, w.lse, B, w.Bp, D, Mi, tiles_s, scale, g, w.dZT);                               \
-    } while (0)
-            if (mode == SM_IMPORT)
+            if (mode != SM_IMPORT) {
+#define SM_STATS_LAUNCH(CFG)                                                                                              \
+    hipLaunchKernelGGL((sm_stats_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, B, \
+                       w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt)
+                SM_FOR_DEPTH(SM_STATS_LAUNCH);
+#undef SM_STATS_LAUNCH
+                mark(2);
+                hipLaunchKernelGGL(sm_combine_soe_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT / 64)), dim3(SM_NT), 0, st,
+                                   w.pm, w.pl, w.zt, n_active, Mi, slabs, B, w.Bp, w.lse, loss_per_sample);
+                mark(3);
+            } else {
                 hipLaunchKernelGGL(sm_import_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT)), dim3(SM_NT), 0, st, io, B, w.lse,
                                    loss_per_sample);
-            if (D == 512) SM_SOE_LAUNCH(8);
-            else if (D == 256) SM_SOE_LAUNCH(4);
-            else SM_SOE_LAUNCH(2);
-#undef SM_SOE_LAUNCH
+            }
+            if (mode != SM_EXPORT) {
+#define SM_GRAD_LAUNCH(CFG)                                                                                               \
+    hipLaunchKernelGGL((sm_grad_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos,     \
+                       w.lse, B, w.Bp, D, Mi, tiles_s, scale, g, w.dZ8)
+                SM_FOR_DEPTH(SM_GRAD_LAUNCH);
+#undef SM_GRAD_LAUNCH
+            }
         } else {
             typedef TileSm T;
             const int tiles = (int)(ks_ceil_div(B, T::BN) * ks_ceil_div(M, T::BM));
@@ -1445,7 +1339,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             }
             if (mode != SM_EXPORT)
                 hipLaunchKernelGGL(sm_grad_kernel<T>, dim3(tiles), dim3(T::NT), 0, st, X, W, active_idx, n_active, target_pos,
-                                   w.lse, B, w.Bp, D, Mi, scale, g, w.dZT);
+                                   w.lse, B, w.Bp, D, Mi, scale, g, w.dZ8);
         }
         if (mode == SM_EXPORT) { // two-sweep paths: the statistics sweep is done, (lse, 1) and the target logit go out
             hipLaunchKernelGGL(sm_export_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT)), dim3(SM_NT), 0, st, w.lse, w.zt,
@@ -1458,8 +1352,8 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             typedef TileDx T;
             const int tiles = (int)(ks_ceil_div(B, T::BM) * ks_ceil_div(D, T::BN));
             if (next.nsel) next.nfetch = (int)ks_ceil_div((int64_t)next.B * (next.K + 1), (int64_t)T::NT);
-            hipLaunchKernelGGL(dx_partial_async_kernel<T>, dim3(tiles * w.S + next.nfetch), dim3(T::NT), 0, st, w.dZT, w.Bp,
-                               w.Mp, W, active_idx, n_active, B, D, Mi, w.S, w.part, next);
+            hipLaunchKernelGGL(dx_partial_async_kernel<T>, dim3(tiles * w.S + next.nfetch), dim3(T::NT), 0, st, w.dZ8, w.Bp,
+                               W, active_idx, n_active, B, D, Mi, w.S, w.part, next);
         }
         mark(5);
         mark(6); // the reduction of the partial products rides along with the next launch
@@ -1475,7 +1369,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             job.dX = dX;
             job.loss_i = loss_per_sample;
             job.loss_mean = loss_mean;
-            hipLaunchKernelGGL(dw_async_kernel, dim3(next.nsel + tiles + DW_REDUCE_BLOCKS), dim3(T::NT), 0, st, w.dZT,
+            hipLaunchKernelGGL(dw_async_kernel, dim3(next.nsel + tiles + DW_REDUCE_BLOCKS), dim3(T::NT), 0, st, w.dZ8,
                                fused ? w.X2 : X, B, w.Bp, n_active, D, Mi, w.Mp, fused ? scale * g : scale, dW_active, tiles,
                                ks_n_cu(), job, up, next);
         }
@@ -1531,8 +1425,8 @@ static int sm_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const int3
     if (!W_bf16 || !X_bf16 || !labels || !active_idx || !n_active || !target_pos || !loss_per_sample || !loss_mean ||
         !dX || !ws)
         return KS_INVALID_ARG;
-    const bool fast = D % 64 == 0; // the update runs inside the dW kernel of these paths; the others keep dW_active
-    if (!dW_active && !(W_master && fast)) return KS_INVALID_ARG;
+    const bool fast = sm_fast(D); // the update runs inside the dW kernel of these paths
+    if (!dW_active && !(W_master && D % 64 == 0)) return KS_INVALID_ARG;
     if (sm_check_dims(C, D, B) != KS_OK || K < 0 || M < 1) return KS_INVALID_ARG;
     if (K > 0 && !graph) return KS_INVALID_ARG;
     if (B > M || (int64_t)K + 1 > M) return KS_INVALID_ARG;
@@ -1793,9 +1687,9 @@ static int sm_selected(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16
         return KS_INVALID_ARG;
     if (sm_selected_check(C, D, B, M) != KS_OK) return KS_INVALID_ARG;
     if (flags & ~(uint32_t)(KS_FLAG_UNIT_ROWS | KS_FLAG_TRUSTED_LIST)) return KS_INVALID_ARG;
-    const bool fast = D % 64 == 0;
+    const bool fast = sm_fast(D);
     const bool trusted = (flags & KS_FLAG_TRUSTED_LIST) != 0;
-    if (!dW_active && !(W_master && fast)) return KS_INVALID_ARG;
+    if (!dW_active && !(W_master && D % 64 == 0)) return KS_INVALID_ARG;
     // a trusted list is read where it lies, until the end of the call: the next batch's list needs buffers of its own
     if (nx && trusted && (nx->active_idx == active_idx || nx->n_active == n_active || nx->target_pos == target_pos))
         return KS_INVALID_ARG;

@@ -63,3 +63,17 @@ def test_hop_cut_into_parts(ks, orc, C_loc, C_vis, D, K, bf16):
             got = graph[i].cpu().numpy()
             assert (got[:n] == best).all() and (got[n:] == -1).all()
             assert np.allclose(sims[i].cpu().numpy()[:n], S[i][best - C_loc], rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("D", [32, 64, 96, 160, 192, 224, 256, 320, 352, 384, 448, 480, 512, 544, 576])
+@pytest.mark.parametrize("C,B,K,M", [(700, 33, 6, 200), (3000, 300, 9, 2500)])
+def test_step_at_every_depth(ks, orc, D, C, B, K, M):
+    """Forward and backward in both softmax modes at whole and ragged depths of one to nine k-tiles (the sweeps with resident
+    samples up to 512, the tile engines beyond), batches that end inside a tile and lists that end inside a chunk."""
+    from test_gpu_parity import run_and_compare
+    print(f"[depths] step D={D} C={C} B={B}", flush=True)
+    W, X = synth.unit_rows(31, synth.TID_W, C, D, bf16=True), synth.unit_rows(31, synth.TID_X, B, D, bf16=True)
+    y = synth.labels_uniform(31, B, C)
+    G = ((np.arange(C)[:, None] * 7 + 1 + np.arange(K)[None, :] * 13) % C).astype(np.int32)
+    X[:5] = synth.bf16_round((0.9 * W[y[:5]] + 0.1 * X[:5]).astype(np.float32))   # a few confident samples
+    run_and_compare(ks, orc, W, X, y, G, C, M, scale=30.0, grad_scale=4.0, tag=f"D={D}")
