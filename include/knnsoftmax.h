@@ -225,8 +225,8 @@ int knn_softmax_fwd_bwd_update_selected(float *W_master, uint16_t *W_bf16, const
  *                       KS_FLAG_TRUSTED_LIST, which reads the list in place: then they must be other buffers, else
  *                       KS_INVALID_ARG -- a loop alternates between two sets).
  *   everything else     as in knn_softmax_fwd_bwd_update_selected, with the same results bit for bit
- * Requires K + 1 <= M besides that call's conditions.  When D is not a multiple of 64, or C exceeds the 393,216 classes
- * whose bitmap one workgroup holds, the selection runs after the step as launches of its own (same results).
+ * Requires K + 1 <= M besides that call's conditions.  When D exceeds 512 and is not a multiple of 64, or C exceeds the
+ * roughly 1.2 million classes whose bitmap one workgroup holds, the selection runs after the step as launches of its own (same results).
  * Workspace: knn_softmax_selected_next_workspace. */
 size_t knn_softmax_selected_next_workspace(int64_t C, int D, int B, int K, int M);
 int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16,
@@ -320,7 +320,7 @@ int apply_weight_grad(float *W_master, uint16_t *W_bf16, const int32_t *idx, con
  * only the next batch's labels and the node's compressed graph, so it runs as extra workgroups of the dX and dW launches
  * and leaves the node's critical path (Section 3.2.1).  Outputs exactly as knn_select_active_csr writes them; they may be
  * the buffers this call's list came in, except with KS_FLAG_TRUSTED_LIST.  Requires B <= M and K_max + 1 <= M.  Nodes of
- * more than 393,216 classes run the selection after the step instead.  Workspace: knn_softmax_split_next_workspace,
+ * more than roughly 1.2 million classes run the selection after the step instead.  Workspace: knn_softmax_split_next_workspace,
  * passed to both calls of a step.
  * ---------------------------------------------------------------------------------------------------- */
 size_t knn_softmax_split_workspace(int64_t C, int D, int B, int M);

@@ -54,46 +54,52 @@ __device__ __forceinline__ uint32_t ks_pack_bf2(float lo, float hi) {
 }
 __device__ __forceinline__ float ks_bf2f(uint32_t b) { return __uint_as_float(b << 16); }
 
-__device__ __forceinline__ float ks_wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ float ks_wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ int ks_wave_sum_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
+// Reductions and scans of a whole wave (all 64 lanes active) by DPP moves: shifts of 1, 2, 4, 8 lanes inside the rows of 16,
+// then the last lane of a row to the next row (0x142) and of the first half to the second (0x143).  A step is one
+// vector instruction's latency; the LDS crossbar that __shfl uses costs about 60 cycles a step, which is what the
+// small kernels around the sweeps consisted of.  KS_DPP(old, v, ctrl, rows): v of the source lane, `old` where there is none
+// or the row is not in the mask.
+#define KS_DPP(old, v, ctrl, rows) __builtin_amdgcn_update_dpp(old, v, ctrl, rows, 0xf, false)
+#define KS_DPP_F(old, v, ctrl, rows) __int_as_float(KS_DPP(__float_as_int(old), __float_as_int(v), ctrl, rows))
 // inclusive scan inside a wave
 __device__ __forceinline__ int ks_wave_iscan(int v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
+    v += KS_DPP(0, v, 0x111, 0xf);
+    v += KS_DPP(0, v, 0x112, 0xf);
+    v += KS_DPP(0, v, 0x114, 0xf);
+    v += KS_DPP(0, v, 0x118, 0xf);
+    v += KS_DPP(0, v, 0x142, 0xa);
+    v += KS_DPP(0, v, 0x143, 0xc);
     return v;
+}
+__device__ __forceinline__ int ks_wave_sum_i(int v) { return __builtin_amdgcn_readlane(ks_wave_iscan(v), 63); }
+__device__ __forceinline__ float ks_wave_sum(float v) {
+    v += KS_DPP_F(0.f, v, 0x111, 0xf);
+    v += KS_DPP_F(0.f, v, 0x112, 0xf);
+    v += KS_DPP_F(0.f, v, 0x114, 0xf);
+    v += KS_DPP_F(0.f, v, 0x118, 0xf);
+    v += KS_DPP_F(0.f, v, 0x142, 0xa);
+    v += KS_DPP_F(0.f, v, 0x143, 0xc);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float ks_wave_max(float v) {
+    v = fmaxf(v, KS_DPP_F(v, v, 0x111, 0xf));
+    v = fmaxf(v, KS_DPP_F(v, v, 0x112, 0xf));
+    v = fmaxf(v, KS_DPP_F(v, v, 0x114, 0xf));
+    v = fmaxf(v, KS_DPP_F(v, v, 0x118, 0xf));
+    v = fmaxf(v, KS_DPP_F(v, v, 0x142, 0xa));
+    v = fmaxf(v, KS_DPP_F(v, v, 0x143, 0xc));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 // exclusive scan over a block of NT threads (NT multiple of 64, <= 1024); returns the exclusive prefix
 // of v, and the block total through *total.  `sh` needs NT/64 + 1 ints of LDS.  Contains barriers.
 template <int NT> __device__ __forceinline__ int ks_block_escan(int v, int *sh, int *total) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int inc = ks_wave_iscan(v);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int inc = ks_wave_iscan(v);
     if (lane == 63) sh[w] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int i = 0; i < NT / 64; ++i) { int t = sh[i]; sh[i] = run; run += t; }
-        sh[NT / 64] = run;
-    }
-    __syncthreads();
-    int r = inc - v + sh[w];
-    *total = sh[NT / 64];
+    const int waves = ks_wave_iscan(lane < NT / 64 ? sh[lane] : 0);
+    *total = __builtin_amdgcn_readlane(waves, 63);
+    const int r = inc - v + (w ? __builtin_amdgcn_readlane(waves, w - 1) : 0);
     __syncthreads();
     return r;
 }

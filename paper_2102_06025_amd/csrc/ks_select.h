@@ -1,6 +1,7 @@
 // Internal interface of the selection stage (see ks_select.hip), and the device code of the single-workgroup selection,
 // which also runs as extra workgroups of the step's own launches (the selection of the NEXT batch, ks_softmax.hip).
 #pragma once
+#include <type_traits>
 #include "ks_common.h"
 
 size_t ks_select_ws_bytes(int64_t C, int B, int K);
@@ -9,14 +10,18 @@ int ks_select_launch(const int32_t *labels, const int32_t *graph, int64_t C, int
                      int32_t *active_idx, int32_t *n_active, int32_t *target_pos, void *ws,
                      int32_t *dev_status, hipStream_t st);
 
-#define SEL1_MAX_WORDS_HOST 12288 /* classes / 32 up to which the single-workgroup path is used */
+#define SEL1_WS_CLASSES 393216 /* up to this many classes the workspace is sized for the staged candidates, beyond for the score table */
 #define SEL1_NT 1024
 #define SEL1_GRID 32
-#define SEL1_MAX_WORDS SEL1_MAX_WORDS_HOST
 #define SEL1_FIRST_WORDS 257 /* one bit per sample of batches up to 8,192 (+ one word so that a clear loop may run over) */
-// LDS words of the single-workgroup selection with nt threads: three bitmaps / prefix arrays, the first-of-its-label
-// bits, the block scan's partial sums and one counter
-__host__ __device__ constexpr int sel1_lds_words(int nt) { return 3 * SEL1_MAX_WORDS + SEL1_FIRST_WORDS + nt / 64 + 2; }
+#define SEL1_LDS_WORDS 40600 /* LDS of the single-workgroup selection (162,400 of 163,840 bytes) */
+#define SEL1_FIXED_WORDS 540 /* first-of-its-label bits (257), digit counts (256), block scan (1024 / 64 + 1), three scalars, to a multiple of 4 */
+// The selection by one workgroup needs LDS for a bit per class, the running count at every 32nd word of them, and (when the
+// cut bites) the classes first seen at the cut position, at most one per sample and per class.
+__host__ __device__ __forceinline__ bool sel1_fits(int64_t C, int B) {
+    const int64_t nq = (C + 1023) >> 10, n_list = B < C ? B : C;
+    return nq * 33 + n_list + SEL1_FIXED_WORDS <= SEL1_LDS_WORDS;
+}
 
 // candidate at list position r of sample i (r = 0: the sample's own class), as an id in [0, C), or -1
 struct SelDense {
@@ -102,140 +107,230 @@ __device__ __forceinline__ uint32_t sel_pad_draw(uint32_t k, const SelPad &p) {
     return (x + p.s_hi) & p.mask;
 }
 
-// exclusive prefix over the words of a bitmap: pre[w] = number of set bits in words < w; returns the total
+// Number of set bits of the bitmap of 32 nq words; coarse[q] = number of set bits in words < 32 q.  Eight lanes add up
+// the 32 words of an entry, four words a lane.
 template <int NT>
-__device__ __forceinline__ int sel1_prefix(const uint32_t *bm, int nw, int *pre, int *sh) {
-    const int per = (nw + NT - 1) / NT;
-    const int w0 = threadIdx.x * per;
-    int local = 0;
-    for (int w = w0; w < w0 + per && w < nw; ++w) local += __popc(bm[w]);
-    int total;
-    int run = ks_block_escan<NT>(local, sh, &total);
-    for (int w = w0; w < w0 + per && w < nw; ++w) {
-        pre[w] = run;
-        run += __popc(bm[w]);
+__device__ __forceinline__ int sel1_count(const uint32_t *bm, int nq, int *coarse, int *sh) {
+    const int lane8 = threadIdx.x & 7;
+    for (int q0 = 0; q0 < nq; q0 += NT / 8) {
+        const int q = q0 + (int)(threadIdx.x >> 3);
+        int n = 0;
+        if (q < nq) {
+            const uint4 v = *(const uint4 *)(bm + q * 32 + lane8 * 4);
+            n = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        }
+        n += KS_DPP(0, n, 0x111, 0xf);
+        n += KS_DPP(0, n, 0x112, 0xf);
+        n += KS_DPP(0, n, 0x114, 0xf); // the last of eight lanes has their sum (others of the row of 16 wrong ones)
+        if (lane8 == 7 && q < nq) coarse[q] = n;
     }
     __syncthreads();
+    int carry = 0;
+    for (int q0 = 0; q0 < nq; q0 += NT) {
+        const int q = q0 + (int)threadIdx.x;
+        int total;
+        const int ex = ks_block_escan<NT>(q < nq ? coarse[q] : 0, sh, &total);
+        if (q < nq) coarse[q] = carry + ex;
+        carry += total;
+    }
+    __syncthreads();
+    return carry;
+}
+// Number of set bits alone; leaves the bitmap cleared.
+template <int NT> __device__ __forceinline__ int sel1_count_clear(uint32_t *bm, int nq, int *sh) {
+    int n = 0;
+    for (int p = threadIdx.x; p < nq * 8; p += NT) {
+        const uint4 v = *(const uint4 *)(bm + p * 4);
+        *(uint4 *)(bm + p * 4) = make_uint4(0u, 0u, 0u, 0u);
+        n += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    int total;
+    ks_block_escan<NT>(n, sh, &total);
     return total;
 }
 
-// The whole selection by one workgroup of NT threads (see ks_select.hip for the method).  `lds` has sel1_lds_words(NT)
+// Candidates of a batch as the selection reads them.  mark(n, first, f): f(class) for every candidate at a list position
+// below n; at(r, f): for those at position r; label(i): the sample's own class, or -1.
+//
+// Staged: the candidates lie in memory, list-position-major (cand[r * B + i]), written by an earlier launch: the scattered
+// reads of many lists are spread over the chip.
+template <int NT> struct Sel1Staged {
+    const int32_t *__restrict__ cand;
+    int B, K;
+    const uint32_t *first; // bit i: sample i is the first of its label (nullptr: not known, all are taken)
+    template <class F> __device__ __forceinline__ void range(int64_t begin, int64_t end, F f) const {
+        const int tid = threadIdx.x;
+        const int64_t n_vec = end >> 2; // (begin is 0 or a multiple of 4; the array is 256-byte aligned: whole pieces, then a tail)
+        for (int64_t t0 = begin >> 2; t0 < n_vec; t0 += (int64_t)NT * 8) {
+            int4 c[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { // many loads in flight: the round trips to L2 are what this costs
+                const int64_t t = t0 + (int64_t)e * NT + tid;
+                c[e] = t < n_vec ? ((const int4 *)cand)[t] : make_int4(-1, -1, -1, -1);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                uint32_t f4 = 0xFu; // which of the four samples are the first of their label (B a power of two)
+                if (first) {
+                    const int i0 = (int)(((t0 + (int64_t)e * NT + tid) << 2) & (B - 1));
+                    f4 = first[i0 >> 5] >> (i0 & 31);
+                }
+                if (c[e].x >= 0 && (f4 & 1u)) f(c[e].x);
+                if (c[e].y >= 0 && (f4 & 2u)) f(c[e].y);
+                if (c[e].z >= 0 && (f4 & 4u)) f(c[e].z);
+                if (c[e].w >= 0 && (f4 & 8u)) f(c[e].w);
+            }
+        }
+        for (int64_t t = (n_vec * 4 > begin ? n_vec * 4 : begin) + tid; t < end; t += NT) {
+            const int32_t c = cand[t];
+            if (c >= 0) f(c);
+        }
+    }
+    template <class F> __device__ __forceinline__ void mark(int n, F f) const { range(0, (int64_t)n * B, f); }
+    template <class F> __device__ __forceinline__ void at(int r, F f) const {
+        for (int i = threadIdx.x; i < B; i += NT) {
+            const int32_t c = cand[(int64_t)r * B + i];
+            if (c >= 0) f(c);
+        }
+    }
+    __device__ __forceinline__ int32_t label(int i) const { return cand[i]; }
+};
+// Direct: batches of at most NT * E candidates are read from the labels and lists by the selecting workgroups themselves
+// (every one of them reads all) and stay in registers: one launch instead of two, and the passes of the cut read nothing.
+template <int NT, int E, class Src> struct Sel1Direct {
+    Src src;
+    int32_t c[E];
+    int r[E];
+    __device__ __forceinline__ void load(int B, int K, bool report, int32_t *dev_status) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int q = e * NT + (int)threadIdx.x;
+            const int i = q / (K + 1);
+            r[e] = q - i * (K + 1);
+            c[e] = i < B ? src.cand(i, r[e], report ? dev_status : nullptr) : -1;
+        }
+    }
+    template <class F> __device__ __forceinline__ void mark(int n, F f) const {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (c[e] >= 0 && r[e] < n) f(c[e]);
+    }
+    template <class F> __device__ __forceinline__ void at(int rr, F f) const {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (c[e] >= 0 && r[e] == rr) f(c[e]);
+    }
+    __device__ __forceinline__ int32_t label(int i) const { return src.cand(i, 0, nullptr); }
+};
+
+// The whole selection by one workgroup of NT threads (see ks_select.hip for the method).  `lds` has SEL1_LDS_WORDS
 // words.  The G workgroups that call this with g = 0 .. G - 1 all do the same LDS work and write a G-th of the outputs
 // each.  A __device__ function so that the workgroups may be those of a kernel of their own or extra workgroups of
 // another launch.
-template <int NT>
-__device__ __forceinline__ void sel1_body(uint32_t *lds, const int32_t *__restrict__ cand, int64_t C, int B, int K, int M,
+template <int NT, class Cands>
+__device__ __forceinline__ void sel1_body(uint32_t *lds, Cands &cands, int64_t C, int B, int K, int M,
                                           int foreign_labels, SelPad pad, int32_t *__restrict__ active_idx,
                                           int32_t *__restrict__ n_active, int32_t *__restrict__ n_found,
                                           int32_t *__restrict__ target_pos, const int G, const int g) {
-    uint32_t *bm = lds, *eq = lds + SEL1_MAX_WORDS;
-    int *pre = (int *)(lds + 2 * SEL1_MAX_WORDS);
-    uint32_t *s_first = lds + 3 * SEL1_MAX_WORDS;
-    int *sh = (int *)(s_first + SEL1_FIRST_WORDS);
-    int &s_new = sh[NT / 64 + 1];
-    const int nw = (int)((C + 31) >> 5);
+    const int nq = (int)((C + 1023) >> 10), n_list = B < C ? B : (int)C; // the bitmap has 32 nq words
     const int tid = threadIdx.x;
-    for (int w = tid; w < nw; w += NT) bm[w] = 0u;
+    uint32_t *s_first = lds;
+    int *hist = (int *)(s_first + SEL1_FIRST_WORDS), *sh = hist + 256; // sh: the block scan, then scalars
+    int &s_new = sh[1024 / 64 + 1], &s_bin = sh[1024 / 64 + 2], &s_rem = sh[1024 / 64 + 3];
+    uint32_t *bm = lds + SEL1_FIXED_WORDS;
+    int *coarse = (int *)(bm + nq * 32), *list = coarse + nq;
+    auto bit_of = [&](int32_t c) { return 1u << (c & 31); };
+    auto set = [&](int32_t c) { atomicOr(&bm[c >> 5], bit_of(c)); };
+    for (int p = tid; p < nq * 8; p += NT) *(uint4 *)(bm + p * 4) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    // optimistic pass: every candidate, whatever its list position (sixteen loads in flight per thread: the
-    // round trips to L2 are what this phase costs)
-    const int64_t n_cand = (int64_t)B * (K + 1);
-    const int64_t n_vec = n_cand >> 2; // the staging array is 256-byte aligned: whole 16-byte pieces, then a tail
-    // Samples with the same label have the same list, and with skewed labels half of the batch are repeats: only the
-    // first sample of a label (whichever thread marks the label first) has its list marked.  s_first holds one bit
-    // per sample; for batch sizes that are a power of two, so that a 16-byte piece of the staging array holds four
-    // samples of one list position and the sample index is a mask away.
-    const bool dedup = B >= 4 && (B & (B - 1)) == 0 && B <= SEL1_FIRST_WORDS * 32;
-    int64_t v_begin = 0;
-    if (dedup) {
-        for (int w = tid; w < B / 32 + 1; w += NT) s_first[w] = 0u;
-        __syncthreads();
-        for (int i = tid; i < B; i += NT) {
-            const int32_t c = cand[i]; // list position 0: the label (or -1: a class of another node, whose list still counts)
-            bool first = true;
-            if (c >= 0) first = !(atomicOr(&bm[c >> 5], 1u << (c & 31)) & (1u << (c & 31)));
-            if (first) atomicOr(&s_first[i >> 5], 1u << (i & 31));
-        }
-        __syncthreads();
-        v_begin = B >> 2; // the labels are done
-    }
-    for (int64_t t0 = v_begin; t0 < n_vec; t0 += (int64_t)NT * 8) {
-        int4 c[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t t = t0 + (int64_t)e * NT + tid;
-            c[e] = t < n_vec ? ((const int4 *)cand)[t] : make_int4(-1, -1, -1, -1);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            uint32_t f4 = 0xFu; // which of the four samples are the first of their label
-            if (dedup) {
-                const int i0 = (int)(((t0 + (int64_t)e * NT + tid) << 2) & (B - 1));
-                f4 = s_first[i0 >> 5] >> (i0 & 31);
-            }
-            if (c[e].x >= 0 && (f4 & 1u)) atomicOr(&bm[c[e].x >> 5], 1u << (c[e].x & 31));
-            if (c[e].y >= 0 && (f4 & 2u)) atomicOr(&bm[c[e].y >> 5], 1u << (c[e].y & 31));
-            if (c[e].z >= 0 && (f4 & 4u)) atomicOr(&bm[c[e].z >> 5], 1u << (c[e].z & 31));
-            if (c[e].w >= 0 && (f4 & 8u)) atomicOr(&bm[c[e].w >> 5], 1u << (c[e].w & 31));
-        }
-    }
-    for (int64_t t = n_vec * 4 + tid; t < n_cand; t += NT) {
-        const int32_t c = cand[t];
-        if (c >= 0) atomicOr(&bm[c >> 5], 1u << (c & 31));
-    }
-    __syncthreads();
-    int total = sel1_prefix<NT>(bm, nw, pre, sh);
-    if (total > M) {
-        // the cut bites: rebuild the bitmap in list-position order
-        for (int w = tid; w < nw; w += NT) { bm[w] = 0u; eq[w] = 0u; }
-        __syncthreads();
-        int cum = 0, quota = 0;
-        for (int r = 0; r <= K; ++r) {
-            if (tid == 0) s_new = 0;
+    // Optimistic pass: every candidate, whatever its list position.  Samples with the same label have the same list, and
+    // with skewed labels half of the batch are repeats: in the staged form only the first sample of a label (whichever
+    // thread marks the label first) has its list marked.  For batch sizes that are a power of two, so that a 16-byte piece
+    // of the staging array holds four samples of one list position and the sample index is a mask away.
+    if constexpr (std::is_same<Cands, Sel1Staged<NT>>::value) {
+        const bool dedup = B >= 4 && (B & (B - 1)) == 0 && B <= SEL1_FIRST_WORDS * 32;
+        if (dedup) {
+            for (int w = tid; w < B / 32 + 1; w += NT) s_first[w] = 0u;
             __syncthreads();
-            int local_new = 0;
             for (int i = tid; i < B; i += NT) {
-                const int c = cand[(int64_t)r * B + i];
-                if (c < 0) continue;
-                const uint32_t bit = 1u << (c & 31);
-                if (bm[c >> 5] & bit) continue; // already in with a better position
-                if (!(atomicOr(&eq[c >> 5], bit) & bit)) ++local_new;
+                const int32_t c = cands.label(i); // (-1: a class of another node, whose list still counts)
+                bool first = true;
+                if (c >= 0) first = !(atomicOr(&bm[c >> 5], bit_of(c)) & bit_of(c));
+                if (first) atomicOr(&s_first[i >> 5], 1u << (i & 31));
             }
-            local_new = ks_wave_sum_i(local_new);
-            if ((tid & 63) == 0 && local_new) atomicAdd(&s_new, local_new);
             __syncthreads();
-            const int total_new = s_new;
-            if (cum + total_new > M) { // classes first seen at position r do not all fit: r is the cut score
-                quota = M - cum;
-                break;
+            cands.first = s_first;
+        }
+        cands.range(dedup ? B : 0, (int64_t)B * (K + 1), set); // (deduplicated: the labels are done)
+    } else {
+        cands.mark(K + 1, set);
+    }
+    __syncthreads();
+    int total = sel1_count<NT>(bm, nq, coarse, sh);
+    if (total > M) {
+        // The cut bites.  r* = the first list position up to which more than M classes are seen, by a search between
+        // positions known to see at most M (lo) and more (hi): an interpolated guess and a halving in turn; each step
+        // marks the candidates up to the guess in the cleared bitmap and counts.  (Position by position, with three
+        // barriers and a read of the staged candidates each, 100,000 classes with 17 positions took 25 us, now 13 in all.)
+        int lo = -1, hi = K, n_lo = 0, n_hi = total;
+        sel1_count_clear<NT>(bm, nq, sh);
+        for (int step = 0; hi - lo > 1; ++step) {
+            int mid = (lo + hi) >> 1;
+            if (!(step & 1)) mid = lo + 1 + (int)((int64_t)(M - n_lo) * (hi - lo - 1) / (n_hi - n_lo));
+            mid = mid < lo + 1 ? lo + 1 : (mid > hi - 1 ? hi - 1 : mid);
+            cands.mark(mid + 1, set);
+            __syncthreads();
+            const int n = sel1_count_clear<NT>(bm, nq, sh);
+            if (n > M) { hi = mid; n_hi = n; }
+            else { lo = mid; n_lo = n; }
+        }
+        cands.mark(lo + 1, set); // (lo >= 0: the labels alone are at most B <= M classes)
+        if (tid == 0) s_new = 0;
+        __syncthreads();
+        // the classes first seen at r*: into the bitmap and into a list; the M - n_lo lowest ids of them stay
+        cands.at(hi, [&](int32_t c) {
+            if (!(atomicOr(&bm[c >> 5], bit_of(c)) & bit_of(c))) {
+                const int slot = atomicAdd(&s_new, 1);
+                if (slot < n_list) list[slot] = c; // always true: a class once, and at most one per sample
             }
-            for (int i = tid; i < B; i += NT) { // commit position r
-                const int c = cand[(int64_t)r * B + i];
-                if (c < 0) continue;
-                const uint32_t bit = 1u << (c & 31);
-                if (eq[c >> 5] & bit) {
-                    atomicOr(&bm[c >> 5], bit);
-                    atomicAnd(&eq[c >> 5], ~bit);
+        });
+        __syncthreads();
+        const int n_new = s_new < n_list ? s_new : n_list;
+        int rem = M - n_lo;       // the rem-th smallest of the list is the last to stay
+        uint32_t top = 0u;        // its leading digits so far
+        int shift = 24;
+        while (shift > 0 && ((uint64_t)(C - 1) >> shift) == 0) shift -= 8;
+        for (int first_shift = shift; rem > 0 && shift >= 0; shift -= 8) {
+            for (int q = tid; q < 256; q += NT) hist[q] = 0;
+            __syncthreads();
+            for (int q = tid; q < n_new; q += NT) {
+                const uint32_t c = (uint32_t)list[q];
+                if (shift == first_shift || (c >> (shift + 8)) == (top >> (shift + 8))) atomicAdd(&hist[(c >> shift) & 255u], 1);
+            }
+            __syncthreads();
+            if (tid < 64) { // one wavefront: four digits a lane
+                int v[4], sum = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { v[e] = hist[tid * 4 + e]; sum += v[e]; }
+                int run = ks_wave_iscan(sum) - sum;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (run < rem && run + v[e] >= rem) { s_bin = tid * 4 + e; s_rem = rem - run; }
+                    run += v[e];
                 }
             }
-            cum += total_new;
+            __syncthreads();
+            top |= (uint32_t)s_bin << shift;
+            rem = s_rem;
             __syncthreads();
         }
-        // eq holds the classes whose best position is the cut score; the `quota` lowest ids of them are kept
-        sel1_prefix<NT>(eq, nw, pre, sh);
-        const int per = (nw + NT - 1) / NT;
-        for (int w = tid * per; w < tid * per + per && w < nw; ++w) {
-            uint32_t e = eq[w], keep = 0u;
-            int left = quota - pre[w];
-            while (left > 0 && e) {
-                keep |= e & (0u - e);
-                e &= e - 1;
-                --left;
-            }
-            bm[w] |= keep;
+        const bool none = M == n_lo; // nothing of r* stays
+        for (int q = tid; q < n_new; q += NT) {
+            const int32_t c = list[q];
+            if (none || (uint32_t)c > top) atomicAnd(&bm[c >> 5], ~bit_of(c));
         }
         __syncthreads();
-        total = sel1_prefix<NT>(bm, nw, pre, sh);
+        total = sel1_count<NT>(bm, nq, coarse, sh);
     }
     const int found = total < M ? total : M;
     const int64_t want = M < C ? M : C;
@@ -243,7 +338,7 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, const int32_t *__restri
         // random fill-up: the first draws that are classes of this GPU and not in the bitmap yet (the draws are
         // distinct, so marking one cannot change the test of another)
         const int need = (int)(want - total);
-        const uint32_t n_draws = 1u << pad.b; // b <= 19 here
+        const uint32_t n_draws = 1u << pad.b; // b <= 21 here
         int got = 0;
         for (uint32_t k0 = 0; got < need && k0 < n_draws; k0 += NT * 8) {
             uint32_t cs[8];
@@ -267,16 +362,19 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, const int32_t *__restri
             got += tot < room ? tot : room;
             __syncthreads();
         }
-        total = sel1_prefix<NT>(bm, nw, pre, sh);
+        total = sel1_count<NT>(bm, nq, coarse, sh);
     }
-    // Every workgroup of the grid has built the same bitmap and prefix (redundantly: it is LDS work, and it
+    // Every workgroup of the grid has built the same bitmap and counts (redundantly: it is LDS work, and it
     // spares a grid-wide synchronisation); each writes its share of the outputs.
-    { // read the bitmap out in ascending order: this workgroup's slice of the words, one word per thread
-        const int per_g = (nw + G - 1) / G;
-        const int w_end = (g + 1) * per_g < nw ? (g + 1) * per_g : nw;
-        for (int w = g * per_g + tid; w < w_end; w += NT) {
-            uint32_t e = bm[w];
-            int pos = pre[w];
+    { // read the bitmap out in ascending order: a wavefront takes 64 words, a lane one of them
+        const int lane = tid & 63, ngrp = (nq + 1) >> 1;
+        for (int q = g * (NT / 64) + (tid >> 6); q < ngrp; q += G * (NT / 64)) {
+            const int w = q * 64 + lane;
+            const bool in = w < nq * 32;
+            uint32_t e = in ? bm[w] : 0u;
+            const int n = __popc(e);
+            const int ex = ks_wave_iscan(n) - n, half = __builtin_amdgcn_readlane(ex, 32); // a coarse entry per 32 words
+            int pos = in ? coarse[w >> 5] + ex - (lane < 32 ? 0 : half) : 0;
             while (e) {
                 const int b = __ffs(e) - 1;
                 if (pos < M) active_idx[pos] = w * 32 + b; // pos < M always holds; the test keeps the store in bounds
@@ -288,11 +386,25 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, const int32_t *__restri
     const int n = total < M ? total : M;
     for (int a = n + g * NT + tid; a < M; a += G * NT) active_idx[a] = -1;
     const int none = foreign_labels ? -1 : 0; // in range even for broken inputs (those are flagged)
-    for (int i = g * NT + tid; i < B; i += G * NT) {
-        const int32_t y = cand[i]; // list position 0: the sample's own class, -1 if it is not one of this GPU's
-        int p = none;
-        if (y >= 0 && y < C) p = pre[y >> 5] + __popc(bm[y >> 5] & ((1u << (y & 31)) - 1u));
-        target_pos[i] = (p >= 0 && p < n) ? p : none;
+    // a half-wave per sample: each lane counts one of the 32 words that share the label's coarse entry
+    for (int i0 = (g * (NT / 64) + (tid >> 6)) * 2; i0 < B; i0 += G * (NT / 64) * 2) {
+        const int lane = tid & 31, i = i0 + ((tid >> 5) & 1);
+        const int32_t y = i < B ? cands.label(i) : -1; // list position 0: the sample's own class, -1 if it is not one of this GPU's
+        const bool own = y >= 0 && y < C;
+        const int word = own ? y >> 5 : 0, below = word & 31;
+        uint32_t v = bm[(word & ~31) + lane];
+        if (lane > below) v = 0u;
+        if (lane == below) v &= (1u << (y & 31)) - 1u;
+        int p = __popc(v);
+        p += KS_DPP(0, p, 0x111, 0xf);
+        p += KS_DPP(0, p, 0x112, 0xf);
+        p += KS_DPP(0, p, 0x114, 0xf);
+        p += KS_DPP(0, p, 0x118, 0xf);
+        p += KS_DPP(0, p, 0x142, 0xa); // the last lane of each half has its half's sum
+        if (lane == 31 && i < B) {
+            p = own ? coarse[word >> 5] + p : none;
+            target_pos[i] = (p >= 0 && p < n) ? p : none;
+        }
     }
     if (g == 0 && tid == 0) {
         *n_active = n;
@@ -324,6 +436,7 @@ template <int NT> __device__ __forceinline__ void ks_sel_next_fetch(const KsSelN
     s.cand[(int64_t)r * s.B + i] = s.csr_source ? s.csr.cand(i, r, s.dev_status) : s.dense.cand(i, r, s.dev_status);
 }
 template <int NT> __device__ __forceinline__ void ks_sel_next_select(const KsSelNext &s, uint32_t *lds, int g) {
-    sel1_body<NT>(lds, s.cand, s.C, s.B, s.K, s.M, s.csr_source, s.pad, s.active_idx, s.n_active, s.n_found, s.target_pos,
+    Sel1Staged<NT> cands{s.cand, s.B, s.K, nullptr};
+    sel1_body<NT>(lds, cands, s.C, s.B, s.K, s.M, s.csr_source, s.pad, s.active_idx, s.n_active, s.n_found, s.target_pos,
                   s.nsel, g);
 }

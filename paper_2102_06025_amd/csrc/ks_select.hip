@@ -49,7 +49,8 @@ static SelWs sel_carve(void *ws, int64_t C, int K) {
 }
 
 size_t ks_select_ws_bytes(int64_t C, int B, int K) {
-    if (C <= (int64_t)SEL1_MAX_WORDS_HOST * 32) return ks_align_up((size_t)B * (K + 1) * sizeof(int32_t), 256);
+    const size_t staged = ks_align_up((size_t)B * (K + 1) * sizeof(int32_t), 256);
+    if (C <= SEL1_WS_CLASSES && sel1_fits(C, B)) return staged;
     KsArena ar(nullptr);
     ar.take<int32_t>((size_t)C);
     ar.take<int32_t>((size_t)K + 1);
@@ -57,7 +58,7 @@ size_t ks_select_ws_bytes(int64_t C, int B, int K) {
     ar.take<int32_t>(nblk * 2);
     ar.take<int32_t>(nblk * 2);
     ar.take<SelPlan>(1);
-    return ar.off;
+    return C <= SEL1_WS_CLASSES && staged > ar.off ? staged : ar.off;
 }
 
 __global__ void __launch_bounds__(SEL_NT) sel_init_kernel(int32_t *score, int64_t C, int32_t *hist, int K) {
@@ -269,15 +270,23 @@ sel_finish_kernel(Src src, const int32_t *__restrict__ score, int B, int M, cons
 }
 
 // ------------------------------------------------------------------------------------------------
-// Whole selection inside a workgroup when the class bitmap fits in LDS (C <= SEL1_MAX_WORDS * 32):
+// Whole selection inside a workgroup when a bit per class fits in LDS (sel1_fits: up to about 1.2 million classes):
 // candidates are marked in an LDS bitmap (duplicates collapse in the atomic OR), the ascending list is the
 // bitmap read out in order, positions are prefix popcounts.  Only when more than M classes are marked
-// is the list-position order needed; then the bitmap is rebuilt position by position (r = 0, 1, ...)
-// until adding the classes first seen at position r would exceed M; of those, the lowest ids fill up.
+// is the list-position order needed: the cut position is searched for, and of the classes first seen there the lowest
+// ids fill up.
 // SEL1_GRID workgroups all do this same LDS work and differ only in which slice of the outputs they
 // write: the global stores and their latency are spread over several compute units with no
 // synchronisation between workgroups.
+// Batches of up to SEL1_DIRECT candidates (and few lists) are read by those workgroups themselves; larger ones are staged by
+// a launch of their own: 32 workgroups that each chase all lists of a large batch spend longer on address translation than a
+// launch costs.  What bounds the kernel is latency: barriers and LDS round trips of a dozen passes over the bitmap.  1,000
+// classes, 16 lists: 9 -> 3.5 us in all; 100,000 classes, 256 lists of 16, cut: 28 -> 13; 1,000,000 classes, 2,048 lists of 64:
+// 54 us as nine launches over a score table -> 24.5, 5 of them the fetch.
 // ------------------------------------------------------------------------------------------------
+#define SEL1_E 8
+#define SEL1_DIRECT (SEL1_NT * SEL1_E) /* candidates */
+#define SEL1_DIRECT_B 512              /* samples: every workgroup pays the address translation of all their lists */
 // Stage 1 (many workgroups, so that the scattered reads of the neighbour lists are spread over the chip):
 // validated candidates, list-position-major: cand[r * B + i] = class at position r of sample i's list
 // (r = 0: the label itself), or -1 for an empty or invalid entry.
@@ -294,9 +303,21 @@ __global__ void __launch_bounds__(SEL1_NT)
 sel_single_kernel(const int32_t *__restrict__ cand, int64_t C, int B, int K, int M, int foreign_labels, SelPad pad,
                   int32_t *__restrict__ active_idx, int32_t *__restrict__ n_active, int32_t *__restrict__ n_found,
                   int32_t *__restrict__ target_pos) {
-    __shared__ uint32_t lds[sel1_lds_words(SEL1_NT)];
-    sel1_body<SEL1_NT>(lds, cand, C, B, K, M, foreign_labels, pad, active_idx, n_active, n_found, target_pos, (int)gridDim.x,
+    __shared__ __attribute__((aligned(16))) uint32_t lds[SEL1_LDS_WORDS];
+    Sel1Staged<SEL1_NT> cands{cand, B, K, nullptr};
+    sel1_body<SEL1_NT>(lds, cands, C, B, K, M, foreign_labels, pad, active_idx, n_active, n_found, target_pos, (int)gridDim.x,
                        (int)blockIdx.x);
+}
+template <class Src, int E>
+__global__ void __launch_bounds__(SEL1_NT)
+sel_direct_kernel(Src src, int64_t C, int B, int K, int M, SelPad pad, int32_t *__restrict__ active_idx,
+                  int32_t *__restrict__ n_active, int32_t *__restrict__ n_found, int32_t *__restrict__ target_pos,
+                  int32_t *dev_status) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[SEL1_LDS_WORDS];
+    Sel1Direct<SEL1_NT, E, Src> cands{src};
+    cands.load(B, K, blockIdx.x == 0, dev_status);
+    sel1_body<SEL1_NT>(lds, cands, C, B, K, M, (int)Src::kForeignLabels, pad, active_idx, n_active, n_found, target_pos,
+                       (int)gridDim.x, (int)blockIdx.x);
 }
 
 template <class Src>
@@ -304,7 +325,21 @@ static int sel_launch(const Src &src, int64_t C, int B, int K, int M, SelPad pad
                       int32_t *n_found, int32_t *target_pos, void *ws, int32_t *dev_status, hipStream_t st) {
     const int64_t n_cand = (int64_t)B * (K + 1);
     if ((uintptr_t)ws & 15) return KS_INVALID_ARG; // the staging array is read in 16-byte pieces
-    if (C <= (int64_t)SEL1_MAX_WORDS * 32) {
+    // (beyond SEL1_WS_CLASSES the workspace is sized for the score table; nearly always the staged candidates fit in there too)
+    if (sel1_fits(C, B) && n_cand <= SEL1_DIRECT && B <= SEL1_DIRECT_B) {
+        const int E = (int)ks_ceil_div(n_cand, SEL1_NT), G = 16;
+#define SEL_DIRECT_LAUNCH(E)                                                                                               \
+    hipLaunchKernelGGL((sel_direct_kernel<Src, E>), dim3(G), dim3(SEL1_NT), 0, st, src, C, B, K, M, pad, active_idx,         \
+                       n_active, n_found, target_pos, dev_status)
+        if (E <= 1) SEL_DIRECT_LAUNCH(1);
+        else if (E <= 2) SEL_DIRECT_LAUNCH(2);
+        else if (E <= 4) SEL_DIRECT_LAUNCH(4);
+        else SEL_DIRECT_LAUNCH(SEL1_E);
+#undef SEL_DIRECT_LAUNCH
+        KS_LAUNCH_CHECK();
+        return KS_OK;
+    }
+    if (sel1_fits(C, B) && ks_select_ws_bytes(C, B, K) >= (size_t)n_cand * sizeof(int32_t)) {
         int32_t *cand = (int32_t *)ws;
         hipLaunchKernelGGL(sel_fetch_kernel<Src>, dim3((unsigned)ks_ceil_div(n_cand, SEL_NT)), dim3(SEL_NT), 0, st, src, B, K,
                            cand, dev_status);

@@ -970,7 +970,7 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
     typedef TileDw T;
     static_assert(TileDw192::NT == T::NT && TileDw128::NT == T::NT && TileDw192::LDS_ELEMS <= T::LDS_ELEMS &&
                       TileDw128::LDS_ELEMS <= T::LDS_ELEMS, "one launch shape for all tile heights");
-    constexpr int LDS_ELEMS = T::LDS_ELEMS > 2 * sel1_lds_words(T::NT) ? T::LDS_ELEMS : 2 * sel1_lds_words(T::NT);
+    constexpr int LDS_ELEMS = T::LDS_ELEMS > 2 * SEL1_LDS_WORDS ? T::LDS_ELEMS : 2 * SEL1_LDS_WORDS;
     __shared__ __attribute__((aligned(16))) uint16_t lds[LDS_ELEMS];
     // The first next.nsel workgroups select the NEXT batch's active classes (Algorithm 1 needs only its labels): with a
     // few hundred tiles this launch leaves compute units idle, and being first they start at once.
@@ -1489,6 +1489,11 @@ extern "C" int knn_softmax_fwd_bwd_profiled(float *W_master, uint16_t *W_bf16, c
                       (hipEvent_t *)events, W_master, W_bf16, alpha);
 }
 
+// whether the next batch's selection can run inside the step's launches: its bitmap fits a workgroup's LDS, its staged
+// candidates the workspace
+static bool sm_next_rides(int64_t C, int B, int K) {
+    return sel1_fits(C, B) && ks_select_ws_bytes(C, B, K) >= (size_t)B * (K + 1) * sizeof(int32_t);
+}
 // The two calls of the softmax split over nodes.  Workspace: the softmax buffers (which carry the first call's
 // exponentials, or nothing on the two-sweep paths, to the second call), then the sanitised copy of the selection.
 struct SmSplitWs {
@@ -1603,7 +1608,7 @@ static int sm_bwd_from_stats(const uint16_t *W_bf16, const uint16_t *X_bf16, con
     io.gsum = global_sumexp;
     io.gtz = global_target_logit;
     KsSelNext next = KsSelNext();
-    const bool ride = nx && C <= (int64_t)SEL1_MAX_WORDS * 32;
+    const bool ride = nx && sm_next_rides(C, B, nx->K_max);
     if (ride) {
         next.nsel = SEL1_GRID;
         next.csr_source = 1;
@@ -1725,7 +1730,7 @@ static int sm_selected(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16
     // fits in LDS; otherwise it follows the step as launches of its own.  Either way it starts after the sanitised copy
     // of this step's list has been made, so its outputs may be the buffers this step's list came in.
     KsSelNext next = KsSelNext();
-    const bool ride = nx && fast && C <= (int64_t)SEL1_MAX_WORDS * 32;
+    const bool ride = nx && fast && sm_next_rides(C, B, nx->K);
     if (ride) {
         next.nsel = SEL1_GRID;
         next.dense = SelDense{nx->labels, nx->graph, C, nx->K};
