@@ -66,8 +66,8 @@ size_t grad_topk_workspace(const int64_t *plan_host);
 /* ------------------------------------------------------------------------------------------------------
  * grad_topk_select -- Section 3.3.2: the selection itself, one launch per level of the plan for the whole group
  * (plain tree: first level one workgroup per chunk of a tensor, last level one workgroup that writes its output;
- * the three steps described above: thresholds, then all chunks in a launch of their own, then the final steps,
- * beside which the tensors of a single chunk run).
+ * the three steps described above: thresholds, beside which the tensors of a single chunk run, then all chunks in a
+ * launch of their own, then the final steps).
  *
  *   g          [offsets[T]]  the gradient tensors, fp32, back to back as planned (4-byte aligned is enough)
  *   plan_dev   the plan in device memory;  plan_host  HOST: the same words (launch geometry is read from it)

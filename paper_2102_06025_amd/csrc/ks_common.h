@@ -71,6 +71,15 @@ __device__ __forceinline__ int ks_wave_iscan(int v) {
     v += KS_DPP(0, v, 0x143, 0xc);
     return v;
 }
+__device__ __forceinline__ int ks_wave_max_i(int v) {
+    v = max(v, KS_DPP(v, v, 0x111, 0xf));
+    v = max(v, KS_DPP(v, v, 0x112, 0xf));
+    v = max(v, KS_DPP(v, v, 0x114, 0xf));
+    v = max(v, KS_DPP(v, v, 0x118, 0xf));
+    v = max(v, KS_DPP(v, v, 0x142, 0xa));
+    v = max(v, KS_DPP(v, v, 0x143, 0xc));
+    return __builtin_amdgcn_readlane(v, 63);
+}
 __device__ __forceinline__ int ks_wave_sum_i(int v) { return __builtin_amdgcn_readlane(ks_wave_iscan(v), 63); }
 __device__ __forceinline__ float ks_wave_sum(float v) {
     v += KS_DPP_F(0.f, v, 0x111, 0xf);

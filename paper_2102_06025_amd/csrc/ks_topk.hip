@@ -3,9 +3,9 @@
 //
 // Every step of the method is the same workgroup-level routine, tk_select: the exact top-k of a list of items that
 // sits in global memory (first step: a chunk of a gradient tensor; later steps: the survivors of several chunks).
-// An item is the 64-bit word  (bits of |g|) << 32 | (0xFFFFFFFF - index) : larger word = larger magnitude, equal
-// magnitudes ordered by ascending index, all words distinct, so "top-k" is unique and no step depends on the
-// order in which it finds its input.
+// An item is the 64-bit word  (bits of |g|) << 32 | (0x7FFFFFFF - index) << 1 | sign of g : larger word = larger magnitude,
+// equal magnitudes ordered by ascending index, all words distinct, so "top-k" is unique and no step depends on the
+// order in which it finds its input; index and value can be read back from it.
 //
 // tk_select (1,024 threads) is a radix selection on the item word, most significant digits first:
 //   1. histogram of the current digit in LDS over the items that share the prefix found so far (first level:
@@ -72,7 +72,8 @@ struct TkSrcGrad {
     const float *g;
     uint32_t first;
     __device__ __forceinline__ uint32_t key(int i) const { return __float_as_uint(g[i]) & 0x7FFFFFFFu; }
-    __device__ __forceinline__ uint32_t aux(int i) const { return 0xFFFFFFFFu - (first + (uint32_t)i); }
+    __device__ __forceinline__ uint32_t aux_from(uint32_t bits, int i) const { return (((0x7FFFFFFFu - first) - (uint32_t)i) << 1) | (bits >> 31); }
+    __device__ __forceinline__ uint32_t aux(int i) const { return aux_from(__float_as_uint(g[i]), i); }
     __device__ __forceinline__ uint64_t item(int i) const { return ((uint64_t)key(i) << 32) | aux(i); }
     __device__ __forceinline__ int head() const { return (int)(((16u - ((uint32_t)(uintptr_t)g & 15u)) & 15u) >> 2); }
     __device__ __forceinline__ uint4 loadv(int i) const { return *(const uint4 *)(g + i); }
@@ -80,11 +81,15 @@ struct TkSrcGrad {
     __device__ __forceinline__ uint32_t key_of(const uint4 &v, int e) const {
         return (e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w))) & 0x7FFFFFFFu;
     }
-    __device__ __forceinline__ uint32_t aux_of(const uint4 &, int i, int e) const { return aux(i + e); }
+    __device__ __forceinline__ uint32_t aux_of(const uint4 &v, int i, int e) const {
+        return aux_from(e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w)), i + e);
+    }
     __device__ __forceinline__ void unpack(const uint4 &v, int i, uint32_t (&k)[VEC], uint32_t (&a)[VEC]) const {
-        k[0] = v.x & 0x7FFFFFFFu, k[1] = v.y & 0x7FFFFFFFu, k[2] = v.z & 0x7FFFFFFFu, k[3] = v.w & 0x7FFFFFFFu;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) a[e] = aux(i + e);
+        for (int e = 0; e < VEC; ++e) {
+            k[e] = key_of(v, e);
+            a[e] = aux_of(v, i, e);
+        }
     }
 };
 // step 2 reads the survivors
@@ -177,7 +182,7 @@ __device__ __forceinline__ void tk_hist_add(bool in_play, uint32_t bin, uint32_t
     const uint64_t act = __builtin_amdgcn_ballot_w64(in_play);
     if (act == 0ull) return;
     const int first = __builtin_ctzll(act);
-    const uint32_t b0 = (uint32_t)__shfl((int)bin, first, 64);
+    const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
     if (__builtin_amdgcn_ballot_w64(in_play && bin == b0) == act) {
         if ((int)(threadIdx.x & 63) == first) atomicAdd(&hist[b0], (uint32_t)__builtin_popcountll(act));
     } else if (in_play) {
@@ -187,25 +192,14 @@ __device__ __forceinline__ void tk_hist_add(bool in_play, uint32_t bin, uint32_t
 
 // exclusive prefix sum of v over the workgroup in thread order (all threads call)
 __device__ __forceinline__ uint32_t tk_block_exclusive_scan(uint32_t v, TkShared &sh, uint32_t *total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t up = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += up;
-    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t inc = (uint32_t)ks_wave_iscan((int)v);
     __syncthreads(); // wave_sum may still be read from the previous call
     if (lane == 63) sh.wave_sum[wave] = inc;
     __syncthreads();
-    uint32_t base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < TK_NT / 64; ++w) {
-        const uint32_t s = sh.wave_sum[w];
-        if (w < wave) base += s;
-        tot += s;
-    }
-    if (total) *total = tot;
-    return base + inc - v;
+    const int sums = ks_wave_iscan(lane < TK_NT / 64 ? (int)sh.wave_sum[lane] : 0);
+    if (total) *total = (uint32_t)__builtin_amdgcn_readlane(sums, 63);
+    return (wave ? (uint32_t)__builtin_amdgcn_readlane(sums, wave - 1) : 0u) + inc - v;
 }
 
 // append `item` to an LDS array for the lanes with sel set (slot = base[dir * position], position from *counter):
@@ -245,25 +239,32 @@ __device__ __forceinline__ int tk_pow2_ceil(int v) {
 }
 
 // The bin of hist[0 .. nb) (an LDS array) in which the need-th largest counted item falls, bins taken in descending order:
-// returns it, the number of items in higher bins (*above) and in the bin itself (*in_bin).  All threads call.
+// returns it, the number of items in higher bins (*above) and in the bin itself (*in_bin).  All threads call.  PER bins a
+// thread, nb <= PER * TK_NT.
+template <int PER>
 __device__ __forceinline__ uint32_t tk_find_bin(const uint32_t *hist, int nb, uint32_t need, TkShared &sh, uint32_t *above, uint32_t *in_bin) {
     const int tid = threadIdx.x;
-    const int per = nb / TK_NT > 0 ? nb / TK_NT : 1; // thread t owns bins nb-1 - t*per ... downwards (per = 2^j)
-    const int top = nb - 1 - tid * per;
+    const int top = nb - 1 - tid * PER; // thread t owns bins nb-1 - t*PER ... downwards
+    const bool owner = top >= PER - 1;
     uint32_t own = 0;
-    if (tid * per < nb) // (summed in rotated order: with 32 bins per thread a straight walk would put all lanes on one bank)
-        for (int q = 0; q < per; ++q) own += hist[top - ((q + tid) & (per - 1))];
+    if (owner) // (summed in rotated order: with 16 bins per thread a straight walk would put all lanes on two banks)
+#pragma unroll
+        for (int q = 0; q < PER; ++q) own += hist[top - ((q + tid) & (PER - 1))];
     if (tid == 0) sh.b_star = sh.above = 0u; // (always overwritten below: at least `need` items were counted)
     uint32_t run = tk_block_exclusive_scan(own, sh, nullptr);
-    if (tid * per < nb && run < need && need <= run + own) { // exactly one thread: the bin is among its own
-        for (int q = 0; q < per; ++q) {
-            const uint32_t h = hist[top - q];
-            if (need <= run + h) {
+    if (owner && run < need && need <= run + own) { // exactly one thread: the bin is among its own
+        uint32_t h[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) h[q] = hist[top - q]; // all under way together
+        bool found = false;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (!found && need <= run + h[q]) {
                 sh.b_star = (uint32_t)(top - q);
                 sh.above = run;
-                break;
+                found = true;
             }
-            run += h;
+            run += h[q];
         }
     }
     __syncthreads();
@@ -318,21 +319,16 @@ template <class List> __device__ __forceinline__ void tk_collect(const List &lis
             }
         }
         const uint32_t mine = (uint32_t)__builtin_popcount(fa) | ((uint32_t)__builtin_popcount(ft) << 16);
-        uint32_t inc = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t up = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += up;
-        }
-        const uint32_t tot = (uint32_t)__shfl((int)inc, 63, 64);
+        const uint32_t inc = (uint32_t)ks_wave_iscan((int)mine);
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
         if (tot == 0u) return; // nothing of this batch is kept by this wavefront
         uint32_t base_a = 0u, base_t = 0u;
         if (lane == 63) {
             if (tot & 0xFFFFu) base_a = atomicAdd(&sh.count, tot & 0xFFFFu);
             if (tot >> 16) base_t = atomicAdd(&sh.count_tie, tot >> 16);
         }
-        uint32_t pa = (uint32_t)__shfl((int)base_a, 63, 64) + ((inc - mine) & 0xFFFFu);
-        uint32_t pt = (uint32_t)__shfl((int)base_t, 63, 64) + ((inc - mine) >> 16);
+        uint32_t pa = (uint32_t)__builtin_amdgcn_readlane((int)base_a, 63) + ((inc - mine) & 0xFFFFu);
+        uint32_t pt = (uint32_t)__builtin_amdgcn_readlane((int)base_t, 63) + ((inc - mine) >> 16);
         const uint32_t any = fa | ft;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -523,7 +519,8 @@ template <class List> __device__ __forceinline__ void tk_select(const List &list
             });
         }
         __syncthreads();
-        const uint32_t b_star = tk_find_bin(hist, nb, need, sh, &above, &in_bin);
+        const uint32_t b_star = lev == 0 ? tk_find_bin<TK_BINS0 / TK_NT>(hist, nb, need, sh, &above, &in_bin)
+                                         : tk_find_bin<TK_BINS / TK_NT>(hist, nb, need, sh, &above, &in_bin);
         P = (prefix << (hi - lo)) | b_star;
         taken += above;
         need -= above;
@@ -601,7 +598,7 @@ template <class List> __device__ __forceinline__ void tk_select(const List &list
             tk_hist_add(i < n_tie && (item >> hi) == prefix, (uint32_t)(item >> lo) & bin_mask, sh.hist);
         }
         __syncthreads();
-        const uint32_t b_star = tk_find_bin(sh.hist, nb, need, sh, &above, &in_bin);
+        const uint32_t b_star = tk_find_bin<TK_BINS / TK_NT>(sh.hist, nb, need, sh, &above, &in_bin);
         P = (prefix << (hi - lo)) | b_star;
         need -= above; // the items above the new bin are taken: they satisfy (item >> lo) > P
         prefix = P;
@@ -637,49 +634,189 @@ template <class List> __device__ __forceinline__ void tk_select(const List &list
 // a step can take (long runs of one magnitude), its workgroup runs the tensor's plain tree of selections itself.  The
 // result is the same bits either way.
 // ------------------------------------------------------------------------------------------------
+// The r-th largest of the workgroup's sampled magnitudes (Q per thread, 0xFFFFFFFF: none), to the exponent and six bits of
+// the mantissa: the threshold is the lower edge of the histogram bin it falls in, so somewhat more elements than r lie at or above
+// it (a tenth to a fifth for bell-shaped values; sorting the sample took five times as long as everything else in this step, a
+// second level of histogram a microsecond).  Overwrites sh.sort.
+template <int Q> __device__ __forceinline__ uint32_t tk_sample_threshold(const uint32_t (&key)[Q], int r, TkShared &sh) {
+    uint32_t *hist = (uint32_t *)sh.sort;
+    for (int b = threadIdx.x; b < TK_BINS0 / 4; b += TK_NT) ((uint4 *)hist)[b] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (key[q] != 0xFFFFFFFFu) atomicAdd(&hist[key[q] >> 17], 1u);
+    __syncthreads();
+    uint32_t above, in_bin;
+    return tk_find_bin<TK_BINS0 / TK_NT>(hist, TK_BINS0, (uint32_t)r, sh, &above, &in_bin) << 17;
+}
 __device__ void tk_threshold(const float *__restrict__ gt, uint32_t n, int r, uint64_t *aux, TkShared &sh) {
-    // The r-th largest of the sampled magnitudes, to 22 of their 31 bits (two histogram levels of 11 bits; the threshold is
-    // the lower edge of the bin it falls in, so a few more elements than r lie at or above it -- sorting the sample
-    // took five times as long as everything else in this step).
-    const int tid = threadIdx.x;
     uint32_t key[TK_SAMPLE / TK_NT];
 #pragma unroll
     for (int q = 0; q < TK_SAMPLE / TK_NT; ++q) {
-        const uint32_t idx = (uint32_t)(((uint64_t)(q * TK_NT + tid) * n) / TK_SAMPLE);
+        const uint32_t idx = (uint32_t)(((uint64_t)(q * TK_NT + (int)threadIdx.x) * n) / TK_SAMPLE);
         key[q] = __float_as_uint(gt[idx]) & 0x7FFFFFFFu;
     }
-    for (int b = tid; b < TK_BINS; b += TK_NT) sh.hist[b] = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < TK_SAMPLE / TK_NT; ++q) atomicAdd(&sh.hist[key[q] >> 20], 1u);
-    __syncthreads();
-    uint32_t above, in_bin;
-    const uint32_t b1 = tk_find_bin(sh.hist, TK_BINS, (uint32_t)r, sh, &above, &in_bin);
-    for (int b = tid; b < TK_BINS; b += TK_NT) sh.hist[b] = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < TK_SAMPLE / TK_NT; ++q)
-        if ((key[q] >> 20) == b1) atomicAdd(&sh.hist[(key[q] >> 9) & (TK_BINS - 1)], 1u);
-    __syncthreads();
-    const uint32_t b2 = tk_find_bin(sh.hist, TK_BINS, (uint32_t)r - above, sh, &above, &in_bin);
-    if (tid == 0) {
-        aux[0] = (b1 << 20) | (b2 << 9);
+    const uint32_t thr = tk_sample_threshold<TK_SAMPLE / TK_NT>(key, r, sh);
+    if (threadIdx.x == 0) {
+        aux[0] = thr;
         aux[1] = 0ull; // items of the tensor's list so far (low word), overflow mark (high word)
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The last step of a tensor, in one pass over its input.  A selection followed by an ordering (tk_select, tk_order) reads its
+// list from memory at least twice, each time waiting for it, and goes through a dozen levels of histogram and scan; here the input
+// is read once, into registers, and what can still matter -- the items at or above a threshold -- is spread over 2,048 buckets of
+// equal width between threshold and largest magnitude; the buckets down to the one that holds the k-th item are ranked, and
+// each item's rank is its place in the output.  Any input that does not suit (a bucket of more than 1,024 items, more items
+// than the LDS array holds) is left to tk_select: `false` is returned, and nothing has been written.
+// What is left is latency: the record, the first touch of the data, the loads themselves (one compute unit reads 128 KB in 5 us).
+// (161 tensors of 25.5 million elements, k = n / 1,000: 28 us for all last steps in one launch, now 10 for those of sampled paths
+// and 10.5 for the tensors of one chunk, which run beside the thresholds.)
+// ------------------------------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t tk_item_index(uint64_t item) { return 0x7FFFFFFFu - ((uint32_t)item >> 1); }
+__device__ __forceinline__ float tk_item_value(uint64_t item) { return __uint_as_float((uint32_t)(item >> 32) | ((uint32_t)item << 31)); }
+
+// item[e] of thread t is number e * TK_NT + t of n >= k items, all of magnitude >= kmin; `cap` words of sh.sort may be used
+template <int E>
+__device__ __forceinline__ bool tk_rank_top(const uint64_t (&item)[E], int n, uint32_t kmin, int k, int cap, TkShared &sh,
+                                            int32_t *__restrict__ out_idx, float *__restrict__ out_val) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int mx = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * TK_NT + tid < n) mx = max(mx, (int)(item[e] >> 32)); // (magnitudes have 31 bits)
+    mx = ks_wave_max_i(mx);
+    for (int b = tid; b < TK_BINS; b += TK_NT) sh.hist[b] = 0u;
+    if (lane == 0) sh.wave_sum[wave] = (uint32_t)mx;
+    __syncthreads();
+    const uint32_t range = (uint32_t)ks_wave_max_i(lane < TK_NT / 64 ? (int)sh.wave_sum[lane] : 0) - kmin;
+    const int bits = range ? 32 - __builtin_clz(range) : 0;
+    const int shift = bits > 11 ? bits - 11 : 0;
+    auto bucket = [&](uint64_t x) { return ((uint32_t)(x >> 32) - kmin) >> shift; };
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * TK_NT + tid < n) atomicAdd(&sh.hist[bucket(item[e])], 1u);
+    __syncthreads();
+    // descending exclusive prefix: bucket b starts at the number of items in higher buckets
+    constexpr int per = TK_BINS / TK_NT;
+    uint32_t cnt[per], own = 0;
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        cnt[q] = sh.hist[TK_BINS - 1 - (tid * per + q)];
+        own += cnt[q];
+    }
+    uint32_t run = tk_block_exclusive_scan(own, sh, nullptr);
+    bool big = false;
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        const int b = TK_BINS - 1 - (tid * per + q);
+        sh.hist[b] = run; // start of the bucket; the scatter below advances it to the bucket's end
+        sh.cnt16[b] = (uint16_t)cnt[q];
+        if (run < (uint32_t)k) { // one of the buckets to be ranked
+            big = big || cnt[q] > 1024u;
+            if ((uint32_t)k <= run + cnt[q]) { // the last of them
+                sh.b_star = (uint32_t)b;
+                sh.above = run + cnt[q];
+            }
+        }
+        run += cnt[q];
+    }
+    const bool unsuited = __syncthreads_or(big);
+    const uint32_t b_star = sh.b_star;
+    const int m = (int)sh.above;
+    if (unsuited || m > cap) return false;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e * TK_NT + tid < n) {
+            const uint32_t b = bucket(item[e]);
+            if (b >= b_star) sh.sort[atomicAdd(&sh.hist[b], 1u)] = item[e];
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < m; i += TK_NT) {
+        const uint64_t x = sh.sort[i];
+        const uint32_t b = bucket(x);
+        const int end = (int)sh.hist[b], begin = end - (int)sh.cnt16[b];
+        int rank = begin;
+        for (int j = begin; j < end; j += 8) { // eight at a time: runs of one magnitude make buckets of hundreds
+            uint64_t y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) y[u] = sh.sort[j + u < end ? j + u : begin];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) rank += (j + u < end && y[u] > x) ? 1 : 0;
+        }
+        if (rank < k) {
+            out_idx[rank] = (int32_t)tk_item_index(x);
+            out_val[rank] = tk_item_value(x);
+        }
+    }
+    return true;
+}
+// From a tensor of one chunk: a quarter of it is the sample of its threshold (the rank as on the sampled path: about four times
+// k elements, at least 64, lie at or above it).
+__device__ __forceinline__ bool tk_top_of_chunk(const TkSrcGrad &src, int n, int k, TkShared &sh, int32_t *__restrict__ out_idx,
+                                                float *__restrict__ out_val) {
+    constexpr int U = TK_LEAF / 4 / TK_NT, LIST = TK_CAP / 2;
+    const int tid = threadIdx.x;
+    TkList<TkSrcGrad> list;
+    list.init(src, n);
+    int r = (int)(((int64_t)4 * k * list.nq + n - 1) / n);
+    if (r < TK_SAMPLE_RANK) r = TK_SAMPLE_RANK;
+    const bool all = r >= list.nq; // few elements for their k: no threshold
+    if (n > TK_LEAF || (all ? n > LIST : 8 * r > LIST)) return false;
+    uint4 v[U];
+    list.template load<U>(v, 0);
+    uint32_t ekey, eaux;
+    const bool evalid = list.edge_item(&ekey, &eaux);
+    uint32_t thr = 0u;
+    if (tid == 0) sh.count = 0u;
+    if (all) {
+        __syncthreads();
+    } else {
+        uint32_t key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = u * TK_NT + tid < list.nq ? src.key_of(v[u], 0) : 0xFFFFFFFFu;
+        thr = tk_sample_threshold<U>(key, r, sh);
+    }
+    auto take = [&](uint32_t key, uint32_t aux) {
+        const uint32_t slot = atomicAdd(&sh.count, 1u);
+        if (slot < LIST) sh.sort[LIST + slot] = ((uint64_t)key << 32) | aux;
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int q = u * TK_NT + tid;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t key = src.key_of(v[u], e);
+            if (q < list.nq && key >= thr) take(key, src.aux_of(v[u], list.head + q * 4, e));
+        }
+    }
+    if (evalid && ekey >= thr) take(ekey, eaux);
+    __syncthreads();
+    const int cnt = (int)sh.count;
+    if (cnt < k || cnt > LIST) {
+        __syncthreads(); // (sh.count is about to be reused)
+        return false;
+    }
+    uint64_t item[LIST / TK_NT];
+#pragma unroll
+    for (int e = 0; e < LIST / TK_NT; ++e) item[e] = e * TK_NT + tid < cnt ? sh.sort[LIST + e * TK_NT + tid] : 0ull;
+    return tk_rank_top<LIST / TK_NT>(item, cnt, thr, k, LIST, sh, out_idx, out_val);
 }
 
 // A chunk on the sampled path: its items with magnitude bits >= the tensor's threshold are appended to the tensor's
 // list.  One pass over memory and almost nothing to keep (about 130 of 32,768 elements), so what matters is how many
 // loads are in flight on a compute unit: four small workgroups per chunk, each with its whole piece requested at once.
+// (102 MB in 18.7 us, 5.4 TB/s, the rate of a large copy; 24 us when every workgroup fetched its record through the plan's header.)
 #define TK_FILTER_NT 256
 #define TK_FILTER_PIECES 4
 #define TK_FILTER_CAP 2048 /* items a piece may keep (its share of what a chunk's array would hold) */
 __global__ void __launch_bounds__(TK_FILTER_NT)
-tk_filter_kernel(const float *__restrict__ g, const int64_t *__restrict__ plan, uint64_t *cand, int first_node) {
+tk_filter_kernel(const float *__restrict__ g, const int64_t *__restrict__ first_rec, uint64_t *cand) {
     __shared__ uint64_t kept[TK_FILTER_CAP];
     __shared__ uint32_t s_cnt, s_base;
-    const int T_ = (int)plan[1];
-    const int64_t *rec = plan + TK_HEADER + (int64_t)T_ * TK_TENSOR + (int64_t)(first_node + (int)blockIdx.x / TK_FILTER_PIECES) * TK_NODE;
+    const int64_t *rec = first_rec + (int64_t)(blockIdx.x / TK_FILTER_PIECES) * TK_NODE;
     const int piece = (int)blockIdx.x % TK_FILTER_PIECES, tid = threadIdx.x;
     const int n = (int)rec[TK_N_ITEMS];
     const int per = ((n + TK_FILTER_PIECES - 1) / TK_FILTER_PIECES + 3) & ~3; // elements per piece, whole 16-byte vectors
@@ -694,7 +831,7 @@ tk_filter_kernel(const float *__restrict__ g, const int64_t *__restrict__ plan, 
         const uint32_t key = bits & 0x7FFFFFFFu;
         if (key >= thr) {
             const uint32_t slot = atomicAdd(&s_cnt, 1u);
-            if (slot < TK_FILTER_CAP) kept[slot] = ((uint64_t)key << 32) | (0xFFFFFFFFu - (first + (uint32_t)i));
+            if (slot < TK_FILTER_CAP) kept[slot] = ((uint64_t)key << 32) | ((0x7FFFFFFFu - (first + (uint32_t)i)) << 1) | (bits >> 31);
         }
     };
     if (begin < end) {
@@ -744,7 +881,9 @@ tk_filter_kernel(const float *__restrict__ g, const int64_t *__restrict__ plan, 
 }
 
 // one step: a selection (from a chunk of gradients or from survivors), or the threshold of a sampled path
-// (returns true when it was the final step of a sampled path and the sample had misled: nothing is written then)
+// (returns true when it was the final step of a sampled path and the sample had misled: nothing is written then).
+// ONE_PASS: try the one-pass form of a last step first (no step of a fallback tree has a use for it).
+template <bool ONE_PASS>
 __device__ __forceinline__ bool tk_run_node(const int64_t *__restrict__ rec, const float *__restrict__ g, uint64_t *cand,
                                             int32_t *__restrict__ out_idx, float *__restrict__ out_val, TkShared &sh) {
     const int flags = (int)rec[TK_N_FLAGS];
@@ -754,17 +893,34 @@ __device__ __forceinline__ bool tk_run_node(const int64_t *__restrict__ rec, con
     }
     int n = (int)rec[TK_N_ITEMS];
     const int k = (int)rec[TK_N_K];
+    const bool final_step = flags & TK_F_FINAL;
+    const int64_t o = rec[TK_N_OUT];
     if (flags & TK_F_COUNTED) {
-        uint32_t *aux32 = (uint32_t *)(cand + rec[TK_N_AUX] + 1);
+        const uint64_t *items = cand + rec[TK_N_SRC];
+        uint64_t item[4];
+        if (ONE_PASS) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) item[e] = items[e * TK_NT + threadIdx.x]; // before the count is known (the list has room for more)
+        }
+        const uint32_t thr = (uint32_t)cand[rec[TK_N_AUX]];
+        const uint32_t *aux32 = (const uint32_t *)(cand + rec[TK_N_AUX] + 1);
         const uint32_t cnt = aux32[0], overflow = aux32[1];
         if (overflow != 0u || cnt < (uint32_t)k || cnt > (uint32_t)TK_NODE_CAP) return true; // the sample misled
         n = (int)cnt;
+        if (ONE_PASS && n <= 4 * TK_NT) {
+            if (tk_rank_top<4>(item, n, thr, k, TK_CAP, sh, out_idx + o, out_val + o)) return false;
+        } else if (ONE_PASS && n <= 16 * TK_NT) {
+            uint64_t more[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) more[e] = e < 4 ? item[e & 3] : (e * TK_NT + (int)threadIdx.x < n ? items[e * TK_NT + threadIdx.x] : 0ull);
+            if (tk_rank_top<16>(more, n, thr, k, TK_CAP, sh, out_idx + o, out_val + o)) return false;
+        }
     }
-    const bool final_step = flags & TK_F_FINAL;
     if (flags & TK_F_LEAF) {
         TkSrcGrad src;
         src.g = g + rec[TK_N_SRC];
         src.first = (uint32_t)rec[TK_N_FIRST];
+        if (ONE_PASS && final_step && tk_top_of_chunk(src, n, k, sh, out_idx + o, out_val + o)) return false;
         TkList<TkSrcGrad> list;
         list.init(src, n);
         tk_select(list, k, sh, final_step);
@@ -776,14 +932,10 @@ __device__ __forceinline__ bool tk_run_node(const int64_t *__restrict__ rec, con
         tk_select(list, k, sh, final_step);
     }
     const int keep = n < k ? n : k; // (a final step has n >= k)
-    const int64_t o = rec[TK_N_OUT];
     if (final_step) {
-        const float *gt = g + rec[TK_N_GBEGIN];
-        const uint32_t gn = (uint32_t)rec[TK_N_GN];
         for (int r = threadIdx.x; r < keep; r += TK_NT) {
-            const uint32_t idx = 0xFFFFFFFFu - (uint32_t)sh.sort[r];
-            out_idx[o + r] = (int32_t)idx;
-            out_val[o + r] = idx < gn ? gt[idx] : 0.f; // (always inside: items carry indices of this tensor)
+            out_idx[o + r] = (int32_t)tk_item_index(sh.sort[r]);
+            out_val[o + r] = tk_item_value(sh.sort[r]);
         }
     } else {
         for (int r = threadIdx.x; r < keep; r += TK_NT) cand[o + r] = sh.sort[r];
@@ -798,21 +950,20 @@ __device__ __noinline__ void tk_plain_tree(const int64_t *nodes, const int64_t *
                                            float *out_val, TkShared &sh) {
     const int64_t *rec = nodes + fin[TK_N_FB_FIRST] * TK_NODE;
     for (int64_t s = 0; s < fin[TK_N_FB_COUNT]; ++s, rec += TK_NODE) {
-        tk_run_node(rec, g, cand, out_idx, out_val, sh);
+        tk_run_node<false>(rec, g, cand, out_idx, out_val, sh);
         __threadfence_block();
         __syncthreads();
     }
 }
 
-// one step of the tree: one workgroup per node of the level
+// one step of the tree: one workgroup per node of the level, of n_first nodes from first_node on, then from second_node on
 __global__ void __launch_bounds__(TK_NT)
-tk_node_kernel(const float *__restrict__ g, const int64_t *__restrict__ plan, uint64_t *cand, int32_t *__restrict__ out_idx,
-               float *__restrict__ out_val, int first_node) {
+tk_node_kernel(const float *__restrict__ g, const int64_t *__restrict__ nodes, uint64_t *cand, int32_t *__restrict__ out_idx,
+               float *__restrict__ out_val, int first_node, int n_first, int second_node) {
     __shared__ TkShared sh;
-    const int T = (int)plan[1];
-    const int64_t *nodes = plan + TK_HEADER + (int64_t)T * TK_TENSOR;
-    const int64_t *rec = nodes + (int64_t)(first_node + blockIdx.x) * TK_NODE;
-    if (tk_run_node(rec, g, cand, out_idx, out_val, sh)) tk_plain_tree(nodes, rec, g, cand, out_idx, out_val, sh);
+    const int b = (int)blockIdx.x;
+    const int64_t *rec = nodes + (int64_t)(b < n_first ? first_node + b : second_node + (b - n_first)) * TK_NODE;
+    if (tk_run_node<true>(rec, g, cand, out_idx, out_val, sh)) tk_plain_tree(nodes, rec, g, cand, out_idx, out_val, sh);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -927,8 +1078,8 @@ static int64_t tk_plan_build(const int64_t *offsets, const int32_t *k, int T, in
         tensors.push_back(steps);
         out += k[t];
     }
-    // Tensors of one step are independent of everything else: with sampled paths in the plan they run beside those
-    // paths' final steps (the launch that otherwise has the fewest workgroups) instead of beside the thresholds.
+    // Tensors of one step are independent of everything else: with sampled paths in the plan they stand in the last level,
+    // before its steps of plain trees, and the launch takes them where it has room (grad_topk_select).
     bool sampled = false;
     for (const TkNode &nd : nodes) sampled = sampled || (nd.flags & TK_F_THRESH);
     if (sampled)
@@ -976,8 +1127,11 @@ static int64_t tk_plan_build(const int64_t *offsets, const int32_t *k, int T, in
             plan[lev == 1 ? 28 : 30] = plan[8 + 2 * lev];
             plan[lev == 1 ? 29 : 31] = w - plan[8 + 2 * lev];
         }
+        auto single = [&](const TkNode &nd) { return sampled && lev == n_levels - 1 && nd.flags == (TK_F_LEAF | TK_F_FINAL); };
         for (const TkNode &nd : nodes)
-            if (nd.level == lev && !(nd.flags & special)) put(nd);
+            if (nd.level == lev && single(nd)) put(nd);
+        for (const TkNode &nd : nodes)
+            if (nd.level == lev && !(nd.flags & special) && !single(nd)) put(nd);
         plan[9 + 2 * lev] = w - plan[8 + 2 * lev];
     }
     // then the plain trees behind sampled paths, tensor by tensor, each in the order of its levels
@@ -1013,17 +1167,42 @@ extern "C" int grad_topk_select(const float *g, const int64_t *plan_dev, const i
     if (ws_bytes < grad_topk_workspace(plan_host)) return KS_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)stream;
     uint64_t *cand = (uint64_t *)ws;
+    const int64_t *nodes = plan_dev + TK_HEADER + plan_host[1] * TK_TENSOR; // (from the host's copy: read on the GPU it is a round trip)
+    // With sampled paths in the plan, the tensors of one step (first in the last level, behind the sampled paths' final steps if
+    // those are there too) run beside the thresholds: the two take about as long, and the final steps are left a launch of
+    // short lists.
+    const int last = (int)plan_host[6] - 1;
+    int64_t singles = 0, single0 = 0;
+    if (plan_host[31] > 0) {
+        single0 = plan_host[8 + 2 * last] + (last == 2 ? plan_host[31] : 0);
+        const int64_t *rec = plan_host + TK_HEADER + plan_host[1] * TK_TENSOR + single0 * TK_NODE;
+        int64_t end = plan_host[9 + 2 * last] - (last == 2 ? plan_host[31] : 0); // number of records of a kind at the front: by halving
+        while (singles < end) {
+            const int64_t mid = (singles + end) >> 1;
+            if (rec[mid * TK_NODE + TK_N_FLAGS] == (TK_F_LEAF | TK_F_FINAL)) singles = mid + 1;
+            else end = mid;
+        }
+    }
     for (int lev = 0; lev < (int)plan_host[6]; ++lev) {
-        int64_t first = plan_host[8 + 2 * lev], count = plan_host[9 + 2 * lev];
+        int64_t first = plan_host[8 + 2 * lev], count = plan_host[9 + 2 * lev], extra = 0;
         if (lev == 1 && plan_host[29] > 0) { // the chunks of the sampled paths
             hipLaunchKernelGGL(tk_filter_kernel, dim3((unsigned)(plan_host[29] * TK_FILTER_PIECES)), dim3(TK_FILTER_NT), 0, st, g,
-                               plan_dev, cand, (int)first);
+                               nodes + first * TK_NODE, cand);
             first += plan_host[29];
             count -= plan_host[29];
         }
-        if (count < 1) continue;
-        hipLaunchKernelGGL(tk_node_kernel, dim3((unsigned)count), dim3(TK_NT), 0, st, g, plan_dev, cand, out_idx, out_val,
-                           (int)first);
+        if (lev == 0) extra = singles;
+        if (lev == last && singles > 0) {
+            // (the records of the level are: final steps of sampled paths, tensors of one step, steps of plain trees)
+            const int64_t before = single0 - first, after = count - before - singles;
+            if (before + after < 1) continue;
+            hipLaunchKernelGGL(tk_node_kernel, dim3((unsigned)(before + after)), dim3(TK_NT), 0, st, g, nodes, cand, out_idx, out_val,
+                               (int)first, (int)before, (int)(single0 + singles));
+            continue;
+        }
+        if (count + extra < 1) continue;
+        hipLaunchKernelGGL(tk_node_kernel, dim3((unsigned)(count + extra)), dim3(TK_NT), 0, st, g, nodes, cand, out_idx, out_val,
+                           (int)first, (int)count, (int)single0);
     }
     KS_LAUNCH_CHECK();
     return KS_OK;

@@ -1,0 +1,71 @@
+"""The last step of a tensor's top-k in its one-pass form: tensors of one chunk at every alignment and around the sizes and
+ranks at which the form is left, samples that mislead it, lists of a sampled path around the sizes it holds in registers."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ks():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2102_06025_amd as ks
+    ks.lib()
+    return ks
+
+
+def check(ks, orc, g, offs, k):
+    import torch
+    print(f"[topk] sizes={np.diff(offs)[:6]} k={k[:6]}", flush=True)
+    offs, k = np.asarray(offs, np.int64), np.asarray(k, np.int32)
+    idx, val = ks.grad_topk_select(torch.from_numpy(g).cuda(), ks.grad_topk_plan(offs, k))
+    torch.cuda.synchronize()
+    eidx, eval_ = orc.topk_group(g, offs, k)
+    assert np.array_equal(idx.cpu().numpy(), eidx)
+    assert np.array_equal(val.cpu().numpy().view(np.uint32), eval_.view(np.uint32))
+
+
+def grad(seed, n):
+    return (synth.normal(seed, synth.TID_GRAD_SET, 0, n) * 1e-2).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,k", [(2, 1), (7, 3), (9, 8), (63, 1), (64, 16), (65, 17), (257, 100), (1024, 1), (4095, 1000), (4096, 1023),
+                                 (4097, 1030), (8191, 512), (8192, 513), (16_000, 511), (16_001, 600), (32_765, 33), (32_767, 512),
+                                 (32_768, 513), (32_768, 1), (32_768, 4096)])
+def test_tensors_of_one_chunk_at_every_alignment(ks, orc, n, k):
+    g = grad(n + k, 4 * n + 6)
+    offs = np.cumsum([0, n, 1, n, 1, n, 1, n, 3])                 # element offsets 0, 1, 2, 3 modulo 4 for n = 0 modulo 4, others else
+    check(ks, orc, g, offs, [k, 1, k, 1, k, 1, k, 2])
+
+
+def test_one_chunk_values_that_mislead_the_sample(ks, orc):
+    n = 30_000
+    a = grad(1, n)
+    on, off = a.copy() * 1e-3, a.copy() * 1e-3
+    on[::4][:40] = 1.0 + np.arange(40, dtype=np.float32)          # large values on sampled positions only: too few arrive
+    off[np.arange(1, n, 4)] = 0.5                                 # a quarter of the tensor equal and unsampled: too many arrive
+    runs = np.where(np.arange(n) < 1500, np.float32(2.0), a)      # more equal magnitudes than one bucket ranks
+    far = a.copy()
+    far[17], far[n - 1], far[5], far[6] = np.inf, -np.float32(3e38), np.nan, -0.0
+    g = np.concatenate([on, off, runs, far, np.zeros(n, np.float32), np.full(n, -0.25, np.float32)]).astype(np.float32)
+    check(ks, orc, g, np.arange(7) * n, [60, 60, 60, 60, 60, 60])
+
+
+@pytest.mark.parametrize("n,k", [(32_769, 33), (200_000, 900), (200_000, 1100), (400_000, 3900), (400_000, 4096), (3_000_000, 3000)])
+def test_lists_of_the_sampled_path(ks, orc, n, k):
+    """Expected list lengths of 4 k: below and above the 4,096 and 16,384 items of the two register forms."""
+    g = grad(n + k, n)
+    g[: n // 50] *= 40                                            # a heavy tail
+    g[n // 2:n // 2 + 3000] = -0.3                                # a run of equal magnitudes
+    check(ks, orc, np.concatenate([grad(3, 5), g]), [0, 5, 5 + n], [2, k])
+
+
+@pytest.mark.parametrize("sizes,k", [([600_000, 5000, 300_000, 20, 32_768], [600, 10, 4096, 20, 40]),
+                                     ([2_400_000, 600_000, 70, 9000], [4096, 500, 7, 9]), ([600_000, 2_400_000], [600, 4096])])
+def test_paths_of_every_kind_in_one_group(ks, orc, sizes, k):
+    """Sampled paths beside plain trees of three and four levels and tensors of one step."""
+    check(ks, orc, grad(7, sum(sizes)), np.cumsum([0] + sizes), k)
