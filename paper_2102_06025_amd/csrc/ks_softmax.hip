@@ -17,7 +17,9 @@
 typedef KsTile<128, 128, 64, 2, 2> TileG;      // generic path (any D % 32 == 0)
 typedef KsATile<256, 256, 2, 4, 2> TileSm;     // fast path (D % 64 == 0): tile = 256 classes x 256 samples
 typedef KsATile<128, 128, 2, 2, 2, KS_K8> TileDx;
-#define DX_IDX_CACHE 4096 /* gather indices of one workgroup's share of the active dimension, staged in LDS */
+typedef KsATile<256, 256, 2, 4, 2, KS_K8> TileDxWide; // see sm_dx_wide
+// gather indices of one workgroup's share of the active dimension, staged in LDS
+template <class T> struct DxIdx { static constexpr int CAP = T::BM == 256 ? 8192 : 4096; };
 // dW tiles: 256 columns of D, and 256, 192 or 128 active rows -- chosen inside the kernel from the number of active
 // rows, which only the device knows (see dw_tile_rows)
 typedef KsATile<256, 256, 2, 4, 2, KS_M8> TileDw;
@@ -864,7 +866,7 @@ dx_partial_async_kernel(const uint16_t *__restrict__ dZ8, int Bp, const uint16_t
                         const int32_t *__restrict__ active_idx, const int32_t *__restrict__ n_active_p, int B, int D, int M,
                         int S, float *__restrict__ part, KsSelNext next) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[T::LDS_ELEMS];
-    __shared__ int32_t s_idx[DX_IDX_CACHE];
+    __shared__ int32_t s_idx[DxIdx<T>::CAP];
     const int n_active = sm_clamp_n(n_active_p, M);
     const int tiles_m = (B + T::BM - 1) / T::BM, tiles_n = (D + T::BN - 1) / T::BN;
     const int n_tiles = tiles_m * tiles_n;
@@ -883,7 +885,7 @@ dx_partial_async_kernel(const uint16_t *__restrict__ dZ8, int Bp, const uint16_t
     if (kt0 < kt1) {
         // gather list of this share, staged in LDS (the host sizes S so that a share fits), clamped at the end:
         // rows at or beyond n_active meet zeros of dZ8
-        for (int e = threadIdx.x; e < (kt1 - kt0) * 64 && e < DX_IDX_CACHE; e += T::NT) {
+        for (int e = threadIdx.x; e < (kt1 - kt0) * 64 && e < DxIdx<T>::CAP; e += T::NT) {
             int k = kt0 * 64 + e;
             if (k >= n_active) k = n_active - 1;
             s_idx[e] = active_idx[k];
@@ -1202,7 +1204,22 @@ struct SmWs {
     bool fast;
 };
 
+// dX tiles of 256 x 256 instead of 128 x 128.  The contraction is bound by the load requests of its operands: a wide tile has
+// half of them per flop, and its share of the active rows is twice as long, so half the partial products travel.  One workgroup
+// per compute unit, so 16 tiles (B = 2,048 at D = 512) are needed for 16 shares to fill the chip; fewer tiles mean more shares,
+// whose partial products cost what the loads save.  So do short lists (narrow tiles have fewer shares then).  Whole steps at
+// D = 512, narrow -> wide: B = 2,048, M = 32,768: 302 -> 305 us (stays narrow); B = 1,793, M = 60,000: 460 -> 427; B = 4,000,
+// M = 50,001: 1,041 -> 905; B = 2,048, M = 131,072: 1,081 -> 971; D = 256, B = 4,000, M = 65,536: 617 -> 592.
+static bool sm_dx_wide(int B, int D, int64_t M) {
+    return D % 256 == 0 && ks_ceil_div(B, TileDxWide::BM) * (D / TileDxWide::BN) >= 16 && M >= 49152;
+}
+
 static int sm_splits(int B, int D, int64_t M, bool fast) {
+    if (fast && sm_dx_wide(B, D, M)) {
+        const int tiles = (int)ks_ceil_div(B, TileDxWide::BM) * (D / TileDxWide::BN);
+        const int S = (int)ks_ceil_div(256, tiles), need = (int)ks_ceil_div(ks_ceil_div(M, 64), DxIdx<TileDxWide>::CAP / 64);
+        return S > need ? S : need;
+    }
     int tiles = fast ? (int)(ks_ceil_div(B, TileDx::BM) * ks_ceil_div(D, TileDx::BN))
                      : (int)(ks_ceil_div(B, TileG::BM) * ks_ceil_div(D, TileG::BN));
     // two workgroups per compute unit
@@ -1211,7 +1228,7 @@ static int sm_splits(int B, int D, int64_t M, bool fast) {
     if (S > 32) S = 32;
     if (fast) { // a share of the active dimension must fit the dX kernel's LDS index cache
         const int64_t nk = ks_ceil_div(M, 64);
-        const int need = (int)ks_ceil_div(nk, DX_IDX_CACHE / 64);
+        const int need = (int)ks_ceil_div(nk, DxIdx<TileDx>::CAP / 64);
         if (S < need) S = need;
     }
     return S;
@@ -1349,11 +1366,15 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
         }
         mark(4);
         {
-            typedef TileDx T;
-            const int tiles = (int)(ks_ceil_div(B, T::BM) * ks_ceil_div(D, T::BN));
-            if (next.nsel) next.nfetch = (int)ks_ceil_div((int64_t)next.B * (next.K + 1), (int64_t)T::NT);
-            hipLaunchKernelGGL(dx_partial_async_kernel<T>, dim3(tiles * w.S + next.nfetch), dim3(T::NT), 0, st, w.dZ8, w.Bp,
-                               W, active_idx, n_active, B, D, Mi, w.S, w.part, next);
+            auto dx = [&](auto tile) {
+                typedef decltype(tile) T;
+                const int tiles = (int)(ks_ceil_div(B, T::BM) * ks_ceil_div(D, T::BN));
+                if (next.nsel) next.nfetch = (int)ks_ceil_div((int64_t)next.B * (next.K + 1), (int64_t)T::NT);
+                hipLaunchKernelGGL(dx_partial_async_kernel<T>, dim3(tiles * w.S + next.nfetch), dim3(T::NT), 0, st, w.dZ8, w.Bp,
+                                   W, active_idx, n_active, B, D, Mi, w.S, w.part, next);
+            };
+            if (sm_dx_wide(B, D, M)) dx(TileDxWide());
+            else dx(TileDx());
         }
         mark(5);
         mark(6); // the reduction of the partial products rides along with the next launch

@@ -77,3 +77,27 @@ def test_step_at_every_depth(ks, orc, D, C, B, K, M):
     G = ((np.arange(C)[:, None] * 7 + 1 + np.arange(K)[None, :] * 13) % C).astype(np.int32)
     X[:5] = synth.bf16_round((0.9 * W[y[:5]] + 0.1 * X[:5]).astype(np.float32))   # a few confident samples
     run_and_compare(ks, orc, W, X, y, G, C, M, scale=30.0, grad_scale=4.0, tag=f"D={D}")
+
+
+@pytest.mark.parametrize("C,D,B,K,M,few", [(60_000, 512, 2048, 32, 49_151, 0), (60_000, 512, 2048, 32, 49_152, 0), (60_001, 512, 1793, 32, 50_011, 0),
+                                           (60_000, 512, 2048, 3, 60_000, 50), (60_000, 256, 3841, 16, 50_001, 0), (56_000, 768, 1537, 34, 55_001, 900)])
+@pytest.mark.parametrize("unit", [True, False])
+def test_feature_gradient_of_large_batches(ks, C, D, B, K, M, few, unit):
+    """Tiles of 256 x 256 of the dX contraction and the last size before them; batches that end inside a tile, lists so short
+    (labels from `few` classes) that most shares of the active dimension are empty.  Against fp32 products of the same bf16 rows:
+    the logit gradient is stored in bf16, 2^-9 of each of its elements, twice that allowed for the exponential and the sums."""
+    import torch
+    print(f"[depths] dX C={C} D={D} B={B} M={M} few={few} unit={unit}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    W = torch.nn.functional.normalize(torch.randn((C, D), generator=gen, device="cuda")).to(torch.bfloat16)
+    X = torch.nn.functional.normalize(torch.randn((B, D), generator=gen, device="cuda")).to(torch.bfloat16)
+    y = torch.randint(0, few or C, (B,), generator=gen, device="cuda", dtype=torch.int32)
+    G = ((torch.arange(C, device="cuda")[:, None] * 7 + 1 + torch.arange(K, device="cuda")[None, :] * 13) % C).to(torch.int32)
+    out = ks.knn_softmax_fwd_bwd(W, X, y, G, M, 30.0, 4.0, unit_rows=unit)
+    n = int(out["n_active"])
+    Wa, Xf, pos = W[out["active_idx"][:n].long()].float(), X.float(), out["target_pos"].long()
+    P = torch.softmax((30.0 * Xf.double() @ Wa.double().T).float(), 1)
+    P[torch.arange(B, device="cuda"), pos] -= 1
+    f = 30.0 * 4.0 / B
+    want, allowed = f * (P @ Wa), f * (P.abs() @ Wa.abs()) * 2.0 ** -8 + 1e-7
+    assert (pos >= 0).all() and ((out["dX"] - want).abs() <= allowed).all()
