@@ -157,8 +157,8 @@ int knn_gather_rows(const uint16_t *W_bf16, const int32_t *active_idx, const int
  *
  * flags: 0, or KS_FLAG_UNIT_ROWS when the caller normalises the rows of W and X as the paper does (Section
  * 3.2: the fc layer works on normalised weights and features).  All logits then lie in [-scale, scale], and
- * for scale <= 40 the library evaluates the softmax against that fixed bound in a single sweep over the
- * active rows instead of a statistics sweep followed by a gradient sweep.  The result is the same function
+ * for D = 128, 256 or 512 and scale <= 40 the library evaluates the softmax against that fixed bound in a single sweep
+ * over the active rows instead of a statistics sweep followed by a gradient sweep (elsewhere the flag has no effect).  The result is the same function
  * of the inputs (the bound only shifts the exponent range), also when some norms exceed 1; should a
  * sample's exponentials overflow or all underflow, KS_DEV_RANGE is raised and the outputs are unspecified.
  *
@@ -295,7 +295,7 @@ int apply_weight_grad(float *W_master, uint16_t *W_bf16, const int32_t *idx, con
  *   knn_select_active or knn_select_active_csr: local ids, target_pos = -1 for a sample whose class another node
  *   owns) and per sample
  *     row_max [B], row_sumexp [B]:  a pair with  sum_a exp(z_ia - row_max_i) = row_sumexp_i, not necessarily
- *                  the maximum itself: where the one-sweep softmax runs (KS_FLAG_UNIT_ROWS, D <= 512,
+ *                  the maximum itself: where the one-sweep softmax runs (KS_FLAG_UNIT_ROWS, D = 128, 256 or 512,
  *                  scale <= 40) row_max = scale for every sample on every node, so that combining the nodes
  *                  comes down to ADDING their sums; otherwise the pair is normalised to row_sumexp = 1.  A node
  *                  without active classes gives (-infinity, 0)

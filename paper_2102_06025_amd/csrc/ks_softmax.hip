@@ -1300,14 +1300,21 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
     if (w.fast) {
         const int tiles_s = (int)ks_ceil_div(B, 256);
         const bool soe = D <= 512 && tiles_s <= SM_SOE_GRID && scale > 0.f && g > 0.f;
-        // unit rows: |logit| <= scale, and exp(-2 scale) must stay a normal number
-        fused = soe && (flags & KS_FLAG_UNIT_ROWS) && scale <= KS_FUSED_MAX_SCALE;
+        // One sweep: unit rows (|logit| <= scale, and exp(-2 scale) must stay a normal number) of 128, 256 or 512.  It rounds more
+        // than two sweeps do: X / sum becomes a bf16 operand of dW, and the own class's gradient is minus the sum of the others
+        // in bf16 (dX and dW 2 to 3 parts in 1,000 from the two-sweep results, which are 1 in 10,000 from exact ones).  Callers at
+        // those depths have chosen that with the flag; at the other ones the flag has no effect.
+        fused = soe && (D == 128 || D == 256 || D == 512) && (flags & KS_FLAG_UNIT_ROWS) && scale <= KS_FUSED_MAX_SCALE;
         const int grid = soe ? SM_SOE_GRID / tiles_s * tiles_s : 0, slabs = soe ? grid / tiles_s : 0;
         if (fused) {
 #define SM_FUSED_LAUNCH(CFG)                                                                                              \
     hipLaunchKernelGGL((sm_fused_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, B, \
                        w.Bp, D, Mi, tiles_s, scale, w.pl, w.pm, w.dZ8)
-            if (mode != SM_IMPORT) SM_FOR_DEPTH(SM_FUSED_LAUNCH); // the first call of a split has left the exponentials in the workspace
+            if (mode != SM_IMPORT) { // the first call of a split has left the exponentials in the workspace
+                if (D == 512) SM_FUSED_LAUNCH(SmSoe<8 SM_COMMA false>);
+                else if (D == 256) SM_FUSED_LAUNCH(SmSoe<4 SM_COMMA false>);
+                else SM_FUSED_LAUNCH(SmSoe<2 SM_COMMA false>);
+            }
 #undef SM_FUSED_LAUNCH
             mark(2);
             hipLaunchKernelGGL(sm_combine_fused_kernel, dim3((unsigned)ks_ceil_div(B, SM_CF_SPB)), dim3(SM_CF_NT), 0, st, w.pl,

@@ -79,6 +79,26 @@ def test_step_at_every_depth(ks, orc, D, C, B, K, M):
     run_and_compare(ks, orc, W, X, y, G, C, M, scale=30.0, grad_scale=4.0, tag=f"D={D}")
 
 
+@pytest.mark.parametrize("D", [32, 64, 96, 192, 320, 384, 480, 576])
+def test_unit_rows_flag_has_no_effect_without_a_one_sweep_form(ks, D):
+    """The one-sweep softmax rounds X / sum and the own class's gradient once more, which callers at D = 128, 256 and 512 choose
+    with the flag; at every other depth losses and gradients are the same bits with and without it."""
+    import torch
+    print(f"[depths] flag D={D}", flush=True)
+    C, B, K, M = 3000, 300, 9, 2500
+    W, X = dev(synth.unit_rows(32, synth.TID_W, C, D, bf16=True), True), dev(synth.unit_rows(32, synth.TID_X, B, D, bf16=True), True)
+    y, G = dev(synth.labels_uniform(32, B, C)), dev(synth.graph_synthetic(32, C, K))
+    a, b = (ks.knn_softmax_fwd_bwd(W, X, y, G, M, 30.0, 4.0, unit_rows=u) for u in (False, True))
+    torch.cuda.synchronize()
+    n = int(a["n_active"])
+    assert int(b["dev_status"]) == 0 and torch.equal(a["loss_per_sample"], b["loss_per_sample"])
+    assert torch.equal(a["dX"], b["dX"]) and torch.equal(a["dW_active"][:n], b["dW_active"][:n])
+    if D % 64 == 0:   # a node's statistics: normalised to a sum of 1, as without the flag
+        s = ks.knn_softmax_fwd_stats(W, X, a["active_idx"], a["n_active"], a["target_pos"], 30.0, unit_rows=True)
+        torch.cuda.synchronize()
+        assert bool((s["row_sumexp"] == 1.0).all())
+
+
 @pytest.mark.parametrize("C,D,B,K,M,few", [(60_000, 512, 2048, 32, 49_151, 0), (60_000, 512, 2048, 32, 49_152, 0), (60_001, 512, 1793, 32, 50_011, 0),
                                            (60_000, 512, 2048, 3, 60_000, 50), (60_000, 256, 3841, 16, 50_001, 0), (56_000, 768, 1537, 34, 55_001, 900)])
 @pytest.mark.parametrize("unit", [True, False])
