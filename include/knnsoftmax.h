@@ -180,9 +180,9 @@ int knn_softmax_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const in
  * weight update of Section 3.1 step 6 (apply_weight_grad with idx = active_idx, idx_sorted_unique), with the
  * same results bit for bit:
  *     W_master[active_idx[a], :] += alpha * dW_active[a, :],   W_bf16[same rows] = bf16 of the new values.
- * For D % 64 == 0 the update runs inside the kernel that produces dW_active, so the gradient does not travel
- * through memory; dW_active may then be NULL (not stored).  Otherwise dW_active is required and the two steps
- * run one after the other.  W_bf16 is read by the forward pass and updated at the end of the call. */
+ * For D % 64 == 0 dW_active may be NULL (not stored): the update runs inside the kernel that produces it, so the gradient
+ * does not travel through memory.  Otherwise dW_active is required; the update still runs there for D <= 512 with
+ * scale > 0, grad_scale > 0 and B <= 65,536, and elsewhere the two steps run one after the other.  W_bf16 is read by the forward pass and updated at the end of the call. */
 int knn_softmax_fwd_bwd_update(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16, const int32_t *labels,
                                const int32_t *graph, int64_t C, int D, int B, int K, int M, float scale,
                                float grad_scale, float alpha, uint32_t flags, int32_t *active_idx, int32_t *n_active,
@@ -225,8 +225,9 @@ int knn_softmax_fwd_bwd_update_selected(float *W_master, uint16_t *W_bf16, const
  *                       KS_FLAG_TRUSTED_LIST, which reads the list in place: then they must be other buffers, else
  *                       KS_INVALID_ARG -- a loop alternates between two sets).
  *   everything else     as in knn_softmax_fwd_bwd_update_selected, with the same results bit for bit
- * Requires K + 1 <= M besides that call's conditions.  When D exceeds 512 and is not a multiple of 64, or C exceeds the
- * roughly 1.2 million classes whose bitmap one workgroup holds, the selection runs after the step as launches of its own (same results).
+ * Requires K + 1 <= M besides that call's conditions.  When D is not a multiple of 64 and exceeds 512 (or scale or grad_scale
+ * is not positive, or B exceeds 65,536), or when C exceeds the roughly 1.2 million classes whose bitmap one workgroup
+ * holds, the selection runs after the step as launches of its own (same results).
  * Workspace: knn_softmax_selected_next_workspace. */
 size_t knn_softmax_selected_next_workspace(int64_t C, int D, int B, int K, int M);
 int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16,

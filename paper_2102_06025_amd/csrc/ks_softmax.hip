@@ -117,32 +117,33 @@ row_stats_kernel(const float *__restrict__ Z, int64_t ldz, const int32_t *__rest
 // dZ = g (exp(Z - lse) - onehot) as bf16; columns in [n_active, round_up(n_active, 256)) are zeroed
 // ------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(SM_NT)
-dz_kernel(const float *__restrict__ Z, int64_t ldz, const int32_t *__restrict__ n_active_p, int M,
+dz_kernel(const float *__restrict__ Z, int64_t ldz, const int32_t *__restrict__ n_active_p, int B, int M,
           const int32_t *__restrict__ target_pos, const float *__restrict__ lse, float g, uint16_t *__restrict__ dZ) {
     const int n = sm_clamp_n(n_active_p, M);
     const int n_pad = (n + KS_MP_ALIGN - 1) / KS_MP_ALIGN * KS_MP_ALIGN; // <= ldz
     const int a0 = (blockIdx.x * SM_NT + threadIdx.x) * 8;
     if (a0 >= n_pad) return;
-    const int i = blockIdx.y;
-    const float ls = lse[i];
-    const int tp = target_pos[i];
-    const float *z = Z + (int64_t)i * ldz + a0;
-    float v[8];
-    if (a0 + 8 <= n) {
-        float4 p = *(const float4 *)z, q = *(const float4 *)(z + 4);
-        v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w; v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
-    } else {
+    for (int i = blockIdx.y; i < B; i += gridDim.y) { // (the y dimension of a grid ends at 65,535)
+        const float ls = lse[i];
+        const int tp = target_pos[i];
+        const float *z = Z + (int64_t)i * ldz + a0;
+        float v[8];
+        if (a0 + 8 <= n) {
+            float4 p = *(const float4 *)z, q = *(const float4 *)(z + 4);
+            v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w; v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
+        } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (a0 + e < n) ? z[e] : 0.f;
-    }
-    uint32_t o[4];
+            for (int e = 0; e < 8; ++e) v[e] = (a0 + e < n) ? z[e] : 0.f;
+        }
+        uint32_t o[4];
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        float d0 = (a0 + e < n) ? g * (__expf(v[e] - ls) - (a0 + e == tp ? 1.f : 0.f)) : 0.f;
-        float d1 = (a0 + e + 1 < n) ? g * (__expf(v[e + 1] - ls) - (a0 + e + 1 == tp ? 1.f : 0.f)) : 0.f;
-        o[e / 2] = ks_pack_bf2(d0, d1);
+        for (int e = 0; e < 8; e += 2) {
+            float d0 = (a0 + e < n) ? g * (__expf(v[e] - ls) - (a0 + e == tp ? 1.f : 0.f)) : 0.f;
+            float d1 = (a0 + e + 1 < n) ? g * (__expf(v[e + 1] - ls) - (a0 + e + 1 == tp ? 1.f : 0.f)) : 0.f;
+            o[e / 2] = ks_pack_bf2(d0, d1);
+        }
+        *(uint4 *)(dZ + (int64_t)i * ldz + a0) = make_uint4(o[0], o[1], o[2], o[3]);
     }
-    *(uint4 *)(dZ + (int64_t)i * ldz + a0) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1185,8 +1186,15 @@ static int ks_n_cu() {
     return n;
 }
 
-// depths that the stationary-operand engine takes, or the tile engine
-static bool sm_fast(int D) { return D <= 512 || D % 64 == 0; }
+// Whether the softmax runs as sweeps with resident samples: a sample block's fragments fit in registers up to D = 512, every
+// block of 256 samples needs a workgroup, and the sweeps take logarithms of the two factors.  (NaN factors: no.)
+static bool sm_sweeps(int D, int B, float scale, float grad_scale) {
+    return D <= 512 && ks_ceil_div(B, 256) <= SM_SOE_GRID && scale > 0.f && grad_scale / (float)B > 0.f;
+}
+// The fast path: those sweeps, or else the tile engine, whose k-tiles are whole (D % 64 == 0).  What neither takes -- an odd
+// multiple of 32 with grad_scale <= 0 (a loss without gradients, ascent), scale <= 0 or more than 65,536 samples, or beyond
+// 512 -- is left to the generic path.
+static bool sm_fast(int D, int B, float scale, float grad_scale) { return D % 64 == 0 || sm_sweeps(D, B, scale, grad_scale); }
 
 struct SmWs {
     void *select;
@@ -1202,6 +1210,7 @@ struct SmWs {
     int64_t Mp;
     int Bp;
     bool fast;
+    size_t bytes;
 };
 
 // dX tiles of 256 x 256 instead of 128 x 128.  The contraction is bound by the load requests of its operands: a wide tile has
@@ -1234,10 +1243,10 @@ static int sm_splits(int B, int D, int64_t M, bool fast) {
     return S;
 }
 
-static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool with_select, size_t *total) {
+static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool with_select, bool fast) {
     KsArena ar(ws);
     SmWs w;
-    w.fast = sm_fast(D);
+    w.fast = fast;
     w.Mp = sm_mp(M);
     w.Bp = (int)ks_align_up((size_t)B, KS_BP_ALIGN);
     w.S = sm_splits(B, D, M, w.fast);
@@ -1261,8 +1270,15 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
         w.Z = ar.take<float>((size_t)B * w.Mp);
         w.dZ = ar.take<uint16_t>((size_t)B * w.Mp);
     }
-    if (total) *total = ar.off;
+    w.bytes = ar.off;
     return w;
+}
+// bytes of the workspace: the factors, which decide between the paths of an odd multiple of 32, are not known to the callers'
+// size queries, so it holds either
+static size_t sm_bytes(int64_t C, int D, int B, int K, int64_t M, bool with_select) {
+    const size_t fast = D <= 512 || D % 64 == 0 ? sm_carve(nullptr, C, D, B, K, M, with_select, true).bytes : 0;
+    const size_t generic = D % 64 != 0 ? sm_carve(nullptr, C, D, B, K, M, with_select, false).bytes : 0;
+    return fast > generic ? fast : generic;
 }
 
 // Sweeps of a depth of up to eight k-tiles (D <= 512, D % 32 == 0): F(CFG) is instantiated for the depth's stage shape
@@ -1299,7 +1315,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
     bool fused = false;
     if (w.fast) {
         const int tiles_s = (int)ks_ceil_div(B, 256);
-        const bool soe = D <= 512 && tiles_s <= SM_SOE_GRID && scale > 0.f && g > 0.f;
+        const bool soe = sm_sweeps(D, B, scale, grad_scale);
         // One sweep: unit rows (|logit| <= scale, and exp(-2 scale) must stay a normal number) of 128, 256 or 512.  It rounds more
         // than two sweeps do: X / sum becomes a bf16 operand of dW, and the own class's gradient is minus the sum of the others
         // in bf16 (dX and dW 2 to 3 parts in 1,000 from the two-sweep results, which are 1 in 10,000 from exact ones).  Callers at
@@ -1416,8 +1432,8 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
     hipLaunchKernelGGL(row_stats_kernel, dim3(B), dim3(SM_NT), 0, st, w.Z, w.Mp, n_active, Mi, target_pos, w.lse,
                        loss_per_sample);
     mark(3);
-    hipLaunchKernelGGL(dz_kernel, dim3((unsigned)ks_ceil_div(w.Mp, SM_NT * 8), B), dim3(SM_NT), 0, st, w.Z, w.Mp, n_active,
-                       Mi, target_pos, w.lse, g, w.dZ);
+    hipLaunchKernelGGL(dz_kernel, dim3((unsigned)ks_ceil_div(w.Mp, SM_NT * 8), B < 65535 ? B : 65535), dim3(SM_NT), 0, st, w.Z, w.Mp,
+                       n_active, B, Mi, target_pos, w.lse, g, w.dZ);
     mark(4);
     hipLaunchKernelGGL(dx_partial_kernel<T>, dim3(tiles_b * tiles_d, w.S), dim3(T::NT), 0, st, w.dZ, w.Mp, W, active_idx,
                        n_active, B, D, Mi, w.part);
@@ -1439,9 +1455,7 @@ static int sm_check_dims(int64_t C, int D, int B) {
 
 extern "C" size_t knn_softmax_workspace(int64_t C, int D, int B, int K, int M) {
     if (sm_check_dims(C, D, B) != KS_OK || K < 0 || M < 1) return 0;
-    size_t total = 0;
-    sm_carve(nullptr, C, D, B, K, M, true, &total);
-    return total;
+    return sm_bytes(C, D, B, K, M, true);
 }
 
 static int sm_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const int32_t *labels, const int32_t *graph,
@@ -1453,14 +1467,13 @@ static int sm_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const int3
     if (!W_bf16 || !X_bf16 || !labels || !active_idx || !n_active || !target_pos || !loss_per_sample || !loss_mean ||
         !dX || !ws)
         return KS_INVALID_ARG;
-    const bool fast = sm_fast(D); // the update runs inside the dW kernel of these paths
     if (!dW_active && !(W_master && D % 64 == 0)) return KS_INVALID_ARG;
     if (sm_check_dims(C, D, B) != KS_OK || K < 0 || M < 1) return KS_INVALID_ARG;
     if (K > 0 && !graph) return KS_INVALID_ARG;
     if (B > M || (int64_t)K + 1 > M) return KS_INVALID_ARG;
-    size_t need = 0;
-    SmWs w = sm_carve(ws, C, D, B, K, M, true, &need);
-    if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < sm_bytes(C, D, B, K, M, true)) return KS_WORKSPACE_TOO_SMALL;
+    const bool fast = sm_fast(D, B, scale, grad_scale); // the update runs inside the dW kernel of this path
+    SmWs w = sm_carve(ws, C, D, B, K, M, true, fast);
     hipStream_t st = (hipStream_t)stream;
     if (ev) (void)hipEventRecord(ev[0], st);
     int rc = ks_select_launch(labels, graph, C, B, K, M, active_idx, n_active, target_pos, w.select, dev_status, st);
@@ -1528,10 +1541,10 @@ struct SmSplitWs {
     SmWs w;
     int32_t *act, *n, *tp;
 };
-static SmSplitWs sm_split_carve(void *ws, int64_t C, int D, int B, int64_t M, size_t *total) {
-    size_t used = 0;
+static SmSplitWs sm_split_carve(void *ws, int64_t C, int D, int B, int64_t M, bool fast, size_t *total) {
+    const size_t used = sm_bytes(C, D, B, 0, M, false);
     SmSplitWs s;
-    s.w = sm_carve(ws, C, D, B, 0, M, false, &used);
+    s.w = sm_carve(ws, C, D, B, 0, M, false, fast);
     KsArena ar(ws ? (void *)((char *)ws + used) : nullptr);
     s.act = ar.take<int32_t>((size_t)M);
     s.tp = ar.take<int32_t>((size_t)B);
@@ -1549,7 +1562,7 @@ static int sm_split_check(int64_t C, int D, int B, int M, float scale, uint32_t 
 extern "C" size_t knn_softmax_split_workspace(int64_t C, int D, int B, int M) {
     if (sm_split_check(C, D, B, M, 1.f, 0) != KS_OK) return 0;
     size_t total = 0;
-    sm_split_carve(nullptr, C, D, B, M, &total);
+    sm_split_carve(nullptr, C, D, B, M, true, &total);
     return total;
 }
 
@@ -1564,7 +1577,7 @@ extern "C" int knn_softmax_fwd_stats(const uint16_t *W_bf16, const uint16_t *X_b
     int rc = sm_split_check(C, D, B, M, scale, flags);
     if (rc != KS_OK) return rc;
     size_t need = 0;
-    SmSplitWs s = sm_split_carve(ws, C, D, B, M, &need);
+    SmSplitWs s = sm_split_carve(ws, C, D, B, M, true, &need);
     if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)stream;
     const int nmax = M > B ? M : B;
@@ -1617,7 +1630,7 @@ static int sm_bwd_from_stats(const uint16_t *W_bf16, const uint16_t *X_bf16, con
             return KS_INVALID_ARG; // a trusted list is read in place: the next one needs buffers of its own
     }
     size_t need = 0;
-    SmSplitWs s = sm_split_carve(ws, C, D, B, M, &need);
+    SmSplitWs s = sm_split_carve(ws, C, D, B, M, true, &need);
     if (nx) need = ks_align_up(need, 256);
     void *sel_ws = (char *)ws + need;
     if (nx) need += ks_select_ws_bytes(C, B, nx->K_max);
@@ -1674,7 +1687,7 @@ extern "C" int knn_softmax_bwd_from_stats(const uint16_t *W_bf16, const uint16_t
 extern "C" size_t knn_softmax_split_next_workspace(int64_t C, int D, int B, int K_max, int M) {
     if (sm_split_check(C, D, B, M, 1.f, 0) != KS_OK || K_max < 0) return 0;
     size_t total = 0;
-    sm_split_carve(nullptr, C, D, B, M, &total);
+    sm_split_carve(nullptr, C, D, B, M, true, &total);
     return ks_align_up(total, 256) + ks_select_ws_bytes(C, B, K_max);
 }
 extern "C" int knn_softmax_bwd_from_stats_next(const uint16_t *W_bf16, const uint16_t *X_bf16, const int32_t *active_idx,
@@ -1703,7 +1716,7 @@ static int sm_selected_check(int64_t C, int D, int B, int M) {
 extern "C" size_t knn_softmax_selected_workspace(int64_t C, int D, int B, int M) {
     if (sm_selected_check(C, D, B, M) != KS_OK) return 0;
     size_t total = 0;
-    sm_split_carve(nullptr, C, D, B, M, &total);
+    sm_split_carve(nullptr, C, D, B, M, true, &total);
     return total;
 }
 // the next batch's selection that rides along with a step on a given selection (nullptr: none)
@@ -1720,7 +1733,7 @@ static int sm_selected(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16
         return KS_INVALID_ARG;
     if (sm_selected_check(C, D, B, M) != KS_OK) return KS_INVALID_ARG;
     if (flags & ~(uint32_t)(KS_FLAG_UNIT_ROWS | KS_FLAG_TRUSTED_LIST)) return KS_INVALID_ARG;
-    const bool fast = sm_fast(D);
+    const bool fast = sm_fast(D, B, scale, grad_scale);
     const bool trusted = (flags & KS_FLAG_TRUSTED_LIST) != 0;
     if (!dW_active && !(W_master && D % 64 == 0)) return KS_INVALID_ARG;
     // a trusted list is read where it lies, until the end of the call: the next batch's list needs buffers of its own
@@ -1732,7 +1745,7 @@ static int sm_selected(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16
         if ((int64_t)nx->K + 1 > M) return KS_INVALID_ARG;
     }
     size_t need = 0;
-    SmSplitWs s = sm_split_carve(ws, C, D, B, M, &need);
+    SmSplitWs s = sm_split_carve(ws, C, D, B, M, fast, &need);
     if (nx) need = ks_align_up(need, 256);
     void *sel_ws = (char *)ws + need; // the selection's staging area follows the step's buffers
     if (nx) need += ks_select_ws_bytes(C, B, nx->K);
@@ -1754,8 +1767,8 @@ static int sm_selected(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16
         up.idx = act;
         up.alpha = alpha;
     }
-    // The selection rides along with the dX and dW launches where those exist (D a multiple of 64) and the class bitmap
-    // fits in LDS; otherwise it follows the step as launches of its own.  Either way it starts after the sanitised copy
+    // The selection rides along with the dX and dW launches of the fast path where the class bitmap fits in LDS; otherwise it
+    // follows the step as launches of its own.  Either way it starts after the sanitised copy
     // of this step's list has been made, so its outputs may be the buffers this step's list came in.
     KsSelNext next = KsSelNext();
     const bool ride = nx && fast && sm_next_rides(C, B, nx->K);
@@ -1794,7 +1807,7 @@ extern "C" int knn_softmax_fwd_bwd_update_selected(float *W_master, uint16_t *W_
 extern "C" size_t knn_softmax_selected_next_workspace(int64_t C, int D, int B, int K, int M) {
     if (sm_selected_check(C, D, B, M) != KS_OK || K < 0) return 0;
     size_t total = 0;
-    sm_split_carve(nullptr, C, D, B, M, &total);
+    sm_split_carve(nullptr, C, D, B, M, true, &total);
     return ks_align_up(total, 256) + ks_select_ws_bytes(C, B, K);
 }
 extern "C" int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16,
@@ -1813,8 +1826,7 @@ extern "C" int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_
 
 extern "C" size_t full_softmax_workspace(int64_t C, int D, int B) {
     if (sm_check_dims(C, D, B) != KS_OK) return 0;
-    size_t total = 0;
-    sm_carve(nullptr, C, D, B, 0, C, false, &total);
+    size_t total = sm_bytes(C, D, B, 0, C, false);
     total += ks_align_up((size_t)C * 4, 256) + ks_align_up((size_t)B * 4, 256) + 256;
     return total;
 }
@@ -1826,9 +1838,8 @@ extern "C" int full_softmax_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf
     if (!W_bf16 || !X_bf16 || !labels || !loss_per_sample || !loss_mean || !dX || !dW || !ws) return KS_INVALID_ARG;
     if (sm_check_dims(C, D, B) != KS_OK) return KS_INVALID_ARG;
     if (ws_bytes < full_softmax_workspace(C, D, B)) return KS_WORKSPACE_TOO_SMALL;
-    size_t used = 0;
-    SmWs w = sm_carve(ws, C, D, B, 0, C, false, &used);
-    KsArena ar((char *)ws + used);
+    SmWs w = sm_carve(ws, C, D, B, 0, C, false, sm_fast(D, B, scale, grad_scale));
+    KsArena ar((char *)ws + sm_bytes(C, D, B, 0, C, false));
     int32_t *active_idx = ar.take<int32_t>((size_t)C);
     int32_t *target_pos = ar.take<int32_t>((size_t)B);
     int32_t *n_active = ar.take<int32_t>(1);

@@ -79,6 +79,70 @@ def test_step_at_every_depth(ks, orc, D, C, B, K, M):
     run_and_compare(ks, orc, W, X, y, G, C, M, scale=30.0, grad_scale=4.0, tag=f"D={D}")
 
 
+@pytest.mark.parametrize("D", [32, 64, 96, 480])
+@pytest.mark.parametrize("scale,grad_scale", [(30.0, 0.0), (30.0, -4.0), (0.0, 4.0), (-20.0, 4.0)])
+def test_factors_that_the_sweeps_do_not_take(ks, orc, D, scale, grad_scale):
+    """No gradient wanted, ascent, a scale of zero or below: the step as one and as two calls, the loop's call with the next
+    batch's selection, the full softmax.  Rows within gradcheck's allowance (the absolute values of the factors are its factors)."""
+    import torch
+    from gradcheck import check_rows, grad_floors
+    print(f"[depths] factors D={D} scale={scale} grad_scale={grad_scale}", flush=True)
+    C, B, K, M, alpha = 900, 70, 6, 400, -0.5
+    W, X = synth.unit_rows(33, synth.TID_W, C, D, bf16=True), synth.unit_rows(33, synth.TID_X, B, D, bf16=True)
+    y, G = synth.labels_uniform(33, B, C), synth.graph_synthetic(33, C, K)
+    active, A, tpos = orc.select_active(y, G, C, M)
+    Wd, Xd, yd, Gd = dev(W, True), dev(X, True), dev(y), dev(G)
+
+    def check(got, ref, W_A, tp, name):
+        floors = [np.abs(f) for f in grad_floors(W_A, X, tp, ref["lse"], scale, grad_scale / B)]
+        assert np.abs(got["loss_per_sample"].cpu().numpy() - ref["loss_i"]).max() <= 1e-3 * max(1.0, np.abs(ref["loss_i"]).max())
+        check_rows(got["dX"].cpu().numpy(), ref["dX"], floors[0], f"{name} dX")
+        check_rows(got["dW"].cpu().numpy()[:W_A.shape[0]], ref["dW"], floors[1], f"{name} dW")
+
+    ref = orc.knn_softmax_fwd_bwd(W, X, active[:A], tpos, scale, grad_scale)
+    ref["dW"] = ref["dWA"]
+    a = ks.knn_softmax_fwd_bwd(Wd, Xd, yd, Gd, M, scale, grad_scale)
+    Wm, Wb = dev(W), Wd.clone()
+    b = ks.knn_softmax_fwd_bwd_update(Wm, Wb, Xd, yd, Gd, M, scale, grad_scale, alpha, want_dW=True)
+    y2 = dev(synth.labels_uniform(34, B, C))
+    Wm2, Wb2 = dev(W), Wd.clone()
+    lst = {k: a[k].clone() for k in ("active_idx", "n_active", "target_pos")}
+    c, nxt = ks.knn_softmax_fwd_bwd_update_selected_next(Wm2, Wb2, Xd, lst["active_idx"], lst["n_active"], lst["target_pos"], y2, Gd, scale,
+                                                         grad_scale, alpha, want_dW=True)
+    sel = ks.knn_select_active(y2, Gd, C, M)
+    f = ks.full_softmax_fwd_bwd(Wd, Xd, yd, scale, grad_scale)
+    torch.cuda.synchronize()
+    for out in (a, b, c):
+        assert int(out["dev_status"]) == 0
+        check(dict(out, dW=out["dW_active"]), ref, W[active[:A]], tpos, "step")
+    assert torch.equal(nxt["active_idx"], sel[0]) and torch.equal(nxt["n_active"], sel[1]) and torch.equal(nxt["target_pos"], sel[2])
+    assert torch.equal(Wm, Wm2) and torch.equal(Wb, Wb2)
+    eW, _ = orc.apply_weight_grad(W, active[:A], b["dW_active"][:A].cpu().numpy(), alpha, want_bf16=False)
+    assert np.array_equal(Wm.cpu().numpy(), eW)
+    fref = orc.full_softmax_fwd_bwd(W, X, y, scale, grad_scale)
+    fref["lse"] = np.log(np.exp(scale * (X.astype(np.float64) @ W.astype(np.float64).T)).sum(axis=1))
+    check(f, fref, W, y, "full softmax")
+
+
+@pytest.mark.parametrize("D", [32, 96, 128])
+def test_more_samples_than_the_sweeps_have_workgroups_for(ks, orc, D):
+    """65,536 samples and a tile more (256 blocks of 256 samples are the most a sweep takes)."""
+    import torch
+    from gradcheck import check_rows, grad_floors
+    C, B = 300, 65_600
+    print(f"[depths] full softmax D={D} B={B}", flush=True)
+    W, X = synth.unit_rows(35, synth.TID_W, C, D, bf16=True), synth.unit_rows(35, synth.TID_X, B, D, bf16=True)
+    y = synth.labels_uniform(35, B, C)
+    f = ks.full_softmax_fwd_bwd(dev(W, True), dev(X, True), dev(y), 20.0, 4.0)
+    torch.cuda.synchronize()
+    ref = orc.full_softmax_fwd_bwd(W, X, y, 20.0, 4.0)
+    lse = np.log(np.exp(20.0 * (X.astype(np.float64) @ W.astype(np.float64).T)).sum(axis=1))
+    floors = grad_floors(W, X, y, lse, 20.0, 4.0 / B)
+    assert np.abs(f["loss_per_sample"].cpu().numpy() - ref["loss_i"]).max() <= 1e-3 * np.abs(ref["loss_i"]).max()
+    check_rows(f["dX"].cpu().numpy(), ref["dX"], floors[0], "dX")
+    check_rows(f["dW"].cpu().numpy(), ref["dW"], floors[1], "dW")
+
+
 @pytest.mark.parametrize("D", [32, 64, 96, 192, 320, 384, 480, 576])
 def test_unit_rows_flag_has_no_effect_without_a_one_sweep_form(ks, D):
     """The one-sweep softmax rounds X / sum and the own class's gradient once more, which callers at D = 128, 256 and 512 choose
