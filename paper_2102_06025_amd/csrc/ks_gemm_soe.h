@@ -32,8 +32,8 @@
 #include "ks_gemm_async.h"
 
 // RAGGED: the depth is 64 * KT - 32 (D an odd multiple of 32).  The second half of the last k-tile is then no data: the
-// lanes that would fetch it fetch the first half of the same rows again (in bounds, finite), and the resident fragments
-// of those k-steps are zero.
+// lanes that would fetch it fetch the first half of the same rows again (in bounds), and its two k-steps are left out.
+// (Multiplied by zeros instead, an infinite element of the first half would make the product NaN.)
 template <int KT_, int CH_, int STAGES_, int KSUB_ = 1, bool RAGGED_ = false> struct KsSoe {
     static constexpr int KT = KT_, STAGES = STAGES_, KSUB = KSUB_;
     static constexpr bool RAGGED = RAGGED_;
@@ -123,10 +123,8 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
             if (kt > 0 && kt - 1 + NS < KT) res_issue(kt - 1 + NS, lds + ((kt - 1) % NS) * CFG::RES * 64);
             const uint16_t *st = lds + (kt % NS) * CFG::RES * 64;
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                if (CFG::RAGGED && kt == KT - 1 && kk >= 2) bres[kt * 4 + kk] = bf16x8_t{};
-                else bres[kt * 4 + kk] = *(const bf16x8_t *)(st + (wave * 32 + r31) * 64 + (((kk * 2 + khalf) ^ swz) * 8));
-            }
+            for (int kk = 0; kk < (CFG::RAGGED && kt == KT - 1 ? 2 : 4); ++kk)
+                bres[kt * 4 + kk] = *(const bf16x8_t *)(st + (wave * 32 + r31) * 64 + (((kk * 2 + khalf) ^ swz) * 8));
         }
     }
 
@@ -237,14 +235,14 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
                 ks_barrier_nofence();
 #pragma unroll
                 for (int u = 0; u < CFG::KSUB; ++u) {
-                    const int kt = kt0 + u;
+                    const int kt = kt0 + u, ksteps = CFG::RAGGED && kt == KT - 1 ? 2 : 4;
                     const uint16_t *st = lds + stage * CFG::STAGE_ELEMS + u * CFG::CH * 64;
                     bf16x8_t a0[FM], a1[FM];
 #pragma unroll
                     for (int fm = 0; fm < FM; ++fm)
                         a0[fm] = *(const bf16x8_t *)(st + (fm * 32 + r31) * 64 + ((khalf ^ swz) * 8));
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) {
+                    for (int kk = 0; kk < ksteps; ++kk) {
                         bf16x8_t(&cur)[FM] = (kk & 1) ? a1 : a0;
                         bf16x8_t(&nxt)[FM] = (kk & 1) ? a0 : a1;
                         __builtin_amdgcn_sched_barrier(0);
@@ -253,7 +251,7 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
 #pragma unroll
                         for (int fm = 0; fm < FM; ++fm) asm volatile("" ::"v"(cur[fm]));
                         __builtin_amdgcn_sched_barrier(0);
-                        if (kk + 1 < 4) {
+                        if (kk + 1 < ksteps) {
 #pragma unroll
                             for (int fm = 0; fm < FM; ++fm)
                                 nxt[fm] = *(const bf16x8_t *)(st + (fm * 32 + r31) * 64 + ((((kk + 1) * 2 + khalf) ^ swz) * 8));

@@ -143,6 +143,46 @@ def test_more_samples_than_the_sweeps_have_workgroups_for(ks, orc, D):
     check_rows(f["dW"].cpu().numpy(), ref["dW"], floors[1], "dW")
 
 
+@pytest.mark.parametrize("D", [32, 64, 96, 224, 480, 544])
+def test_infinite_weights_in_the_last_elements_of_a_row(ks, orc, D):
+    """The padding of a ragged depth takes no part.  Graph: a row with an infinite element is the first neighbour of the rows
+    whose sign agrees, and takes its own in ascending order of their ids.  Step: a class that every sample's logit is -inf for has
+    probability 0, and losses and gradients are those without it (where the infinity itself is not a factor)."""
+    import torch
+    print(f"[depths] infinite weights D={D}", flush=True)
+    C, K, d, c = 200, 8, D - 30, 37
+    W = synth.unit_rows(36, synth.TID_W, C, D, bf16=True)
+    Wi = W.copy()
+    Wi[c, d] = np.inf
+    g, s = ks.knn_graph_build(dev(Wi, True), K, want_sims=True)
+    torch.cuda.synchronize()
+    g, s = g.cpu().numpy(), s.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        S = Wi.astype(np.float64) @ Wi.astype(np.float64).T
+    others = W[:, d] != 0                                         # (infinity times zero is no similarity)
+    for i in np.nonzero(others)[0]:
+        S[i, i] = -np.inf
+        if i != c or others.all():
+            assert np.array_equal(g[i], np.argsort(-S[i], kind="stable")[:K]) and np.isinf(s[i, 0]) == (np.inf in S[i])
+    B, M = 40, 190
+    X = np.abs(synth.unit_rows(36, synth.TID_X, B, D, bf16=True)) + np.float32(2.0 ** -9)   # every x[d] > 0
+    X = synth.bf16_round(X)
+    Wi[c, d] = -np.inf
+    y = np.array([v for v in synth.labels_uniform(36, 4 * B, C) if v != c][:B], np.int32)
+    G = synth.graph_synthetic(36, C, K)
+    G[y[0], 0] = c                                                # the class is active
+    active, A, tpos = orc.select_active(y, G, C, M)
+    assert c in active[:A]
+    keep = active[:A][active[:A] != c]
+    ref = orc.knn_softmax_fwd_bwd(W, X, keep, np.searchsorted(keep, y).astype(np.int32), 20.0, 2.0)
+    out = ks.knn_softmax_fwd_bwd(dev(Wi, True), dev(X, True), dev(y), dev(G), M, 20.0, 2.0)
+    torch.cuda.synchronize()
+    dX, dW = out["dX"].cpu().numpy(), out["dW_active"][:A].cpu().numpy()[active[:A] != c]
+    assert np.abs(out["loss_per_sample"].cpu().numpy() - ref["loss_i"]).max() <= 1e-3 * np.abs(ref["loss_i"]).max()
+    for got, want in ((np.delete(dX, d, 1), np.delete(ref["dX"], d, 1)), (dW, ref["dWA"])):
+        assert np.linalg.norm(got - want) <= 2e-2 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("D", [32, 64, 96, 192, 320, 384, 480, 576])
 def test_unit_rows_flag_has_no_effect_without_a_one_sweep_form(ks, D):
     """The one-sweep softmax rounds X / sum and the own class's gradient once more, which callers at D = 128, 256 and 512 choose
