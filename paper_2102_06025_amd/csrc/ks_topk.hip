@@ -48,7 +48,8 @@
 #define TK_SAMPLE_RANK 16  /* the threshold is at least the TK_SAMPLE_RANK-th largest of the sample */
 
 // node record (int64 words)
-enum { TK_N_SRC = 0, TK_N_ITEMS, TK_N_K, TK_N_OUT, TK_N_FLAGS, TK_N_FIRST, TK_N_GBEGIN, TK_N_GN, TK_N_AUX, TK_N_FB_FIRST, TK_N_FB_COUNT };
+enum { TK_N_SRC = 0, TK_N_ITEMS, TK_N_K, TK_N_OUT, TK_N_FLAGS, TK_N_FIRST, TK_N_GBEGIN, TK_N_GN, TK_N_AUX, TK_N_FB_FIRST, TK_N_FB_COUNT,
+       TK_N_RUN /* first of the tensors of one step in a plan with sampled paths: how many of them follow one another */ };
 #define TK_F_LEAF 1  /* reads gradients (src = element offset in g); otherwise items (src = offset in the workspace) */
 #define TK_F_FINAL 2 /* writes the tensor's output (out = offset in out_idx / out_val); otherwise items (workspace) */
 // The sampled path of a tensor of several chunks (three steps whatever its size):
@@ -1128,8 +1129,10 @@ static int64_t tk_plan_build(const int64_t *offsets, const int32_t *k, int T, in
             plan[lev == 1 ? 29 : 31] = w - plan[8 + 2 * lev];
         }
         auto single = [&](const TkNode &nd) { return sampled && lev == n_levels - 1 && nd.flags == (TK_F_LEAF | TK_F_FINAL); };
+        const int64_t run0 = w;
         for (const TkNode &nd : nodes)
             if (nd.level == lev && single(nd)) put(nd);
+        if (w > run0) nrec[run0 * TK_NODE + TK_N_RUN] = w - run0;
         for (const TkNode &nd : nodes)
             if (nd.level == lev && !(nd.flags & special) && !single(nd)) put(nd);
         plan[9 + 2 * lev] = w - plan[8 + 2 * lev];
@@ -1170,18 +1173,15 @@ extern "C" int grad_topk_select(const float *g, const int64_t *plan_dev, const i
     const int64_t *nodes = plan_dev + TK_HEADER + plan_host[1] * TK_TENSOR; // (from the host's copy: read on the GPU it is a round trip)
     // With sampled paths in the plan, the tensors of one step (first in the last level, behind the sampled paths' final steps if
     // those are there too) run beside the thresholds: the two take about as long, and the final steps are left a launch of
-    // short lists.
+    // short lists.  A plan says so in the first of their records (TK_N_RUN); in one saved by a version that did not sort
+    // them to the front that word is 0, and its levels are launched as they stand.
     const int last = (int)plan_host[6] - 1;
     int64_t singles = 0, single0 = 0;
     if (plan_host[31] > 0) {
         single0 = plan_host[8 + 2 * last] + (last == 2 ? plan_host[31] : 0);
-        const int64_t *rec = plan_host + TK_HEADER + plan_host[1] * TK_TENSOR + single0 * TK_NODE;
-        int64_t end = plan_host[9 + 2 * last] - (last == 2 ? plan_host[31] : 0); // number of records of a kind at the front: by halving
-        while (singles < end) {
-            const int64_t mid = (singles + end) >> 1;
-            if (rec[mid * TK_NODE + TK_N_FLAGS] == (TK_F_LEAF | TK_F_FINAL)) singles = mid + 1;
-            else end = mid;
-        }
+        const int64_t end = plan_host[9 + 2 * last] - (last == 2 ? plan_host[31] : 0);
+        if (end > 0) singles = plan_host[TK_HEADER + plan_host[1] * TK_TENSOR + single0 * TK_NODE + TK_N_RUN];
+        if (singles < 0 || singles > end) return KS_INVALID_ARG; // (not a plan of grad_topk_plan)
     }
     for (int lev = 0; lev < (int)plan_host[6]; ++lev) {
         int64_t first = plan_host[8 + 2 * lev], count = plan_host[9 + 2 * lev], extra = 0;

@@ -69,3 +69,27 @@ def test_lists_of_the_sampled_path(ks, orc, n, k):
 def test_paths_of_every_kind_in_one_group(ks, orc, sizes, k):
     """Sampled paths beside plain trees of three and four levels and tensors of one step."""
     check(ks, orc, grad(7, sum(sizes)), np.cumsum([0] + sizes), k)
+
+
+def test_plan_saved_before_its_last_level_was_sorted(ks, orc):
+    """Plans are plain words that a program may keep in a file.  Those of earlier versions have the last level's steps in tensor
+    order (tensors of one step between the last steps of plain trees, whose inputs the level before writes)."""
+    import torch
+    sizes, k = [600_000, 5000, 300_000, 20, 32_768, 310_000, 9], [600, 10, 4096, 20, 40, 4096, 4]
+    offs, k = np.cumsum([0] + sizes).astype(np.int64), np.asarray(k, np.int32)
+    host = ks.grad_topk_plan(offs, k).host.copy()
+    nodes = host[32 + 4 * len(sizes):].reshape(-1, 12)
+    last, n_counted = int(host[6]) - 1, int(host[31])
+    assert last == 2 and n_counted == 1
+    lo, hi = int(host[8 + 2 * last]) + n_counted, int(host[8 + 2 * last] + host[9 + 2 * last])
+    kinds = nodes[lo:hi, 4].tolist()                              # flags: 3 = a tensor of one step, 2 = the last step of a plain tree
+    assert kinds == [3, 3, 3, 3, 2, 2] and nodes[lo, 11] == 4
+    old = nodes[lo:hi][np.argsort(nodes[lo:hi, 3])]               # by place in the output: tensor order
+    old[:, 11] = 0
+    nodes[lo:hi] = old
+    assert old[:, 4].tolist() == [3, 2, 3, 3, 2, 3]
+    g = grad(11, int(offs[-1]))
+    idx, val = ks.grad_topk_select(torch.from_numpy(g).cuda(), ks.GradTopkPlan(host, "cuda"))
+    torch.cuda.synchronize()
+    eidx, eval_ = orc.topk_group(g, offs, k)
+    assert np.array_equal(idx.cpu().numpy(), eidx) and np.array_equal(val.cpu().numpy().view(np.uint32), eval_.view(np.uint32))
