@@ -637,8 +637,9 @@ template <class List> __device__ __forceinline__ void tk_select(const List &list
 // ------------------------------------------------------------------------------------------------
 // The r-th largest of the workgroup's sampled magnitudes (Q per thread, 0xFFFFFFFF: none), to the exponent and six bits of
 // the mantissa: the threshold is the lower edge of the histogram bin it falls in, so somewhat more elements than r lie at or above
-// it (a tenth to a fifth for bell-shaped values; sorting the sample took five times as long as everything else in this step, a
-// second level of histogram a microsecond).  Overwrites sh.sort.
+// it (a tenth to a fifth for bell-shaped values; sorting the sample took five times as long as everything else in this step).
+// Where the bin brings the count beyond 3/2 r -- values that crowd at the top of their range, as uniform ones do, or all within
+// one bin -- a second level adds eleven bits (a microsecond), and only equal values are left to exceed r.  Overwrites sh.sort.
 template <int Q> __device__ __forceinline__ uint32_t tk_sample_threshold(const uint32_t (&key)[Q], int r, TkShared &sh) {
     uint32_t *hist = (uint32_t *)sh.sort;
     for (int b = threadIdx.x; b < TK_BINS0 / 4; b += TK_NT) ((uint4 *)hist)[b] = make_uint4(0u, 0u, 0u, 0u);
@@ -648,7 +649,16 @@ template <int Q> __device__ __forceinline__ uint32_t tk_sample_threshold(const u
         if (key[q] != 0xFFFFFFFFu) atomicAdd(&hist[key[q] >> 17], 1u);
     __syncthreads();
     uint32_t above, in_bin;
-    return tk_find_bin<TK_BINS0 / TK_NT>(hist, TK_BINS0, (uint32_t)r, sh, &above, &in_bin) << 17;
+    const uint32_t b1 = tk_find_bin<TK_BINS0 / TK_NT>(hist, TK_BINS0, (uint32_t)r, sh, &above, &in_bin);
+    if (2u * (above + in_bin) <= 3u * (uint32_t)r) return b1 << 17; // (the same for all threads)
+    for (int b = threadIdx.x; b < TK_BINS; b += TK_NT) sh.hist[b] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (key[q] >> 17 == b1) atomicAdd(&sh.hist[(key[q] >> 6) & (TK_BINS - 1)], 1u);
+    __syncthreads();
+    const uint32_t b2 = tk_find_bin<TK_BINS / TK_NT>(sh.hist, TK_BINS, (uint32_t)r - above, sh, &above, &in_bin);
+    return (b1 << 17) | (b2 << 6);
 }
 __device__ void tk_threshold(const float *__restrict__ gt, uint32_t n, int r, uint64_t *aux, TkShared &sh) {
     uint32_t key[TK_SAMPLE / TK_NT];

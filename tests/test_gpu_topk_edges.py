@@ -64,6 +64,32 @@ def test_lists_of_the_sampled_path(ks, orc, n, k):
     check(ks, orc, np.concatenate([grad(3, 5), g]), [0, 5, 5 + n], [2, k])
 
 
+@pytest.mark.parametrize("n,k", [(40_000, 40), (600_000, 600), (2_359_296, 2359), (2_700_000, 2600)])
+@pytest.mark.parametrize("kind", ["uniform", "narrow", "normal"])
+def test_list_length_of_the_sampled_path_whatever_the_values_are(ks, orc, n, k, kind):
+    """The list of a tensor is an order statistic's count, n / 4,096 times a Gamma(r) variable, times at most 3/2 for the
+    histogram bin: beyond three times its mean for less than one tensor in a million (r >= 16).  Values that crowd in
+    one bin of the first histogram level (uniform ones near their maximum; all of them in [1, 1 + 1 / 64)) are no exception."""
+    import torch
+    print(f"[topk] list length n={n} k={k} {kind}", flush=True)
+    gen = np.random.default_rng(n + k)
+    g = {"uniform": lambda: gen.random(n), "narrow": lambda: -1.0 - gen.random(n) / 65.0, "normal": lambda: gen.standard_normal(n)}[kind]().astype(np.float32)
+    offs, kk = np.array([0, n], np.int64), np.array([k], np.int32)
+    plan = ks.grad_topk_plan(offs, kk)
+    ws = torch.zeros(plan.ws_bytes, dtype=torch.uint8, device="cuda")
+    idx, val = ks.grad_topk_select(torch.from_numpy(g).cuda(), plan, ws=ws)
+    torch.cuda.synchronize()
+    nodes = plan.host[32 + 4:].reshape(-1, 12)
+    final, thresh = nodes[(nodes[:, 4] & 16) != 0], nodes[(nodes[:, 4] & 4) != 0]
+    assert len(final) == len(thresh) == 1
+    count, overflow = ws.view(torch.int32)[2 * (int(final[0, 8]) + 1):][:2].tolist()   # the tensor's second workspace word
+    r = int(thresh[0, 2])
+    print(f"        r={r} count={count} of {r * n / 4096:.0f}", flush=True)
+    assert overflow == 0 and k <= count <= 3 * r * n / 4096
+    eidx, eval_ = orc.topk_group(g, offs, kk)
+    assert np.array_equal(idx.cpu().numpy(), eidx) and np.array_equal(val.cpu().numpy().view(np.uint32), eval_.view(np.uint32))
+
+
 @pytest.mark.parametrize("sizes,k", [([600_000, 5000, 300_000, 20, 32_768], [600, 10, 4096, 20, 40]),
                                      ([2_400_000, 600_000, 70, 9000], [4096, 500, 7, 9]), ([600_000, 2_400_000], [600, 4096])])
 def test_paths_of_every_kind_in_one_group(ks, orc, sizes, k):
