@@ -782,7 +782,12 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
 //    exhaustive pass computes it.
 // ------------------------------------------------------------------------------------------------
 #define GR_SYM_SB 768            /* rows of a super-block */
-#define GR_SYM_LOG_PER_ROW 384   /* log records per row (expected: 192 stream-side hits, plus a tenth) */
+// Log records per row: what a row's stream segment takes.  Half of a row's hits are stream-side ones where its neighbours lie
+// anywhere; but where they crowd in a run of ids (classes in order of frequency, with norms to match), the rows of the half
+// ring behind that run find ALL of theirs on the stream side, and all the same ones: the mean of a log is then a single
+// order statistic, beyond 384 for one build in four at K = 32 and for half of them at K = 64.  One lost record sends all
+// rows of the log to the exhaustive search.
+#define GR_SYM_LOG_PER_ROW GR_SYM_SCAP
 #define GR_SYM_STAGE 192         /* records a wavefront collects in LDS between two appends to a log */
 #define GR_SYM_MAX_GROUP 10      /* super-blocks per group at most: 30 shares, about the compute units of an XCD */
 
@@ -990,8 +995,8 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
                 // on in the lanes 32..63.  (Testing against the smaller of the two thresholds, held in a scalar register,
                 // and sorting out the surplus later was tried: the number of records then depends on how well
                 // neighbouring rows match; a tight cluster row beside a lone one got four times its share, the logs
-                // overflowed and every row went to the exhaustive pass.  With the exact test the counts depend on
-                // nothing but the sample.)
+                // overflowed and every row went to the exhaustive pass.  With the exact test a row's hits on both
+                // sides together are the sample's order statistic and nothing else.)
                 // Every instruction here runs once per chunk and fragment, so there are few: a lane's hits become a bit
                 // mask (bit 15 - r for element r); while any lane has a hit left, every lane that has picks one with a
                 // binary tree of selects and the slots come from one ballot.

@@ -225,3 +225,38 @@ def test_feature_gradient_of_large_batches(ks, C, D, B, K, M, few, unit):
     f = 30.0 * 4.0 / B
     want, allowed = f * (P @ Wa), f * (P.abs() @ Wa.abs()) * 2.0 ** -8 + 1e-7
     assert (pos >= 0).all() and ((out["dX"] - want).abs() <= allowed).all()
+
+
+@pytest.mark.parametrize("K,rank", [(16, 8), (32, 10), (64, 12)])
+def test_neighbours_that_crowd_in_a_run_of_ids(ks, orc, K, rank):
+    """Classes in order of frequency with norms to match: every row's neighbours are the same few hundred, in the first three
+    super-blocks, and half of all rows find all of theirs on the stream side of the symmetric sweep.  The sample is an unlucky
+    one (450 rows above its rank-th largest; 32 * rank on average).  No row may be left for the exhaustive search."""
+    import torch
+    C, D, hubs, above = 30_011, 512, 2304, 450
+    assert C * D >= 15_000_000                                    # (the symmetric sweep)
+    print(f"[depths] hubs C={C} K={K}", flush=True)
+    s = np.arange(C // 32, dtype=np.int64)
+    sampled = s * 32 + (((s * 2654435761) & 0xFFFFFFFF) >> 16) % 32
+    rng = np.random.default_rng(K)
+    in_hub = rng.permutation(sampled[sampled < hubs])
+    free = rng.permutation(np.setdiff1d(np.arange(hubs), in_hub))
+    n_free = above - rank + 1
+    order = np.concatenate([rng.permutation(np.concatenate([in_hub[:rank - 1], free[:n_free]])), in_hub[rank - 1:rank],
+                            rng.permutation(np.concatenate([in_hub[rank:], free[n_free:]]))])
+    norm = np.ones(C)
+    norm[order] = np.linspace(12.0, 8.0, hubs)
+    u = synth.unit_rows(41, synth.TID_X, 1, D).astype(np.float64)
+    W = norm[:, None] * (u + 0.05 * synth.unit_rows(41, synth.TID_W, C, D))
+    W = synth.bf16_round(W.astype(np.float32))
+    ws = torch.zeros(ks.knn_graph_build_workspace(C, D, K, 0), dtype=torch.uint8, device="cuda")
+    g, sims = ks.knn_graph_build(dev(W, True), K, want_sims=True, ws=ws)
+    torch.cuda.synchronize()
+    # the workspace begins with the row norms, 1,024 maxima, the maximum, the number of rows searched exhaustively
+    pad = lambda n: (n + 255) // 256 * 256
+    at = pad(4 * C) + 4096
+    assert abs(float(ws[at:at + 4].view(torch.float32)) - np.sqrt((W.astype(np.float64) ** 2).sum(1)).max()) < 1e-3
+    assert int(ws[at + 256:at + 260].view(torch.int32)) == 0
+    rows = np.unique(np.concatenate([synth.class_permutation(41, C)[:100], order[:5], [0, hubs - 1, hubs, C - 1]])).astype(np.int32)
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (sims.cpu().numpy()[rows] == es.astype(np.float32)).all()
