@@ -24,9 +24,9 @@
 
 // Layouts of an operand in memory and in LDS (A: m index, B: n index, k: contraction)
 //   ROWS   row = m or n, k contiguous                                              (KsARows)
-//   KMAJ   row = k, m or n contiguous: fragments by the transposing LDS read       (KsAKmaj)
-//   K8     [k / 8][m][8 k]: blocks of eight k's of one m                           (KsAK8)
-//   M8     the same array with the roles of its indexes exchanged: [m / 8][k][8 m], fragments by the transposing read (KsAM8)
+//   KMAJ   (B only) row = k, n contiguous: fragments by the transposing LDS read   (KsAKmaj)
+//   K8     (A only) [k / 8][m][8 k]: blocks of eight k's of one m                           (KsAK8)
+//   M8     (A only) the same array with the roles of its indexes exchanged: [m / 8][k][8 m], fragments by the transposing read (KsAM8)
 enum { KS_ROWS = 0, KS_KMAJ = 1, KS_K8 = 2, KS_M8 = 3 };
 #define KS_M8_SLAB 544 /* LDS elements from one 64 x 8 block of an M8 tile to the next: 1 KB + 64 bytes, so that the blocks that
                           one transposing read touches fall on different banks */
@@ -289,8 +289,7 @@ __device__ __forceinline__ void ks_a_load_frags(KsAFrags<T> &f, const uint16_t *
     const uint32_t m8 = AL == KS_M8 ? ks_a_m8_addr(stA, wm * T::FM) : 0u;
     ks_static_for<T::FM>([&](auto fmc) __attribute__((always_inline)) {
         constexpr int fm = decltype(fmc)::value;
-        if constexpr (AL == KS_KMAJ) f.a[fm] = ks_a_frag_kmaj<T::BM, KK>(ks_a_kmaj_addr<T::BM>(stA, wm * T::FM + fm));
-        else if constexpr (AL == KS_M8) f.a[fm] = ks_a_frag_m8<fm, KK>(m8);
+        if constexpr (AL == KS_M8) f.a[fm] = ks_a_frag_m8<fm, KK>(m8);
         else if constexpr (AL == KS_K8) f.a[fm] = ks_a_frag_k8<T::BM, fm, KK>(k8);
         else f.a[fm] = *(const bf16x8_t *)(stA + (wm * T::WM + fm * 32 + r) * 64 + co);
     });
@@ -304,7 +303,8 @@ __device__ __forceinline__ void ks_a_load_frags(KsAFrags<T> &f, const uint16_t *
 // LDS instructions of one fragment set (a transposed fragment takes two reads)
 template <class T, int AL, int BL> struct KsAFragCount {
     static constexpr bool ASM = AL != KS_ROWS || BL == KS_KMAJ; // some reads are issued from assembly
-    static constexpr int N = ((AL == KS_KMAJ || AL == KS_M8) ? 2 : 1) * T::FM + (BL == KS_KMAJ ? 2 : 1) * T::FN;
+    static_assert(AL != KS_KMAJ, "no reader for a k-major A operand");
+    static constexpr int N = (AL == KS_M8 ? 2 : 1) * T::FM + (BL == KS_KMAJ ? 2 : 1) * T::FN;
     static_assert(N <= 15, "lgkmcnt range");
 };
 // Wait until at most YOUNGER LDS instructions issued after this fragment set's reads are outstanding, and tie
@@ -367,7 +367,7 @@ __device__ __forceinline__ void ks_a_mainloop(AR &ar, BR &br, int kt0, int kt1, 
                                               f32x16_t (&acc)[T::FM][T::FN]) {
     constexpr int S = T::STAGES;
     constexpr int PER_TILE = T::NI_A + T::NI_B;
-    static_assert(S == 2 || (AK != KS_KMAJ && BK != KS_KMAJ), "k-major loaders issue their gather-index loads in between: two stages only");
+    static_assert(S == 2 || BK != KS_KMAJ, "k-major loaders issue their gather-index loads in between: two stages only");
 #pragma unroll
     for (int s = 0; s < S - 1; ++s) {
         if (kt0 + s < kt1) {

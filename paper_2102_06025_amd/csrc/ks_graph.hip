@@ -542,8 +542,10 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 //
 // A first sweep (gr_threshold_kernel) finds for every row its r-th largest similarity to a sample of one in 32 of the
 // searched rows; r = 8 for K <= 16, 10 for K <= 32, 12 for K <= 64.  The number of searched rows at or above it is
-// 32 * Gamma(r) whatever their distribution (an order statistic of a uniform sample): 256, 320 or 384 on average, beyond
-// 1,100 or at most K (then r of the row's K + 1 best would have to be in the sample) for less than one row in a million.
+// 32 * Gamma(r) whatever their distribution (an order statistic of a uniform sample): 256, 320 or 384 on average.  The
+// largest K of each r is the worst case: beyond 1,100 (a row's segments take 2,048, a lane's share of them 512) for 0.02, 0.3
+// and 3.4 rows in a million; at most K (then r of the row's K + 1 best would have to be in the sample) for 0.1 to 1.4 in a
+// million, and for 1.0, 1.1 and 8.3 in a million of the rows that are in their own sample.
 // The candidate segments are sized for those counts and nothing is cut back during the sweep, so that
 //   * a row's candidates may come from several workgroups: gr_recall_fix_kernel cuts the searched rows into `parts`, one
 //     workgroup per (256 resident rows, part).  10,000 rows are 40 blocks; with one workgroup each, 216 compute units idle.
@@ -773,11 +775,11 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
 //    takes there for both sides), then the super-blocks it takes inside its group, then all rows of the groups its
 //    group takes.  A share's chunks are cut into `parts` runs, one workgroup each (one part per share in problems that
 //    fill the chip without it).  The shares of a group run on one XCD (or two neighbouring ones) and stream the same long
-//    ranges at the same pace, so a streamed row is fetched from memory about once per group.
+//    ranges, so a streamed row is fetched from memory about once per group -- less often where two groups that stream
+//    different ranges share an XCD (390,625 rows of 512: 31.6 GB in all, 26.3 when whole groups were dealt to XCDs).
 //  * the stream side's candidates.  A hit for streamed row j is a record (j, i, similarity): a wavefront collects them
-//    in LDS and appends them, with one atomic per batch, to the log of j's run of `log_rows` rows (a super-block in a
-//    large problem; as little as a chunk in a small one, whose chunks have a batch's worth of hits each);
-//    gr_sym_scatter_kernel (one workgroup per log, row counters in LDS) then moves them into the rows' stream segments.
+//    in LDS and appends them, with one atomic per batch, to the log of j's run of `log_rows` rows (a super-block, or half
+//    of one in a smaller problem); gr_sym_scatter_kernel (one workgroup per log, row counters in LDS) then moves them into the rows' stream segments.
 //  * A row whose segments or log overflowed gets a threshold no similarity exceeds: its certificate fails and the
 //    exhaustive pass computes it.
 // ------------------------------------------------------------------------------------------------
@@ -1597,9 +1599,9 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, bool sym) {
     f.log_rows = GR_SYM_SB;
     f.logs = 0;
     if (sym) {
-        // a wavefront finds about 96 * 32 * 384 / C stream-side hits per chunk: logs of as few chunks as still give it a
-        // batch's worth, so that small problems have a log for every compute unit in the scatter kernel
-        while (f.log_rows > 96 && (double)(f.log_rows / 2) * 32.0 * 384.0 / (double)Cs >= 96.0) f.log_rows /= 2;
+        // A wavefront finds about 96 * 32 * 384 / C stream-side hits per chunk.  Logs of half a super-block where four chunks
+        // still give it half a batch (C <= 49,152): the scatter kernel then has 77 workgroups or more instead of 39.
+        if ((double)(GR_SYM_SB / 2) * 32.0 * 384.0 / (double)Cs >= 96.0) f.log_rows = GR_SYM_SB / 2;
         f.logs = (int)ks_ceil_div(Cr, f.log_rows);
     }
     return f;

@@ -1,7 +1,7 @@
 """GPU parity of one node of the sharded layer (Section 3.2.3 and the fill-up branch of Algorithm 1): graph
 compression, selection on the compressed graph with labels of other nodes' classes, random fill-up to M.  All
 outputs are integers and are compared bit for bit with the CPU oracle, on both selection paths (class bitmap in
-LDS for nodes of up to 393,216 classes, score table in memory beyond) and at the size of the headline shard."""
+LDS for nodes of up to some 1.2 million classes, score table in memory beyond) and at the size of the headline shard."""
 import numpy as np
 import pytest
 import torch
@@ -89,10 +89,10 @@ def select_both(ks, orc, labels, dev_csr, cpu_csr, c0, C_loc, K_max, M, pad=Fals
     return a, n, nf, t
 
 
-@pytest.mark.parametrize("Cg,K,B,P", [(100_000, 16, 256, 4), (20_000, 32, 512, 3), (1_600_000, 16, 1024, 2)])
+@pytest.mark.parametrize("Cg,K,B,P", [(100_000, 16, 256, 4), (20_000, 32, 512, 3), (1_600_000, 16, 1024, 2), (2_600_000, 16, 1024, 2)])
 def test_selection_on_compressed_graph(ks, orc, Cg, K, B, P):
     """Every node of a P-node layer, with and without a cut, with and without the fill-up.  The last case has
-    nodes of 800,000 classes (score table in memory), the others use the bitmap in LDS."""
+    nodes of 1,300,000 classes (score table in memory), the others use the bitmap in LDS."""
     G = synth.graph_synthetic(2, Cg, K, locality=64, empty_frac=0.05) if Cg <= 100_000 else arithmetic_graph(Cg, K)
     labels = synth.labels_uniform(2, B, Cg)
     for p in range(P):

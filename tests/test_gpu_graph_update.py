@@ -49,12 +49,16 @@ def run_node(ks, orc, W, bf16, K, shards, node, order, check_hops):
 
 
 @pytest.mark.parametrize("C,D,K,bf16,bounds", [
-    (3000, 128, 8, True, [0, 1000, 1001, 2200, 3000]),      # stationary-operand recall, a one-row shard
+    (3000, 128, 8, True, [0, 1000, 1001, 2200, 3000]),      # recall with fixed thresholds, a one-row shard
     (3000, 128, 8, False, [0, 1500, 3000]),                 # fp32 input: 16-bit copies for the recall, fp32 rows for the merge
     (2500, 512, 32, True, [0, 700, 2500]),
-    (2000, 96, 16, True, [0, 1200, 2000]),                  # generic recall tile
-    (2000, 192, 64, True, [0, 900, 2000]),                  # asynchronous recall tile, k' = 128
-    (1500, 256, 100, True, [0, 800, 1500]),                 # k' = 256
+    (2000, 96, 16, True, [0, 1200, 2000]),                  # ... of a ragged depth
+    (2000, 192, 64, True, [0, 900, 2000]),                  # ... K = 64
+    (1500, 256, 100, True, [0, 800, 1500]),                 # running thresholds: stationary-operand recall, k' = 256
+    (1500, 192, 70, True, [0, 700, 1500]),                  # asynchronous recall tile, K > 64
+    (1200, 576, 16, True, [0, 700, 1200]),                  # ... D > 512
+    (1500, 96, 80, True, [0, 800, 1500]),                   # generic recall tile, K > 64
+    (1200, 544, 24, False, [0, 1, 1200]),                   # ... D > 512, fp32 rows
 ])
 def test_hops_over_all_shards_give_the_exact_graph(ks, orc, C, D, K, bf16, bounds):
     print(f"[hop] C={C} D={D} K={K} bf16={bf16} shards={bounds}", flush=True)

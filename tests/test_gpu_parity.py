@@ -86,8 +86,10 @@ def _run_and_compare_one(ks, W, X, y, G, C, M, scale, grad_scale, tag, unit_rows
     (100_000, 16, 256, 4_096, 0, 0.0),  # the "small" configuration: cut bites
     (390_625, 32, 1_024, 32_768, 0, 0.0),
     (390_625, 32, 1_024, 20_000, 1, 0.1),   # single-workgroup path, cut bites
-    (393_217, 16, 512, 4_000, 2, 0.0),      # just above the single-workgroup limit: table path, cut bites
+    (393_217, 16, 512, 4_000, 2, 0.0),      # workspace sized for the score table, the bitmap used, cut bites
     (1_000_000, 64, 2_048, 131_072, 0, 0.0),
+    (1_300_000, 16, 512, 4_000, 2, 0.0),    # above the single-workgroup limit: table path, cut bites
+    (1_300_000, 16, 512, 20_000, 2, 0.1),
     (5000, 2500, 4, 3000, 5, 0.0),      # more list positions than the LDS histogram holds
 ])
 def test_select_matches_oracle(ks, orc, C, K, B, M, seed, empty):
@@ -436,36 +438,70 @@ def test_graph_sweep_kernel_buffer_sizes_and_ties(ks, orc, C, D, K, bf16, kind):
     _check_graph(ks, orc, W, K, bf16, rows=rows, tag=f"sweep kernel {kind}")
 
 
+def _rows_of_kind(kind, C, D, bf16):
+    if kind == "unit":
+        return synth.unit_rows(11, synth.TID_W, C, D, bf16=bf16)
+    if kind == "integers":
+        W = np.random.default_rng(C + D).integers(-1, 2, (C, D)).astype(np.float32)
+        W[C // 2] = W[3]
+        W[C - 1] = W[3]
+        return W
+    if kind == "copies":   # more rows equal to one another than a row's segments, or a log, hold
+        W = synth.unit_rows(11, synth.TID_W, C, D, bf16=bf16)
+        W[1000:6000] = W[3]
+        return W
+    return synth.clustered_rows(11, C, D, n_centres=97, bf16=bf16)
+
+
+def _sampled_rows(C, n_rows):
+    rows = np.sort(synth.class_permutation(11, C)[:n_rows]).astype(np.int32)
+    return np.unique(np.concatenate([rows, [0, 3, 255, 256, 767, 768, C // 2, C - 257, C - 2, C - 1]])).astype(np.int32)
+
+
 @pytest.mark.parametrize("C,D,K,bf16,kind", [(6400, 128, 32, True, "unit"), (7000, 128, 8, True, "unit"),
                                              (8330, 256, 16, False, "unit"), (6913, 512, 32, True, "clustered"),
                                              (25_000, 128, 32, True, "unit"), (50_011, 128, 16, True, "clustered"),
                                              (6400, 128, 32, True, "integers"), (9000, 256, 64, True, "unit"),
                                              (12_345, 128, 40, False, "clustered"), (7000, 512, 64, True, "integers")])
+def test_graph_recall_with_fixed_thresholds(ks, orc, C, D, K, bf16, kind):
+    """Thresholds from a sample, all rows past all blocks (C * D below 15 million): block counts that are odd, even and
+    ragged, all three ranks of the sample, clustered rows, and rows with so many equal similarities that their segments
+    overflow and the rows go to the exhaustive pass."""
+    _check_graph(ks, orc, _rows_of_kind(kind, C, D, bf16), K, bf16, rows=_sampled_rows(C, 400 if C <= 10_000 else 160),
+                 tag=f"fixed thresholds {kind}")
+
+
+def _takes_the_symmetric_sweep(ks, C, D, K, bf16):
+    """For C * D from 15 million on: its workspace is 25 or 33 KB a row (two or four segments of 512 slots, the stream side's of
+    1,024, a log of 1,024 records); the pass of all rows by all blocks would take 9 KB, or 90 and more."""
+    return 24_000 < ks.knn_graph_build_workspace(C, D, K, 0 if bf16 else 1) / C < 36_000
+
+
+@pytest.mark.parametrize("C,D,K,bf16,kind", [(29_297, 512, 32, True, "unit"), (29_584, 512, 64, True, "integers"),
+                                             (29_884, 512, 16, False, "unit"), (30_011, 512, 40, False, "clustered"),
+                                             (31_000, 512, 32, True, "copies"), (59_000, 256, 8, True, "clustered"),
+                                             (58_700, 256, 64, False, "unit"), (117_300, 128, 32, True, "clustered"),
+                                             (118_000, 128, 64, True, "copies")])
 def test_graph_every_similarity_computed_once(ks, orc, C, D, K, bf16, kind):
-    """The recall pass that uses the symmetry of the similarities (D = 128, 256, 512, K <= 64): block, super-block and
-    group counts that are odd, even and ragged (a last super-block of one, two and three blocks; groups of one, two and
-    four super-blocks), all three values of k' (48, 64, 128), clustered rows, and rows with so many equal similarities
-    that the fixed-size buffers overflow and the rows go to the exhaustive pass."""
-    if kind == "unit":
-        W = synth.unit_rows(11, synth.TID_W, C, D, bf16=bf16)
-    elif kind == "integers":
-        W = np.random.default_rng(C + D).integers(-1, 2, (C, D)).astype(np.float32)
-        W[C // 2] = W[3]
-        W[C - 1] = W[3]
-    else:
-        W = synth.clustered_rows(11, C, D, n_centres=97, bf16=bf16)
-    n_rows = 400 if C <= 10_000 else 160
-    rows = np.sort(synth.class_permutation(11, C)[:n_rows]).astype(np.int32)
-    rows = np.unique(np.concatenate([rows, [0, 3, 255, 256, 767, 768, C // 2, C - 257, C - 2, C - 1]])).astype(np.int32)
-    _check_graph(ks, orc, W, K, bf16, rows=rows, tag=f"symmetric recall {kind}")
+    """The recall pass that uses the symmetry of the similarities (D = 128, 256, 512, K <= 64, C * D from 15 million on), with
+    shares cut into parts and logs of half a super-block (D = 512) and without: last super-blocks of one, two and three
+    blocks, all three ranks of the sample, fp32 rows, clustered rows, many equal similarities, and so many equal rows that
+    segments and logs overflow and the rows go to the exhaustive pass."""
+    assert _takes_the_symmetric_sweep(ks, C, D, K, bf16)
+    rows = _sampled_rows(C, 160)
+    if kind == "copies":
+        rows = np.unique(np.concatenate([rows, [999, 1000, 1535, 1536, 3000, 5999, 6000]])).astype(np.int32)
+    _check_graph(ks, orc, _rows_of_kind(kind, C, D, bf16), K, bf16, rows=rows, tag=f"symmetric recall {kind}")
 
 
-def test_graph_tight_clusters_beside_lone_rows(ks, orc):
+@pytest.mark.parametrize("C,D,symmetric", [(40_000, 128, False), (30_000, 512, True)])
+def test_graph_tight_clusters_beside_lone_rows(ks, orc, C, D, symmetric):
     """Rows that alternate, four by four, between tight clusters (hundreds of neighbours a few 1e-6 apart: no k' of a few
     dozen certifies the K-th one) and random directions (rows four apart share accumulator registers in the sweep and have
     nothing else in common).  The lists must be exact, and the build must not fall back on the exhaustive search for
     more than a handful of rows: uncertified rows are ranked again over everything the sweep kept for them."""
-    C, D, K = 40_000, 128, 32
+    K = 32
+    assert not symmetric or _takes_the_symmetric_sweep(ks, C, D, K, True)
     rnd = synth.unit_rows(13, synth.TID_W, C, D).astype(np.float64)
     centres = synth.unit_rows(14, synth.TID_W, 64, D).astype(np.float64)
     idx = np.arange(C)
@@ -486,9 +522,10 @@ def test_graph_tight_clusters_beside_lone_rows(ks, orc):
     assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
 
 
-@pytest.mark.parametrize("C", [6000, 9000])   # the plain recall pass; the one that computes every similarity once
-def test_graph_is_deterministic(ks, orc, C):
-    W = synth.unit_rows(6, synth.TID_W, C, 128, bf16=True)
+@pytest.mark.parametrize("C,D", [(6000, 128), (9000, 128), (30_000, 512)])   # all rows by all blocks; every similarity once
+def test_graph_is_deterministic(ks, orc, C, D):
+    assert D < 512 or _takes_the_symmetric_sweep(ks, C, D, 16, True)
+    W = synth.unit_rows(6, synth.TID_W, C, D, bf16=True)
     g1, s1 = ks.knn_graph_build(dev(W, torch.bfloat16), 16, want_sims=True)
     g2, s2 = ks.knn_graph_build(dev(W, torch.bfloat16), 16, want_sims=True)
     torch.cuda.synchronize()
@@ -643,18 +680,23 @@ def test_step_on_an_earlier_selection_equals_the_one_call_step(ks, orc, name, un
     ("the cut bites", dict(C=20_000, D=128, B=128, K=16, M=700, labels="zipf"), True, False, True),
     ("D = 96", dict(C=5_000, D=96, B=70, K=9, M=300), False, False, False),
     ("D = 96", dict(C=5_000, D=96, B=70, K=9, M=300), False, False, True),
-    ("the table path", dict(C=400_000, D=128, B=64, K=8, M=1_024), True, True, False),
+    ("400,000 classes", dict(C=400_000, D=128, B=64, K=8, M=1_024), True, True, False),
+    ("the table path", dict(C=1_300_000, D=64, B=64, K=8, M=1_024), True, True, False),
+    ("the table path", dict(C=1_300_000, D=64, B=64, K=8, M=1_024), False, False, True),
+    ("D = 544", dict(C=3_000, D=544, B=70, K=9, M=300), False, True, False),
+    ("D = 544", dict(C=3_000, D=544, B=70, K=9, M=300), True, False, True),
     ("one sample", dict(C=300, D=64, B=1, K=3, M=4), False, True, False),
     ("lists as long as M allows", dict(C=3_000, D=128, B=5, K=7, M=8), True, False, True),
     ("batch not a power of two, 393,216 classes", dict(C=393_216, D=64, B=100, K=5, M=600), True, False, True),
     ("a large batch", dict(C=200_000, D=128, B=3000, K=32, M=65_536, labels="zipf"), True, False, True),
-    ("a large batch, the cut bites", dict(C=200_000, D=128, B=4096, K=32, M=20_000), True, True, False)])
+    ("a large batch, the cut bites", dict(C=200_000, D=128, B=4096, K=32, M=20_000), True, True, False),
+    ("a large batch, wide dX tiles", dict(C=60_000, D=256, B=3900, K=32, M=50_001), True, True, False)])
 def test_selection_of_the_next_batch_rides_along_with_the_step(ks, orc, name, shape, unit_rows, in_place, trusted):
     """A loop of knn_softmax_fwd_bwd_update_selected_next calls (the step on this batch's list, the next batch's list
     made by extra workgroups of the same launches) against a loop of one-call steps on the same batches: every
     batch's active list, target positions, losses and dX, and the weights after the last step, bit for bit.  With the
-    list buffers reused in place and with separate ones; D a multiple of 64 (the selection rides along) and not, and
-    more classes than one workgroup's bitmap holds (then it follows the step); a batch whose lists exceed M; and with
+    list buffers reused in place and with separate ones; D at most 512 or a multiple of 64 (the selection rides along) and
+    neither, and more classes than one workgroup's bitmap holds (then it follows the step); a batch whose lists exceed M; and with
     the list declared trusted (read in place, no validating copy: separate buffers are then required)."""
     cfg = dict(synth.CONFIGS["tiny"], **shape) if shape else synth.CONFIGS[name]
     C, D, B, K, M, scale = cfg["C"], cfg["D"], cfg["B"], cfg["K"], cfg["M"], cfg["scale"]

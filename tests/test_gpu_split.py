@@ -233,12 +233,13 @@ def test_split_node_of_the_headline_shard_size(ks, orc):
 
 @pytest.mark.parametrize("Cg,D,K,B,M,P,pad,trusted,unit_rows", [
     (40_000, 128, 16, 128, 2048, 4, False, False, True), (40_000, 128, 16, 128, 2048, 4, True, True, True),
-    (9_000, 256, 8, 64, 400, 3, True, False, False), (1_600_000, 64, 8, 96, 1024, 4, False, True, True)])
+    (9_000, 256, 8, 64, 400, 3, True, False, False), (1_600_000, 64, 8, 96, 1024, 4, False, True, True),
+    (2_600_000, 64, 8, 96, 1024, 2, False, True, True), (2_600_000, 64, 8, 96, 1024, 2, True, False, False)])
 def test_node_loop_with_the_next_selection_inside_the_second_call(ks, Cg, D, K, B, M, P, pad, trusted, unit_rows):
     """One node of a P-node layer over three batches: knn_softmax_fwd_stats + knn_softmax_bwd_from_stats_next (the next
     batch's selection on the compressed graph inside the second call's launches, with and without the fill-up, the
     list in place or trusted and alternating) against knn_select_active_csr + the two plain calls: lists, counts,
-    losses, dX and dW_active bit for bit.  The last case is a node of 400,000 classes (the selection follows the step)."""
+    losses, dX and dW_active bit for bit.  The last two are a node of 1,300,000 classes (the selection follows the step)."""
     rng = np.random.default_rng(Cg + D)
     c0, C_loc = Cg // P, Cg // P
     W = synth.unit_rows(3, synth.TID_W, C_loc, D, bf16=True)

@@ -1,6 +1,6 @@
 """knn_select_active_static (the selection for callers that cannot allocate: its scratch memory is a static device
 array inside the library) against knn_select_active, through the C ABI: two calls in a row, the second with a
-smaller input, every output bit for bit; then the table path of large class counts, and a repeat of the first
+smaller input, every output bit for bit; then the table path of large problems, and a repeat of the first
 call (the array keeps the previous call's contents)."""
 import numpy as np
 import pytest
@@ -48,7 +48,8 @@ def test_static_selection_equals_the_workspace_one_on_two_calls_in_a_row(ks):
     n_small = _both(ks, 3_000, 16, 128, 600, 2, empty=0.3)      # a smaller input right after it
     assert n_big > n_small > 0
     _both(ks, 100_000, 16, 256, 4_096, 0)                       # the cut bites
-    _both(ks, 450_000, 8, 300, 2_000, 3)                        # above the bitmap path's limit: the table path
+    _both(ks, 450_000, 8, 300, 2_000, 3)                        # scratch memory sized for the score table, the bitmap used
+    _both(ks, 450_000, 8, 26_000, 30_000, 3)                    # bitmap and list of the samples exceed LDS: the table path
     assert _both(ks, 390_625, 32, 1_024, 32_768, 0) == n_big    # and the first one again
 
 
