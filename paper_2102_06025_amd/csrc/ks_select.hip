@@ -320,13 +320,21 @@ sel_direct_kernel(Src src, int64_t C, int B, int K, int M, SelPad pad, int32_t *
                        (int)gridDim.x, (int)blockIdx.x);
 }
 
+static bool sel_overlaps(const int32_t *a, int64_t na, const int32_t *b, int64_t nb) {
+    return (uintptr_t)a < (uintptr_t)(b + nb) && (uintptr_t)b < (uintptr_t)(a + na);
+}
 template <class Src>
 static int sel_launch(const Src &src, int64_t C, int B, int K, int M, SelPad pad, int32_t *active_idx, int32_t *n_active,
                       int32_t *n_found, int32_t *target_pos, void *ws, int32_t *dev_status, hipStream_t st) {
     const int64_t n_cand = (int64_t)B * (K + 1);
     if ((uintptr_t)ws & 15) return KS_INVALID_ARG; // the staging array is read in 16-byte pieces
+    // Outputs may lie where the labels are (target positions in place of them).  The workgroups of the direct form read all labels
+    // and write their share of the outputs in one launch, so one that starts late would read what another has written; staged,
+    // the labels are read in a launch of their own.
+    const bool in_place = sel_overlaps(src.labels, B, active_idx, M) || sel_overlaps(src.labels, B, target_pos, B) ||
+                          sel_overlaps(src.labels, B, n_active, 1) || (n_found && sel_overlaps(src.labels, B, n_found, 1));
     // (beyond SEL1_WS_CLASSES the workspace is sized for the score table; nearly always the staged candidates fit in there too)
-    if (sel1_fits(C, B) && n_cand <= SEL1_DIRECT && B <= SEL1_DIRECT_B) {
+    if (sel1_fits(C, B) && n_cand <= SEL1_DIRECT && B <= SEL1_DIRECT_B && !in_place) {
         const int E = (int)ks_ceil_div(n_cand, SEL1_NT), G = 16;
 #define SEL_DIRECT_LAUNCH(E)                                                                                               \
     hipLaunchKernelGGL((sel_direct_kernel<Src, E>), dim3(G), dim3(SEL1_NT), 0, st, src, C, B, K, M, pad, active_idx,         \

@@ -70,3 +70,32 @@ def test_batches_larger_than_the_list_in_lds(ks, orc):
     for C, B, K, M in [(900, 50_000, 3, 50_000), (60_000, 42_000, 2, 42_000), (60_000, 42_000, 2, 55_000)]:
         y = synth.labels_uniform(5, B, C)
         check(ks, orc, y, synth.graph_synthetic(5, C, K, locality=8, empty_frac=0.0), C, M)
+
+
+@pytest.mark.parametrize("C,B,K,M", [(3000, 64, 31, 2048), (70_000, 512, 15, 600), (70_000, 300, 0, 300)])
+@pytest.mark.parametrize("where", ["target_pos", "active_idx"])
+def test_outputs_in_place_of_the_labels(ks, orc, where, C, B, K, M):
+    """Positions or list written over the labels, beside work on another stream that makes some workgroups start late."""
+    import torch
+    G = synth.graph_synthetic(6, C, K, locality=4, empty_frac=0.05) if K else np.full((C, 0), -1, np.int32)
+    g = dev(G) if K else None
+    W = torch.nn.functional.normalize(torch.randn(40_000, 128, device="cuda"), dim=1).bfloat16()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for seed in range(4):
+        y = synth.labels_uniform(20 + seed, B, C)
+        print(f"[select in place] {where} C={C} B={B} K={K} seed={seed}", flush=True)
+        ea, eA, et = orc.select_active(y, G, C, M)
+        shared = torch.full((max(B, M),), -7, dtype=torch.int32, device="cuda")
+        labels = shared[:B]
+        labels.copy_(dev(y))
+        a = shared[:M] if where == "active_idx" else torch.empty(M, dtype=torch.int32, device="cuda")
+        t = labels if where == "target_pos" else torch.empty(B, dtype=torch.int32, device="cuda")
+        n = torch.empty(1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            ks.knn_graph_build(W, 8)
+        _, _, _, st = ks.knn_select_active_static(labels, g, C, M, out=(a, n, t))
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0 and int(n.item()) == eA
+        assert np.array_equal(a.cpu().numpy(), ea) and np.array_equal(t.cpu().numpy(), et)
