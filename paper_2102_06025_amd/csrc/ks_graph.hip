@@ -543,8 +543,8 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 // A first sweep (gr_threshold_kernel) finds for every row its r-th largest similarity to a sample of one in 32 of the
 // searched rows; r = 8 for K <= 16, 10 for K <= 32, 12 for K <= 64.  The number of searched rows at or above it is
 // 32 * Gamma(r) whatever their distribution (an order statistic of a uniform sample): 256, 320 or 384 on average.  The
-// largest K of each r is the worst case: beyond 1,100 (a row's segments take 2,048, a lane's share of them 512) for 0.02, 0.3
-// and 3.4 rows in a million; at most K (then r of the row's K + 1 best would have to be in the sample) for 0.1 to 1.4 in a
+// largest K of each r is the worst case: beyond 1,152, 1,280 and 1,408 (what a row's segments take, see GrSegs) for less than
+// five rows in a billion; at most K (then r of the row's K + 1 best would have to be in the sample) for 0.1 to 1.4 in a
 // million, and for 1.0, 1.1 and 8.3 in a million of the rows that are in their own sample.
 // The candidate segments are sized for those counts and nothing is cut back during the sweep, so that
 //   * a row's candidates may come from several workgroups: gr_recall_fix_kernel cuts the searched rows into `parts`, one
@@ -552,7 +552,7 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 //   * a similarity may serve both of its rows: gr_recall_sym_kernel.
 // A row that does end up with too many or too few candidates is caught by the certificate like any other uncertain row.
 // ------------------------------------------------------------------------------------------------
-#define GR_SYM_Q 512             /* slots of a candidate segment (one lane's hits) */
+#define GR_SYM_Q 512             /* symmetric sweep: slots of a candidate segment (one lane's hits) */
 #define GR_SYM_SCAP 1024         /* slots of the stream-side segment */
 #define GR_MAX_CAND 2048         /* candidates of a row that the ranking takes */
 #define GR_SYM_RANK 12           /* places of the sorted list that finds a row's threshold */
@@ -560,10 +560,40 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 #define GR_CUS 256               /* compute units that the parts are planned for */
 
 // A row's candidate segments: 2 * parts of q slots (the two lanes of a part that hold the row), then `stream` slots.
+// Symmetric sweep: a lane has its q slots.  Passes with parts (no stream segment): the two lanes of a part share 2 q slots and
+// fill them from both ends, so that however a row's hits fall on lanes and parts, all of them fit: a lane sees the streamed
+// rows whose id has bit 2 clear, or set, and neighbours with ids of one residue modulo 8 are all one lane's.  2 q = 64 (r + 10).
+// (With 512 slots for each lane, four rows in 100,000 of K > 32 overflowed even with hits that fall evenly, and a row in the
+// exhaustive search costs 4 to 30 ms: 60,000 x 128, K = 64: 5.6 ms instead of 2.0; a hop of 65,000 rows of 512 against
+// a million 194 ms instead of 57.)
 struct GrSegs {
     int parts, q, stream;
     __host__ __device__ int cap() const { return 2 * parts * q + stream; }
 };
+// What is in the segments of a row: lane s gets the count of segment s (0 beyond the last) and where it begins.  Returns
+// whether one has overflowed; the count is then of what it holds.  All lanes of a wavefront call.
+__device__ __forceinline__ bool gr_segments(const GrSegs &seg, const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str,
+                                            int64_t i, int &c, int &begin) {
+    const int lane = threadIdx.x & 63, nres = 2 * seg.parts;
+    int raw = 0, most = seg.q;
+    if (lane < nres) raw = cnt_res[i * nres + lane];
+    else if (lane == nres && seg.stream > 0) { raw = cnt_str[i]; most = seg.stream; }
+    begin = lane * seg.q;
+    if (seg.stream > 0) {
+        c = raw < most ? raw : most;
+    } else {
+        const int other = __shfl_xor(raw, 1, 64), room = 2 * seg.q;
+        if (lane & 1) { // from the end downwards, as far as the first lane's
+            most = room - (other < room ? other : room);
+            c = raw < most ? raw : most;
+            begin += seg.q - c;
+        } else {
+            most = room;
+            c = raw < most ? raw : most;
+        }
+    }
+    return __ballot(c != raw) != 0ull;
+}
 // stage shape of the sweeps for a depth of KT k-tiles: twelve k-tiles in flight, two per stage where KT is even (a barrier
 // per stage); a single k-tile per chunk (KT = 1): six, so that at most seven chunks are in flight
 template <int KT, bool RAGGED> using GrSoe = KsSoe<KT, 96, (KT % 2 == 0 || KT == 1) ? 6 : 12, KT % 2 == 0 ? 2 : 1, RAGGED>;
@@ -713,7 +743,7 @@ __device__ __forceinline__ uint32_t gr_hit_mask(float t, const f32x16_t &a) {
     return hm;
 }
 
-// Resident rows against one part of the searched rows.  Lane (row, half) appends to segment (part, half) of the row and
+// Resident rows against one part of the searched rows.  Lane (row, half) appends to the row's segment of the part and
 // counts in a register: an append is a store and an increment.  In the problems that come here one value in 30 to 1,000
 // passes, so that of 64 lanes x 16 values nearly always some do: the hits of a lane become a bit mask and are taken one by
 // one (testing value by value costs a branch around the append for each of them).
@@ -727,11 +757,13 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
     const int row0 = id % nb * CFG::RES;
     const int s0 = part * part_rows, s1 = (int64_t)s0 + part_rows < pr.Cs ? s0 + part_rows : (int)pr.Cs;
     const int Cr = (int)pr.Cr;
-    const int cap = seg.cap(), Q = seg.q;
+    const int cap = seg.cap(), last = 2 * seg.q - 1;
     const int64_t self0 = row0 + pr.self; // streamed rows [self0, self0 + RES) are this workgroup's own rows
     const float thf = row0 + ks_soe_col() < Cr ? thf_row[row0 + ks_soe_col()] : INFINITY;
     uint64_t *const wg_cand = cand + (int64_t)row0 * cap;
-    const uint32_t my_base = (uint32_t)(ks_soe_col() * cap + (2 * part + ((threadIdx.x & 63) >> 5)) * Q);
+    // the lanes 0..31 fill their row's slots from the first one upwards, the lanes 32..63 from the last one downwards
+    const int down = (threadIdx.x & 32) ? -1 : 0;
+    const uint32_t my_base = (uint32_t)(ks_soe_col() * cap + 2 * part * seg.q + (down ? last + 1 : 0));
     int my_cnt = 0;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
         const int lane = threadIdx.x & 63;
@@ -746,8 +778,8 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
                     const float v = gr_sym_pick16(acc[fm], r);
                     const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), j = c0 + lr;
                     if (!special || (lr < rows_here && (int64_t)j != (int64_t)row0 + ks_soe_col() + pr.self)) {
-                        // (the mask keeps the store inside the segment; a count beyond Q marks the row as overflowed)
-                        wg_cand[my_base + ((uint32_t)my_cnt & (uint32_t)(Q - 1))] =
+                        // (the minimum keeps the store inside the slots; counts that add up to more mark the row as overflowed)
+                        wg_cand[my_base + (uint32_t)((my_cnt < last ? my_cnt : last) ^ down)] =
                             ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
                         ++my_cnt;
                     }
@@ -1170,13 +1202,10 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
     const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + wave;
     if (i >= C) return;
     // the row's segments: lane s looks at segment s
-    const int nres = 2 * seg.parts, nseg = nres + (seg.stream > 0 ? 1 : 0);
-    int c = 0, c_max = seg.q;
-    if (lane < nres) c = cnt_res[i * nres + lane];
-    else if (lane < nseg) { c = cnt_str[i]; c_max = seg.stream; }
-    bool overflow = __ballot(c > c_max) != 0ull;
-    if (c > c_max) c = c_max;
-    const int incl = ks_wave_iscan(c), excl = incl - c;
+    const int nseg = 2 * seg.parts + (seg.stream > 0 ? 1 : 0);
+    int c, begin;
+    bool overflow = gr_segments(seg, cnt_res, cnt_str, i, c, begin);
+    const int incl = ks_wave_iscan(c), excl = incl - c, shift = begin - excl;
     int n = __builtin_amdgcn_readlane(incl, 63);
     if (n > GR_MAX_CAND) { n = GR_MAX_CAND; overflow = true; }
     const uint32_t tb = tbits[i];
@@ -1195,10 +1224,11 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
             val[r] = 0ull; // below every real key
             if (r * 64 < n) {
                 const int idx = r * 64 + lane;
-                int adj = 0;
+                int adj = 0; // (the first segment begins at 0)
                 for (int sg = 1; sg < nseg; ++sg) {
                     const int st = __builtin_amdgcn_readlane(excl, sg);
-                    if (idx >= st) adj = sg * seg.q - st;
+                    const int sh = __builtin_amdgcn_readlane(shift, sg);
+                    if (idx >= st) adj = sh;
                 }
                 if (idx < n) val[r] = row[idx + adj];
             }
@@ -1487,24 +1517,25 @@ gr_second_kernel(const IN *__restrict__ W, int64_t C, int D, int K, GrSegs seg, 
     __shared__ double s_s[GR_NT / 64][GR_MAX_CAND];
     __shared__ int32_t s_id[GR_NT / 64][GR_MAX_CAND];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nres = 2 * seg.parts, nseg = nres + (seg.stream > 0 ? 1 : 0);
+    const int nseg = 2 * seg.parts + (seg.stream > 0 ? 1 : 0);
     int64_t n_list = *list_count;
     if (n_list > C) n_list = C;
     for (int64_t e0 = (int64_t)blockIdx.x * (GR_NT / 64); e0 < n_list; e0 += (int64_t)gridDim.x * (GR_NT / 64)) {
         const int64_t e = e0 + wave;
         const int64_t i = e < n_list ? list_rows[e] : -1;
-        bool usable = i >= 0; // (an overflowed segment does not hold everything above the threshold)
-        int n = 0, n_valid = 0;
+        int c_seg = 0, begin_seg = 0, n = 0, n_valid = 0;
+        // (an overflowed segment does not hold everything above the threshold)
+        bool usable = i >= 0 && !gr_segments(seg, cnt_res, cnt_str, i, c_seg, begin_seg);
         for (int sg = 0; sg < nseg && usable; ++sg) {
-            const int c = sg < nres ? cnt_res[i * nres + sg] : cnt_str[i];
-            if (c > (sg < nres ? seg.q : seg.stream) || n + c > GR_MAX_CAND) {
+            const int c = __builtin_amdgcn_readlane(c_seg, sg), begin = __builtin_amdgcn_readlane(begin_seg, sg);
+            if (n + c > GR_MAX_CAND) {
                 usable = false;
                 break;
             }
             for (int q = lane; q < c; q += 64) {
                 double sv = -INFINITY;
                 int32_t id = GR_NO_ID;
-                const uint32_t j = 0xFFFFFFFFu - (uint32_t)cand[i * seg.cap() + sg * seg.q + q];
+                const uint32_t j = 0xFFFFFFFFu - (uint32_t)cand[i * seg.cap() + begin + q];
                 if (j < (uint32_t)C && (int64_t)j != i) { // always true for keys written by the recall pass
                     id = (int32_t)j;
                     sv = gr_canon(W + i * D, W + (int64_t)j * D, D);
@@ -1568,7 +1599,7 @@ static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && 
 // 0.5 and 0.4 us more per k-tile: measured on the sweeps).  Bounded by memory: a part costs every row two segments.
 static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
     const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 1.2 + 0.4 * kt;
-    int64_t most = ((int64_t)1 << 19) / C; // 4 GiB of segments
+    int64_t most = ((int64_t)1 << 19) / C; // 4.5 to 5.5 GiB of segments
     if (most > GR_MAX_PARTS) most = GR_MAX_PARTS;
     if (most > chunks) most = chunks;
     int best = 1;
@@ -1591,11 +1622,11 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, bool sym) {
     GrFixPlan f;
     const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(Cs, 96);
     f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
-    f.seg.q = GR_SYM_Q;
+    f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K) + 10);
     f.seg.stream = sym ? GR_SYM_SCAP : 0;
     f.part_rows = (int)ks_ceil_div(chunks, f.seg.parts) * 96;
     if (!sym) f.seg.parts = (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
-    while (!sym && f.seg.q > 64 && f.seg.q / 2 >= f.part_rows / 2) f.seg.q /= 2; // a lane sees half of the part's rows
+    if (!sym && f.seg.q > f.part_rows / 2) f.seg.q = f.part_rows / 2;
     f.log_rows = GR_SYM_SB;
     f.logs = 0;
     if (sym) {

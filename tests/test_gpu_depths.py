@@ -252,11 +252,74 @@ def test_neighbours_that_crowd_in_a_run_of_ids(ks, orc, K, rank):
     ws = torch.zeros(ks.knn_graph_build_workspace(C, D, K, 0), dtype=torch.uint8, device="cuda")
     g, sims = ks.knn_graph_build(dev(W, True), K, want_sims=True, ws=ws)
     torch.cuda.synchronize()
-    # the workspace begins with the row norms, 1,024 maxima, the maximum, the number of rows searched exhaustively
-    pad = lambda n: (n + 255) // 256 * 256
-    at = pad(4 * C) + 4096
-    assert abs(float(ws[at:at + 4].view(torch.float32)) - np.sqrt((W.astype(np.float64) ** 2).sum(1)).max()) < 1e-3
-    assert int(ws[at + 256:at + 260].view(torch.int32)) == 0
+    assert _exhaustive_rows(ws, C, np.sqrt((W.astype(np.float64) ** 2).sum(1)).max(), 1) == 0
     rows = np.unique(np.concatenate([synth.class_permutation(41, C)[:100], order[:5], [0, hubs - 1, hubs, C - 1]])).astype(np.int32)
     eg, es = orc.graph_bruteforce(W, K, rows)
     assert (g.cpu().numpy()[rows] == eg).all() and (sims.cpu().numpy()[rows] == es.astype(np.float32)).all()
+
+
+def _exhaustive_rows(ws, norms, largest, maxima):
+    """The rows that went to the exhaustive search.  The workspace begins with the row norms, 1,024 maxima of each matrix, the
+    largest norm, their number."""
+    import torch
+    at = (4 * norms + 255) // 256 * 256 + maxima * 4096
+    assert abs(float(ws[at:at + 4].view(torch.float32)) - largest) < 1e-3
+    return int(ws[at + 256:at + 260].view(torch.int32))
+
+
+@pytest.mark.parametrize("K,rank,above", [(16, 8, 1100), (32, 10, 1200), (64, 12, 1350)])
+@pytest.mark.parametrize("residues", [(0, 1, 2, 3), (5,), range(8)])
+def test_neighbours_of_one_residue_modulo_8(ks, orc, residues, K, rank, above):
+    """The pass of all rows by all blocks: the two lanes that hold a row see the searched rows with bit 2 of their id clear, or
+    set.  All rows share their neighbours, which are all one lane's, or fall to both (one residue, half, any), and the sample is an
+    unlucky one (`above` rows above its rank-th largest).  No row may be left for the exhaustive search, in the build (one
+    part) or in a hop (several, the neighbours in one of them)."""
+    import torch
+    C, D = 60_000, 128
+    print(f"[depths] residues {list(residues)} K={K}", flush=True)
+    ids = np.arange(C)
+    hubs = ids[np.isin(ids % 8, list(residues))][:2304]
+    s = np.arange(C // 32, dtype=np.int64)
+    sampled = s * 32 + (((s * 2654435761) & 0xFFFFFFFF) >> 16) % 32
+    rng = np.random.default_rng(K)
+    in_hub, free = rng.permutation(np.intersect1d(hubs, sampled)), rng.permutation(np.setdiff1d(hubs, sampled))
+    n_free = above - rank + 1
+    assert in_hub.size >= rank and free.size >= n_free
+    order = np.concatenate([rng.permutation(np.concatenate([in_hub[:rank - 1], free[:n_free]])), in_hub[rank - 1:rank],
+                            rng.permutation(np.concatenate([in_hub[rank:], free[n_free:]]))])
+    norm = np.ones(C)
+    norm[order] = np.linspace(12.0, 8.0, order.size)
+    u = synth.unit_rows(43, synth.TID_X, 1, D).astype(np.float64)
+    W = synth.bf16_round((norm[:, None] * (u + 0.05 * synth.unit_rows(43, synth.TID_W, C, D))).astype(np.float32))
+    largest = np.sqrt((W.astype(np.float64) ** 2).sum(1)).max()
+    Wd = dev(W, True)
+    ws = torch.zeros(ks.knn_graph_build_workspace(C, D, K, 0), dtype=torch.uint8, device="cuda")
+    assert ws.numel() < 13_000 * C                                # (one part)
+    g, sims = ks.knn_graph_build(Wd, K, want_sims=True, ws=ws)
+    torch.cuda.synchronize()
+    assert _exhaustive_rows(ws, C, largest, 1) == 0
+    rows = np.unique(np.concatenate([synth.class_permutation(43, C)[:60], order[:5], [0, C - 1]])).astype(np.int32)
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (sims.cpu().numpy()[rows] == es.astype(np.float32)).all()
+    n = 2000
+    lists = torch.full((n, K), -1, dtype=torch.int32, device="cuda")
+    best = torch.full((n, K), -np.inf, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(ks.knn_graph_update_workspace(n, C, D, K, 0), dtype=torch.uint8, device="cuda")
+    ks.knn_graph_update(Wd[C - n:].contiguous(), Wd, C - n, 0, lists, best, ws=ws)
+    torch.cuda.synchronize()
+    assert _exhaustive_rows(ws, n, largest, 2) == 0
+    assert torch.equal(lists, g[C - n:])
+
+
+def test_candidate_counts_of_many_rows_fit(ks):
+    """Rows of any direction, more than 32 neighbours: the number of candidates is spread widely (a row in 25,000 has 1,024 or
+    more), and none may overflow what a row has room for."""
+    import torch
+    C, D, K = 65_000, 64, 40
+    print("[depths] candidate counts", flush=True)
+    W = synth.unit_rows(44, synth.TID_W, C, D, bf16=True)
+    ws = torch.zeros(ks.knn_graph_build_workspace(C, D, K, 0), dtype=torch.uint8, device="cuda")
+    assert ws.numel() < 13_000 * C                                # (one part)
+    ks.knn_graph_build(dev(W, True), K, ws=ws)
+    torch.cuda.synchronize()
+    assert _exhaustive_rows(ws, C, np.sqrt((W.astype(np.float64) ** 2).sum(1)).max(), 1) == 0

@@ -472,9 +472,10 @@ def test_graph_recall_with_fixed_thresholds(ks, orc, C, D, K, bf16, kind):
 
 
 def _takes_the_symmetric_sweep(ks, C, D, K, bf16):
-    """For C * D from 15 million on: its workspace is 25 or 33 KB a row (two or four segments of 512 slots, the stream side's of
-    1,024, a log of 1,024 records); the pass of all rows by all blocks would take 9 KB, or 90 and more."""
-    return 24_000 < ks.knn_graph_build_workspace(C, D, K, 0 if bf16 else 1) / C < 36_000
+    """For C * D from 15 million on: its segments are the same for every K, those of the pass of all rows by all blocks grow
+    with the rank of the sample."""
+    of_k = [ks.knn_graph_build_workspace(C, D, k, 0 if bf16 else 1) for k in (K, 8, 20, 64)]
+    return K <= 64 and min(of_k) == max(of_k) > 24_000 * C
 
 
 @pytest.mark.parametrize("C,D,K,bf16,kind", [(29_297, 512, 32, True, "unit"), (29_584, 512, 64, True, "integers"),
