@@ -15,7 +15,8 @@ int ks_select_launch(const int32_t *labels, const int32_t *graph, int64_t C, int
 #define SEL1_GRID 32
 #define SEL1_FIRST_WORDS 257 /* one bit per sample of batches up to 8,192 (+ one word so that a clear loop may run over) */
 #define SEL1_LDS_WORDS 40600 /* LDS of the single-workgroup selection (162,400 of 163,840 bytes) */
-#define SEL1_FIXED_WORDS 540 /* first-of-its-label bits (257), digit counts (256), block scan (1024 / 64 + 1), three scalars, to a multiple of 4 */
+#define SEL1_FIXED_WORDS 540 /* first-of-its-label bits (257), digit counts (256), block scan (1024 / 64 + 1), five scalars, to a multiple of 4 */
+#define SEL1_WALK 8          /* list positions that the search of the cut takes one by one (see sel1_body) */
 // The selection by one workgroup needs LDS for a bit per class, the running count at every 32nd word of them, and (when the
 // cut bites) the classes first seen at the cut position, at most one per sample and per class.
 __host__ __device__ __forceinline__ bool sel1_fits(int64_t C, int B) {
@@ -136,12 +137,11 @@ __device__ __forceinline__ int sel1_count(const uint32_t *bm, int nq, int *coars
     __syncthreads();
     return carry;
 }
-// Number of set bits alone; leaves the bitmap cleared.
-template <int NT> __device__ __forceinline__ int sel1_count_clear(uint32_t *bm, int nq, int *sh) {
+// Number of set bits alone.
+template <int NT> __device__ __forceinline__ int sel1_total(const uint32_t *bm, int nq, int *sh) {
     int n = 0;
     for (int p = threadIdx.x; p < nq * 8; p += NT) {
         const uint4 v = *(const uint4 *)(bm + p * 4);
-        *(uint4 *)(bm + p * 4) = make_uint4(0u, 0u, 0u, 0u);
         n += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
     }
     int total;
@@ -149,8 +149,13 @@ template <int NT> __device__ __forceinline__ int sel1_count_clear(uint32_t *bm, 
     return total;
 }
 
-// Candidates of a batch as the selection reads them.  mark(n, first, f): f(class) for every candidate at a list position
-// below n; at(r, f): for those at position r; label(i): the sample's own class, or -1.
+template <int NT> __device__ __forceinline__ void sel1_clear(uint32_t *bm, int nq) {
+    for (int p = threadIdx.x; p < nq * 8; p += NT) *(uint4 *)(bm + p * 4) = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+}
+
+// Candidates of a batch as the selection reads them.  mark(r, n, f): f(class) for every candidate at a list position
+// in [r, n), possibly for some below r too; at(r, f): for those at position r; label(i): the sample's own class, or -1.
 //
 // Staged: the candidates lie in memory, list-position-major (cand[r * B + i]), written by an earlier launch: the scattered
 // reads of many lists are spread over the chip.
@@ -160,7 +165,7 @@ template <int NT> struct Sel1Staged {
     const uint32_t *first; // bit i: sample i is the first of its label (nullptr: not known, all are taken)
     template <class F> __device__ __forceinline__ void range(int64_t begin, int64_t end, F f) const {
         const int tid = threadIdx.x;
-        const int64_t n_vec = end >> 2; // (begin is 0 or a multiple of 4; the array is 256-byte aligned: whole pieces, then a tail)
+        const int64_t n_vec = end >> 2; // (from begin / 4 on; the array is 256-byte aligned: whole pieces, then a tail)
         for (int64_t t0 = begin >> 2; t0 < n_vec; t0 += (int64_t)NT * 8) {
             int4 c[8];
 #pragma unroll
@@ -186,11 +191,18 @@ template <int NT> struct Sel1Staged {
             if (c >= 0) f(c);
         }
     }
-    template <class F> __device__ __forceinline__ void mark(int n, F f) const { range(0, (int64_t)n * B, f); }
+    template <class F> __device__ __forceinline__ void mark(int r, int n, F f) const { range((int64_t)r * B, (int64_t)n * B, f); }
     template <class F> __device__ __forceinline__ void at(int r, F f) const {
-        for (int i = threadIdx.x; i < B; i += NT) {
-            const int32_t c = cand[(int64_t)r * B + i];
-            if (c >= 0) f(c);
+        for (int i0 = 0; i0 < B; i0 += NT * 4) {
+            int32_t c[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = i0 + e * NT + (int)threadIdx.x;
+                c[e] = i < B ? cand[(int64_t)r * B + i] : -1;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (c[e] >= 0) f(c[e]);
         }
     }
     __device__ __forceinline__ int32_t label(int i) const { return cand[i]; }
@@ -210,7 +222,7 @@ template <int NT, int E, class Src> struct Sel1Direct {
             c[e] = i < B ? src.cand(i, r[e], report ? dev_status : nullptr) : -1;
         }
     }
-    template <class F> __device__ __forceinline__ void mark(int n, F f) const {
+    template <class F> __device__ __forceinline__ void mark(int, int n, F f) const {
 #pragma unroll
         for (int e = 0; e < E; ++e)
             if (c[e] >= 0 && r[e] < n) f(c[e]);
@@ -236,13 +248,12 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, Cands &cands, int64_t C
     const int tid = threadIdx.x;
     uint32_t *s_first = lds;
     int *hist = (int *)(s_first + SEL1_FIRST_WORDS), *sh = hist + 256; // sh: the block scan, then scalars
-    int &s_new = sh[1024 / 64 + 1], &s_bin = sh[1024 / 64 + 2], &s_rem = sh[1024 / 64 + 3];
+    int *const s_new = sh + 1024 / 64 + 1, &s_bin = s_new[3], &s_rem = s_new[4];
     uint32_t *bm = lds + SEL1_FIXED_WORDS;
     int *coarse = (int *)(bm + nq * 32), *list = coarse + nq;
     auto bit_of = [&](int32_t c) { return 1u << (c & 31); };
     auto set = [&](int32_t c) { atomicOr(&bm[c >> 5], bit_of(c)); };
-    for (int p = tid; p < nq * 8; p += NT) *(uint4 *)(bm + p * 4) = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
+    sel1_clear<NT>(bm, nq);
     // Optimistic pass: every candidate, whatever its list position.  Samples with the same label have the same list, and
     // with skewed labels half of the batch are repeats: in the staged form only the first sample of a label (whichever
     // thread marks the label first) has its list marked.  For batch sizes that are a power of two, so that a 16-byte piece
@@ -263,49 +274,89 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, Cands &cands, int64_t C
         }
         cands.range(dedup ? B : 0, (int64_t)B * (K + 1), set); // (deduplicated: the labels are done)
     } else {
-        cands.mark(K + 1, set);
+        cands.mark(0, K + 1, set);
     }
     __syncthreads();
     int total = sel1_count<NT>(bm, nq, coarse, sh);
     if (total > M) {
-        // The cut bites.  r* = the first list position up to which more than M classes are seen, by a search between
-        // positions known to see at most M (lo) and more (hi): an interpolated guess and a halving in turn; each step
-        // marks the candidates up to the guess in the cleared bitmap and counts.  (Position by position, with three
-        // barriers and a read of the staged candidates each, 100,000 classes with 17 positions took 25 us, now 13 in all.)
-        int lo = -1, hi = K, n_lo = 0, n_hi = total;
-        sel1_count_clear<NT>(bm, nq, sh);
-        for (int step = 0; hi - lo > 1; ++step) {
-            int mid = (lo + hi) >> 1;
-            if (!(step & 1)) mid = lo + 1 + (int)((int64_t)(M - n_lo) * (hi - lo - 1) / (n_hi - n_lo));
-            mid = mid < lo + 1 ? lo + 1 : (mid > hi - 1 ? hi - 1 : mid);
-            cands.mark(mid + 1, set);
-            __syncthreads();
-            const int n = sel1_count_clear<NT>(bm, nq, sh);
-            if (n > M) { hi = mid; n_hi = n; }
-            else { lo = mid; n_lo = n; }
-        }
-        cands.mark(lo + 1, set); // (lo >= 0: the labels alone are at most B <= M classes)
-        if (tid == 0) s_new = 0;
-        __syncthreads();
-        // the classes first seen at r*: into the bitmap and into a list; the M - n_lo lowest ids of them stay
-        cands.at(hi, [&](int32_t c) {
-            if (!(atomicOr(&bm[c >> 5], bit_of(c)) & bit_of(c))) {
-                const int slot = atomicAdd(&s_new, 1);
-                if (slot < n_list) list[slot] = c; // always true: a class once, and at most one per sample
+        // The cut bites.  r* = the first list position up to which more than M classes are seen, between positions known to see
+        // at most M (lo) and more (hi).  Two kinds of step, on a bitmap that holds what is seen up to `built`:
+        //   probe  mark the candidates of the positions up to another one and count the bits: first, while that is far, the
+        //          last position up to which all candidates together cannot bring more than M classes, then an interpolated
+        //          guess and a halving in turn.  Costs a pass over those candidates and one over the bitmap; where there
+        //          are more than M the bitmap is cleared and built anew up to lo.
+        //   walk   position by position from lo on; the classes that are new go into a list.  Costs a read of B candidates
+        //          and a barrier, and where it ends at r*, bitmap and list are what the rest needs.
+        // Walks are taken where the guess (too high where counts flatten out, as they do) lies within SEL1_WALK positions.
+        // 20,000 classes, 1,024 lists of 32, M = 4,096 (r* = 4): position by position 22 us in all, with halvings and guesses on a
+        // cleared bitmap 27, so 22.  1,100,000 classes, 2,048 lists of 64, r* in their middle: 64 us -> 40 (26 without a cut).
+        int lo = -1, hi = K, n_lo = 0, n_hi = total, built = -1;
+        int ctr = 0; // of three counters of the list, this position's: it is cleared while the one before is in use
+        bool walked = false;
+        sel1_clear<NT>(bm, nq);
+        for (int step = 0;; ++step) {
+            int mid = lo + 1 + (int)((int64_t)(M - n_lo) * (hi - lo - 1) / (n_hi - n_lo));
+            if (hi - lo > SEL1_WALK && (walked || mid - lo > SEL1_WALK)) {
+                const int sure = lo + (M - n_lo) / B; // (below hi: that many positions bring no more than M classes)
+                if (step < 3 && sure - lo > 2) mid = sure;
+                else if (walked || (step & 1)) mid = (lo + hi) >> 1;
+                if (mid > hi - 1) mid = hi - 1;
+                walked = false;
+                cands.mark(built + 1, mid + 1, set);
+                __syncthreads();
+                const int n = sel1_total<NT>(bm, nq, sh);
+                if (n > M) {
+                    hi = mid;
+                    n_hi = n;
+                    built = -1;
+                    sel1_clear<NT>(bm, nq);
+                } else {
+                    lo = built = mid;
+                    n_lo = n;
+                }
+                continue;
             }
-        });
-        __syncthreads();
-        const int n_new = s_new < n_list ? s_new : n_list;
+            if (built != lo) cands.mark(built + 1, lo + 1, set);
+            walked = true;
+            if (tid == 0) s_new[ctr] = 0;
+            __syncthreads();
+            const int end = hi - lo > SEL1_WALK ? lo + SEL1_WALK : hi;
+            int r = lo + 1;
+            for (;; ++r) {
+                cands.at(r, [&](int32_t c) {
+                    if (!(atomicOr(&bm[c >> 5], bit_of(c)) & bit_of(c))) {
+                        const uint64_t act = __ballot(1);
+                        const int before = __popcll(act & ((1ull << (tid & 63)) - 1ull));
+                        int slot = 0;
+                        if (before == 0) slot = atomicAdd(&s_new[ctr], __popcll(act));
+                        slot = __builtin_amdgcn_readfirstlane(slot) + before;
+                        if (slot < n_list) list[slot] = c; // always true: a class once, and at most one per sample
+                    }
+                });
+                const int next = ctr == 2 ? 0 : ctr + 1;
+                if (tid == 0) s_new[next] = 0; // (read last two positions ago)
+                __syncthreads();
+                const int n = n_lo + s_new[ctr];
+                if (n > M) { hi = r; break; }
+                n_lo = n;
+                lo = built = r;
+                ctr = next;
+                if (r == end) break;
+            }
+            if (hi == lo + 1 && r == hi) break; // ended at r* = hi
+        }
+        // the classes first seen at r* are in the bitmap and in the list; the M - n_lo lowest ids of them stay
+        const int n_new = s_new[ctr] < n_list ? s_new[ctr] : n_list;
         int rem = M - n_lo;       // the rem-th smallest of the list is the last to stay
         uint32_t top = 0u;        // its leading digits so far
-        int shift = 24;
-        while (shift > 0 && ((uint64_t)(C - 1) >> shift) == 0) shift -= 8;
-        for (int first_shift = shift; rem > 0 && shift >= 0; shift -= 8) {
+        int bits = 32 - __builtin_clz((uint32_t)(C > 1 ? C - 1 : 1)); // not yet looked at, eight at a time from the top
+        while (rem > 0 && bits > 0) {
+            const int shift = bits > 8 ? bits - 8 : 0;
             for (int q = tid; q < 256; q += NT) hist[q] = 0;
             __syncthreads();
             for (int q = tid; q < n_new; q += NT) {
                 const uint32_t c = (uint32_t)list[q];
-                if (shift == first_shift || (c >> (shift + 8)) == (top >> (shift + 8))) atomicAdd(&hist[(c >> shift) & 255u], 1);
+                if (c >> bits == top >> bits) atomicAdd(&hist[(c >> shift) & ((1u << (bits - shift)) - 1u)], 1);
             }
             __syncthreads();
             if (tid < 64) { // one wavefront: four digits a lane
@@ -322,6 +373,7 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, Cands &cands, int64_t C
             __syncthreads();
             top |= (uint32_t)s_bin << shift;
             rem = s_rem;
+            bits = shift;
             __syncthreads();
         }
         const bool none = M == n_lo; // nothing of r* stays
@@ -368,7 +420,8 @@ __device__ __forceinline__ void sel1_body(uint32_t *lds, Cands &cands, int64_t C
     // spares a grid-wide synchronisation); each writes its share of the outputs.
     { // read the bitmap out in ascending order: a wavefront takes 64 words, a lane one of them
         const int lane = tid & 63, ngrp = (nq + 1) >> 1;
-        for (int q = g * (NT / 64) + (tid >> 6); q < ngrp; q += G * (NT / 64)) {
+        // (neighbouring groups on different workgroups: 100,000 classes, all active, are 49 groups)
+        for (int q = (tid >> 6) * G + g; q < ngrp; q += G * (NT / 64)) {
             const int w = q * 64 + lane;
             const bool in = w < nq * 32;
             uint32_t e = in ? bm[w] : 0u;

@@ -333,7 +333,6 @@ static int sel_launch(const Src &src, int64_t C, int B, int K, int M, SelPad pad
     // the labels are read in a launch of their own.
     const bool in_place = sel_overlaps(src.labels, B, active_idx, M) || sel_overlaps(src.labels, B, target_pos, B) ||
                           sel_overlaps(src.labels, B, n_active, 1) || (n_found && sel_overlaps(src.labels, B, n_found, 1));
-    // (beyond SEL1_WS_CLASSES the workspace is sized for the score table; nearly always the staged candidates fit in there too)
     if (sel1_fits(C, B) && n_cand <= SEL1_DIRECT && B <= SEL1_DIRECT_B && !in_place) {
         const int E = (int)ks_ceil_div(n_cand, SEL1_NT), G = 16;
 #define SEL_DIRECT_LAUNCH(E)                                                                                               \
@@ -347,7 +346,13 @@ static int sel_launch(const Src &src, int64_t C, int B, int K, int M, SelPad pad
         KS_LAUNCH_CHECK();
         return KS_OK;
     }
-    if (sel1_fits(C, B) && ks_select_ws_bytes(C, B, K) >= (size_t)n_cand * sizeof(int32_t)) {
+    // Beyond SEL1_WS_CLASSES the score table is taken for large batches and many candidates: every workgroup here reads all of them,
+    // again where the cut bites, and the table's launches spread them over the chip.  (The workspace is sized for the table there;
+    // the staged candidates fit in it all the same.)  400,000 to 1,100,000 classes, table -> bitmap with a cut and without: 3,000 lists
+    // of 32 36-44 -> 32-39 and 21-24 us; 4,096 lists of 32 36-45 -> 38-56 and 26-28; 8,192 lists of 4 36 -> 36-45 and 24.
+    // With M at seven eighths of the candidates or more there is nearly never a cut (lists overlap and labels repeat).
+    const bool bitmap = sel1_fits(C, B) && (C <= SEL1_WS_CLASSES || (B <= 4096 && (n_cand <= 100000 || (n_cand <= 200000 && 8 * (int64_t)M >= 7 * n_cand))));
+    if (bitmap && ks_select_ws_bytes(C, B, K) >= (size_t)n_cand * sizeof(int32_t)) {
         int32_t *cand = (int32_t *)ws;
         hipLaunchKernelGGL(sel_fetch_kernel<Src>, dim3((unsigned)ks_ceil_div(n_cand, SEL_NT)), dim3(SEL_NT), 0, st, src, B, K,
                            cand, dev_status);

@@ -99,3 +99,30 @@ def test_outputs_in_place_of_the_labels(ks, orc, where, C, B, K, M):
         torch.cuda.synchronize()
         assert int(st.item()) == 0 and int(n.item()) == eA
         assert np.array_equal(a.cpu().numpy(), ea) and np.array_equal(t.cpu().numpy(), et)
+
+
+@pytest.mark.parametrize("C,B,K", [(30_000, 60, 100), (30_000, 301, 100), (60_000, 512, 127), (500_000, 700, 100)])
+@pytest.mark.parametrize("shape", ["late", "early", "steps", "empty"])
+def test_counts_that_do_not_grow_evenly(ks, orc, shape, C, B, K):
+    """The search of the cut guesses from how many classes the positions bring: all of them at the last ones, at the first ones,
+    in runs between runs that bring none (the same classes in every list, or empty entries)."""
+    rng = np.random.default_rng(K + B)
+    G = rng.integers(0, C, (C, K)).astype(np.int32)
+    same = np.broadcast_to(np.arange(K, dtype=np.int32), (C, K))
+    quiet = {"late": np.arange(K) < K - 12, "early": np.arange(K) >= 12, "steps": (np.arange(K) // 11) % 2 == 0,
+             "empty": (np.arange(K) // 9) % 3 != 2}[shape]
+    G[:, quiet] = -1 if shape == "empty" else same[:, quiet]
+    y = synth.labels_uniform(8, B, C)
+    lists = np.concatenate([y[:, None], G[y]], axis=1)
+    seen = [len(np.unique(lists[:, :r + 1][lists[:, :r + 1] >= 0])) for r in range(K + 1)]
+    floor = max(B, K + 1)
+    for M in sorted({max(floor, m) for s in (seen[5], seen[K // 2], seen[K - 6], seen[K - 1], seen[K]) for m in (s - 1, s, s + 3)} | {floor}):
+        check(ks, orc, y, G, C, M)
+
+
+@pytest.mark.parametrize("B,K,M", [(1000, 99, 60_000), (1001, 99, 60_000), (2000, 99, 174_999), (2000, 99, 175_000), (2000, 99, 120_000),
+                                   (4096, 23, 50_000), (4097, 23, 50_000)])
+def test_many_classes_and_many_candidates(ks, orc, B, K, M):
+    """Both sides of the lines between the bitmap and the score table beyond 393,216 classes."""
+    C = 450_000
+    check(ks, orc, synth.labels_uniform(10, B, C), synth.graph_synthetic(10, C, K, locality=8, empty_frac=0.0), C, M)
