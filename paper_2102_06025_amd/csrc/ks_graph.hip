@@ -562,7 +562,8 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 // A row's candidate segments: 2 * parts of q slots (the two lanes of a part that hold the row), then `stream` slots.
 // Symmetric sweep: a lane has its q slots.  Passes with parts (no stream segment): the two lanes of a part share 2 q slots and
 // fill them from both ends, so that however a row's hits fall on lanes and parts, all of them fit: a lane sees the streamed
-// rows whose id has bit 2 clear, or set, and neighbours with ids of one residue modulo 8 are all one lane's.  2 q = 64 (r + 10).
+// rows whose id has bit 2 clear, or set, and neighbours with ids of one residue modulo 8 are all one lane's.  2 q = 64 (r + 10),
+// and what a lane can find in one chunk, before which it looks whether it has room.
 // (With 512 slots for each lane, four rows in 100,000 of K > 32 overflowed even with hits that fall evenly, and a row in the
 // exhaustive search costs 4 to 30 ms: 60,000 x 128, K = 64: 5.6 ms instead of 2.0; a hop of 65,000 rows of 512 against
 // a million 194 ms instead of 57.)
@@ -571,28 +572,22 @@ struct GrSegs {
     __host__ __device__ int cap() const { return 2 * parts * q + stream; }
 };
 // What is in the segments of a row: lane s gets the count of segment s (0 beyond the last) and where it begins.  Returns
-// whether one has overflowed; the count is then of what it holds.  All lanes of a wavefront call.
+// whether one has overflowed, which makes all counts 0.  All lanes of a wavefront call.
 __device__ __forceinline__ bool gr_segments(const GrSegs &seg, const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str,
                                             int64_t i, int &c, int &begin) {
     const int lane = threadIdx.x & 63, nres = 2 * seg.parts;
-    int raw = 0, most = seg.q;
-    if (lane < nres) raw = cnt_res[i * nres + lane];
-    else if (lane == nres && seg.stream > 0) { raw = cnt_str[i]; most = seg.stream; }
+    int most = seg.q;
+    c = 0;
+    if (lane < nres) c = cnt_res[i * nres + lane];
+    else if (lane == nres && seg.stream > 0) { c = cnt_str[i]; most = seg.stream; }
     begin = lane * seg.q;
-    if (seg.stream > 0) {
-        c = raw < most ? raw : most;
-    } else {
-        const int other = __shfl_xor(raw, 1, 64), room = 2 * seg.q;
-        if (lane & 1) { // from the end downwards, as far as the first lane's
-            most = room - (other < room ? other : room);
-            c = raw < most ? raw : most;
-            begin += seg.q - c;
-        } else {
-            most = room;
-            c = raw < most ? raw : most;
-        }
+    if (seg.stream == 0) {
+        most = 2 * seg.q - KS_DPP(0, c, 0xB1, 0xf); // what the other lane of the pair has left
+        if (lane & 1) begin += seg.q - c;           // from the end downwards
     }
-    return __ballot(c != raw) != 0ull;
+    const bool overflow = __ballot(c > most) != 0ull;
+    if (overflow) c = 0;
+    return overflow;
 }
 // stage shape of the sweeps for a depth of KT k-tiles: twelve k-tiles in flight, two per stage where KT is even (a barrier
 // per stage); a single k-tile per chunk (KT = 1): six, so that at most seven chunks are in flight
@@ -767,10 +762,14 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
     int my_cnt = 0;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
         const int lane = threadIdx.x & 63;
+        // (a lane finds half of a chunk's rows at most; one that may run out of slots here stores nothing any more, and its
+        // count, which no segment holds, marks the row as overflowed)
+        const bool full = my_cnt > last + 1 - CFG::CH / 2;
+        if (full) my_cnt = 1 << 20;
         const bool special = rows_here < CFG::CH || ((int64_t)c0 < self0 + CFG::RES && (int64_t)c0 + CFG::CH > self0);
 #pragma unroll
         for (int fm = 0; fm < CFG::FM; ++fm) {
-            uint32_t hm = gr_hit_mask(thf, acc[fm]);
+            uint32_t hm = full ? 0u : gr_hit_mask(thf, acc[fm]);
             while (__ballot(hm != 0u) != 0ull) { // as often as the lane with the most hits has some
                 if (hm != 0u) {
                     const int r = 15 - __builtin_ctz(hm);
@@ -778,8 +777,7 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
                     const float v = gr_sym_pick16(acc[fm], r);
                     const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), j = c0 + lr;
                     if (!special || (lr < rows_here && (int64_t)j != (int64_t)row0 + ks_soe_col() + pr.self)) {
-                        // (the minimum keeps the store inside the slots; counts that add up to more mark the row as overflowed)
-                        wg_cand[my_base + (uint32_t)((my_cnt < last ? my_cnt : last) ^ down)] =
+                        wg_cand[my_base + (uint32_t)(my_cnt ^ down)] =
                             ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
                         ++my_cnt;
                     }
@@ -1622,7 +1620,7 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, bool sym) {
     GrFixPlan f;
     const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(Cs, 96);
     f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
-    f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K) + 10);
+    f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K) + 10) + 24;
     f.seg.stream = sym ? GR_SYM_SCAP : 0;
     f.part_rows = (int)ks_ceil_div(chunks, f.seg.parts) * 96;
     if (!sym) f.seg.parts = (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
