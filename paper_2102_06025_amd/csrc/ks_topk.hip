@@ -640,24 +640,40 @@ template <class List> __device__ __forceinline__ void tk_select(const List &list
 // it (a tenth to a fifth for bell-shaped values; sorting the sample took five times as long as everything else in this step).
 // Where the bin brings the count beyond 3/2 r -- values that crowd at the top of their range, as uniform ones do, or all within
 // one bin -- a second level adds eleven bits (a microsecond), and only equal values are left to exceed r.  Overwrites sh.sort.
-template <int Q> __device__ __forceinline__ uint32_t tk_sample_threshold(const uint32_t (&key)[Q], int r, TkShared &sh) {
+// Magnitudes of the lowest bin, zeros nearly always, are not counted: without r others the threshold is 0 all the same, and
+// thousands of atomics on one address are spared.
+// room > 0: the sample is one element in four of the n that a list of `room` items is to be taken from, and TK_UNSUITED is returned
+// where it shows that many more than that are at or above the threshold: zeros, or a run of another value.  (A tensor of 32,768
+// elements with one in a hundred not zero, k = 327: 63 us by tk_select alone, 73 to 82 when all elements were collected on one
+// counter first, now 62.)
+#define TK_UNSUITED 0xFFFFFFFFu
+template <int Q> __device__ __forceinline__ uint32_t tk_sample_threshold(const uint32_t (&key)[Q], int r, TkShared &sh, int n, int room) {
     uint32_t *hist = (uint32_t *)sh.sort;
     for (int b = threadIdx.x; b < TK_BINS0 / 4; b += TK_NT) ((uint4 *)hist)[b] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < Q; ++q)
-        if (key[q] != 0xFFFFFFFFu) atomicAdd(&hist[key[q] >> 17], 1u);
+        if (key[q] - (1u << 17) < 0xFFFFFFFFu - (1u << 17)) atomicAdd(&hist[key[q] >> 17], 1u);
     __syncthreads();
     uint32_t above, in_bin;
     const uint32_t b1 = tk_find_bin<TK_BINS0 / TK_NT>(hist, TK_BINS0, (uint32_t)r, sh, &above, &in_bin);
-    if (2u * (above + in_bin) <= 3u * (uint32_t)r) return b1 << 17; // (the same for all threads)
+    if (b1 == 0u) return n > room ? TK_UNSUITED : 0u;
+    // (the same for all threads; a list that holds the whole tensor needs no second level)
+    if (2u * (above + in_bin) <= 3u * (uint32_t)r || (room > 0 && n <= room)) return b1 << 17;
     for (int b = threadIdx.x; b < TK_BINS; b += TK_NT) sh.hist[b] = 0u;
     __syncthreads();
+    if (in_bin > 2048u) { // (runs of one magnitude: one atomic per wavefront)
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
-        if (key[q] >> 17 == b1) atomicAdd(&sh.hist[(key[q] >> 6) & (TK_BINS - 1)], 1u);
+        for (int q = 0; q < Q; ++q) tk_hist_add(key[q] >> 17 == b1, (key[q] >> 6) & (TK_BINS - 1), sh.hist);
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (key[q] >> 17 == b1) atomicAdd(&sh.hist[(key[q] >> 6) & (TK_BINS - 1)], 1u);
+    }
     __syncthreads();
+    const uint32_t higher = above;
     const uint32_t b2 = tk_find_bin<TK_BINS / TK_NT>(sh.hist, TK_BINS, (uint32_t)r - above, sh, &above, &in_bin);
+    if (n > room && 16u * (higher + above + in_bin) > 5u * (uint32_t)room) return TK_UNSUITED; // (a quarter more than fits: the sample may mislead)
     return (b1 << 17) | (b2 << 6);
 }
 __device__ void tk_threshold(const float *__restrict__ gt, uint32_t n, int r, uint64_t *aux, TkShared &sh) {
@@ -667,7 +683,7 @@ __device__ void tk_threshold(const float *__restrict__ gt, uint32_t n, int r, ui
         const uint32_t idx = (uint32_t)(((uint64_t)(q * TK_NT + (int)threadIdx.x) * n) / TK_SAMPLE);
         key[q] = __float_as_uint(gt[idx]) & 0x7FFFFFFFu;
     }
-    const uint32_t thr = tk_sample_threshold<TK_SAMPLE / TK_NT>(key, r, sh);
+    const uint32_t thr = tk_sample_threshold<TK_SAMPLE / TK_NT>(key, r, sh, 0, 0);
     if (threadIdx.x == 0) {
         aux[0] = thr;
         aux[1] = 0ull; // items of the tensor's list so far (low word), overflow mark (high word)
@@ -788,7 +804,11 @@ __device__ __forceinline__ bool tk_top_of_chunk(const TkSrcGrad &src, int n, int
         uint32_t key[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) key[u] = u * TK_NT + tid < list.nq ? src.key_of(v[u], 0) : 0xFFFFFFFFu;
-        thr = tk_sample_threshold<U>(key, r, sh);
+        thr = tk_sample_threshold<U>(key, r, sh, n, LIST);
+        if (thr == TK_UNSUITED) {
+            __syncthreads(); // (the shared arrays are about to be reused)
+            return false;
+        }
     }
     auto take = [&](uint32_t key, uint32_t aux) {
         const uint32_t slot = atomicAdd(&sh.count, 1u);

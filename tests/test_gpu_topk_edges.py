@@ -119,3 +119,27 @@ def test_plan_saved_before_its_last_level_was_sorted(ks, orc):
     torch.cuda.synchronize()
     eidx, eval_ = orc.topk_group(g, offs, k)
     assert np.array_equal(idx.cpu().numpy(), eidx) and np.array_equal(val.cpu().numpy().view(np.uint32), eval_.view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [4000, 4096, 4200, 20_000, 32_768])
+@pytest.mark.parametrize("run", [0.0, -0.375])
+def test_one_chunk_with_runs_at_and_around_the_rank(ks, orc, n, run):
+    """Most of a tensor zero, or equal: few larger elements, as many as k, one more or fewer; about as many as the one-pass form
+    lists; runs of 1,024 elements and a few more above the rest."""
+    a = np.sign(grad(n, n)) * (1.0 + np.abs(grad(n, n)))
+    at = np.random.default_rng(n).permutation(n)
+    g, k = [], []
+    for m in (3, 40, 41, 300, 1000, 1024, 1030, 1100, 2000, 3900):
+        t = np.full(n, run, np.float32)
+        t[at[:m]] = a[at[:m]]
+        for kk in sorted({5, 40, min(m, 4096), min(m + 1, 4096)}):
+            if kk < n:
+                g.append(t)
+                k.append(kk)
+    for m in (1000, 1024, 1025, 1100):                            # the run is what the ranks fall in
+        t = (a * 0.1).astype(np.float32)
+        t[at[:m]] = 2.0
+        t[at[m:m + 30]] = 3.0
+        g += [t, t]
+        k += [20, 60]
+    check(ks, orc, np.concatenate(g).astype(np.float32), np.arange(len(g) + 1) * n, k)
