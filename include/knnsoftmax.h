@@ -78,9 +78,9 @@ const char *ks_version(void);
  * a row whose recall cannot be certified from the matrix-core pass' error bound is redone by exhaustive
  * fp64 search inside the same call.
  * Requires 2 <= C < 2^31, D % 32 == 0, 1 <= K <= min(C - 1, KS_MAX_GRAPH_K).
- * Workspace: for K <= 64 and D <= 512 the candidates of all rows at once, 9 KB a row, 25 to 33 where every similarity is
- * computed once, and up to 125 (at most 4.5 GB in all) where a problem of fewer than some 260,000 rows is cut into parts: 0.5 GB
- * at 10,000 x 128, 9.9 GB at 390,625 x 512, 35 GB at 4,000,000 x 96.  Otherwise 3 to 5 KB a row.
+ * Workspace: for K <= 64 and D <= 512 the candidates of all rows at once, 10 to 12 KB a row, 25 to 33 where every similarity is
+ * computed once, and up to 164 (at most 6.2 GB in all) where a problem of fewer than some 260,000 rows is cut into parts: 0.6 GB
+ * at 10,000 x 128, 9.9 GB at 390,625 x 512, 45 GB at 4,000,000 x 96.  Otherwise 3 to 5 KB a row.
  * ---------------------------------------------------------------------------------------------------- */
 size_t knn_graph_build_workspace(int64_t C, int D, int K, int dtype);
 int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K, int32_t *graph, float *sims,
@@ -364,7 +364,7 @@ int knn_softmax_bwd_from_stats_next(const uint16_t *W_bf16, const uint16_t *X_bf
  * visiting row that is in the list already is ignored, so a shard that visits twice changes nothing.  After
  * every shard has visited, the lists equal the graph knn_graph_build computes on the whole W.
  * Requires D % 32 == 0, K <= KS_MAX_GRAPH_K, all ids < 2^31.  Workspace: knn_graph_update_workspace (per row of W_local as
- * for knn_graph_build: 3.4 GB for 390,625 rows of 512).
+ * for knn_graph_build: 4.4 GB for 390,625 rows of 512, K = 32).
  * ---------------------------------------------------------------------------------------------------- */
 size_t knn_graph_update_workspace(int64_t C_loc, int64_t C_vis, int D, int K, int dtype);
 int knn_graph_update(const void *W_local, const void *W_visit, int dtype, int64_t C_loc, int64_t C_vis, int D, int K,
