@@ -20,11 +20,13 @@ typedef KsATile<128, 128, 2, 2, 2, KS_K8> TileDx;
 typedef KsATile<256, 256, 2, 4, 2, KS_K8> TileDxWide; // see sm_dx_wide
 // gather indices of one workgroup's share of the active dimension, staged in LDS
 template <class T> struct DxIdx { static constexpr int CAP = T::BM == 256 ? 8192 : 4096; };
-// dW tiles: 256 columns of D, and 256, 192 or 128 active rows -- chosen inside the kernel from the number of active
-// rows, which only the device knows (see dw_tile_rows)
+// dW tiles (active rows x columns of D): chosen inside the kernel from the number of active rows, which only the device
+// knows (see dw_tile_kind)
 typedef KsATile<256, 256, 2, 4, 2, KS_M8> TileDw;
 typedef KsATile<192, 256, 2, 4, 2, KS_M8> TileDw192;
 typedef KsATile<128, 256, 2, 4, 2, KS_M8> TileDw128;
+typedef KsATile<128, 128, 2, 4, 2, KS_M8> TileDw128n; // (n: 128 columns)
+typedef KsATile<64, 128, 2, 4, 2, KS_M8> TileDw64n;
 #define KS_BP_ALIGN 256
 #define SM_LIDX_CAP 1536 // gather-list entries a sweep keeps in LDS (longer slabs read the list from memory)
 #define SM_SOE_GRID 256 /* workgroups of the stationary-operand softmax passes (one per compute unit) */
@@ -945,22 +947,35 @@ struct DwUpdate {
     const int32_t *idx;
     float alpha;
 };
-// Height of the dW tiles for n_active rows on a chip of n_cu compute units (one tile per compute unit at a time).
-// With few active rows 256-row tiles leave compute units idle (17,425 rows x 512 columns are 138 tiles); lower tiles
-// cost more per flop (the X panel is loaded per tile whatever its height) but fill the chip: estimated time =
-// rounds x relative cost per tile (measured: 1, 0.81, 0.57), the smallest wins, ties to the taller tile.
-__device__ __forceinline__ int dw_tile_rows(int n_active, int tiles_n, int n_cu) {
-    const int heights[3] = {256, 192, 128}, cost[3] = {100, 81, 57};
-    int best = 256, best_t = 0x7fffffff;
+// Shape of the dW tiles for n_active rows on a chip of n_cu compute units (one tile per compute unit at a time); the launch
+// has workgroups for tiles_max of them.  A tile is a chain -- its k-tiles, then its part of the update, round trip after round
+// trip -- so with few rows the smallest tiles that still fit the chip in one round are the fastest; tall tiles load the X panel
+// and a wide tile the dZ8 panel less often, which counts once every compute unit has a tile.  Estimated time = rounds x cost
+// of a lone tile x (1 + share of the compute units at work: the memory is shared); the smallest wins, ties to the larger tile.
+// The costs are those that reproduce the order of the five shapes at sixteen sizes.  us, 256 x 256, 192 x 256, 128 x 256,
+// 128 x 128, 64 x 128 (dW and update, list of A classes): D = 128, B = 64, A = 600: 16.3, 11.2, 8.4, 5.9, 5.1; D = 320,
+// B = 333, A = 3,001: 21.3, 16.6, 12.4, 9.0, 7.8; D = 512, B = 1,024, A = 4,725: 36.5, 29.1, 24.0, 21.6, 25.2;
+// A = 17,425: 48.9, 40.0, 51.0, 51.6, 58.7; A = 32,374: 54.0, 58.8, 57.8, 67.3, 91.0.  (64 x 256: never ahead of 128 x 128.)
+enum { DW_KINDS = 5 };
+__device__ __forceinline__ int dw_tile_kind(int n_active, int D, int n_cu, int tiles_max) {
+    const int rows[DW_KINDS] = {TileDw::BM, TileDw192::BM, TileDw128::BM, TileDw128n::BM, TileDw64n::BM};
+    const int cols[DW_KINDS] = {TileDw::BN, TileDw192::BN, TileDw128::BN, TileDw128n::BN, TileDw64n::BN};
+    const float cost[DW_KINDS] = {33.5f, 24.4f, 17.7f, 13.8f, 10.8f};
+    const float per_cu = 1.f / (float)n_cu;
+    int best = 0;
+    float best_t = INFINITY;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int tiles = tiles_n * ((n_active + heights[k] - 1) / heights[k]);
-        const int t = ((tiles + n_cu - 1) / n_cu) * cost[k];
-        if (t < best_t) { best_t = t; best = heights[k]; }
+    for (int k = 0; k < DW_KINDS; ++k) {
+        const int tiles = ((D + cols[k] - 1) / cols[k]) * ((n_active + rows[k] - 1) / rows[k]);
+        const float share = (float)tiles * per_cu;
+        const float t = ceilf(share) * cost[k] * (1.f + fminf(share, 1.f));
+        if (t < best_t && tiles <= tiles_max) { best_t = t; best = k; }
     }
     return best;
 }
 
+// LDS of the launch: a tile's stages and its rows' classes, or the bitmap of the next batch's selection
+constexpr int DW_LDS_ELEMS = TileDw::LDS_ELEMS + 2 * TileDw::BM > 2 * SEL1_LDS_WORDS ? TileDw::LDS_ELEMS + 2 * TileDw::BM : 2 * SEL1_LDS_WORDS;
 template <class T>
 __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
@@ -971,10 +986,7 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
                 const int32_t *__restrict__ n_active_p, int D, int M, int64_t Mp, float scale, float *__restrict__ dW,
                 int tiles_max, int n_cu, DxReduceJob job, DwUpdate up, KsSelNext next) {
     typedef TileDw T;
-    static_assert(TileDw192::NT == T::NT && TileDw128::NT == T::NT && TileDw192::LDS_ELEMS <= T::LDS_ELEMS &&
-                      TileDw128::LDS_ELEMS <= T::LDS_ELEMS, "one launch shape for all tile heights");
-    constexpr int LDS_ELEMS = T::LDS_ELEMS > 2 * SEL1_LDS_WORDS ? T::LDS_ELEMS : 2 * SEL1_LDS_WORDS;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[LDS_ELEMS];
+    __shared__ __attribute__((aligned(16))) uint16_t lds[DW_LDS_ELEMS];
     // The first next.nsel workgroups select the NEXT batch's active classes (Algorithm 1 needs only its labels): with a
     // few hundred tiles this launch leaves compute units idle, and being first they start at once.
     const int bid = (int)blockIdx.x - next.nsel;
@@ -985,12 +997,16 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
     if (bid >= tiles_max) { // reduction blocks
         const int rb = bid - tiles_max, nrb = (int)gridDim.x - next.nsel - tiles_max;
         for (int64_t e = ((int64_t)rb * T::NT + threadIdx.x) * 4; e < job.BD; e += (int64_t)nrb * T::NT * 4) {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int sp = 0; sp < job.S; ++sp) {
-                const float4 v = *(const float4 *)(job.part + (int64_t)sp * job.BD + e);
-                acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-            }
             const float f = job.row_factor ? job.scale * job.row_factor[e / D] : job.scale;
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int s0 = 0; s0 < job.S; s0 += 8) { // eight loads in flight, added in order
+                float4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = s0 + u < job.S ? *(const float4 *)(job.part + (int64_t)(s0 + u) * job.BD + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+            }
             *(float4 *)(job.dX + e) = make_float4(f * acc.x, f * acc.y, f * acc.z, f * acc.w);
         }
         if (rb == nrb - 1) { // thread t takes samples t, t + NT, ..., then a tree: a fixed order
@@ -1008,10 +1024,14 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
         return;
     }
     const int n_active = sm_clamp_n(n_active_p, M);
-    const int rows = dw_tile_rows(n_active, (D + T::BN - 1) / T::BN, n_cu);
-    if (rows == 256) dw_tile<TileDw>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up);
-    else if (rows == 192) dw_tile<TileDw192>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up);
-    else dw_tile<TileDw128>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up);
+    const int kind = dw_tile_kind(n_active, D, n_cu, tiles_max);
+#define DW_TILE(T) dw_tile<T>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up)
+    if (kind == 0) DW_TILE(TileDw);
+    else if (kind == 1) DW_TILE(TileDw192);
+    else if (kind == 2) DW_TILE(TileDw128);
+    else if (kind == 3) DW_TILE(TileDw128n);
+    else DW_TILE(TileDw64n);
+#undef DW_TILE
 }
 
 template <class T>
@@ -1023,6 +1043,14 @@ __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *
     if (bid >= n_tiles) return;
     const int t = ks_xcd_remap(bid, n_tiles);
     const int tn = t % tiles_n, tm = t / tiles_n;
+    // the classes of the tile's rows, for the update: requested before the first k-tile, straight into LDS behind the stages
+    static_assert(T::NT == TileDw::NT && T::LDS_ELEMS + 2 * T::BM <= DW_LDS_ELEMS, "one launch shape for all tiles");
+    int32_t *s_cls = (int32_t *)(lds + T::LDS_ELEMS);
+    if (up.Wm && threadIdx.x < T::BM) {
+        const int a = tm * T::BM + (int)threadIdx.x;
+        __builtin_amdgcn_global_load_lds(KS_GPTR(up.idx + (a < n_active ? a : n_active - 1)),
+                                         KS_LPTR(s_cls + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u)), 4, 0, 0);
+    }
     KsAM8<T::BM, T::NW> ar;
     KsAKmaj<T::BN, T::NW> br;
     ar.init(dZ8, Bp, tm * T::BM, (int)Mp);
@@ -1032,46 +1060,61 @@ __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *
     // (samples B .. of the last k-tile: zeros of dZ8 meet the last row of X)
     ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, (B + 63) / 64, lds, acc);
     // epilogue, row-wise through LDS: gradient rows out (if wanted) and, if asked for, the update of the master
-    // rows and of their 16-bit copy.  Four rows per thread are in flight at a time.
+    // rows and of their 16-bit copy.  Up to four rows per thread are in flight at a time, the next ones requested before
+    // the present ones are stored (and the first before the slab is staged): 192 x 256 tiles of 17,425 rows 43 -> 40 us,
+    // 256 x 256 of 124,580 rows 420 -> 350.  (Two at a time beside the 128 accumulators of a 256 x 256 tile: four spill.)
     typedef KsASlab<T> SL;
     float *st = (float *)lds;
     const int d_base = tn * T::BN;
+    constexpr int PER = SL::ROWS * SL::QUADS / T::NT; // pieces per thread and slab
+    constexpr int U = T::BM * T::BN > 192 * 256 ? 2 : (PER < 4 ? PER : 4), NB = PER / U; // batches per slab
+    static_assert(SL::ROWS * SL::QUADS % T::NT == 0 && PER % U == 0, "slab shape");
+    float4 wn[U];
+    int cn[U]; // the classes of the next batch's pieces (-1: no piece)
+    auto request = [&](int b) __attribute__((always_inline)) { // batch b of all slabs
+        const int p = b / NB, q0 = b % NB * U;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = (q0 + u) * T::NT + threadIdx.x;
+            const int row = p * SL::ROWS + q / SL::QUADS, d = d_base + q % SL::QUADS * 4;
+            cn[u] = -1;
+            if (tm * T::BM + row < n_active && d < D) cn[u] = up.Wm ? s_cls[row] : 0; // D % 4 == 0
+            if (up.Wm) wn[u] = cn[u] >= 0 ? *(const float4 *)(up.Wm + (int64_t)cn[u] * D + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    request(0);
     for (int p = 0; p < T::WAVES_M; ++p) {
         ks_a_stage_slab<T>(acc, st, p);
         __syncthreads();
-        constexpr int PER = SL::ROWS * SL::QUADS / T::NT; // pieces per thread
-        static_assert(SL::ROWS * SL::QUADS % T::NT == 0 && PER % 4 == 0, "slab shape");
-        for (int q0 = 0; q0 < PER; q0 += 4) {
-            float4 g[4], w[4];
-            int64_t at[4];
-            int a_[4], d_[4];
+        for (int q0 = 0; q0 < PER; q0 += U) {
+            float4 g[U], w[U];
+            int cls[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
+                w[u] = wn[u];
+                cls[u] = cn[u];
+            }
+            const int b = p * NB + q0 / U + 1;
+            if (b < T::WAVES_M * NB) request(b);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
                 const int q = (q0 + u) * T::NT + threadIdx.x;
-                const int row = q / SL::QUADS, quad = q % SL::QUADS;
-                a_[u] = tm * T::BM + p * SL::ROWS + row;
-                d_[u] = d_base + quad * 4;
-                const float4 v = ks_a_slab_quad<T>(st, row, quad);
+                const float4 v = ks_a_slab_quad<T>(st, q / SL::QUADS, q % SL::QUADS);
                 g[u] = make_float4(scale * v.x, scale * v.y, scale * v.z, scale * v.w);
-                at[u] = -1;
-                if (a_[u] < n_active && d_[u] < D) at[u] = up.Wm ? (int64_t)up.idx[a_[u]] * D + d_[u] : 0; // D % 4 == 0
-            }
-            if (up.Wm) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    w[u] = at[u] >= 0 ? *(const float4 *)(up.Wm + at[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (at[u] < 0) continue;
-                if (dW) *(float4 *)(dW + (int64_t)a_[u] * D + d_[u]) = g[u];
+            for (int u = 0; u < U; ++u) {
+                if (cls[u] < 0) continue;
+                const int q = (q0 + u) * T::NT + threadIdx.x, d = d_base + q % SL::QUADS * 4;
+                if (dW) *(float4 *)(dW + (int64_t)(tm * T::BM + p * SL::ROWS + q / SL::QUADS) * D + d) = g[u];
                 if (up.Wm) {
                     w[u].x = fmaf(up.alpha, g[u].x, w[u].x);
                     w[u].y = fmaf(up.alpha, g[u].y, w[u].y);
                     w[u].z = fmaf(up.alpha, g[u].z, w[u].z);
                     w[u].w = fmaf(up.alpha, g[u].w, w[u].w);
-                    *(float4 *)(up.Wm + at[u]) = w[u];
-                    if (up.Wb) *(uint2 *)(up.Wb + at[u]) = make_uint2(ks_pack_bf2(w[u].x, w[u].y), ks_pack_bf2(w[u].z, w[u].w));
+                    const int64_t at = (int64_t)cls[u] * D + d;
+                    *(float4 *)(up.Wm + at) = w[u];
+                    if (up.Wb) *(uint2 *)(up.Wb + at) = make_uint2(ks_pack_bf2(w[u].x, w[u].y), ks_pack_bf2(w[u].z, w[u].w));
                 }
             }
         }
@@ -1403,7 +1446,10 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
         mark(6); // the reduction of the partial products rides along with the next launch
         {
             typedef TileDw T;
-            const int tiles = (int)(ks_ceil_div(M, TileDw128::BM) * ks_ceil_div(D, T::BN)); // the most any tile height needs
+            // workgroups for 128-row tiles, or, where those leave compute units without one, for as many tiles of the smallest shape
+            int tiles = (int)(ks_ceil_div(M, TileDw128::BM) * ks_ceil_div(D, T::BN));
+            const int least = (int)(ks_ceil_div(M, TileDw64n::BM) * ks_ceil_div(D, TileDw64n::BN)), n_cu = ks_n_cu();
+            if (tiles < n_cu) tiles = least < n_cu ? least : n_cu;
             DxReduceJob job;
             job.part = w.part;
             job.S = w.S;
@@ -1415,7 +1461,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             job.loss_mean = loss_mean;
             hipLaunchKernelGGL(dw_async_kernel, dim3(next.nsel + tiles + DW_REDUCE_BLOCKS), dim3(T::NT), 0, st, w.dZ8,
                                fused ? w.X2 : X, B, w.Bp, n_active, D, Mi, w.Mp, fused ? scale * g : scale, dW_active, tiles,
-                               ks_n_cu(), job, up, next);
+                               n_cu, job, up, next);
         }
         mark(7);
         KS_LAUNCH_CHECK();

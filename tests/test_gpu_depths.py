@@ -323,3 +323,36 @@ def test_candidate_counts_of_many_rows_fit(ks):
     ks.knn_graph_build(dev(W, True), K, ws=ws)
     torch.cuda.synchronize()
     assert _exhaustive_rows(ws, C, np.sqrt((W.astype(np.float64) ** 2).sum(1)).max(), 1) == 0
+
+
+@pytest.mark.parametrize("D,A,B", [
+    (64, 2, 1), (128, 63, 33), (320, 65, 64), (128, 4097, 65),       # tiles of 64 x 128: two rows, one short, one over, many
+    (512, 4737, 40), (320, 5000, 33),                                # 128 x 128
+    (512, 6529, 33), (512, 6527, 129),                               # 128 x 256
+    (2048, 4225, 40), (2048, 6209, 33)])                             # 192 x 256, 256 x 256
+def test_gradient_rows_and_update_in_every_tile_shape(ks, orc, D, A, B):
+    """The dW launch picks its tile from the active count: lists that end inside a tile of each shape, depths that end inside
+    one.  Gradient rows against the oracle, rows beyond the list untouched, the update bit for bit the stand-alone one."""
+    import torch
+    from gradcheck import check_rows, grad_floors
+    print(f"[depths] dW tiles D={D} A={A} B={B}", flush=True)
+    C, M, scale, gs, alpha = A + 77, A + 13, 20.0, 4.0, -0.5
+    W, X = synth.unit_rows(41, synth.TID_W, C, D, bf16=True), synth.unit_rows(41, synth.TID_X, B, D, bf16=True)
+    active = np.sort(synth.class_permutation(41, C)[:A]).astype(np.int32)
+    tpos = ((np.arange(B) * 7919 + A - 1) % A).astype(np.int32)
+    act = np.full(M, -1, np.int32)
+    act[:A] = active
+    Wm, Wb, n = dev(W), dev(W, True), dev(np.array([A], np.int32))
+    out = dict(loss_per_sample=torch.empty(B, device="cuda"), loss_mean=torch.empty(1, device="cuda"),
+               dX=torch.empty((B, D), device="cuda"), dW_active=torch.full((M, D), 123.0, device="cuda"))
+    ks.knn_softmax_fwd_bwd_update_selected(Wm, Wb, dev(X, True), dev(act), n, dev(tpos), scale, gs, alpha, out=out, want_dW=True)
+    Wm2, Wb2 = dev(W), dev(W, True)
+    ks.apply_weight_grad(Wm2, Wb2, dev(act), n, out["dW_active"], alpha, idx_sorted_unique=True)
+    torch.cuda.synchronize()
+    assert int(out["dev_status"]) == 0
+    ref = orc.knn_softmax_fwd_bwd(W, X, active, tpos, scale, gs)
+    floors = grad_floors(W[active], X, tpos, ref["lse"], scale, gs / B)
+    check_rows(out["dX"].cpu().numpy(), ref["dX"], floors[0], "dX")
+    check_rows(out["dW_active"][:A].cpu().numpy(), ref["dWA"], floors[1], "dW")
+    assert bool((out["dW_active"][A:] == 123.0).all())
+    assert torch.equal(Wm, Wm2) and torch.equal(Wb, Wb2) and not torch.equal(Wm, dev(W))
