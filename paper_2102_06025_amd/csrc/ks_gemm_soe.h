@@ -84,6 +84,19 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
     constexpr int KT = CFG::KT, ST = CFG::STAGES, NI = CFG::NI, FM = CFG::FM;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_chunks = ctab ? ctab_n : (s_end - s_begin + CFG::CH - 1) / CFG::CH;
+    // The gather list is requested before the resident block, which hides its round trip; it goes to LDS behind the block's
+    // staging.
+    constexpr int LPT = 3; // list entries per thread
+    const bool use_lidx = gidx && lidx && n_chunks * CFG::CH <= lidx_cap && lidx_cap <= LPT * CFG::NT;
+    int32_t lreg[LPT] = {0, 0, 0};
+    if (use_lidx) {
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const int i = u * CFG::NT + (int)threadIdx.x, g = s_begin + i;
+            if (i < n_chunks * CFG::CH) lreg[u] = gidx[g < s_clamp ? g : s_clamp - 1];
+        }
+    }
 
     // ---- resident fragments: staged through LDS (coalesced row loads), then kept in registers ----------------
     bf16x8_t bres[KT * 4];
@@ -129,19 +142,17 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
     }
 
     // ---- stream state ---------------------------------------------------------------------------------------
-    const int n_chunks = ctab ? ctab_n : (s_end - s_begin + CFG::CH - 1) / CFG::CH;
     auto chunk_first = [&](int c) __attribute__((always_inline)) { return ctab ? ctab[c].x : s_begin + c * CFG::CH; };
     auto chunk_rows = [&](int c) __attribute__((always_inline)) {
         if (ctab) return ctab[c].y;
         return (s_end - (s_begin + c * CFG::CH)) < CFG::CH ? (s_end - (s_begin + c * CFG::CH)) : CFG::CH;
     };
     const int n_tiles = n_chunks * (KT / CFG::KSUB); // pipeline stages in the whole sweep
-    const bool use_lidx = gidx && lidx && n_chunks * CFG::CH <= lidx_cap;
     if (use_lidx) {
-        for (int i = threadIdx.x; i < n_chunks * CFG::CH; i += CFG::NT) {
-            int g = s_begin + i;
-            if (g >= s_clamp) g = s_clamp - 1;
-            lidx[i] = gidx[g];
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const int i = u * CFG::NT + (int)threadIdx.x;
+            if (i < n_chunks * CFG::CH) lidx[i] = lreg[u];
         }
     }
     __builtin_amdgcn_s_waitcnt(0xC07F); // the fragment reads have returned before the stages are reused
