@@ -454,9 +454,13 @@ __device__ __forceinline__ void ks_a_tile_mma_il(const uint16_t *st, f32x16_t (&
     ks_a_mma_il<T, 3, SLOTS>(f1, acc, do_load, issue);
 }
 
-template <class T, int AK = KS_ROWS, int BK = KS_ROWS, int SPREAD = 3, class AR, class BR>
+// landed(kt, stage): called by all threads when k-tile kt lies in LDS, before its fragments are read.
+struct KsANothing {
+    __device__ __forceinline__ void operator()(int, uint16_t *) const {}
+};
+template <class T, int AK = KS_ROWS, int BK = KS_ROWS, int SPREAD = 3, class AR, class BR, class Landed = KsANothing>
 __device__ __forceinline__ void ks_a_mainloop_il(AR &ar, BR &br, int kt0, int kt1, uint16_t *lds,
-                                                 f32x16_t (&acc)[T::FM][T::FN]) {
+                                                 f32x16_t (&acc)[T::FM][T::FN], Landed landed = Landed()) {
     static_assert(T::STAGES == 2 && SPREAD >= 1 && SPREAD <= 4, "two stages");
     if (kt0 >= kt1) return;
     ar.issue(kt0 * 64, lds);
@@ -465,6 +469,7 @@ __device__ __forceinline__ void ks_a_mainloop_il(AR &ar, BR &br, int kt0, int kt
     for (int kt = kt0; kt < kt1; ++kt) {
         ks_wait_vmcnt<0>();
         ks_barrier_nofence();
+        landed(kt, lds + stage * T::STAGE_ELEMS);
         uint16_t *nst = lds + (stage ^ 1) * T::STAGE_ELEMS;
         const int k0n = (kt + 1) * 64;
         auto issue = [&](int q) __attribute__((always_inline)) {

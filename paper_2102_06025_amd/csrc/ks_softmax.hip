@@ -680,16 +680,15 @@ sm_fused_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     }
 }
 
-// Combine step of the one-sweep variant.  A block owns 32 samples, eight threads per sample: sum of the slab
-// sums (every eighth slab each, then the eight partial sums in order); the target logit as an fp32 dot
-// product of the two bf16 rows (an eighth of the row each); with it the target's exponential E_t, which
-// replaces the stored rounded one in the sum, so that the stored column (with the target entry set to
-// E_t - sum = -(sum of the others)) sums to zero and P_t - 1 carries no cancellation; the loss; the
-// reciprocal sum for dX; the scaled row of X2.
+// Combine step of the one-sweep variant, per sample: the sum of the slab sums; the target logit as an fp32 dot product of
+// the two bf16 rows and with it the target's exponential E_t and the loss; the reciprocal sum for dX; the scaled row of X2.
+// The column of the logit gradient is (P - onehot) * sum when the target's entry, which the sweep has stored as 0, is
+// E_t - sum = -(sum of the others): so it sums to zero and P_t - 1 carries no cancellation.  That entry does not go into the
+// stored column, which the dX launch is reading: its term of dX, entry times the class's row, becomes one more partial product
+// (fp32, where the other entries are rounded to bf16), and the dW kernel puts the rounded entry into its tile in LDS.  So the
+// step needs no launch of its own here, only blocks beside the dX tiles (before: a kernel between the sweep and dX, 5.2 to
+// 7.9 us of every step).
 #define SM_CF_NT 256
-#ifndef SM_CF_SPB
-#define SM_CF_SPB 8 /* samples per workgroup of the combine kernel */
-#endif
 // The softmax split over the nodes of the model-parallel layer (Section 3.1 steps 3-5) runs the same kernels in two
 // calls with an exchange of the per-sample statistics in between:
 #define SM_WHOLE 0  /* one GPU owns all classes: statistics and gradient in one go */
@@ -699,139 +698,150 @@ struct SmSplitIO {
     float *row_max, *row_sum, *tz_out;    // SM_EXPORT
     const float *gmax, *gsum, *gtz;       // SM_IMPORT
 };
-__global__ void __launch_bounds__(SM_CF_NT)
-sm_combine_fused_kernel(const float *__restrict__ pl, const float *__restrict__ pl_others, const int32_t *__restrict__ n_active_p,
-                        const int32_t *__restrict__ active_idx, const int32_t *__restrict__ target_pos,
-                        const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, int M, int slabs, int B, int Bp, int D,
-                        float scale, float *__restrict__ inv_sum, float *__restrict__ loss_i, uint16_t *__restrict__ dZ8,
-                        uint16_t *__restrict__ X2, int32_t *dev_status, int mode, SmSplitIO io) {
-    // SM_CF_SPB samples per workgroup, SM_CF_PARTS threads per sample (each takes a share of the slab sums and of
-    // the dot product): the kernel is a chain of dependent round trips, so it is spread over many compute units
-    constexpr int SPB = SM_CF_SPB, PARTS = SM_CF_NT / SPB;
-    __shared__ float sh[SM_CF_NT], sh_dot[SM_CF_NT], sh_oth[SM_CF_NT];
-    __shared__ float s_inv[SPB];
+struct SmCombine {
+    int blocks;             // workgroups that do it (0: nothing to do), SM_CF_FEW or SM_CF_MANY samples each
+    int many;
+    const float *pl, *pl_others; // the sweep's slab sums
+    int slabs, D;                // D: 128, 256 or 512
+    const int32_t *target_pos;
+    const uint16_t *X;
+    float scale;
+    float *inv_sum, *loss_i;
+    uint16_t *X2;
+    float *extra;           // [B][D]: the targets' terms of dX (a further partial product)
+    int32_t *cell_pos;      // [Bp]: where dW's target entry goes (-1: nowhere) ...
+    uint32_t *cell;         // [Bp]: ... and its bf16 value
+    int32_t *dev_status;
+    int mode;
+    SmSplitIO io;
+};
+#define SM_CF_FEW 8   /* the kernel is a chain of dependent round trips: spread over many compute units where there is room */
+#define SM_CF_MANY 32
+// Workgroup blk of job.blocks.  sh: 2 * NT + 4 * SPB floats of LDS.
+template <int NT, int SPB>
+__device__ __forceinline__ void sm_combine(const SmCombine &job, int blk, const int32_t *__restrict__ n_active_p, int M, int B, int Bp,
+                                           const int32_t *__restrict__ active_idx, const uint16_t *__restrict__ W, float *sh) {
+    constexpr int PARTS = NT / SPB;                      // threads per sample: each takes a share of the slab sums
+    constexpr int U = SPB * 64 >= NT ? SPB * 64 / NT : 1; // 16-byte pieces of rows per thread, at D = 512
+    const int D = job.D, per_row = D / 8;
+    const int rows = B - blk * SPB < SPB ? B - blk * SPB : SPB, total = rows * per_row;
+    const int64_t first = (int64_t)blk * SPB * D; // the block's rows are contiguous
+    float *const s_inv = sh + 2 * NT, *const s_cell = s_inv + SPB, *const s_dot = s_cell + SPB;
+    // pieces of the rows of X and of the samples' classes, the slab sums: requested before anything is waited for
+    int tp[U], cls[U];
+    uint4 x[U], w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int q = u * NT + threadIdx.x;
+        tp[u] = q < total ? job.target_pos[blk * SPB + q / per_row] : -1;
+        x[u] = q < total ? *(const uint4 *)(job.X + first + (int64_t)q * 8) : make_uint4(0u, 0u, 0u, 0u);
+    }
+    const int j = threadIdx.x % SPB, gq = threadIdx.x / SPB, i = blk * SPB + j;
     const int n = sm_clamp_n(n_active_p, M);
-    const int n64 = (n + 63) & ~63;
-    const int h = sm_slab_rows(n64, slabs);
-    const int nt = (n64 + h - 1) / h; // slabs that hold rows
-    const int j = threadIdx.x % SPB, gq = threadIdx.x / SPB;
-    const int i = blockIdx.x * SPB + j;
-    int tp = 0;
-    bool owned = n > 0; // split over nodes: does this node hold the sample's class?  (one GPU: always)
-    {
-        float part = 0.f, dot = 0.f, oth = 0.f;
-        if (i < B && n > 0) {
-            // all loads of a batch are issued before the first use: these are dependent only through the
-            // running sums, and one round trip to another L2 costs as much as everything else here
-            tp = target_pos[i];
-            if (mode != SM_WHOLE) owned = tp >= 0 && tp < n;
-            tp = tp < 0 ? 0 : (tp >= n ? n - 1 : tp); // stays in bounds whatever the selection flagged
-            const int cls = active_idx[tp];
-            for (int t0 = gq; mode != SM_IMPORT && t0 < nt; t0 += 4 * PARTS) {
-                float v[4], u[4];
+    const int n64 = (n + 63) & ~63, h = sm_slab_rows(n64, job.slabs);
+    float part = 0.f, oth = 0.f;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    v[q] = (t0 + PARTS * q < nt) ? pl[(int64_t)(t0 + PARTS * q) * Bp + i] : 0.f;
-                    u[q] = (t0 + PARTS * q < nt) ? pl_others[(int64_t)(t0 + PARTS * q) * Bp + i] : 0.f;
-                }
+    for (int u = 0; u < U; ++u) cls[u] = tp[u] >= 0 && tp[u] < n ? active_idx[tp[u]] : -1;
+    if (i < B && job.mode != SM_IMPORT) {
+        for (int t0 = gq; t0 * h < n64; t0 += 4 * PARTS) { // (slabs that hold rows)
+            float v[4], o[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    part += v[q];
-                    oth += u[q];
-                }
-            }
-            // this thread's share of the dot product: pieces gq, gq + PARTS, ... of four elements (D <= 512, D % 4 == 0)
-            const uint16_t *xr = X + (int64_t)i * D, *wr = W + (int64_t)cls * D;
-            constexpr int MAXP = 512 / PARTS / 4;
-            uint2 xv[MAXP], wv[MAXP];
-#pragma unroll
-            for (int q = 0; q < MAXP; ++q) {
-                const int e = (gq + q * PARTS) * 4;
-                xv[q] = e < D ? *(const uint2 *)(xr + e) : make_uint2(0u, 0u);
-                wv[q] = e < D ? *(const uint2 *)(wr + e) : make_uint2(0u, 0u);
+            for (int q = 0; q < 4; ++q) {
+                const bool in = (t0 + PARTS * q) * h < n64;
+                v[q] = in ? job.pl[(int64_t)(t0 + PARTS * q) * Bp + i] : 0.f;
+                o[q] = in ? job.pl_others[(int64_t)(t0 + PARTS * q) * Bp + i] : 0.f;
             }
 #pragma unroll
-            for (int q = 0; q < MAXP; ++q) {
-                dot = fmaf(ks_bf2f(xv[q].x & 0xFFFFu), ks_bf2f(wv[q].x & 0xFFFFu), dot);
-                dot = fmaf(ks_bf2f(xv[q].x >> 16), ks_bf2f(wv[q].x >> 16), dot);
-                dot = fmaf(ks_bf2f(xv[q].y & 0xFFFFu), ks_bf2f(wv[q].y & 0xFFFFu), dot);
-                dot = fmaf(ks_bf2f(xv[q].y >> 16), ks_bf2f(wv[q].y >> 16), dot);
+            for (int q = 0; q < 4; ++q) {
+                part += v[q];
+                oth += o[q];
             }
         }
-        sh[threadIdx.x] = part;
-        sh_dot[threadIdx.x] = dot;
-        sh_oth[threadIdx.x] = oth;
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        w[u] = cls[u] >= 0 ? *(const uint4 *)(W + (int64_t)cls[u] * D + (u * NT + threadIdx.x) % per_row * 8) : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t xs[4] = {x[u].x, x[u].y, x[u].z, x[u].w}, ws[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+        float dot = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            dot = fmaf(ks_bf2f(xs[e] & 0xFFFFu), ks_bf2f(ws[e] & 0xFFFFu), dot);
+            dot = fmaf(ks_bf2f(xs[e] >> 16), ks_bf2f(ws[e] >> 16), dot);
+        }
+        for (int o = per_row / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64); // (a row's pieces are neighbouring lanes)
+        const int q = u * NT + threadIdx.x;
+        if (q < total && q % per_row == 0) {
+            s_dot[q / per_row] = dot;
+            s_cell[q / per_row] = cls[u] >= 0 ? 1.f : 0.f; // (for now: whether the sample's class is here)
+        }
+    }
+    sh[threadIdx.x] = part;
+    sh[NT + threadIdx.x] = oth;
     __syncthreads();
-    if (threadIdx.x < SPB) {
-        float inv = 0.f;
-        if (i < B) {
-            float sum = 0.f, dot = 0.f, oth = 0.f;
-            for (int q = 0; q < PARTS; ++q) { // a fixed order
-                sum += sh[q * SPB + j];
-                dot += sh_dot[q * SPB + j];
-                oth += sh_oth[q * SPB + j];
-            }
-            const float z_t = scale * dot;
-            const float e_t = __expf(z_t - scale);
-            uint16_t *cell = dZ8 + sm_dz_at(tp, i, Bp);
-            if (mode == SM_IMPORT) {
-                // the sum over the classes of all nodes, brought to this kernel's reference `scale`
-                const float S = io.gsum[i] * __expf(io.gmax[i] - scale);
-                if (!(S > 0.f) || !(S < INFINITY)) ks_flag(dev_status, KS_DEV_RANGE);
-                loss_i[i] = (io.gmax[i] + __logf(io.gsum[i])) - io.gtz[i];
-                inv = 1.f / S;
-                inv_sum[i] = inv;
-                if (owned) *cell = (uint16_t)ks_f2bf(e_t - S); // (P_t - 1) * S
+    if ((int)threadIdx.x < SPB && i < B) {
+        float inv = 0.f, cell = 0.f, others = 0.f;
+        oth = 0.f;
+        for (int q = 0; q < PARTS; ++q) { // a fixed order
+            others += sh[q * SPB + j];
+            oth += sh[NT + q * SPB + j];
+        }
+        const bool owned = s_cell[j] != 0.f; // (one GPU: always, unless the list is broken; split over nodes: this node's class)
+        const float z_t = job.scale * s_dot[j];
+        const float e_t = __expf(z_t - job.scale);
+        if (job.mode == SM_IMPORT) {
+            // the sum over the classes of all nodes, brought to this kernel's reference `scale`
+            const float S = job.io.gsum[i] * __expf(job.io.gmax[i] - job.scale);
+            if (!(S > 0.f) || !(S < INFINITY)) ks_flag(job.dev_status, KS_DEV_RANGE);
+            job.loss_i[i] = (job.io.gmax[i] + __logf(job.io.gsum[i])) - job.io.gtz[i];
+            inv = 1.f / S;
+            cell = e_t - S; // (P_t - 1) * S
+        } else {
+            const float sum = owned ? others + e_t : others; // (the sweep leaves the sample's own class out)
+            if (job.mode == SM_EXPORT) {
+                job.io.row_max[i] = job.scale;
+                job.io.row_sum[i] = sum;
+                job.io.tz_out[i] = owned ? z_t : 0.f;
             } else {
-                float others = sum;
-                if (owned) {
-                    sum = others + e_t; // (the sweep leaves the sample's own class out)
-                }
-                if (mode == SM_EXPORT) {
-                    io.row_max[i] = scale;
-                    io.row_sum[i] = sum;
-                    io.tz_out[i] = owned ? z_t : 0.f;
-                } else {
-                    if (!(sum > 0.f) || !(sum < INFINITY)) ks_flag(dev_status, KS_DEV_RANGE);
-                    // loss = log(1 + (unrounded exponentials of the other classes) / E_t): no difference of nearly
-                    // equal numbers, and no bf16 rounding in it (a class list without the sample's class: plain form)
-                    const float ratio = oth / e_t;
-                    loss_i[i] = (owned && ratio < 1e30f) ? log1pf(ratio) : (scale + __logf(sum)) - z_t;
-                    inv = 1.f / sum;
-                    inv_sum[i] = inv;
-                    *cell = (uint16_t)ks_f2bf(-others); // the column now holds (P - onehot) * sum
-                }
+                if (!(sum > 0.f) || !(sum < INFINITY)) ks_flag(job.dev_status, KS_DEV_RANGE);
+                // loss = log(1 + (unrounded exponentials of the other classes) / E_t): no difference of nearly
+                // equal numbers, and no bf16 rounding in it
+                const float ratio = oth / e_t;
+                job.loss_i[i] = (owned && ratio < 1e30f) ? log1pf(ratio) : (job.scale + __logf(sum)) - z_t;
+                inv = 1.f / sum;
+                cell = -others;
             }
+        }
+        if (job.mode != SM_EXPORT) {
+            job.inv_sum[i] = inv;
+            job.cell_pos[i] = owned ? job.target_pos[i] : -1;
+            job.cell[i] = ks_f2bf(cell);
         }
         s_inv[j] = inv;
+        s_cell[j] = owned ? cell : 0.f;
     }
+    if (job.mode == SM_EXPORT) return; // nothing is normalised before the nodes have exchanged their sums
     __syncthreads();
-    if (mode == SM_EXPORT) return; // nothing is normalised before the nodes have exchanged their sums
-    const int rows = (B - blockIdx.x * SPB < SPB) ? B - blockIdx.x * SPB : SPB;
-    const int per_row = D / 8; // 16-byte pieces per row
-    const int total = rows * per_row;
-    const uint16_t *xb = X + (int64_t)blockIdx.x * SPB * D; // the block's rows are contiguous
-    uint16_t *ob = X2 + (int64_t)blockIdx.x * SPB * D;
-    for (int q0 = threadIdx.x; q0 < total; q0 += 4 * SM_CF_NT) {
-        uint4 v[4];
+    auto scaled = [](uint32_t v, float f) __attribute__((always_inline)) { return ks_pack_bf2(ks_bf2f(v & 0xFFFFu) * f, ks_bf2f(v >> 16) * f); };
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (q0 + u * SM_CF_NT < total) v[u] = *(const uint4 *)(xb + (int64_t)(q0 + u * SM_CF_NT) * 8);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int q = q0 + u * SM_CF_NT;
-            if (q < total) {
-                const float f = s_inv[q / per_row];
-                uint4 o;
-                o.x = ks_pack_bf2(ks_bf2f(v[u].x & 0xFFFFu) * f, ks_bf2f(v[u].x >> 16) * f);
-                o.y = ks_pack_bf2(ks_bf2f(v[u].y & 0xFFFFu) * f, ks_bf2f(v[u].y >> 16) * f);
-                o.z = ks_pack_bf2(ks_bf2f(v[u].z & 0xFFFFu) * f, ks_bf2f(v[u].z >> 16) * f);
-                o.w = ks_pack_bf2(ks_bf2f(v[u].w & 0xFFFFu) * f, ks_bf2f(v[u].w >> 16) * f);
-                *(uint4 *)(ob + (int64_t)q * 8) = o;
-            }
+    for (int u = 0; u < U; ++u) {
+        const int q = u * NT + threadIdx.x;
+        if (q < total) {
+            const float f = s_inv[q / per_row], c = s_cell[q / per_row];
+            *(uint4 *)(job.X2 + first + (int64_t)q * 8) = make_uint4(scaled(x[u].x, f), scaled(x[u].y, f), scaled(x[u].z, f), scaled(x[u].w, f));
+            float4 *e = (float4 *)(job.extra + first + (int64_t)q * 8);
+            e[0] = make_float4(c * ks_bf2f(w[u].x & 0xFFFFu), c * ks_bf2f(w[u].x >> 16), c * ks_bf2f(w[u].y & 0xFFFFu), c * ks_bf2f(w[u].y >> 16));
+            e[1] = make_float4(c * ks_bf2f(w[u].z & 0xFFFFu), c * ks_bf2f(w[u].z >> 16), c * ks_bf2f(w[u].w & 0xFFFFu), c * ks_bf2f(w[u].w >> 16));
         }
     }
+}
+// the same as a launch of its own: the first call of a softmax split over nodes ends with it
+__global__ void __launch_bounds__(SM_CF_NT)
+sm_combine_fused_kernel(SmCombine job, const int32_t *__restrict__ n_active_p, int M, int B, int Bp, const int32_t *__restrict__ active_idx,
+                        const uint16_t *__restrict__ W) {
+    __shared__ float sh[2 * SM_CF_NT + 4 * SM_CF_FEW];
+    sm_combine<SM_CF_NT, SM_CF_FEW>(job, blockIdx.x, n_active_p, M, B, Bp, active_idx, W, sh);
 }
 
 // one wavefront per sample: merge the per-slab (max, sum) pairs in slab order -> lse_i, loss_i
@@ -867,17 +877,23 @@ template <class T>
 __global__ void __launch_bounds__(T::NT)
 dx_partial_async_kernel(const uint16_t *__restrict__ dZ8, int Bp, const uint16_t *__restrict__ W,
                         const int32_t *__restrict__ active_idx, const int32_t *__restrict__ n_active_p, int B, int D, int M,
-                        int S, float *__restrict__ part, KsSelNext next) {
+                        int S, float *__restrict__ part, SmCombine comb, KsSelNext next) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[T::LDS_ELEMS];
     __shared__ int32_t s_idx[DxIdx<T>::CAP];
+    const int bid = (int)blockIdx.x - comb.blocks;
+    if (bid < 0) { // blocks before the tiles: the one-sweep softmax's combine step
+        if (comb.many) sm_combine<T::NT, SM_CF_MANY>(comb, (int)blockIdx.x, n_active_p, M, B, Bp, active_idx, W, (float *)lds);
+        else sm_combine<T::NT, SM_CF_FEW>(comb, (int)blockIdx.x, n_active_p, M, B, Bp, active_idx, W, (float *)lds);
+        return;
+    }
     const int n_active = sm_clamp_n(n_active_p, M);
     const int tiles_m = (B + T::BM - 1) / T::BM, tiles_n = (D + T::BN - 1) / T::BN;
     const int n_tiles = tiles_m * tiles_n;
-    if ((int)blockIdx.x >= n_tiles * S) { // blocks behind the tiles: the next batch's candidates are staged (if asked for)
-        ks_sel_next_fetch<T::NT>(next, (int)blockIdx.x - n_tiles * S);
+    if (bid >= n_tiles * S) { // blocks behind the tiles: the next batch's candidates are staged (if asked for)
+        ks_sel_next_fetch<T::NT>(next, bid - n_tiles * S);
         return;
     }
-    const int L = ks_xcd_remap(blockIdx.x, n_tiles * S);
+    const int L = ks_xcd_remap(bid, n_tiles * S);
     const int s = L / n_tiles, t = L % n_tiles;
     const int tm = t % tiles_m, tn = t / tiles_m;
     const int nk = (n_active + 63) / 64;
@@ -947,6 +963,12 @@ struct DwUpdate {
     const int32_t *idx;
     float alpha;
 };
+// Entries of the logit gradient that are not in the stored array (its place holds 0): sample i has the bf16 value val[i] in row
+// pos[i] (-1: none).  pos == nullptr: the array is complete.
+struct DwCells {
+    const int32_t *pos;
+    const uint32_t *val;
+};
 // Shape of the dW tiles for n_active rows on a chip of n_cu compute units (one tile per compute unit at a time); the launch
 // has workgroups for tiles_max of them.  A tile is a chain -- its k-tiles, then its part of the update, round trip after round
 // trip -- so with few rows the smallest tiles that still fit the chip in one round are the fastest; tall tiles load the X panel
@@ -974,17 +996,19 @@ __device__ __forceinline__ int dw_tile_kind(int n_active, int D, int n_cu, int t
     return best;
 }
 
-// LDS of the launch: a tile's stages and its rows' classes, or the bitmap of the next batch's selection
-constexpr int DW_LDS_ELEMS = TileDw::LDS_ELEMS + 2 * TileDw::BM > 2 * SEL1_LDS_WORDS ? TileDw::LDS_ELEMS + 2 * TileDw::BM : 2 * SEL1_LDS_WORDS;
+// LDS of the launch: a tile's stages, its rows' classes and its k-tiles' cells, or the bitmap of the next batch's selection
+#define DW_CELL_SLOTS 4 /* k-tiles whose cells lie in LDS */
+constexpr int DW_TILE_ELEMS = TileDw::LDS_ELEMS + 2 * (TileDw::BM + DW_CELL_SLOTS * 128);
+constexpr int DW_LDS_ELEMS = DW_TILE_ELEMS > 2 * SEL1_LDS_WORDS ? DW_TILE_ELEMS : 2 * SEL1_LDS_WORDS;
 template <class T>
 __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
-                                        const DwUpdate &up);
+                                        const DwUpdate &up, const DwCells &cells);
 
 __global__ void __launch_bounds__(TileDw::NT)
 dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B, int Bp,
                 const int32_t *__restrict__ n_active_p, int D, int M, int64_t Mp, float scale, float *__restrict__ dW,
-                int tiles_max, int n_cu, DxReduceJob job, DwUpdate up, KsSelNext next) {
+                int tiles_max, int n_cu, DxReduceJob job, DwUpdate up, DwCells cells, KsSelNext next) {
     typedef TileDw T;
     __shared__ __attribute__((aligned(16))) uint16_t lds[DW_LDS_ELEMS];
     // The first next.nsel workgroups select the NEXT batch's active classes (Algorithm 1 needs only its labels): with a
@@ -1025,7 +1049,7 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
     }
     const int n_active = sm_clamp_n(n_active_p, M);
     const int kind = dw_tile_kind(n_active, D, n_cu, tiles_max);
-#define DW_TILE(T) dw_tile<T>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up)
+#define DW_TILE(T) dw_tile<T>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up, cells)
     if (kind == 0) DW_TILE(TileDw);
     else if (kind == 1) DW_TILE(TileDw192);
     else if (kind == 2) DW_TILE(TileDw128);
@@ -1037,14 +1061,14 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
 template <class T>
 __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
-                                        const DwUpdate &up) {
+                                        const DwUpdate &up, const DwCells &cells) {
     const int tiles_n = (D + T::BN - 1) / T::BN;
     const int n_tiles = tiles_n * ((n_active + T::BM - 1) / T::BM);
     if (bid >= n_tiles) return;
     const int t = ks_xcd_remap(bid, n_tiles);
     const int tn = t % tiles_n, tm = t / tiles_n;
     // the classes of the tile's rows, for the update: requested before the first k-tile, straight into LDS behind the stages
-    static_assert(T::NT == TileDw::NT && T::LDS_ELEMS + 2 * T::BM <= DW_LDS_ELEMS, "one launch shape for all tiles");
+    static_assert(T::NT == TileDw::NT && T::LDS_ELEMS + 2 * (T::BM + DW_CELL_SLOTS * 128) <= DW_LDS_ELEMS, "one launch shape for all tiles");
     int32_t *s_cls = (int32_t *)(lds + T::LDS_ELEMS);
     if (up.Wm && threadIdx.x < T::BM) {
         const int a = tm * T::BM + (int)threadIdx.x;
@@ -1057,8 +1081,36 @@ __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *
     br.init(X, D, nullptr, tn * T::BN, D, B, 0);
     f32x16_t acc[T::FM][T::FN];
     ks_a_clear<T>(acc);
+    // Cells: lane l of a wavefront looks after sample l of the k-tile and the rows that the wavefront reads, so that its own
+    // write before its own fragment reads is all the order it takes (wavefronts that share the rows write the same value).
+    // The k-tiles' cells are requested two k-tiles ahead, by one wavefront each, and looked at one ahead.
+    int32_t *const s_cells = s_cls + T::BM; // [slot][pos, val][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nk = (B + 63) / 64;
+    const int m_first = tm * T::BM + wave / T::WAVES_N * T::WM; // the wavefront's first row
+    auto cells_request = [&](int kt) __attribute__((always_inline)) {
+        if (wave < 2 && kt < nk)
+            __builtin_amdgcn_global_load_lds(KS_GPTR((wave ? (const int32_t *)cells.val : cells.pos) + kt * 64 + lane),
+                                             KS_LPTR(s_cells + ((kt & (DW_CELL_SLOTS - 1)) * 2 + wave) * 64), 4, 0, 0);
+    };
+    int pos_next = -1; // of the lane's sample in the next k-tile; as read (a wait for it would stand here otherwise)
+    auto place = [&](int kt, uint16_t *st) __attribute__((always_inline)) {
+        if (!cells.pos) return;
+        const int32_t *const here = s_cells + (kt & (DW_CELL_SLOTS - 1)) * 128 + lane;
+        const int pos = (kt == 0 ? here[0] : pos_next) - m_first;
+        pos_next = s_cells[((kt + 1) & (DW_CELL_SLOTS - 1)) * 128 + lane]; // (beyond the last k-tile: not used)
+        if ((unsigned)pos < (unsigned)T::WM && kt * 64 + lane < B) {
+            const int m = wave / T::WAVES_N * T::WM + pos;
+            // (as assembly, like the reads that must come after it)
+            asm volatile("ds_write_b16 %0, %1" ::"v"(ks_lds_addr(st + (m >> 3) * KS_M8_SLAB + lane * 8 + (m & 7))), "v"(here[64]) : "memory");
+        }
+        cells_request(kt + 2);
+    };
+    if (cells.pos) {
+        cells_request(0);
+        cells_request(1);
+    }
     // (samples B .. of the last k-tile: zeros of dZ8 meet the last row of X)
-    ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, (B + 63) / 64, lds, acc);
+    ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, nk, lds, acc, place);
     // epilogue, row-wise through LDS: gradient rows out (if wanted) and, if asked for, the update of the master
     // rows and of their 16-bit copy.  Up to four rows per thread are in flight at a time, the next ones requested before
     // the present ones are stored (and the first before the slab is staged): 192 x 256 tiles of 17,425 rows 43 -> 40 us,
@@ -1249,6 +1301,8 @@ struct SmWs {
     float *pm, *pl, *zt; // fast path: per class-tile softmax statistics, target logits
     float *inv;          // one-sweep softmax: 1 / sum_a exp(z_ia - scale) per sample
     uint16_t *X2;        // one-sweep softmax: rows of X scaled by that
+    int32_t *cell_pos;   // one-sweep softmax: the target entries (DwCells)
+    uint32_t *cell;
     int S;
     int64_t Mp;
     int Bp;
@@ -1295,11 +1349,13 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
     w.S = sm_splits(B, D, M, w.fast);
     w.select = with_select ? (void *)ar.take<char>(ks_select_ws_bytes(C, B, K)) : nullptr;
     w.lse = ar.take<float>((size_t)B);
-    w.part = ar.take<float>((size_t)w.S * B * D);
+    w.part = ar.take<float>((size_t)(w.S + (fast ? 1 : 0)) * B * D); // (the one-sweep softmax adds a product: SmCombine)
     w.Z = nullptr;
     w.dZ = w.dZ8 = nullptr;
     w.pm = w.pl = w.zt = w.inv = nullptr;
     w.X2 = nullptr;
+    w.cell_pos = nullptr;
+    w.cell = nullptr;
     if (w.fast) {
         w.dZ8 = ar.take<uint16_t>((size_t)w.Mp * w.Bp);
         size_t nt = (size_t)(w.Mp / TileSm::BM);
@@ -1309,6 +1365,8 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
         w.zt = ar.take<float>((size_t)w.Bp);
         w.inv = ar.take<float>((size_t)w.Bp);
         w.X2 = ar.take<uint16_t>((size_t)w.Bp * D);
+        w.cell_pos = ar.take<int32_t>((size_t)w.Bp);
+        w.cell = ar.take<uint32_t>((size_t)w.Bp);
     } else {
         w.Z = ar.take<float>((size_t)B * w.Mp);
         w.dZ = ar.take<uint16_t>((size_t)B * w.Mp);
@@ -1356,6 +1414,8 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
     const int Mi = (int)M;
     const float g = grad_scale / (float)B;
     bool fused = false;
+    SmCombine comb = SmCombine();
+    int S = w.S; // shares of the active classes in dX
     if (w.fast) {
         const int tiles_s = (int)ks_ceil_div(B, 256);
         const bool soe = sm_sweeps(D, B, scale, grad_scale);
@@ -1376,14 +1436,39 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             }
 #undef SM_FUSED_LAUNCH
             mark(2);
-            hipLaunchKernelGGL(sm_combine_fused_kernel, dim3((unsigned)ks_ceil_div(B, SM_CF_SPB)), dim3(SM_CF_NT), 0, st, w.pl,
-                               w.pm, n_active, active_idx, target_pos, X, W, Mi, slabs, B, w.Bp, D, scale, w.inv, loss_per_sample,
-                               w.dZ8, w.X2, dev_status, mode, io);
-            mark(3);
+            comb.pl = w.pl;
+            comb.pl_others = w.pm;
+            comb.slabs = slabs;
+            comb.D = D;
+            comb.target_pos = target_pos;
+            comb.X = X;
+            comb.scale = scale;
+            comb.inv_sum = w.inv;
+            comb.loss_i = loss_per_sample;
+            comb.X2 = w.X2;
+            comb.cell_pos = w.cell_pos;
+            comb.cell = w.cell;
+            comb.dev_status = dev_status;
+            comb.mode = mode;
+            comb.io = io;
+            // Beside narrow dX tiles, two to a compute unit, all workgroups should run at once: few samples each if there is
+            // room, or else many, and a twelfth less shares for the tiles if that does it.  (B = 1,024, D = 512: combine and dX
+            // 37.0 us one after the other; 33.8 with 16 shares beside 128 workgroups, 32.1 with 15 beside 32.)
+            const bool wide = sm_dx_wide(B, D, M);
+            const int tiles = (int)(ks_ceil_div(B, TileDx::BM) * ks_ceil_div(D, TileDx::BN)), slots = 2 * 256;
+            comb.many = mode != SM_EXPORT && (wide || tiles * S + ks_ceil_div(B, SM_CF_FEW) > slots);
+            comb.blocks = (int)ks_ceil_div(B, comb.many ? SM_CF_MANY : SM_CF_FEW);
+            const int fit = (slots - comb.blocks) / tiles; // shares that leave room
+            if (!wide && tiles * S <= slots && fit < S && fit >= S - S / 12 && (int64_t)fit * DxIdx<TileDx>::CAP >= M) S = fit;
+            comb.extra = w.part + (int64_t)S * B * D;
             if (mode == SM_EXPORT) {
+                hipLaunchKernelGGL(sm_combine_fused_kernel, dim3((unsigned)comb.blocks), dim3(SM_CF_NT), 0, st, comb, n_active, Mi, B,
+                                   w.Bp, active_idx, W);
+                mark(3);
                 KS_LAUNCH_CHECK();
                 return KS_OK;
             }
+            mark(3);
         } else if (soe) {
             if (mode != SM_IMPORT) {
 #define SM_STATS_LAUNCH(CFG)                                                                                              \
@@ -1436,8 +1521,8 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
                 typedef decltype(tile) T;
                 const int tiles = (int)(ks_ceil_div(B, T::BM) * ks_ceil_div(D, T::BN));
                 if (next.nsel) next.nfetch = (int)ks_ceil_div((int64_t)next.B * (next.K + 1), (int64_t)T::NT);
-                hipLaunchKernelGGL(dx_partial_async_kernel<T>, dim3(tiles * w.S + next.nfetch), dim3(T::NT), 0, st, w.dZ8, w.Bp,
-                                   W, active_idx, n_active, B, D, Mi, w.S, w.part, next);
+                hipLaunchKernelGGL(dx_partial_async_kernel<T>, dim3(comb.blocks + tiles * S + next.nfetch), dim3(T::NT), 0, st, w.dZ8,
+                                   w.Bp, W, active_idx, n_active, B, D, Mi, S, w.part, comb, next);
             };
             if (sm_dx_wide(B, D, M)) dx(TileDxWide());
             else dx(TileDx());
@@ -1452,7 +1537,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             if (tiles < n_cu) tiles = least < n_cu ? least : n_cu;
             DxReduceJob job;
             job.part = w.part;
-            job.S = w.S;
+            job.S = S + (fused ? 1 : 0);
             job.BD = (int64_t)B * D;
             job.scale = fused ? scale * g : scale;
             job.row_factor = fused ? w.inv : nullptr;
@@ -1461,7 +1546,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             job.loss_mean = loss_mean;
             hipLaunchKernelGGL(dw_async_kernel, dim3(next.nsel + tiles + DW_REDUCE_BLOCKS), dim3(T::NT), 0, st, w.dZ8,
                                fused ? w.X2 : X, B, w.Bp, n_active, D, Mi, w.Mp, fused ? scale * g : scale, dW_active, tiles,
-                               n_cu, job, up, next);
+                               n_cu, job, up, fused ? DwCells{w.cell_pos, w.cell} : DwCells(), next);
         }
         mark(7);
         KS_LAUNCH_CHECK();

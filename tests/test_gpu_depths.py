@@ -356,3 +356,19 @@ def test_gradient_rows_and_update_in_every_tile_shape(ks, orc, D, A, B):
     check_rows(out["dW_active"][:A].cpu().numpy(), ref["dWA"], floors[1], "dW")
     assert bool((out["dW_active"][A:] == 123.0).all())
     assert torch.equal(Wm, Wm2) and torch.equal(Wb, Wb2) and not torch.equal(Wm, dev(W))
+
+
+@pytest.mark.parametrize("C,D,B,K,M", [(300, 128, 7, 3, 40), (400, 512, 1, 5, 9), (2000, 256, 8, 6, 70),   # eight samples to a workgroup
+                                       (3000, 512, 1000, 1, 1500), (2500, 256, 1024, 1, 1300),             # 32, and fewer shares for dX
+                                       (2500, 512, 1030, 1, 1200), (2200, 128, 2001, 0, 2001)])            # 32, shares as they are
+def test_one_sweep_combine_beside_the_dx_tiles(ks, orc, C, D, B, K, M):
+    """Unit rows: the combine step in workgroups beside the dX tiles, with few and with many samples each, batches that end
+    inside a workgroup; confident samples, whose target entries (put into dW's tiles, added to dX) carry the gradient."""
+    from test_gpu_parity import run_and_compare
+    print(f"[depths] combine D={D} B={B}", flush=True)
+    W, X = synth.unit_rows(51, synth.TID_W, C, D, bf16=True), synth.unit_rows(51, synth.TID_X, B, D, bf16=True)
+    y = synth.labels_uniform(51, B, C)
+    y[B // 2:] = y[: B - B // 2]                                                      # classes with several samples
+    G = ((np.arange(C)[:, None] * 7 + 1 + np.arange(K)[None, :] * 13) % C).astype(np.int32)
+    X[::3] = synth.bf16_round((0.8 * W[y[::3]] + 0.2 * X[::3]).astype(np.float32))
+    run_and_compare(ks, orc, W, X, y, G, C, M, scale=30.0, grad_scale=4.0, tag=f"D={D} B={B}", modes=(True,))
