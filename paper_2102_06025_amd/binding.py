@@ -70,8 +70,10 @@ def _ptr(t):
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ct.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ct.c_void_p(stream.cuda_stream)
+    # the handle alone: a Stream object costs 3 us, as much as two launches
+    return ct.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _check(fn, rc):
@@ -89,9 +91,7 @@ def _dtype_code(t):
     return 0 if t.dtype == torch.bfloat16 else 1  # KS_DTYPE_BF16 / KS_DTYPE_FP32
 
 
-def _ws(nbytes, device, ws):
-    if ws is not None:
-        return ws
+def _ws(nbytes, device):
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
@@ -126,12 +126,11 @@ def knn_graph_build(W, K, want_sims=False, graph=None, sims=None, ws=None, dev_s
     if not (W.is_cuda and W.is_contiguous() and W.dim() == 2):
         raise TypeError("W must be a contiguous 2-D device tensor")
     C, D = W.shape
-    need = knn_graph_build_workspace(C, D, K, dtype)
     if graph is None:
         graph = torch.empty((C, K), dtype=torch.int32, device=W.device)
     if want_sims and sims is None:
         sims = torch.empty((C, K), dtype=torch.float32, device=W.device)
-    ws = _ws(need, W.device, ws)
+    ws = ws if ws is not None else _ws(knn_graph_build_workspace(C, D, K, dtype), W.device)
     dev_status = _status(W.device, dev_status)
     rc = lib().knn_graph_build(_ptr(W), ct.c_int(dtype), ct.c_int64(C), ct.c_int(D), ct.c_int(K), _ptr(graph),
                                _ptr(sims), _ptr(ws), ct.c_size_t(ws.numel()), _ptr(dev_status), _stream(stream))
@@ -154,7 +153,7 @@ def knn_select_active(labels, graph, C, M, ws=None, dev_status=None, stream=None
     active_idx = torch.empty(M, dtype=torch.int32, device=dev)
     n_active = torch.empty(1, dtype=torch.int32, device=dev)
     target_pos = torch.empty(B, dtype=torch.int32, device=dev)
-    ws = _ws(knn_select_workspace(C, B, K, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_select_workspace(C, B, K, M), dev)
     dev_status = _status(dev, dev_status)
     rc = lib().knn_select_active(_ptr(labels), _ptr(graph), ct.c_int64(C), ct.c_int(B), ct.c_int(K), ct.c_int(M),
                                  _ptr(active_idx), _ptr(n_active), _ptr(target_pos), _ptr(ws),
@@ -234,7 +233,7 @@ def knn_softmax_fwd_bwd(W_bf16, X_bf16, labels, graph, M, scale, grad_scale=1.0,
                    loss_mean=torch.empty(1, dtype=torch.float32, device=dev),
                    dX=torch.empty((B, D), dtype=torch.float32, device=dev),
                    dW_active=torch.empty((M, D), dtype=torch.float32, device=dev))
-    ws = _ws(knn_softmax_workspace(C, D, B, K, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_softmax_workspace(C, D, B, K, M), dev)
     dev_status = _status(dev, dev_status if dev_status is not None else out.get("dev_status"))
     out["dev_status"] = dev_status
     out["ws"] = ws
@@ -272,7 +271,7 @@ def knn_softmax_fwd_bwd_update(W_master, W_bf16, X_bf16, labels, graph, M, scale
                    loss_mean=torch.empty(1, dtype=torch.float32, device=dev),
                    dX=torch.empty((B, D), dtype=torch.float32, device=dev),
                    dW_active=torch.empty((M, D), dtype=torch.float32, device=dev) if (want_dW or D % 64) else None)
-    ws = _ws(knn_softmax_workspace(C, D, B, K, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_softmax_workspace(C, D, B, K, M), dev)
     dev_status = _status(dev, dev_status if dev_status is not None else out.get("dev_status"))
     out["dev_status"] = dev_status
     out["ws"] = ws
@@ -311,7 +310,7 @@ def knn_softmax_fwd_bwd_update_selected(W_master, W_bf16, X_bf16, active_idx, n_
                    loss_mean=torch.empty(1, dtype=torch.float32, device=dev),
                    dX=torch.empty((B, D), dtype=torch.float32, device=dev),
                    dW_active=torch.empty((M, D), dtype=torch.float32, device=dev) if need_dW else None)
-    ws = _ws(knn_softmax_selected_workspace(C, D, B, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_softmax_selected_workspace(C, D, B, M), dev)
     dev_status = _status(dev, dev_status if dev_status is not None else out.get("dev_status"))
     out["dev_status"], out["ws"] = dev_status, ws
     rc = lib().knn_softmax_fwd_bwd_update_selected(_ptr(W_master), _ptr(W_bf16), _ptr(X_bf16), _ptr(active_idx), _ptr(n_active),
@@ -354,7 +353,7 @@ def knn_softmax_fwd_bwd_update_selected_next(W_master, W_bf16, X_bf16, active_id
                    dW_active=torch.empty((M, D), dtype=torch.float32, device=dev) if need_dW else None)
     if next_out is None:
         next_out = dict(active_idx=active_idx, n_active=n_active, target_pos=target_pos)
-    ws = _ws(knn_softmax_selected_next_workspace(C, D, B, K, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_softmax_selected_next_workspace(C, D, B, K, M), dev)
     dev_status = _status(dev, dev_status if dev_status is not None else out.get("dev_status"))
     out["dev_status"], out["ws"] = dev_status, ws
     rc = lib().knn_softmax_fwd_bwd_update_selected_next(
@@ -387,7 +386,7 @@ def full_softmax_fwd_bwd(W_bf16, X_bf16, labels, scale, grad_scale=1.0, out=None
                    loss_mean=torch.empty(1, dtype=torch.float32, device=dev),
                    dX=torch.empty((B, D), dtype=torch.float32, device=dev),
                    dW=torch.empty((C, D), dtype=torch.float32, device=dev))
-    ws = _ws(full_softmax_workspace(C, D, B), dev, ws)
+    ws = ws if ws is not None else _ws(full_softmax_workspace(C, D, B), dev)
     dev_status = _status(dev, dev_status if dev_status is not None else out.get("dev_status"))
     out["dev_status"] = dev_status
     out["ws"] = ws
@@ -417,7 +416,7 @@ def apply_weight_grad(W_master, W_bf16, idx, n, dW, alpha, idx_sorted_unique=Fal
     n_max = idx.numel()
     if dW.shape[0] < n_max or dW.shape[1] != D:
         raise ValueError("dW must be [n_max, D]")
-    ws = _ws(apply_weight_grad_workspace(C, D, n_max, idx_sorted_unique), W_master.device, ws)
+    ws = ws if ws is not None else _ws(apply_weight_grad_workspace(C, D, n_max, idx_sorted_unique), W_master.device)
     dev_status = _status(W_master.device, dev_status)
     rc = lib().apply_weight_grad(_ptr(W_master), _ptr(W_bf16), _ptr(idx), _ptr(n), ct.c_int(n_max), _ptr(dW),
                                  ct.c_float(alpha), ct.c_int64(C), ct.c_int(D), ct.c_int(int(idx_sorted_unique)),
@@ -485,7 +484,7 @@ def apply_weight_grad_normalized(W_master, W_hat_bf16, inv_norm, idx, n, dW_hat,
     n_max = idx.numel()
     if dW_hat.shape[0] < n_max or dW_hat.shape[1] != D:
         raise ValueError("dW_hat must be [n_max, D]")
-    ws = _ws(apply_weight_grad_normalized_workspace(C, D, n_max, idx_sorted_unique), W_master.device, ws)
+    ws = ws if ws is not None else _ws(apply_weight_grad_normalized_workspace(C, D, n_max, idx_sorted_unique), W_master.device)
     dev_status = _status(W_master.device, dev_status)
     rc = lib().apply_weight_grad_normalized(_ptr(W_master), _ptr(W_hat_bf16), _ptr(inv_norm), _ptr(idx), _ptr(n),
                                             ct.c_int(n_max), _ptr(dW_hat), ct.c_float(alpha), ct.c_int64(C), ct.c_int(D),
@@ -504,7 +503,7 @@ def knn_graph_compress(graph, c0, C_loc, dev_status=None, stream=None):
     dev = graph.device
     counts = torch.empty(Cg, dtype=torch.int32, device=dev)
     offsets = torch.empty(Cg + 1, dtype=torch.int64, device=dev)
-    ws = _ws(int(lib().knn_graph_compress_workspace(ct.c_int64(Cg), ct.c_int(K))), dev, None)
+    ws = _ws(int(lib().knn_graph_compress_workspace(ct.c_int64(Cg), ct.c_int(K))), dev)
     dev_status = _status(dev, dev_status)
 
     def call(flat, cap):
@@ -541,7 +540,7 @@ def knn_select_active_csr(labels, counts, offsets, flat, c0, C_loc, K_max, M, pa
                n_active=torch.empty(1, dtype=torch.int32, device=dev),
                n_found=torch.empty(1, dtype=torch.int32, device=dev),
                target_pos=torch.empty(B, dtype=torch.int32, device=dev))
-    ws = _ws(knn_select_active_csr_workspace(C_loc, B, K_max, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_select_active_csr_workspace(C_loc, B, K_max, M), dev)
     dev_status = _status(dev, dev_status)
     out["dev_status"] = dev_status
     rc = lib().knn_select_active_csr(_ptr(labels), _ptr(counts), _ptr(offsets), _ptr(flat if flat.numel() else None),
@@ -573,7 +572,7 @@ def knn_graph_update(W_local, W_visit, local_offset, visit_offset, graph, sims, 
     if W_visit.shape[1] != D or tuple(graph.shape) != (C_loc, K) or tuple(sims.shape) != (C_loc, K):
         raise ValueError("shapes: W_visit [C_vis, D], graph and sims [C_loc, K]")
     dtype = _dtype_code(W_local)
-    ws = _ws(knn_graph_update_workspace(C_loc, C_vis, D, K, dtype), W_local.device, ws)
+    ws = ws if ws is not None else _ws(knn_graph_update_workspace(C_loc, C_vis, D, K, dtype), W_local.device)
     dev_status = _status(W_local.device, dev_status)
     rc = lib().knn_graph_update(_ptr(W_local), _ptr(W_visit), ct.c_int(dtype), ct.c_int64(C_loc), ct.c_int64(C_vis),
                                 ct.c_int(D), ct.c_int(K), ct.c_int64(local_offset), ct.c_int64(visit_offset), _ptr(graph),
@@ -600,7 +599,7 @@ def knn_softmax_fwd_stats(W_bf16, X_bf16, active_idx, n_active, target_pos, scal
         out = dict(row_max=torch.empty(B, dtype=torch.float32, device=dev),
                    row_sumexp=torch.empty(B, dtype=torch.float32, device=dev),
                    target_logit=torch.empty(B, dtype=torch.float32, device=dev))
-    ws = _ws(knn_softmax_split_workspace(C, D, B, M), dev, ws)
+    ws = ws if ws is not None else _ws(knn_softmax_split_workspace(C, D, B, M), dev)
     dev_status = _status(dev, dev_status)
     out["ws"], out["dev_status"] = ws, dev_status
     rc = lib().knn_softmax_fwd_stats(_ptr(W_bf16), _ptr(X_bf16), _ptr(active_idx), _ptr(n_active), _ptr(target_pos),
@@ -737,7 +736,7 @@ def grad_topk_select(g, plan: GradTopkPlan, out_idx=None, out_val=None, ws=None,
     _need(out_val, torch.float32, "out_val")
     if g.numel() < int(plan.host[5]) or out_idx.numel() < plan.n_out or out_val.numel() < plan.n_out:
         raise ValueError("g, out_idx or out_val is smaller than the plan requires")
-    ws = _ws(plan.ws_bytes, g.device, ws)
+    ws = ws if ws is not None else _ws(plan.ws_bytes, g.device)
     _check("grad_topk_select", lib().grad_topk_select(_ptr(g), _ptr(plan.dev), plan.host.ctypes.data_as(ct.c_void_p),
                                                       _ptr(out_idx), _ptr(out_val), _ptr(ws), ct.c_size_t(ws.numel()),
                                                       _stream(stream)))
