@@ -2,7 +2,7 @@
 // similarity; 16-bit matrix-core pass that recalls k' > K candidates, then an exact re-rank).
 //
 //   prepare   bf16 copy of W when the input is fp32; row norms and their maximum (for the error bound); the sampled rows
-//   threshold (K <= 64, D <= 512) per row the 8th, 10th or 12th largest similarity to a sample of one in 32 of the searched rows: what lies below
+//   threshold (K <= 64, D <= 512) per row the 8th, 10th or 12th largest similarity to a sample of one in 32 (or 16) of the searched rows: what lies below
 //             it is not recalled.  Some 256 to 384 rows lie above it, whatever the data (an order statistic).
 //   recall    each workgroup keeps a block of 256 rows resident and streams rows of W by them: bf16 MFMA tiles of
 //             similarities; an element above its row's threshold is appended to one of the row's candidate segments.
@@ -91,6 +91,7 @@ struct GrPrepJob {
     float *blockmax; // largest norm seen by each of this job's workgroups
     uint16_t *Ws;    // [n_sample, D] rows picked by gr_sample_row, or nullptr
     int64_t n_sample;
+    int every;       // rows per sampled row
     int blocks;
 };
 struct GrClear {
@@ -99,10 +100,9 @@ struct GrClear {
     float *thf; // thresholds of the padding rows [pad0, pad1): nothing passes
     int64_t pad0, pad1;
 };
-#define GR_SYM_RATIO 32          /* rows of W per sampled row */
-// rows sampled: one of every 32 consecutive rows, at a position that varies from one run of 32 rows to the next
-__device__ __forceinline__ int64_t gr_sample_row(int64_t s) {
-    return s * GR_SYM_RATIO + (int64_t)(((uint32_t)s * 2654435761u) >> 16) % GR_SYM_RATIO;
+// rows sampled: one of every 32 (or 16) consecutive rows, at a position that varies from one run of rows to the next
+__device__ __forceinline__ int64_t gr_sample_row(int64_t s, int every) { // every: a power of two
+    return s * every + (int64_t)((((uint32_t)s * 2654435761u) >> 16) & (uint32_t)(every - 1));
 }
 template <typename IN>
 __global__ void __launch_bounds__(GR_NT)
@@ -125,6 +125,7 @@ gr_prepare_kernel(GrPrepJob job0, GrPrepJob job1, int D, GrClear clr) {
     const int l = lane & (lpr - 1), rpw = 64 / lpr;
     const int64_t stride = (int64_t)job.blocks * (GR_NT / 64) * rpw;
     const IN *__restrict__ W = (const IN *)job.W;
+    const int every_log = job.Ws ? __builtin_ctz(job.every) : 0;
     float mx = 0.f;
     for (int64_t i0 = ((int64_t)bid * (GR_NT / 64) + wave) * rpw + lane / lpr; i0 < job.C; i0 += U * stride) {
         float s[U];
@@ -133,8 +134,8 @@ gr_prepare_kernel(GrPrepJob job0, GrPrepJob job1, int D, GrClear clr) {
         for (int u = 0; u < U; ++u) {
             const int64_t i = i0 + u * stride;
             s[u] = 0.f;
-            const int64_t sm = i / GR_SYM_RATIO;
-            pick[u] = job.Ws && sm < job.n_sample && gr_sample_row(sm) == i;
+            const int64_t sm = i >> every_log;
+            pick[u] = job.Ws && sm < job.n_sample && gr_sample_row(sm, job.every) == i;
         }
         for (int d = l * EPL; d < D; d += lpr * EPL) {
             uint4 v[U];
@@ -155,7 +156,7 @@ gr_prepare_kernel(GrPrepJob job0, GrPrepJob job1, int D, GrClear clr) {
                         s[u] = fmaf(lo, lo, s[u]);
                         s[u] = fmaf(hi, hi, s[u]);
                     }
-                    if (pick[u]) *(uint4 *)(job.Ws + (i / GR_SYM_RATIO) * D + d) = v[u];
+                    if (pick[u]) *(uint4 *)(job.Ws + (i >> every_log) * D + d) = v[u];
                 } else {
                     float f[4];
 #pragma unroll
@@ -165,7 +166,7 @@ gr_prepare_kernel(GrPrepJob job0, GrPrepJob job1, int D, GrClear clr) {
                     }
                     const uint2 b = make_uint2(ks_pack_bf2(f[0], f[1]), ks_pack_bf2(f[2], f[3]));
                     *(uint2 *)(job.Wb + i * D + d) = b;
-                    if (pick[u]) *(uint2 *)(job.Ws + (i / GR_SYM_RATIO) * D + d) = b;
+                    if (pick[u]) *(uint2 *)(job.Ws + (i >> every_log) * D + d) = b;
                 }
             }
         }
@@ -542,7 +543,8 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 //
 // A first sweep (gr_threshold_kernel) finds for every row its r-th largest similarity to a sample of one in 32 of the
 // searched rows; r = 8 for K <= 16, 10 for K <= 32, 12 for K <= 64.  The number of searched rows at or above it is
-// 32 * Gamma(r) whatever their distribution (an order statistic of a uniform sample): 256, 320 or 384 on average.  The
+// 32 * Gamma(r) whatever their distribution (an order statistic of a uniform sample): 256, 320 or 384 on average.
+// (Smaller builds: one in 16, see gr_every.)  The
 // largest K of each r is the worst case: beyond 1,152, 1,280 and 1,408 (what a row's segments take, see GrSegs) for less than
 // five rows in a billion; at most K (then r of the row's K + 1 best would have to be in the sample) for 0.1 to 1.4 in a
 // million, and for 1.0, 1.1 and 8.3 in a million of the rows that are in their own sample.
@@ -555,7 +557,8 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 #define GR_SYM_Q 512             /* symmetric sweep: slots of a candidate segment (one lane's hits) */
 #define GR_SYM_SCAP 1024         /* slots of the stream-side segment */
 #define GR_MAX_CAND 2048         /* candidates of a row that the ranking takes */
-#define GR_SYM_RANK 12           /* places of the sorted list that finds a row's threshold */
+#define GR_RANK 12               /* places of the sorted list that finds a row's threshold */
+#define GR_SAMPLE_PARTS 8        /* workgroups per block of resident rows that search the sample, at most */
 #define GR_MAX_PARTS 24
 #define GR_CUS 256               /* compute units that the parts are planned for */
 
@@ -613,22 +616,56 @@ __device__ __forceinline__ uint32_t gr_hop_threshold(const GrHop &hop, int64_t i
     return (f == f && f > -INFINITY) ? gr_orderable(f) : 0u;
 }
 
-// thf[i]: a similarity of row i passes if it is above this; tbits[i]: the key of thf[i], so that "key value <= tbits"
-// holds for everything that fails.  (thf is the float below the sample's r-th largest: that one passes.)
-// A lane keeps the GR_SYM_RANK largest similarities of its row that it has seen, sorted, in registers: an insertion is one
+// The r-th largest of the sorted lists of the two lanes that hold one row.  (Of a pair of places k, RANK - 1 - k the larger
+// value is one of the RANK largest of both; what is left is sorted by inserting it again.)
+__device__ __forceinline__ void gr_insert(float (&top)[GR_RANK], float v) { // top: descending
+#pragma unroll
+    for (int k = GR_RANK - 1; k > 0; --k) top[k] = __builtin_amdgcn_fmed3f(top[k - 1], top[k], v);
+    top[0] = fmaxf(top[0], v);
+}
+__device__ __forceinline__ void gr_merge_halves(float (&top)[GR_RANK]) {
+    float u[GR_RANK];
+#pragma unroll
+    for (int k = 0; k < GR_RANK; ++k) u[k] = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < GR_RANK; ++k) gr_insert(u, fmaxf(top[k], __shfl_xor(top[GR_RANK - 1 - k], 32, 64)));
+#pragma unroll
+    for (int k = 0; k < GR_RANK; ++k) top[k] = u[k];
+}
+// Threshold of row i as a key (as a float: gr_unorder of it) from the descending list of its largest similarities to the
+// sample: the float below the r-th largest, so that one passes.  "Key value <= threshold" holds for everything that fails.
+__device__ __forceinline__ uint32_t gr_threshold_of(const float (&top)[GR_RANK], int r, const GrHop &hop, int64_t i, float maxnorm) {
+    float t = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < GR_RANK; ++k) t = k + 1 == r ? top[k] : t;
+    const uint32_t lowest = gr_orderable(-INFINITY), tb = gr_orderable(t);
+    const uint32_t bits = tb > lowest + 1u ? tb - 1u : lowest, hb = gr_hop_threshold(hop, i, maxnorm);
+    return hb > bits ? hb : bits;
+}
+// How a sample is searched: rank of the threshold, workgroups per block of resident rows, sampled rows of each.  With one, the
+// thresholds are ready when the kernel ends; with several, each leaves its sorted lists and the recall pass merges them
+// (gr_merge_parts): 10,000 rows are 40 blocks, and the chip has 256 compute units.
+struct GrSample {
+    int r, parts, part_rows;
+    float *tops; // [parts][GR_RANK][Cr], parts > 1
+};
+
+// A lane keeps the GR_RANK largest similarities of its row that it has seen, sorted, in registers: an insertion is one
 // median-of-three per place.  (The first version appended to candidate buffers in memory and cut them back: every cut is
 // 32 rows in turn per wavefront, 199 us for 10,000 rows of 128 against a sample of 312.)
 template <class CFG>
 __global__ void __launch_bounds__(512)
 gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *__restrict__ Ws, int n_sample, int D,
-                    int r, const float *__restrict__ blockmax, int n_blockmax, float *maxnorm, GrHop hop, float *__restrict__ thf,
+                    GrSample smp, const float *__restrict__ blockmax, int n_blockmax, float *maxnorm, GrHop hop, float *__restrict__ thf,
                     uint32_t *__restrict__ tbits) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
-    constexpr int RANK = GR_SYM_RANK;
-    const int64_t row0 = (int64_t)blockIdx.x * CFG::RES;
-    float top[RANK]; // descending
+    const int id = smp.parts > 1 ? ks_xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x, nb = gridDim.x / smp.parts;
+    const int part = id / nb;
+    const int64_t row0 = (int64_t)(id % nb) * CFG::RES;
+    const int s0 = part * smp.part_rows, s1 = s0 + smp.part_rows < n_sample ? s0 + smp.part_rows : n_sample;
+    float top[GR_RANK]; // descending
 #pragma unroll
-    for (int k = 0; k < RANK; ++k) top[k] = -INFINITY;
+    for (int k = 0; k < GR_RANK; ++k) top[k] = -INFINITY;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
         (void)c0;
         const int lane = threadIdx.x & 63;
@@ -644,44 +681,43 @@ gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *
                     for (int e = 0; e < 4; ++e)
                         if (ks_soe_row(fm, 4 * q + e, lane) >= rows_here) v[e] = -INFINITY;
                 }
-                if (fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > top[RANK - 1]) {
+                if (fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > top[GR_RANK - 1]) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-#pragma unroll
-                        for (int k = RANK - 1; k > 0; --k) top[k] = __builtin_amdgcn_fmed3f(top[k - 1], top[k], v[e]);
-                        top[0] = fmaxf(top[0], v[e]);
-                    }
+                    for (int e = 0; e < 4; ++e) gr_insert(top, v[e]);
                 }
             }
     };
-    ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, 0, n_sample, n_sample, lds, epi);
-    // The two lanes of a row hold disjoint sampled rows: the r-th largest of both sorted lists together is the r-th largest
-    // of the 2 RANK values.  (Of a pair of places k, RANK - 1 - k the larger value is one of the RANK largest; what is left
-    // is sorted by inserting it again.)
-    float u[RANK];
-#pragma unroll
-    for (int k = 0; k < RANK; ++k) u[k] = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < RANK; ++k) {
-        const float v = fmaxf(top[k], __shfl_xor(top[RANK - 1 - k], 32, 64));
-#pragma unroll
-        for (int j = RANK - 1; j > 0; --j) u[j] = __builtin_amdgcn_fmed3f(u[j - 1], u[j], v);
-        u[0] = fmaxf(u[0], v);
-    }
-    float t = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < RANK; ++k) t = k + 1 == r ? u[k] : t;
-    const float mx = (hop.graph || blockIdx.x == 0) ? gr_max_norm(blockmax, n_blockmax) : 0.f;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *maxnorm = mx;
+    ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, s0, s1, n_sample, lds, epi);
+    gr_merge_halves(top); // the two lanes of a row hold disjoint sampled rows
+    const float mx = (smp.parts == 1 && hop.graph) || id == 0 ? gr_max_norm(blockmax, n_blockmax) : 0.f;
+    if (id == 0 && threadIdx.x == 0) *maxnorm = mx;
     const int64_t i = row0 + ks_soe_col();
     if ((threadIdx.x & 63) < 32 && i < Cr) {
-        const uint32_t lowest = gr_orderable(-INFINITY), tb = gr_orderable(t);
-        uint32_t bits = tb > lowest + 1u ? tb - 1u : lowest;
-        const uint32_t hb = gr_hop_threshold(hop, i, mx);
-        if (hb > bits) bits = hb;
-        thf[i] = gr_unorder(bits);
-        tbits[i] = bits;
+        if (smp.parts > 1) {
+#pragma unroll
+            for (int k = 0; k < GR_RANK; ++k) smp.tops[((int64_t)part * GR_RANK + k) * Cr + i] = top[k];
+        } else {
+            const uint32_t bits = gr_threshold_of(top, smp.r, hop, i, mx);
+            thf[i] = gr_unorder(bits);
+            tbits[i] = bits;
+        }
     }
+}
+// The threshold of row i (the same row in lanes l and l + 32) from the parts' lists; all lanes of a wavefront call.
+__device__ __forceinline__ uint32_t gr_merge_parts(const GrSample &smp, const GrHop &hop, int64_t Cr, int64_t i, const float *maxnorm) {
+    float top[GR_RANK];
+#pragma unroll
+    for (int k = 0; k < GR_RANK; ++k) top[k] = -INFINITY;
+    const int64_t row = i < Cr ? i : Cr - 1;
+    for (int p = (threadIdx.x >> 5) & 1; p < smp.parts; p += 2) { // the two lanes take every other part
+        float v[GR_RANK];
+#pragma unroll
+        for (int k = 0; k < GR_RANK; ++k) v[k] = smp.tops[((int64_t)p * GR_RANK + k) * Cr + row];
+#pragma unroll
+        for (int k = 0; k < GR_RANK; ++k) gr_insert(top, v[k]);
+    }
+    gr_merge_halves(top);
+    return gr_threshold_of(top, smp.r, hop, row, hop.graph ? *maxnorm : 0.f);
 }
 
 // Element r (0 .. 15, different from lane to lane) of a lane's 16 accumulator values: a binary tree of selects on the
@@ -744,8 +780,9 @@ __device__ __forceinline__ uint32_t gr_hit_mask(float t, const f32x16_t &a) {
 // one (testing value by value costs a branch around the append for each of them).
 template <class CFG>
 __global__ void __launch_bounds__(512)
-gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const float *__restrict__ thf_row,
-                     uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res) {
+gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, GrSample smp, GrHop hop, const float *__restrict__ maxnorm,
+                     const float *__restrict__ thf_row, uint32_t *__restrict__ tbits, uint64_t *__restrict__ cand,
+                     int32_t *__restrict__ cnt_res) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
     const int id = ks_xcd_remap(blockIdx.x, gridDim.x); // the workgroups of an XCD stream the same parts
     const int part = id / nb;
@@ -754,7 +791,16 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, const 
     const int Cr = (int)pr.Cr;
     const int cap = seg.cap(), last = 2 * seg.q - 1;
     const int64_t self0 = row0 + pr.self; // streamed rows [self0, self0 + RES) are this workgroup's own rows
-    const float thf = row0 + ks_soe_col() < Cr ? thf_row[row0 + ks_soe_col()] : INFINITY;
+    float thf = INFINITY;
+    if (smp.parts > 1) {
+        const uint32_t bits = gr_merge_parts(smp, hop, Cr, row0 + ks_soe_col(), maxnorm);
+        if (row0 + ks_soe_col() < Cr) {
+            thf = gr_unorder(bits);
+            if (part == 0 && (threadIdx.x & 32) == 0) tbits[row0 + ks_soe_col()] = bits; // for the ranking
+        }
+    } else if (row0 + ks_soe_col() < Cr) {
+        thf = thf_row[row0 + ks_soe_col()];
+    }
     uint64_t *const wg_cand = cand + (int64_t)row0 * cap;
     // the lanes 0..31 fill their row's slots from the first one upwards, the lanes 32..63 from the last one downwards
     const int down = (threadIdx.x & 32) ? -1 : 0;
@@ -1306,7 +1352,8 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
             }
         }
     };
-    if (n <= 512) select(std::integral_constant<int, 8>());
+    if (n <= 256) select(std::integral_constant<int, 4>());
+    else if (n <= 512) select(std::integral_constant<int, 8>());
     else select(std::integral_constant<int, GR_MAX_CAND / 64>());
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the keys written by the other lanes are in LDS
     if (overflow) thr = 0xFFFFFFFFu; // nothing is known about what was left out
@@ -1608,19 +1655,59 @@ static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
     }
     return best;
 }
-static int gr_rank_of(int K) { return K <= 16 ? 8 : (K <= 32 ? 10 : GR_SYM_RANK); }
+
+// Searched rows per sampled row, and the place in the sorted list.  A hit costs the recall and the ranking the same whatever
+// the problem's size, a sampled row costs a product per row: the denser sample pays in smaller problems.  One in 16 (place 8, 10,
+// 12 for K <= 8, 16, 32: 128, 160, 192 candidates instead of 256, 256, 320), us, 32 -> 16: 10,000 x 128, K = 8: 119 -> 106;
+// 10,000 x 512, K = 32: 232 -> 217; 20,000 x 64, K = 16: 248 -> 225; 60,000 x 256, K = 16: 2,402 -> 2,242; 180,000 x 256,
+// K = 32: 16,489 -> 15,852; 100,000 x 512, K = 32: 7,372 -> 7,378, hence C * D <= 50 million.
+// fp32 rows stay: their error bound is that of rounding the rows to bf16, and with a threshold closer to the K-th neighbour
+// more rows of tight clusters have no certificate (20,000 x 256 in clusters of 200 with noise of 0.1: 36 -> 290 ms).  So
+// does K > 32 (a list of 17 places).  A hop's lists give better thresholds than a denser sample after the first one (2,000 x
+// 2,000 x 256 with full lists: 42 -> 44): it stays too.
+// The chance that a row finds at most K is below two in a million, as before.
+static int gr_every(int64_t C, int D, int K, int dtype, bool hop) {
+    return !hop && dtype == KS_DTYPE_BF16 && K <= 32 && C * D <= 50000000 ? 16 : 32;
+}
+static int gr_rank_of(int K, int every) {
+    if (every == 16) return K <= 8 ? 8 : (K <= 16 ? 10 : 12);
+    return K <= 16 ? 8 : (K <= 32 ? 10 : GR_RANK);
+}
+// Workgroups per block of resident rows for the sample: the number with the least estimated time (rounds of workgroups x
+// (set-up + chunks), as in gr_parts, a chunk's insertions 1.5 us more; merging the lists in the recall pass 4 us and 0.3 per list).
+// 10,000 x 128: 40 blocks of 4 chunks, 19.8 -> 11.2 us with four; 25,000 x 256: 98 of 9, 47 -> 32 with two.
+static GrSample gr_sample_plan(int64_t Cr, int64_t n_sample, int D, int r, bool sym) {
+    const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(n_sample, 96);
+    const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 2.7 + 0.4 * kt;
+    int best = 1;
+    double best_t = 0.0;
+    for (int p = 1; p == 1 || (p <= chunks && p <= GR_SAMPLE_PARTS && !sym); ++p) { // (the symmetric sweep wants the thresholds ready)
+        const double t = (double)ks_ceil_div(nb * p, GR_CUS) * (setup + (double)ks_ceil_div(chunks, p) * per_chunk) + (p > 1 ? 4.0 + 0.3 * p : 0.0);
+        if (p == 1 || t < 0.98 * best_t) { best = p; best_t = t; }
+    }
+    GrSample smp;
+    smp.r = r;
+    smp.part_rows = (int)(ks_ceil_div(chunks, best) * 96);
+    smp.parts = chunks > 0 ? (int)ks_ceil_div(n_sample, smp.part_rows) : 1; // (rounding up may leave the last without rows)
+    smp.tops = nullptr;
+    return smp;
+}
 
 // how a pass with fixed thresholds divides its work and a row's segments
 struct GrFixPlan {
     GrSegs seg;
     int part_rows;        // streamed rows per part (not the symmetric sweep)
     int log_rows, logs;   // symmetric sweep: rows per log, number of logs
+    int every;            // searched rows per sampled row
+    GrSample smp;
 };
-static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, bool sym) {
+static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bool sym, bool hop) {
     GrFixPlan f;
+    f.every = gr_every(Cs, D, K, dtype, hop);
+    f.smp = gr_sample_plan(Cr, Cs / f.every, D, gr_rank_of(K, f.every), sym);
     const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(Cs, 96);
     f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
-    f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K) + 10) + 24;
+    f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K, 32) + 10) + 24; // (with the denser sample: room for ties)
     f.seg.stream = sym ? GR_SYM_SCAP : 0;
     f.part_rows = (int)ks_ceil_div(chunks, f.seg.parts) * 96;
     if (!sym) f.seg.parts = (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
@@ -1648,7 +1735,7 @@ struct GrWs {
     uint32_t *thr;
     // fixed thresholds
     uint16_t *Ws;      // sampled rows
-    float *thf;
+    float *tops, *thf;
     uint32_t *tbits;
     int32_t *cnt_res, *cnt_str;
     int32_t *second_count, *second_rows; // rows for gr_second_kernel
@@ -1675,10 +1762,11 @@ static GrWs gr_carve(void *ws, int64_t C, int D, int K, int dtype, size_t *total
         w.cnt = ar.take<int32_t>((size_t)C);
         w.thr = ar.take<uint32_t>((size_t)C);
     } else {
-        const GrFixPlan f = gr_fix_plan(C, C, D, K, sym);
+        const GrFixPlan f = gr_fix_plan(C, C, D, K, dtype, sym, false);
         const int64_t Cpad = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
         w.cand = ar.take<uint64_t>((size_t)C * f.seg.cap());
-        w.Ws = ar.take<uint16_t>((size_t)(C / GR_SYM_RATIO) * D);
+        w.Ws = ar.take<uint16_t>((size_t)(C / 16) * D); // (the denser sample, whatever K)
+        w.tops = f.smp.parts > 1 ? ar.take<float>((size_t)f.smp.parts * GR_RANK * C) : nullptr;
         w.thf = ar.take<float>((size_t)Cpad);
         w.tbits = ar.take<uint32_t>((size_t)C);
         w.cnt_res = ar.take<int32_t>((size_t)C * 2 * f.seg.parts);
@@ -1735,15 +1823,16 @@ extern "C" size_t knn_graph_build_workspace(int64_t C, int D, int K, int dtype) 
     return total;
 }
 
-static GrPrepJob gr_prep_job(const void *W, int64_t C, int D, int dtype, uint16_t *Wb, float *norms, float *blockmax, uint16_t *Ws) {
+static GrPrepJob gr_prep_job(const void *W, int64_t C, int D, int dtype, uint16_t *Wb, float *norms, float *blockmax, uint16_t *Ws, int every) {
     GrPrepJob j;
+    j.every = every;
     j.W = W;
     j.C = C;
     j.Wb = Wb;
     j.norms = norms;
     j.blockmax = blockmax;
     j.Ws = Ws;
-    j.n_sample = Ws ? C / GR_SYM_RATIO : 0;
+    j.n_sample = Ws ? C / every : 0;
     // four row groups per wavefront: a wavefront takes 64 / (lanes per row) rows at a time
     const int pieces = D * (dtype == KS_DTYPE_BF16 ? 2 : 4) / 16;
     int64_t rows = 64 / (pieces > 32 ? 64 : (pieces > 16 ? 32 : (pieces > 8 ? 16 : (pieces > 4 ? 8 : 4)))) * (GR_NT / 64) * 2;
@@ -1775,21 +1864,22 @@ static void gr_launch_prepare(const GrPrepJob &j0, const GrPrepJob &j1, int D, i
     } while (0)
 #define COMMA ,
 
-static void gr_launch_threshold(const uint16_t *R, int64_t Cr, const uint16_t *Ws, int64_t n_sample, int D, int K, const float *blockmax,
+static void gr_launch_threshold(const uint16_t *R, int64_t Cr, const uint16_t *Ws, int64_t n_sample, int D, const GrSample &smp, const float *blockmax,
                                 int n_blockmax, float *maxnorm, const GrHop &hop, float *thf, uint32_t *tbits, hipStream_t st) {
-    const dim3 grid((unsigned)ks_ceil_div(Cr, 256));
+    const dim3 grid((unsigned)(ks_ceil_div(Cr, 256) * smp.parts));
 #define GR_THR_LAUNCH(CFG)                                                                                                    \
-    hipLaunchKernelGGL((gr_threshold_kernel<CFG>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, gr_rank_of(K), blockmax, \
+    hipLaunchKernelGGL((gr_threshold_kernel<CFG>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
                        n_blockmax, maxnorm, hop, thf, tbits)
     GR_FOR_DEPTH(GR_THR_LAUNCH);
 #undef GR_THR_LAUNCH
 }
-static void gr_launch_recall_fix(const GrPair &pr, int D, const GrFixPlan &f, const float *thf, uint64_t *cand, int32_t *cnt_res,
-                                 hipStream_t st) {
+static void gr_launch_recall_fix(const GrPair &pr, int D, const GrFixPlan &f, const GrSample &smp, const GrHop &hop, const float *maxnorm,
+                                 const float *thf, uint32_t *tbits, uint64_t *cand, int32_t *cnt_res, hipStream_t st) {
     const int nb = (int)ks_ceil_div(pr.Cr, 256);
     const dim3 grid((unsigned)(nb * f.seg.parts));
 #define GR_FIX_LAUNCH(CFG) \
-    hipLaunchKernelGGL((gr_recall_fix_kernel<CFG>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, thf, cand, cnt_res)
+    hipLaunchKernelGGL((gr_recall_fix_kernel<CFG>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, smp, hop, maxnorm, thf, \
+                       tbits, cand, cnt_res)
     GR_FOR_DEPTH(GR_FIX_LAUNCH);
 #undef GR_FIX_LAUNCH
 }
@@ -1888,7 +1978,7 @@ extern "C" int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K
     const GrParams p = gr_params(K, D, dtype);
     hipStream_t st = (hipStream_t)stream;
     const bool fixed = gr_use_fixed(C, C, D, K), sym = gr_use_sym(C, D, K);
-    const GrFixPlan f = gr_fix_plan(C, C, D, K, sym);
+    const GrFixPlan f = gr_fix_plan(C, C, D, K, dtype, sym, false);
     GrClear clr = GrClear();
     clr.fb_count = w.fb_count;
     if (fixed) clr.second_count = w.second_count;
@@ -1899,15 +1989,17 @@ extern "C" int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K
         clr.pad0 = C;
         clr.pad1 = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
     }
-    const GrPrepJob job = gr_prep_job(W, C, D, dtype, w.Wb, w.norms, w.blockmax, fixed ? w.Ws : nullptr);
+    const GrPrepJob job = gr_prep_job(W, C, D, dtype, w.Wb, w.norms, w.blockmax, fixed ? w.Ws : nullptr, f.every);
     gr_launch_prepare(job, GrPrepJob(), D, dtype, clr, st);
     const uint16_t *Wb = dtype == KS_DTYPE_FP32 ? w.Wb : (const uint16_t *)W;
     const GrPair pr{Wb, C, Wb, C, 0};
     const float gamma = gr_gamma(D, dtype);
     if (fixed) {
-        gr_launch_threshold(Wb, C, w.Ws, job.n_sample, D, K, w.blockmax, job.blocks, w.maxnorm, GrHop(), w.thf, w.tbits, st);
+        GrSample smp = f.smp;
+        smp.tops = w.tops;
+        gr_launch_threshold(Wb, C, w.Ws, job.n_sample, D, smp, w.blockmax, job.blocks, w.maxnorm, GrHop(), w.thf, w.tbits, st);
         if (sym) gr_launch_recall_sym(Wb, C, D, f, w, st);
-        else gr_launch_recall_fix(pr, D, f, w.thf, w.cand, w.cnt_res, st);
+        else gr_launch_recall_fix(pr, D, f, smp, GrHop(), w.maxnorm, w.thf, w.tbits, w.cand, w.cnt_res, st);
         if (dtype == KS_DTYPE_FP32) gr_launch_rank<float>((const float *)W, C, D, K, f, w, gamma, graph, sims, st);
         else gr_launch_rank<uint16_t>((const uint16_t *)W, C, D, K, f, w, gamma, graph, sims, st);
     } else {
@@ -2138,7 +2230,7 @@ struct GrUpWs {
     int32_t *cnt;  // running thresholds
     uint32_t *thr;
     uint16_t *Ws;  // fixed thresholds
-    float *thf;
+    float *tops, *thf;
     uint32_t *tbits;
     int32_t *cnt_res;
 };
@@ -2156,9 +2248,10 @@ static GrUpWs gr_up_carve(void *ws, int64_t C_loc, int64_t C_vis, int D, int K, 
     w.fb_rows = ar.take<int32_t>((size_t)C_loc);
     w.scratch = ar.take<double>((size_t)GR_FB_BLOCKS * C_vis);
     if (gr_use_fixed(C_loc, C_vis, D, K)) {
-        const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, false);
+        const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, dtype, false, true);
         w.cand = ar.take<uint64_t>((size_t)C_loc * f.seg.cap());
-        w.Ws = ar.take<uint16_t>((size_t)(C_vis / GR_SYM_RATIO) * D);
+        w.Ws = ar.take<uint16_t>((size_t)(C_vis / f.every) * D);
+        w.tops = f.smp.parts > 1 ? ar.take<float>((size_t)f.smp.parts * GR_RANK * C_loc) : nullptr;
         w.thf = ar.take<float>((size_t)C_loc);
         w.tbits = ar.take<uint32_t>((size_t)C_loc);
         w.cnt_res = ar.take<int32_t>((size_t)C_loc * 2 * f.seg.parts);
@@ -2216,11 +2309,11 @@ extern "C" int knn_graph_update(const void *W_local, const void *W_visit, int dt
     const GrParams p = gr_params(K, D, dtype);
     hipStream_t st = (hipStream_t)stream;
     const bool fixed = gr_use_fixed(C_loc, C_vis, D, K);
-    const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, false);
+    const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, dtype, false, true);
     GrClear clr = GrClear();
     clr.fb_count = w.fb_count;
-    const GrPrepJob jl = gr_prep_job(W_local, C_loc, D, dtype, w.Wlb, w.norms_l, w.blockmax_l, nullptr);
-    const GrPrepJob jv = gr_prep_job(W_visit, C_vis, D, dtype, w.Wvb, nullptr, w.blockmax_v, fixed ? w.Ws : nullptr);
+    const GrPrepJob jl = gr_prep_job(W_local, C_loc, D, dtype, w.Wlb, w.norms_l, w.blockmax_l, nullptr, 0);
+    const GrPrepJob jv = gr_prep_job(W_visit, C_vis, D, dtype, w.Wvb, nullptr, w.blockmax_v, fixed ? w.Ws : nullptr, f.every);
     gr_launch_prepare(jl, jv, D, dtype, clr, st);
     const uint16_t *Rl = dtype == KS_DTYPE_FP32 ? w.Wlb : (const uint16_t *)W_local;
     const uint16_t *Sv = dtype == KS_DTYPE_FP32 ? w.Wvb : (const uint16_t *)W_visit;
@@ -2228,8 +2321,10 @@ extern "C" int knn_graph_update(const void *W_local, const void *W_visit, int dt
     const float gamma = gr_gamma(D, dtype);
     const GrHop hop{graph, sims, w.norms_l, K, gamma};
     if (fixed) {
-        gr_launch_threshold(Rl, C_loc, w.Ws, jv.n_sample, D, K, w.blockmax_v, jv.blocks, w.maxnorm_v, hop, w.thf, w.tbits, st);
-        gr_launch_recall_fix(pr, D, f, w.thf, w.cand, w.cnt_res, st);
+        GrSample smp = f.smp;
+        smp.tops = w.tops;
+        gr_launch_threshold(Rl, C_loc, w.Ws, jv.n_sample, D, smp, w.blockmax_v, jv.blocks, w.maxnorm_v, hop, w.thf, w.tbits, st);
+        gr_launch_recall_fix(pr, D, f, smp, hop, w.maxnorm_v, w.thf, w.tbits, w.cand, w.cnt_res, st);
     } else {
         hipLaunchKernelGGL(gr_maxnorm_kernel, dim3(1), dim3(64), 0, st, w.blockmax_v, jv.blocks, w.maxnorm_v);
         hipLaunchKernelGGL(gr_hop_threshold_kernel, dim3((unsigned)ks_ceil_div(C_loc, GR_NT)), dim3(GR_NT), 0, st, C_loc, hop,

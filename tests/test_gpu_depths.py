@@ -372,3 +372,39 @@ def test_one_sweep_combine_beside_the_dx_tiles(ks, orc, C, D, B, K, M):
     G = ((np.arange(C)[:, None] * 7 + 1 + np.arange(K)[None, :] * 13) % C).astype(np.int32)
     X[::3] = synth.bf16_round((0.8 * W[y[::3]] + 0.2 * X[::3]).astype(np.float32))
     run_and_compare(ks, orc, W, X, y, G, C, M, scale=30.0, grad_scale=4.0, tag=f"D={D} B={B}", modes=(True,))
+
+
+@pytest.mark.parametrize("C,D,K,bf16", [(95, 64, 3, True), (1537, 64, 8, True), (1800, 128, 16, True), (10_000, 128, 8, False), (10_000, 128, 8, True),
+                                        (30_001, 64, 32, True), (66_000, 32, 9, True), (97_657, 512, 24, True), (97_656, 512, 24, True)])
+def test_graph_on_both_sides_of_the_denser_sample(ks, orc, C, D, K, bf16):
+    """Samples of one row in 16 (less than a chunk, one chunk, several workgroups' lists merged, more blocks than compute units)
+    and of one in 32, on either side of C * D = 50 million: with clustered rows and exact twins."""
+    import torch
+    print(f"[depths] sample C={C} D={D} K={K}", flush=True)
+    rng = np.random.default_rng(C)
+    centres = synth.unit_rows(61, synth.TID_W, 64, D)
+    W = centres[np.arange(C) % 64] + rng.standard_normal((C, D), dtype=np.float32) * (0.7 / np.sqrt(D))
+    W /= np.linalg.norm(W, axis=1, keepdims=True)
+    W[C - 1] = W[C // 3]
+    W = synth.bf16_round(W) if bf16 else W.astype(np.float32)
+    rows = np.unique(np.concatenate([rng.integers(0, C, 60), [0, C // 3, C - 1]])).astype(np.int32)
+    g, s = ks.knn_graph_build(dev(W, bf16), K, want_sims=True)
+    torch.cuda.synchronize()
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("C_loc,C_vis,D,K", [(40, 7_000, 64, 8), (600, 30_000, 256, 33)])
+def test_hop_with_the_sample_in_parts(ks, orc, C_loc, C_vis, D, K):
+    """Few local rows against many: the sample's lists come from several workgroups and meet the lists of earlier hops."""
+    import torch
+    print(f"[depths] hop sample {C_loc} x {C_vis}", flush=True)
+    W = synth.unit_rows(62, synth.TID_W, C_loc + 2 * C_vis, D, bf16=True)
+    S = W[:C_loc].astype(np.float64) @ W.astype(np.float64).T
+    graph = torch.full((C_loc, K), -1, dtype=torch.int32, device="cuda")
+    sims = torch.full((C_loc, K), -np.inf, dtype=torch.float64, device="cuda")
+    for lo in (C_loc, C_loc + C_vis):
+        ks.knn_graph_update(dev(W[:C_loc], True), dev(W[lo:lo + C_vis], True), 0, lo, graph, sims)
+    torch.cuda.synchronize()
+    best = np.argsort(-S[:, C_loc:], axis=1, kind="stable")[:, :K] + C_loc
+    assert (graph.cpu().numpy() == best).all()
