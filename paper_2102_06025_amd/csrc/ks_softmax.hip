@@ -441,11 +441,16 @@ __host__ __device__ __forceinline__ int sm_slab_rows(int n64, int slabs) {
     return h < 32 ? 32 : h;
 }
 
+// Products kept between the two passes of a small problem (see sm_grad_kept_kernel), in the order in which the accumulators of
+// a 32 x 32 block hold them: four pieces of 64 lanes x 16 bytes.  In 16-byte pieces: the first of class block cb, sample block sb.
+__device__ __forceinline__ int64_t sm_kept_at(int cb, int sb, int Bp, int lane) { return ((int64_t)cb * (Bp >> 5) + sb) * 256 + lane; }
+
 template <class CFG>
 __global__ void __launch_bounds__(512)
 sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const int32_t *__restrict__ active_idx,
                     const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, int B, int Bp, int D, int M,
-                    int tiles_s, float scale, float *__restrict__ pm, float *__restrict__ pl, float *__restrict__ zt) {
+                    int tiles_s, float scale, float *__restrict__ pm, float *__restrict__ pl, float *__restrict__ zt,
+                    float *__restrict__ kept) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS + 2 * SM_LIDX_CAP]; // one array: see ks_gemm_soe.h
     int32_t *const s_lidx = (int32_t *)(lds + CFG::LDS_ELEMS);
     const int n = sm_clamp_n(n_active_p, M);
@@ -465,7 +470,16 @@ sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     // l = sum exp(scale * (acc - m)) = sum exp2(fma(acc, k1, -k1 * m)); one fused multiply-add per element
     const float k1 = scale * 1.4426950408889634f;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
-        (void)rows_here;
+        if (kept) {
+            float4 *p = (float4 *)kept + sm_kept_at(c0 >> 5, i >> 5, Bp, lane);
+#pragma unroll
+            for (int fm = 0; fm < CFG::FM; ++fm)
+                if (fm * 32 < rows_here) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        p[(int64_t)fm * Bp * 8 + q * 64] = make_float4(acc[fm][4 * q], acc[fm][4 * q + 1], acc[fm][4 * q + 2], acc[fm][4 * q + 3]);
+                }
+        }
         // the target logit of a sample whose label sits in this chunk (rare: a scan over this lane's rows)
         if (tp >= c0 && tp < c0 + CFG::CH && tp < lim) {
 #pragma unroll
@@ -588,6 +602,88 @@ sm_grad_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
     ks_soe_sweep<CFG, 2 * CFG::FM>(X, D, ts * CFG::RES, B, W, D, active_idx, s0, s1, n, lds, epi, s_lidx, SM_LIDX_CAP);
 }
 
+
+// Small problems (sm_keeps): the second sweep and the merge of the slabs' statistics before it as one pass over the products, which the
+// first sweep has kept (fp32, as they stood in its accumulators: the same gradient bit for bit but for the order of the merge).
+// A workgroup has 32 samples and takes every gridDim.y-th group of four class blocks; it merges its samples' statistics itself,
+// while its first block is on the way.  (2,297 classes x 320, batch 333: merge and sweep 3.9 + 9.2 us, this 6.3.)
+__global__ void __launch_bounds__(SM_NT)
+sm_grad_kept_kernel(const float *__restrict__ kept, const float *__restrict__ pm, const float *__restrict__ pl, const float *__restrict__ zt,
+                    const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, int B, int Bp, int M, int slabs,
+                    float scale, float g, float *__restrict__ loss_i, uint16_t *__restrict__ dZ8) {
+    constexpr int PARTS = SM_NT / 32;
+    __shared__ float s_m[PARTS][32], s_l[PARTS][32];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sb = blockIdx.x, cb0 = blockIdx.y * 4 + wave;
+    float4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto fetch = [&](int cb) __attribute__((always_inline)) {
+        const float4 *p = (const float4 *)kept + sm_kept_at(cb, sb, Bp, lane);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = p[q * 64];
+    };
+    if (cb0 * 32 < M) fetch(cb0); // (the array has whole blocks for M rows)
+    const int n = sm_clamp_n(n_active_p, M);
+    const int n64 = (n + 63) & ~63, h = sm_slab_rows(n64, slabs);
+    const int j = threadIdx.x & 31, part = threadIdx.x >> 5;
+    {
+        const int i = sb * 32 + j;
+        float m = -INFINITY, l = 0.f;
+        for (int t0 = part; t0 * h < n64; t0 += 8 * PARTS) { // (slabs that hold rows; i < Bp)
+            float tm[8], tl[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int t = t0 + u * PARTS;
+                const bool in = t * h < n64 && i < B;
+                tm[u] = in ? pm[(int64_t)t * Bp + i] : -INFINITY;
+                tl[u] = in ? pl[(int64_t)t * Bp + i] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (tm[u] != -INFINITY) {
+                    const float mm = fmaxf(m, tm[u]);
+                    l = l * __expf(m - mm) + tl[u] * __expf(tm[u] - mm); // (m = -inf, l = 0 at the start)
+                    m = mm;
+                }
+        }
+        s_m[part][j] = m;
+        s_l[part][j] = l;
+    }
+    __syncthreads();
+    const int i = sb * 32 + (lane & 31);
+    const bool ok = i < B;
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) m = fmaxf(m, s_m[p][lane & 31]);
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) // a fixed order
+        if (s_m[p][lane & 31] != -INFINITY) l += s_l[p][lane & 31] * __expf(s_m[p][lane & 31] - m);
+    const float lse = m + __logf(l);
+    const int tp = ok ? target_pos[i] : -1;
+    if (blockIdx.y == 0 && threadIdx.x < 32 && ok) loss_i[i] = lse - zt[i];
+    // scale > 0 and g > 0 (checked by the host), as in sm_grad_soe_kernel
+    const float k1 = scale * 1.4426950408889634f;
+    const float k2 = __log2f(g) - (ok ? lse : 0.f) * 1.4426950408889634f;
+    for (int cb = cb0; cb * 32 < n64; cb += gridDim.y * 4) {
+        const int c0 = cb * 32, tq = tp - c0 - 4 * (lane >> 5), lq = ok ? n - c0 - 4 * (lane >> 5) : 0;
+        uint32_t pk[4][2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float d[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                d[e] = 8 * q + e >= lq ? 0.f : __builtin_amdgcn_exp2f(fmaf(d[e], k1, k2));
+                if (8 * q + e == tq) d[e] -= g;
+            }
+            pk[q][0] = ks_pack_bf2(d[0], d[1]);
+            pk[q][1] = ks_pack_bf2(d[2], d[3]);
+        }
+        const int next = cb + gridDim.y * 4;
+        if (next * 32 < n64) fetch(next);
+        sm_store_block(pk, dZ8 + sm_dz_at(c0 + 8 * (lane >> 5), i, Bp), Bp);
+    }
+}
 
 // ------------------------------------------------------------------------------------------------
 // One-sweep variant for rows of norm <= 1 (the paper normalises W and X, section 3.2): every logit
@@ -1301,6 +1397,7 @@ struct SmWs {
     float *pm, *pl, *zt; // fast path: per class-tile softmax statistics, target logits
     float *inv;          // one-sweep softmax: 1 / sum_a exp(z_ia - scale) per sample
     uint16_t *X2;        // one-sweep softmax: rows of X scaled by that
+    float *kept;         // two-sweep softmax of a small problem: the first sweep's products
     int32_t *cell_pos;   // one-sweep softmax: the target entries (DwCells)
     uint32_t *cell;
     int S;
@@ -1340,6 +1437,15 @@ static int sm_splits(int B, int D, int64_t M, bool fast) {
     return S;
 }
 
+// Whether the two-sweep softmax keeps its products instead of forming them again.  It spares a launch (the merge, 4 us) and the
+// second sweep's set-up, and costs 10 bytes of traffic per product against 2 D operations.  Whole calls, us, sweep -> kept: 900
+// classes x 64, batch 64: 34.5 -> 31.3; 3,001 x 320, 333: 54.9 -> 51.8; 4,000 x 512, 128: 56.6 -> 50.4; 8,300 x 512, 500: 78.1 -> 75.7;
+// 7,000 x 192, 300: 57.6 -> 60.6; 25,000 x 384, 600: 130 -> 135; 32,319 x 512, 1,024: 212 -> 216.
+static bool sm_keeps(int B, int D, int64_t M) {
+    const int64_t n = (int64_t)ks_align_up((size_t)B, KS_BP_ALIGN) * M;
+    return D <= 512 && (n <= 1 << 20 || n <= 32 * (int64_t)D * D);
+}
+
 static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool with_select, bool fast) {
     KsArena ar(ws);
     SmWs w;
@@ -1354,6 +1460,7 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
     w.dZ = w.dZ8 = nullptr;
     w.pm = w.pl = w.zt = w.inv = nullptr;
     w.X2 = nullptr;
+    w.kept = nullptr;
     w.cell_pos = nullptr;
     w.cell = nullptr;
     if (w.fast) {
@@ -1365,6 +1472,7 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
         w.zt = ar.take<float>((size_t)w.Bp);
         w.inv = ar.take<float>((size_t)w.Bp);
         w.X2 = ar.take<uint16_t>((size_t)w.Bp * D);
+        w.kept = sm_keeps(B, D, M) ? ar.take<float>((size_t)w.Mp * w.Bp) : nullptr;
         w.cell_pos = ar.take<int32_t>((size_t)w.Bp);
         w.cell = ar.take<uint32_t>((size_t)w.Bp);
     } else {
@@ -1470,21 +1578,28 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             }
             mark(3);
         } else if (soe) {
+            const bool keep = mode == SM_WHOLE && w.kept;
             if (mode != SM_IMPORT) {
 #define SM_STATS_LAUNCH(CFG)                                                                                              \
     hipLaunchKernelGGL((sm_stats_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, B, \
-                       w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt)
+                       w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt, keep ? w.kept : nullptr)
                 SM_FOR_DEPTH(SM_STATS_LAUNCH);
 #undef SM_STATS_LAUNCH
                 mark(2);
-                hipLaunchKernelGGL(sm_combine_soe_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT / 64)), dim3(SM_NT), 0, st,
-                                   w.pm, w.pl, w.zt, n_active, Mi, slabs, B, w.Bp, w.lse, loss_per_sample);
+                if (!keep)
+                    hipLaunchKernelGGL(sm_combine_soe_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT / 64)), dim3(SM_NT), 0, st,
+                                       w.pm, w.pl, w.zt, n_active, Mi, slabs, B, w.Bp, w.lse, loss_per_sample);
                 mark(3);
             } else {
                 hipLaunchKernelGGL(sm_import_kernel, dim3((unsigned)ks_ceil_div(B, SM_NT)), dim3(SM_NT), 0, st, io, B, w.lse,
                                    loss_per_sample);
             }
-            if (mode != SM_EXPORT) {
+            if (keep) {
+                const int sbs = w.Bp / 32, groups = (int)ks_ceil_div(M, 128); // class blocks in fours
+                const int gy = (int)ks_ceil_div(1024, sbs);
+                hipLaunchKernelGGL(sm_grad_kept_kernel, dim3(sbs, gy < groups ? gy : groups), dim3(SM_NT), 0, st, w.kept, w.pm, w.pl,
+                                   w.zt, n_active, target_pos, B, w.Bp, Mi, slabs, scale, g, loss_per_sample, w.dZ8);
+            } else if (mode != SM_EXPORT) {
 #define SM_GRAD_LAUNCH(CFG)                                                                                               \
     hipLaunchKernelGGL((sm_grad_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos,     \
                        w.lse, B, w.Bp, D, Mi, tiles_s, scale, g, w.dZ8)

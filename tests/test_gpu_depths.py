@@ -408,3 +408,20 @@ def test_hop_with_the_sample_in_parts(ks, orc, C_loc, C_vis, D, K):
     torch.cuda.synchronize()
     best = np.argsort(-S[:, C_loc:], axis=1, kind="stable")[:, :K] + C_loc
     assert (graph.cpu().numpy() == best).all()
+
+
+@pytest.mark.parametrize("D", [224, 256, 288, 320, 384, 416, 448, 480, 512])
+@pytest.mark.parametrize("over", [-1, 1])
+def test_two_sweeps_and_one_with_kept_products(ks, orc, D, over):
+    """General rows on both sides of the line (512 rows of the batch's tiles times M = 32 D^2) between keeping the first sweep's
+    products and sweeping again, at every depth the smaller tests leave to the first."""
+    from test_gpu_parity import run_and_compare
+    B, K = 300, 63
+    M = 32 * D * D // 512 + (over if over > 0 else 0)
+    C = M + 400
+    print(f"[depths] kept or swept D={D} M={M}", flush=True)
+    W, X = synth.unit_rows(71, synth.TID_W, C, D, bf16=True), synth.unit_rows(71, synth.TID_X, B, D, bf16=True)
+    W *= 1.25
+    y = synth.labels_uniform(71, B, C)
+    G = ((np.arange(C)[:, None] * 7 + 1 + np.arange(K)[None, :] * 13) % C).astype(np.int32)
+    run_and_compare(ks, orc, W, X, y, G, C, M, scale=20.0, grad_scale=4.0, tag=f"D={D}", modes=(False,))
