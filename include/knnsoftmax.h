@@ -246,8 +246,9 @@ int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_t *W_bf16, 
  * recorded on `stream` at each stage boundary, so that a caller can time the stages of a step without a profiler.
  * events[0..KS_N_PHASE_EVENTS) are created by the caller (hipEventCreate); event k is recorded: 0 at entry, 1
  * after the selection, 2 after the first sweep over the active rows (softmax statistics; with KS_FLAG_UNIT_ROWS
- * the only sweep, which also writes the exponentials), 3 after the per-sample combine and the loss mean, 4 after
- * the second sweep (logit gradient; nothing with KS_FLAG_UNIT_ROWS), 5 after the dX partial GEMM, 6 after the dX
+ * the only sweep, which also writes the exponentials), 3 after the merge of its statistics, 4 after
+ * the logit gradient (2 to 4: nothing between them with KS_FLAG_UNIT_ROWS, whose per-sample combine is part of the dX
+ * launch; small problems merge in the pass that forms the gradient), 5 after the dX partial GEMM, 6 after the dX
  * reduction, 7 after the dW GEMM (and the update, if any).  Same results as the entry points it stands for. */
 #define KS_N_PHASE_EVENTS 8
 int knn_softmax_fwd_bwd_profiled(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16, const int32_t *labels,

@@ -265,7 +265,7 @@ __device__ __forceinline__ void sm_store_block(uint32_t (&pk)[4][2], uint16_t *p
     }
 }
 
-// The logits are never stored on the fast path.  Two passes over the same tile product
+// Only small problems store their logits on the fast path (sm_keeps).  Two passes over the same tile product
 //     Zt[a][i] = scale * <W[active[a]], X[i]>            (classes = MFMA rows, samples = MFMA columns)
 // First pass: per-sample running max / sum of exponentials of each class tile, and the target logit.
 // Second pass (after the per-sample log-sum-exp is known): the same product again, turned into the logit
