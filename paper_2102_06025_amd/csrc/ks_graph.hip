@@ -1352,7 +1352,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
             }
         }
     };
-    if (n <= 256) select(std::integral_constant<int, 4>());
+    if (K <= 24 && n <= 256) select(std::integral_constant<int, 4>()); // (beyond, too few rows have so few)
     else if (n <= 512) select(std::integral_constant<int, 8>());
     else select(std::integral_constant<int, GR_MAX_CAND / 64>());
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the keys written by the other lanes are in LDS
@@ -1658,16 +1658,21 @@ static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
 
 // Searched rows per sampled row, and the place in the sorted list.  A hit costs the recall and the ranking the same whatever
 // the problem's size, a sampled row costs a product per row: the denser sample pays in smaller problems.  One in 16 (place 8, 10,
-// 12 for K <= 8, 16, 32: 128, 160, 192 candidates instead of 256, 256, 320), us, 32 -> 16: 10,000 x 128, K = 8: 119 -> 106;
-// 10,000 x 512, K = 32: 232 -> 217; 20,000 x 64, K = 16: 248 -> 225; 60,000 x 256, K = 16: 2,402 -> 2,242; 180,000 x 256,
-// K = 32: 16,489 -> 15,852; 100,000 x 512, K = 32: 7,372 -> 7,378, hence C * D <= 50 million.
+// 12 for K <= 8, 16, 24: 128, 160, 192 candidates instead of 256, 256, 320), us, 32 -> 16: 10,000 x 128, K = 8: 119 -> 106;
+// 20,000 x 64, K = 16: 248 -> 225; 60,000 x 256, K = 16: 2,402 -> 2,242; 130,000 x 128, K = 24: 6,646 -> 6,199; 300,000 x 128,
+// K = 16: 30,532 -> 29,495, hence C * D <= 50 million.  Deeper than 256 a sampled row costs more and it pays up to 15 million
+// (30,000 x 512, K = 16: 969 -> 962; 45,000 x 320, K = 8: 1,679 -> 1,678; but 48,000 x 512, K = 16: 1,813 -> 1,818; 100,000 x 320,
+// K = 16: 7,518 -> 7,650; 90,000 x 512, K = 16: 5,854 -> 5,977), at D = 512 with K > 16, the symmetric sweep and 128 fewer
+// candidates, up to 30 million (58,000, K = 24: 2,738 -> 2,659; but 70,000: 4,187 -> 4,204).
 // fp32 rows stay: their error bound is that of rounding the rows to bf16, and with a threshold closer to the K-th neighbour
-// more rows of tight clusters have no certificate (20,000 x 256 in clusters of 200 with noise of 0.1: 36 -> 290 ms).  So
-// does K > 32 (a list of 17 places).  A hop's lists give better thresholds than a denser sample after the first one (2,000 x
-// 2,000 x 256 with full lists: 42 -> 44): it stays too.
-// The chance that a row finds at most K is below two in a million, as before.
+// more rows of tight clusters have no certificate (20,000 x 256 in clusters of 200 with noise of 0.1: 36 -> 290 ms).  So does
+// K > 24: with 12 places two rows in a million find at most 32 (a tenth of that as it is), and one such row in the exhaustive
+// pass costs more than the sample gives (120,000 x 64, K = 32: 3,921 -> 5,298).  A hop's lists give better thresholds than a
+// denser sample after the first one (2,000 x 2,000 x 256 with full lists: 42 -> 44): it stays too.
+// The chance that a row finds at most K is one in ten million at K = 24.
 static int gr_every(int64_t C, int D, int K, int dtype, bool hop) {
-    return !hop && dtype == KS_DTYPE_BF16 && K <= 32 && C * D <= 50000000 ? 16 : 32;
+    const int64_t most = D <= 256 ? 50000000 : (D == 512 && K > 16 ? 30000000 : 15000000);
+    return !hop && dtype == KS_DTYPE_BF16 && K <= 24 && C * D <= most ? 16 : 32;
 }
 static int gr_rank_of(int K, int every) {
     if (every == 16) return K <= 8 ? 8 : (K <= 16 ? 10 : 12);

@@ -375,10 +375,11 @@ def test_one_sweep_combine_beside_the_dx_tiles(ks, orc, C, D, B, K, M):
 
 
 @pytest.mark.parametrize("C,D,K,bf16", [(95, 64, 3, True), (1537, 64, 8, True), (1800, 128, 16, True), (10_000, 128, 8, False), (10_000, 128, 8, True),
-                                        (30_001, 64, 32, True), (66_000, 32, 9, True), (97_657, 512, 24, True), (97_656, 512, 24, True)])
+                                        (30_001, 64, 32, True), (66_000, 32, 9, True), (58_594, 512, 24, True), (58_593, 512, 24, True),
+                                        (46_876, 320, 9, True), (46_875, 320, 9, True), (195_313, 256, 5, True), (195_312, 256, 5, True)])
 def test_graph_on_both_sides_of_the_denser_sample(ks, orc, C, D, K, bf16):
     """Samples of one row in 16 (less than a chunk, one chunk, several workgroups' lists merged, more blocks than compute units)
-    and of one in 32, on either side of C * D = 50 million: with clustered rows and exact twins."""
+    and of one in 32, on either side of the lines between them (C * D = 50, 15 and 30 million): with clustered rows and exact twins."""
     import torch
     print(f"[depths] sample C={C} D={D} K={K}", flush=True)
     rng = np.random.default_rng(C)
