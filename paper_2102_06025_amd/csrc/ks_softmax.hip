@@ -265,7 +265,7 @@ __device__ __forceinline__ void sm_store_block(uint32_t (&pk)[4][2], uint16_t *p
     }
 }
 
-// Only small problems store their logits on the fast path (sm_keeps).  Two passes over the same tile product
+// Only small problems store their logits on the fast path (sm_kept_bytes).  Two passes over the same tile product
 //     Zt[a][i] = scale * <W[active[a]], X[i]>            (classes = MFMA rows, samples = MFMA columns)
 // First pass: per-sample running max / sum of exponentials of each class tile, and the target logit.
 // Second pass (after the per-sample log-sum-exp is known): the same product again, turned into the logit
@@ -603,7 +603,7 @@ sm_grad_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
 }
 
 
-// Small problems (sm_keeps): the second sweep and the merge of the slabs' statistics before it as one pass over the products, which the
+// Small problems (sm_kept_bytes): the second sweep and the merge of the slabs' statistics before it as one pass over the products, which the
 // first sweep has kept (fp32, as they stood in its accumulators: the same gradient bit for bit but for the order of the merge).
 // A workgroup has 32 samples and takes every gridDim.y-th group of four class blocks; it merges its samples' statistics itself,
 // while its first block is on the way.  (2,297 classes x 320, batch 333: merge and sweep 3.9 + 9.2 us, this 6.3.)
@@ -1441,9 +1441,10 @@ static int sm_splits(int B, int D, int64_t M, bool fast) {
 // second sweep's set-up, and costs 10 bytes of traffic per product against 2 D operations.  Whole calls, us, sweep -> kept: 900
 // classes x 64, batch 64: 34.5 -> 31.3; 3,001 x 320, 333: 54.9 -> 51.8; 4,000 x 512, 128: 56.6 -> 50.4; 8,300 x 512, 500: 78.1 -> 75.7;
 // 7,000 x 192, 300: 57.6 -> 60.6; 25,000 x 384, 600: 130 -> 135; 32,319 x 512, 1,024: 212 -> 216.
-static bool sm_keeps(int B, int D, int64_t M) {
-    const int64_t n = (int64_t)ks_align_up((size_t)B, KS_BP_ALIGN) * M;
-    return D <= 512 && (n <= 1 << 20 || n <= 32 * (int64_t)D * D);
+// Bytes of the array (0: not kept), at most 34 MB.
+static size_t sm_kept_bytes(int B, int D, int64_t M) {
+    const int64_t n = (int64_t)ks_align_up((size_t)B, KS_BP_ALIGN) * sm_mp(M);
+    return D <= 512 && (n <= 1 << 20 || n <= 32 * (int64_t)D * D) ? (size_t)n * sizeof(float) : 0;
 }
 
 static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool with_select, bool fast) {
@@ -1460,7 +1461,7 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
     w.dZ = w.dZ8 = nullptr;
     w.pm = w.pl = w.zt = w.inv = nullptr;
     w.X2 = nullptr;
-    w.kept = nullptr;
+    w.kept = nullptr; // see sm_take_kept
     w.cell_pos = nullptr;
     w.cell = nullptr;
     if (w.fast) {
@@ -1472,7 +1473,6 @@ static SmWs sm_carve(void *ws, int64_t C, int D, int B, int K, int64_t M, bool w
         w.zt = ar.take<float>((size_t)w.Bp);
         w.inv = ar.take<float>((size_t)w.Bp);
         w.X2 = ar.take<uint16_t>((size_t)w.Bp * D);
-        w.kept = sm_keeps(B, D, M) ? ar.take<float>((size_t)w.Mp * w.Bp) : nullptr;
         w.cell_pos = ar.take<int32_t>((size_t)w.Bp);
         w.cell = ar.take<uint32_t>((size_t)w.Bp);
     } else {
@@ -1488,6 +1488,16 @@ static size_t sm_bytes(int64_t C, int D, int B, int K, int64_t M, bool with_sele
     const size_t fast = D <= 512 || D % 64 == 0 ? sm_carve(nullptr, C, D, B, K, M, with_select, true).bytes : 0;
     const size_t generic = D % 64 != 0 ? sm_carve(nullptr, C, D, B, K, M, with_select, false).bytes : 0;
     return fast > generic ? fast : generic;
+}
+// The kept products lie behind everything else, and only the size queries of the calls that can use them ask for their room:
+// `need` bytes are enough to run, without the array the call sweeps twice.  (A workspace sized for a large batch serves a
+// smaller one as well: the larger problem keeps nothing and may need less than the smaller one with its products.)
+static size_t sm_with_kept(size_t need, int B, int D, int64_t M) {
+    const size_t bytes = sm_kept_bytes(B, D, M);
+    return bytes ? ks_align_up(need, 256) + bytes : need;
+}
+static void sm_take_kept(SmWs &w, void *ws, size_t need, size_t ws_bytes, int B, int D, int64_t M) {
+    if (w.fast && sm_kept_bytes(B, D, M) && ws_bytes >= sm_with_kept(need, B, D, M)) w.kept = (float *)((char *)ws + ks_align_up(need, 256));
 }
 
 // Sweeps of a depth of up to eight k-tiles (D <= 512, D % 32 == 0): F(CFG) is instantiated for the depth's stage shape
@@ -1701,7 +1711,7 @@ static int sm_check_dims(int64_t C, int D, int B) {
 
 extern "C" size_t knn_softmax_workspace(int64_t C, int D, int B, int K, int M) {
     if (sm_check_dims(C, D, B) != KS_OK || K < 0 || M < 1) return 0;
-    return sm_bytes(C, D, B, K, M, true);
+    return sm_with_kept(sm_bytes(C, D, B, K, M, true), B, D, M);
 }
 
 static int sm_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const int32_t *labels, const int32_t *graph,
@@ -1717,9 +1727,11 @@ static int sm_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const int3
     if (sm_check_dims(C, D, B) != KS_OK || K < 0 || M < 1) return KS_INVALID_ARG;
     if (K > 0 && !graph) return KS_INVALID_ARG;
     if (B > M || (int64_t)K + 1 > M) return KS_INVALID_ARG;
-    if (ws_bytes < sm_bytes(C, D, B, K, M, true)) return KS_WORKSPACE_TOO_SMALL;
+    const size_t need = sm_bytes(C, D, B, K, M, true);
+    if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
     const bool fast = sm_fast(D, B, scale, grad_scale); // the update runs inside the dW kernel of this path
     SmWs w = sm_carve(ws, C, D, B, K, M, true, fast);
+    sm_take_kept(w, ws, need, ws_bytes, B, D, M);
     hipStream_t st = (hipStream_t)stream;
     if (ev) (void)hipEventRecord(ev[0], st);
     int rc = ks_select_launch(labels, graph, C, B, K, M, active_idx, n_active, target_pos, w.select, dev_status, st);
@@ -1963,7 +1975,7 @@ extern "C" size_t knn_softmax_selected_workspace(int64_t C, int D, int B, int M)
     if (sm_selected_check(C, D, B, M) != KS_OK) return 0;
     size_t total = 0;
     sm_split_carve(nullptr, C, D, B, M, true, &total);
-    return total;
+    return sm_with_kept(total, B, D, M);
 }
 // the next batch's selection that rides along with a step on a given selection (nullptr: none)
 struct SmNextArgs {
@@ -1996,6 +2008,7 @@ static int sm_selected(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16
     void *sel_ws = (char *)ws + need; // the selection's staging area follows the step's buffers
     if (nx) need += ks_select_ws_bytes(C, B, nx->K);
     if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
+    sm_take_kept(s.w, ws, need, ws_bytes, B, D, M);
     hipStream_t st = (hipStream_t)stream;
     const int nmax = M > B ? M : B;
     const int32_t *act = active_idx, *n_act = n_active, *tp = target_pos;
@@ -2054,7 +2067,7 @@ extern "C" size_t knn_softmax_selected_next_workspace(int64_t C, int D, int B, i
     if (sm_selected_check(C, D, B, M) != KS_OK || K < 0) return 0;
     size_t total = 0;
     sm_split_carve(nullptr, C, D, B, M, true, &total);
-    return ks_align_up(total, 256) + ks_select_ws_bytes(C, B, K);
+    return sm_with_kept(ks_align_up(total, 256) + ks_select_ws_bytes(C, B, K), B, D, M);
 }
 extern "C" int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_t *W_bf16, const uint16_t *X_bf16,
                                                         const int32_t *active_idx, const int32_t *n_active,
@@ -2070,11 +2083,12 @@ extern "C" int knn_softmax_fwd_bwd_update_selected_next(float *W_master, uint16_
                        loss_per_sample, loss_mean, dX, dW_active, &nx, ws, ws_bytes, dev_status, stream);
 }
 
+static size_t full_bytes(int64_t C, int D, int B) {
+    return sm_bytes(C, D, B, 0, C, false) + ks_align_up((size_t)C * 4, 256) + ks_align_up((size_t)B * 4, 256) + 256;
+}
 extern "C" size_t full_softmax_workspace(int64_t C, int D, int B) {
     if (sm_check_dims(C, D, B) != KS_OK) return 0;
-    size_t total = sm_bytes(C, D, B, 0, C, false);
-    total += ks_align_up((size_t)C * 4, 256) + ks_align_up((size_t)B * 4, 256) + 256;
-    return total;
+    return sm_with_kept(full_bytes(C, D, B), B, D, C);
 }
 
 extern "C" int full_softmax_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf16, const int32_t *labels, int64_t C,
@@ -2083,8 +2097,10 @@ extern "C" int full_softmax_fwd_bwd(const uint16_t *W_bf16, const uint16_t *X_bf
                                     int32_t *dev_status, void *stream) {
     if (!W_bf16 || !X_bf16 || !labels || !loss_per_sample || !loss_mean || !dX || !dW || !ws) return KS_INVALID_ARG;
     if (sm_check_dims(C, D, B) != KS_OK) return KS_INVALID_ARG;
-    if (ws_bytes < full_softmax_workspace(C, D, B)) return KS_WORKSPACE_TOO_SMALL;
+    const size_t need = full_bytes(C, D, B);
+    if (ws_bytes < need) return KS_WORKSPACE_TOO_SMALL;
     SmWs w = sm_carve(ws, C, D, B, 0, C, false, sm_fast(D, B, scale, grad_scale));
+    sm_take_kept(w, ws, need, ws_bytes, B, D, C);
     KsArena ar((char *)ws + sm_bytes(C, D, B, 0, C, false));
     int32_t *active_idx = ar.take<int32_t>((size_t)C);
     int32_t *target_pos = ar.take<int32_t>((size_t)B);

@@ -61,6 +61,15 @@ def test_workspace_sizes(ks):
     assert ks.apply_weight_grad_workspace(1000, 128, 100, 0) >= 128 * 8
 
 
+def test_only_calls_that_can_keep_products_ask_for_their_room(ks):
+    def kept(D, B, M):
+        return ks.knn_softmax_selected_workspace(100_000, D, B, M) - ks.knn_softmax_split_workspace(100_000, D, B, M)
+    for D, B, M in ((512, 500, 8_192), (64, 256, 4_096), (320, 300, 4_096)):
+        assert kept(D, B, M) >= 4 * B * M
+    # never more than 34 MB, however the rows are rounded up
+    assert all(kept(D, B, M) < 34 << 20 for D in (64, 256, 512) for B, M in ((1, 32_768), (65_536, 65_600), (257, 16_385), (512, 16_384)))
+
+
 def test_argument_errors_are_reported_before_any_launch(ks):
     L = ks.lib()
     null = ct.c_void_p(0)
