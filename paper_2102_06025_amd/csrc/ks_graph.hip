@@ -1681,12 +1681,19 @@ static int gr_rank_of(int K, int every) {
 // Workgroups per block of resident rows for the sample: the number with the least estimated time (rounds of workgroups x
 // (set-up + chunks), as in gr_parts, a chunk's insertions 1.5 us more; merging the lists in the recall pass 4 us and 0.3 per list).
 // 10,000 x 128: 40 blocks of 4 chunks, 19.8 -> 11.2 us with four; 25,000 x 256: 98 of 9, 47 -> 32 with two.
-static GrSample gr_sample_plan(int64_t Cr, int64_t n_sample, int D, int r, bool sym) {
+// The sampled rows and their lists are done with when the ranking starts and lie in the exhaustive pass's scratch, 512 bytes per
+// searched row: 64 at most for the rows, 48 per part and resident row for the lists.  A hop of many rows over few has parts only
+// as far as that goes.
+static_assert(GR_FB_BLOCKS * sizeof(double) >= 2 * 512 / 16 + GR_SAMPLE_PARTS * GR_RANK * sizeof(float), "a build has room for all parts");
+static GrSample gr_sample_plan(int64_t Cr, int64_t Cs, int every, int D, int r, bool sym) {
+    const int64_t n_sample = Cs / every;
+    const size_t room = (size_t)GR_FB_BLOCKS * Cs * sizeof(double), rows = ks_align_up((size_t)n_sample * D * sizeof(uint16_t), 256);
     const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(n_sample, 96);
     const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 2.7 + 0.4 * kt;
     int best = 1;
     double best_t = 0.0;
     for (int p = 1; p == 1 || (p <= chunks && p <= GR_SAMPLE_PARTS && !sym); ++p) { // (the symmetric sweep wants the thresholds ready)
+        if (p > 1 && rows + (size_t)p * GR_RANK * Cr * sizeof(float) > room) break;
         const double t = (double)ks_ceil_div(nb * p, GR_CUS) * (setup + (double)ks_ceil_div(chunks, p) * per_chunk) + (p > 1 ? 4.0 + 0.3 * p : 0.0);
         if (p == 1 || t < 0.98 * best_t) { best = p; best_t = t; }
     }
@@ -1709,7 +1716,7 @@ struct GrFixPlan {
 static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bool sym, bool hop) {
     GrFixPlan f;
     f.every = gr_every(Cs, D, K, dtype, hop);
-    f.smp = gr_sample_plan(Cr, Cs / f.every, D, gr_rank_of(K, f.every), sym);
+    f.smp = gr_sample_plan(Cr, Cs, f.every, D, gr_rank_of(K, f.every), sym);
     const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(Cs, 96);
     f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
     f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K, 32) + 10) + 24; // (with the denser sample: room for ties)
@@ -1770,8 +1777,9 @@ static GrWs gr_carve(void *ws, int64_t C, int D, int K, int dtype, size_t *total
         const GrFixPlan f = gr_fix_plan(C, C, D, K, dtype, sym, false);
         const int64_t Cpad = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
         w.cand = ar.take<uint64_t>((size_t)C * f.seg.cap());
-        w.Ws = ar.take<uint16_t>((size_t)(C / 16) * D); // (the denser sample, whatever K)
-        w.tops = f.smp.parts > 1 ? ar.take<float>((size_t)f.smp.parts * GR_RANK * C) : nullptr;
+        KsArena over(w.scratch); // see gr_sample_plan
+        w.Ws = over.take<uint16_t>((size_t)(C / f.every) * D);
+        w.tops = f.smp.parts > 1 ? over.take<float>((size_t)f.smp.parts * GR_RANK * C) : nullptr;
         w.thf = ar.take<float>((size_t)Cpad);
         w.tbits = ar.take<uint32_t>((size_t)C);
         w.cnt_res = ar.take<int32_t>((size_t)C * 2 * f.seg.parts);
@@ -2255,8 +2263,9 @@ static GrUpWs gr_up_carve(void *ws, int64_t C_loc, int64_t C_vis, int D, int K, 
     if (gr_use_fixed(C_loc, C_vis, D, K)) {
         const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, dtype, false, true);
         w.cand = ar.take<uint64_t>((size_t)C_loc * f.seg.cap());
-        w.Ws = ar.take<uint16_t>((size_t)(C_vis / f.every) * D);
-        w.tops = f.smp.parts > 1 ? ar.take<float>((size_t)f.smp.parts * GR_RANK * C_loc) : nullptr;
+        KsArena over(w.scratch);
+        w.Ws = over.take<uint16_t>((size_t)(C_vis / f.every) * D);
+        w.tops = f.smp.parts > 1 ? over.take<float>((size_t)f.smp.parts * GR_RANK * C_loc) : nullptr;
         w.thf = ar.take<float>((size_t)C_loc);
         w.tbits = ar.take<uint32_t>((size_t)C_loc);
         w.cnt_res = ar.take<int32_t>((size_t)C_loc * 2 * f.seg.parts);

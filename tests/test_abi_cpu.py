@@ -70,6 +70,18 @@ def test_only_calls_that_can_keep_products_ask_for_their_room(ks):
     assert all(kept(D, B, M) < 34 << 20 for D in (64, 256, 512) for B, M in ((1, 32_768), (65_536, 65_600), (257, 16_385), (512, 16_384)))
 
 
+def test_graph_workspace_serves_shorter_lists_and_bf16_rows(ks):
+    """The sample's density and division, which differ from K to K and from fp32 to bf16 rows, add nothing to the size."""
+    for C in (1_000, 3_125, 6_167, 10_000, 25_000, 37_192, 60_000, 195_000, 390_625):
+        for D in (64, 96, 256, 320, 512):
+            size = [ks.knn_graph_build_workspace(C, D, K, 0) for K in (4, 8, 16, 17, 24, 25, 32, 33, 64)]
+            assert size == sorted(size), (C, D, size)
+            assert all(ks.knn_graph_build_workspace(C, D, K, 1) >= n + 2 * C * D for K, n in ((8, size[1]), (24, size[4]), (64, size[8])))
+    for C_loc, large, small, D, K, dtype in ((74_118, 32_640, 21_913, 64, 24, 1), (82_841, 66_745, 62_305, 64, 4, 1),
+                                             (212_230, 248_023, 245_316, 64, 48, 0)):
+        assert ks.knn_graph_update_workspace(C_loc, small, D, K, dtype) <= ks.knn_graph_update_workspace(C_loc, large, D, K, dtype)
+
+
 def test_argument_errors_are_reported_before_any_launch(ks):
     L = ks.lib()
     null = ct.c_void_p(0)
