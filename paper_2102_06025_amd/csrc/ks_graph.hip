@@ -653,16 +653,17 @@ struct GrSample {
 // A lane keeps the GR_RANK largest similarities of its row that it has seen, sorted, in registers: an insertion is one
 // median-of-three per place.  (The first version appended to candidate buffers in memory and cut them back: every cut is
 // 32 rows in turn per wavefront, 199 us for 10,000 rows of 128 against a sample of 312.)
-template <class CFG>
+// PARTS: whether smp.parts > 1.
+template <class CFG, bool PARTS>
 __global__ void __launch_bounds__(512)
 gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *__restrict__ Ws, int n_sample, int D,
                     GrSample smp, const float *__restrict__ blockmax, int n_blockmax, float *maxnorm, GrHop hop, float *__restrict__ thf,
                     uint32_t *__restrict__ tbits) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
-    const int id = smp.parts > 1 ? ks_xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x, nb = gridDim.x / smp.parts;
-    const int part = id / nb;
-    const int64_t row0 = (int64_t)(id % nb) * CFG::RES;
-    const int s0 = part * smp.part_rows, s1 = s0 + smp.part_rows < n_sample ? s0 + smp.part_rows : n_sample;
+    const int id = PARTS ? ks_xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x, nb = PARTS ? gridDim.x / smp.parts : gridDim.x;
+    const int part = PARTS ? id / nb : 0;
+    const int64_t row0 = (int64_t)(PARTS ? id % nb : id) * CFG::RES;
+    const int s0 = PARTS ? part * smp.part_rows : 0, s1 = PARTS && s0 + smp.part_rows < n_sample ? s0 + smp.part_rows : n_sample;
     float top[GR_RANK]; // descending
 #pragma unroll
     for (int k = 0; k < GR_RANK; ++k) top[k] = -INFINITY;
@@ -689,11 +690,11 @@ gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *
     };
     ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, s0, s1, n_sample, lds, epi);
     gr_merge_halves(top); // the two lanes of a row hold disjoint sampled rows
-    const float mx = (smp.parts == 1 && hop.graph) || id == 0 ? gr_max_norm(blockmax, n_blockmax) : 0.f;
+    const float mx = (!PARTS && hop.graph) || id == 0 ? gr_max_norm(blockmax, n_blockmax) : 0.f;
     if (id == 0 && threadIdx.x == 0) *maxnorm = mx;
     const int64_t i = row0 + ks_soe_col();
     if ((threadIdx.x & 63) < 32 && i < Cr) {
-        if (smp.parts > 1) {
+        if (PARTS) {
 #pragma unroll
             for (int k = 0; k < GR_RANK; ++k) smp.tops[((int64_t)part * GR_RANK + k) * Cr + i] = top[k];
         } else {
@@ -703,8 +704,18 @@ gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *
         }
     }
 }
+// What the recall pass needs to merge the parts' lists, or nothing where the thresholds are ready.  (Two kernels: the merge as
+// a branch of one made that one 1.5 % slower at every size that does not take it, 60,000 x 320: 2,486 -> 2,524 us.)
+struct GrReady {};
+struct GrMerge {
+    GrSample smp;
+    GrHop hop;
+    const float *maxnorm;
+    uint32_t *tbits; // for the ranking
+};
 // The threshold of row i (the same row in lanes l and l + 32) from the parts' lists; all lanes of a wavefront call.
-__device__ __forceinline__ uint32_t gr_merge_parts(const GrSample &smp, const GrHop &hop, int64_t Cr, int64_t i, const float *maxnorm) {
+__device__ __forceinline__ uint32_t gr_merge_parts(const GrMerge &merge, int64_t Cr, int64_t i) {
+    const GrSample &smp = merge.smp;
     float top[GR_RANK];
 #pragma unroll
     for (int k = 0; k < GR_RANK; ++k) top[k] = -INFINITY;
@@ -717,7 +728,7 @@ __device__ __forceinline__ uint32_t gr_merge_parts(const GrSample &smp, const Gr
         for (int k = 0; k < GR_RANK; ++k) gr_insert(top, v[k]);
     }
     gr_merge_halves(top);
-    return gr_threshold_of(top, smp.r, hop, row, hop.graph ? *maxnorm : 0.f);
+    return gr_threshold_of(top, smp.r, merge.hop, row, merge.hop.graph ? *merge.maxnorm : 0.f);
 }
 
 // Element r (0 .. 15, different from lane to lane) of a lane's 16 accumulator values: a binary tree of selects on the
@@ -778,11 +789,10 @@ __device__ __forceinline__ uint32_t gr_hit_mask(float t, const f32x16_t &a) {
 // counts in a register: an append is a store and an increment.  In the problems that come here one value in 30 to 1,000
 // passes, so that of 64 lanes x 16 values nearly always some do: the hits of a lane become a bit mask and are taken one by
 // one (testing value by value costs a branch around the append for each of them).
-template <class CFG>
+template <class CFG, class MERGE>
 __global__ void __launch_bounds__(512)
-gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, GrSample smp, GrHop hop, const float *__restrict__ maxnorm,
-                     const float *__restrict__ thf_row, uint32_t *__restrict__ tbits, uint64_t *__restrict__ cand,
-                     int32_t *__restrict__ cnt_res) {
+gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE merge, const float *__restrict__ thf_row,
+                     uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
     const int id = ks_xcd_remap(blockIdx.x, gridDim.x); // the workgroups of an XCD stream the same parts
     const int part = id / nb;
@@ -791,15 +801,13 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, GrSamp
     const int Cr = (int)pr.Cr;
     const int cap = seg.cap(), last = 2 * seg.q - 1;
     const int64_t self0 = row0 + pr.self; // streamed rows [self0, self0 + RES) are this workgroup's own rows
-    float thf = INFINITY;
-    if (smp.parts > 1) {
-        const uint32_t bits = gr_merge_parts(smp, hop, Cr, row0 + ks_soe_col(), maxnorm);
-        if (row0 + ks_soe_col() < Cr) {
-            thf = gr_unorder(bits);
-            if (part == 0 && (threadIdx.x & 32) == 0) tbits[row0 + ks_soe_col()] = bits; // for the ranking
-        }
-    } else if (row0 + ks_soe_col() < Cr) {
-        thf = thf_row[row0 + ks_soe_col()];
+    float thf;
+    if constexpr (std::is_same<MERGE, GrMerge>::value) {
+        const uint32_t bits = gr_merge_parts(merge, Cr, row0 + ks_soe_col());
+        thf = row0 + ks_soe_col() < Cr ? gr_unorder(bits) : INFINITY;
+        if (part == 0 && (threadIdx.x & 32) == 0 && row0 + ks_soe_col() < Cr) merge.tbits[row0 + ks_soe_col()] = bits;
+    } else {
+        thf = row0 + ks_soe_col() < Cr ? thf_row[row0 + ks_soe_col()] : INFINITY;
     }
     uint64_t *const wg_cand = cand + (int64_t)row0 * cap;
     // the lanes 0..31 fill their row's slots from the first one upwards, the lanes 32..63 from the last one downwards
@@ -1233,8 +1241,14 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // One kernel does what were three passes over the candidates (cut, re-rank, and before them a gather of the
 // segments): the keys are read once, and the row's own data and the other lanes' entries come through scalar registers
 // (the ranking by shuffles cost three LDS permutes and 24 instructions per entry, now three lane reads and 6).
+// SHORT: lists of at most 256 candidates have a copy of the search of their own, taken for K <= 24 (beyond, too few rows have
+// so few).  For K <= 32 the kernel of K > 24 does without the copy, which alone costs it 1 %.  For K > 32 and bf16 rows the
+// compiler needs 83 registers with it and 123 without: five wavefronts to a SIMD instead of four, but the longer chain of one.
+// So it has the copy where the rows need more than one round of the chip at four (GR_RANK_AT_ONCE).  Builds, us, without -> with:
+// 2,000 x 512, K = 64: 87.3 -> 88.6; 4,000 x 320, K = 33: 92.2 -> 93.0; 5,000 x 512, K = 64: 162.9 -> 149.4; 20,000 x 64, K = 64: 319 -> 301.
 // ------------------------------------------------------------------------------------------------
-template <typename IN, int KP, bool HOP>
+#define GR_RANK_AT_ONCE 4096 /* 256 compute units x 4 workgroups x 4 rows */
+template <typename IN, int KP, bool HOP, bool SHORT>
 __global__ void __launch_bounds__(GR_NT)
 gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, int64_t Cv, int D, int K, GrSegs seg,
                const uint64_t *__restrict__ cand, const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str,
@@ -1352,7 +1366,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
             }
         }
     };
-    if (K <= 24 && n <= 256) select(std::integral_constant<int, 4>()); // (beyond, too few rows have so few)
+    if (SHORT && K <= 24 && n <= 256) select(std::integral_constant<int, 4>());
     else if (n <= 512) select(std::integral_constant<int, 8>());
     else select(std::integral_constant<int, GR_MAX_CAND / 64>());
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the keys written by the other lanes are in LDS
@@ -1881,8 +1895,14 @@ static void gr_launch_threshold(const uint16_t *R, int64_t Cr, const uint16_t *W
                                 int n_blockmax, float *maxnorm, const GrHop &hop, float *thf, uint32_t *tbits, hipStream_t st) {
     const dim3 grid((unsigned)(ks_ceil_div(Cr, 256) * smp.parts));
 #define GR_THR_LAUNCH(CFG)                                                                                                    \
-    hipLaunchKernelGGL((gr_threshold_kernel<CFG>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
-                       n_blockmax, maxnorm, hop, thf, tbits)
+    do {                                                                                                                      \
+        if (smp.parts > 1)                                                                                                    \
+            hipLaunchKernelGGL((gr_threshold_kernel<CFG, true>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
+                               n_blockmax, maxnorm, hop, thf, tbits);                                                         \
+        else                                                                                                                  \
+            hipLaunchKernelGGL((gr_threshold_kernel<CFG, false>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
+                               n_blockmax, maxnorm, hop, thf, tbits);                                                         \
+    } while (0)
     GR_FOR_DEPTH(GR_THR_LAUNCH);
 #undef GR_THR_LAUNCH
 }
@@ -1890,9 +1910,16 @@ static void gr_launch_recall_fix(const GrPair &pr, int D, const GrFixPlan &f, co
                                  const float *thf, uint32_t *tbits, uint64_t *cand, int32_t *cnt_res, hipStream_t st) {
     const int nb = (int)ks_ceil_div(pr.Cr, 256);
     const dim3 grid((unsigned)(nb * f.seg.parts));
-#define GR_FIX_LAUNCH(CFG) \
-    hipLaunchKernelGGL((gr_recall_fix_kernel<CFG>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, smp, hop, maxnorm, thf, \
-                       tbits, cand, cnt_res)
+    const GrMerge merge{smp, hop, maxnorm, tbits};
+#define GR_FIX_LAUNCH(CFG)                                                                                                          \
+    do {                                                                                                                            \
+        if (smp.parts > 1)                                                                                                          \
+            hipLaunchKernelGGL((gr_recall_fix_kernel<CFG, GrMerge>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, merge, thf, \
+                               cand, cnt_res);                                                                                      \
+        else                                                                                                                        \
+            hipLaunchKernelGGL((gr_recall_fix_kernel<CFG, GrReady>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, GrReady(), \
+                               thf, cand, cnt_res);                                                                                 \
+    } while (0)
     GR_FOR_DEPTH(GR_FIX_LAUNCH);
 #undef GR_FIX_LAUNCH
 }
@@ -1968,12 +1995,14 @@ template <typename IN>
 static void gr_launch_rank(const IN *W, int64_t C, int D, int K, const GrFixPlan &f, const GrWs &w, float gamma,
                            int32_t *graph, float *sims, hipStream_t st) {
     const dim3 grid((unsigned)ks_ceil_div(C, GR_NT / 64));
-#define GR_RANK_LAUNCH(KP)                                                                                                     \
-    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, false>), grid, dim3(GR_NT), 0, st, W, C, W, C, D, K, f.seg, w.cand,               \
+#define GR_RANK_LAUNCH(KP, SHORT)                                                                                              \
+    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, false, SHORT>), grid, dim3(GR_NT), 0, st, W, C, W, C, D, K, f.seg, w.cand,               \
                        w.cnt_res, w.cnt_str, w.tbits, w.norms, w.maxnorm, gamma, (int64_t)0, graph, (void *)sims, w.second_count, \
                        w.second_rows)
-    if (K <= 32) GR_RANK_LAUNCH(1);
-    else GR_RANK_LAUNCH(2);
+    if (K <= 24) GR_RANK_LAUNCH(1, true);
+    else if (K <= 32) GR_RANK_LAUNCH(1, false);
+    else if (sizeof(IN) == 2 && C > GR_RANK_AT_ONCE) GR_RANK_LAUNCH(2, true);
+    else GR_RANK_LAUNCH(2, false);
 #undef GR_RANK_LAUNCH
     hipLaunchKernelGGL(gr_second_kernel<IN>, dim3(1024), dim3(GR_NT), 0, st, W, C, D, K, f.seg, w.cand, w.cnt_res, w.cnt_str, w.tbits,
                        w.norms, w.maxnorm, gamma, w.second_count, w.second_rows, graph, sims, w.fb_count, w.fb_rows);
@@ -2296,12 +2325,14 @@ template <typename IN>
 static void gr_up_exact(const IN *Wl, int64_t C_loc, const IN *Wv, int64_t C_vis, int D, int K, const GrParams &p, const GrFixPlan *f,
                         const GrUpWs &w, float gamma, int64_t lo, int64_t vo, int32_t *graph, double *sims, hipStream_t st) {
     const dim3 grid((unsigned)ks_ceil_div(C_loc, GR_NT / 64));
-#define GR_HOP_RANK_LAUNCH(KP)                                                                                                 \
-    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, true>), grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, f->seg,             \
+#define GR_HOP_RANK_LAUNCH(KP, SHORT)                                                                                          \
+    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, true, SHORT>), grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, f->seg,             \
                        w.cand, w.cnt_res, (const int32_t *)nullptr, w.tbits, w.norms_l, w.maxnorm_v, gamma, vo, graph, (void *)sims, \
                        w.fb_count, w.fb_rows)
-    if (f && K <= 32) GR_HOP_RANK_LAUNCH(1);
-    else if (f) GR_HOP_RANK_LAUNCH(2);
+    if (f && K <= 24) GR_HOP_RANK_LAUNCH(1, true);
+    else if (f && K <= 32) GR_HOP_RANK_LAUNCH(1, false);
+    else if (f && sizeof(IN) == 2 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(2, true);
+    else if (f) GR_HOP_RANK_LAUNCH(2, false);
     else
         hipLaunchKernelGGL(gr_merge_kernel<IN>, grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, p.cap, w.cand, w.cnt, w.thr,
                            w.norms_l, w.maxnorm_v, gamma, lo, vo, graph, sims, w.fb_count, w.fb_rows);
