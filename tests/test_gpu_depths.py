@@ -267,20 +267,39 @@ def _exhaustive_rows(ws, norms, largest, maxima):
     return int(ws[at + 256:at + 260].view(torch.int32))
 
 
-@pytest.mark.parametrize("K,rank,above", [(16, 8, 1100), (32, 10, 1200), (64, 12, 1350)])
+def _sampled_rows_of(C, every):
+    """One row of every 16 or 32 searched ones."""
+    s = np.arange(C // every, dtype=np.int64)
+    return s * every + (((s * 2654435761) & 0xFFFFFFFF) >> 16) % every
+
+
+def _searched_sample(ws, norms, maxima, Wv):
+    """How many searched rows there are to a sampled one in what a call without exhaustive rows has left in its workspace: the
+    list of rows for the exhaustive search follows their number, and then come the sampled rows (bf16)."""
+    import torch
+    at = 2 * ((4 * norms + 255) // 256 * 256) + maxima * 4096 + 512
+    for every in (16, 32):
+        rows = torch.from_numpy(_sampled_rows_of(Wv.shape[0], every)).cuda()
+        n = rows.numel() * Wv.shape[1] * 2
+        if n and torch.equal(ws[at:at + n].view(torch.bfloat16).view(rows.numel(), -1), Wv[rows].to(torch.bfloat16)):
+            return every
+    return 0
+
+
+@pytest.mark.parametrize("D,K,every,rank,above", [(128, 16, 16, 10, 1100), (320, 16, 32, 8, 1100), (128, 32, 32, 10, 1200), (128, 64, 32, 12, 1350)])
 @pytest.mark.parametrize("residues", [(0, 1, 2, 3), (5,), range(8)])
-def test_neighbours_of_one_residue_modulo_8(ks, orc, residues, K, rank, above):
+def test_neighbours_of_one_residue_modulo_8(ks, orc, residues, D, K, every, rank, above):
     """The pass of all rows by all blocks: the two lanes that hold a row see the searched rows with bit 2 of their id clear, or
     set.  All rows share their neighbours, which are all one lane's, or fall to both (one residue, half, any), and the sample is an
     unlucky one (`above` rows above its rank-th largest).  No row may be left for the exhaustive search, in the build (one
-    part) or in a hop (several, the neighbours in one of them)."""
+    part) or in a hop (several, the neighbours in one of them; its sample is one in 32 for every K and the build's own for
+    D = 320 and K > 24)."""
     import torch
-    C, D = 60_000, 128
-    print(f"[depths] residues {list(residues)} K={K}", flush=True)
+    C = 60_000
+    print(f"[depths] residues {list(residues)} D={D} K={K}", flush=True)
     ids = np.arange(C)
     hubs = ids[np.isin(ids % 8, list(residues))][:2304]
-    s = np.arange(C // 32, dtype=np.int64)
-    sampled = s * 32 + (((s * 2654435761) & 0xFFFFFFFF) >> 16) % 32
+    sampled = _sampled_rows_of(C, every)
     rng = np.random.default_rng(K)
     in_hub, free = rng.permutation(np.intersect1d(hubs, sampled)), rng.permutation(np.setdiff1d(hubs, sampled))
     n_free = above - rank + 1
@@ -298,6 +317,7 @@ def test_neighbours_of_one_residue_modulo_8(ks, orc, residues, K, rank, above):
     g, sims = ks.knn_graph_build(Wd, K, want_sims=True, ws=ws)
     torch.cuda.synchronize()
     assert _exhaustive_rows(ws, C, largest, 1) == 0
+    assert _searched_sample(ws, C, 1, Wd) == every
     rows = np.unique(np.concatenate([synth.class_permutation(43, C)[:60], order[:5], [0, C - 1]])).astype(np.int32)
     eg, es = orc.graph_bruteforce(W, K, rows)
     assert (g.cpu().numpy()[rows] == eg).all() and (sims.cpu().numpy()[rows] == es.astype(np.float32)).all()
@@ -308,6 +328,7 @@ def test_neighbours_of_one_residue_modulo_8(ks, orc, residues, K, rank, above):
     ks.knn_graph_update(Wd[C - n:].contiguous(), Wd, C - n, 0, lists, best, ws=ws)
     torch.cuda.synchronize()
     assert _exhaustive_rows(ws, n, largest, 2) == 0
+    assert _searched_sample(ws, n, 2, Wd) == 32
     assert torch.equal(lists, g[C - n:])
 
 
