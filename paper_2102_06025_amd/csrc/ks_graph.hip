@@ -1677,7 +1677,10 @@ static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
 // K = 16: 30,532 -> 29,495, hence C * D <= 50 million.  Deeper than 256 a sampled row costs more and it pays up to 15 million
 // (30,000 x 512, K = 16: 969 -> 962; 45,000 x 320, K = 8: 1,679 -> 1,678; but 48,000 x 512, K = 16: 1,813 -> 1,818; 100,000 x 320,
 // K = 16: 7,518 -> 7,650; 90,000 x 512, K = 16: 5,854 -> 5,977), at D = 512 with K > 16, the symmetric sweep and 128 fewer
-// candidates, up to 30 million (58,000, K = 24: 2,738 -> 2,659; but 70,000: 4,187 -> 4,204).
+// candidates, up to 30 million (58,000, K = 24: 2,738 -> 2,659; but 70,000: 4,187 -> 4,204).  Without that sweep and
+// with K > 8 it pays up to 96,000 rows (95,000 x 64, K = 16: 2,463 -> 2,439; 90,000 x 128: 3,425 -> 3,416; x 192: 4,367 -> 4,352;
+// but 110,000 x 64: 3,020 -> 3,064; x 128: 4,928 -> 4,986; x 192: 6,371 -> 6,454; 180,000 x 192: 16,860 -> 17,067; with K = 8 still
+// 4,914 -> 4,883 at 110,000 x 128 and 16,797 -> 16,752 at 180,000 x 192), at 96 throughout (195,000, K = 16: 12,754 -> 12,696).
 // fp32 rows stay: their error bound is that of rounding the rows to bf16, and with a threshold closer to the K-th neighbour
 // more rows of tight clusters have no certificate (20,000 x 256 in clusters of 200 with noise of 0.1: 36 -> 290 ms).  So does
 // K > 24: with 12 places two rows in a million find at most 32 (a tenth of that as it is), and one such row in the exhaustive
@@ -1685,7 +1688,8 @@ static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
 // denser sample after the first one (2,000 x 2,000 x 256 with full lists: 42 -> 44): it stays too.
 // The chance that a row finds at most K is one in ten million at K = 24.
 static int gr_every(int64_t C, int D, int K, int dtype, bool hop) {
-    const int64_t most = D <= 256 ? 50000000 : (D == 512 && K > 16 ? 30000000 : 15000000);
+    int64_t most = D <= 256 ? 50000000 : (D == 512 && K > 16 ? 30000000 : 15000000);
+    if (!gr_use_sym(C, D, K) && K > 8 && (D == 64 || D >= 128) && C > 96000) most = 0;
     return !hop && dtype == KS_DTYPE_BF16 && K <= 24 && C * D <= most ? 16 : 32;
 }
 static int gr_rank_of(int K, int every) {

@@ -397,10 +397,13 @@ def test_one_sweep_combine_beside_the_dx_tiles(ks, orc, C, D, B, K, M):
 
 @pytest.mark.parametrize("C,D,K,bf16", [(95, 64, 3, True), (1537, 64, 8, True), (1800, 128, 16, True), (10_000, 128, 8, False), (10_000, 128, 8, True),
                                         (30_001, 64, 32, True), (66_000, 32, 9, True), (58_594, 512, 24, True), (58_593, 512, 24, True),
-                                        (46_876, 320, 9, True), (46_875, 320, 9, True), (195_313, 256, 5, True), (195_312, 256, 5, True)])
+                                        (46_876, 320, 9, True), (46_875, 320, 9, True), (195_313, 256, 5, True), (195_312, 256, 5, True),
+                                        (96_000, 64, 9, True), (96_001, 64, 9, True), (96_001, 128, 8, True), (96_001, 192, 16, True)])
 def test_graph_on_both_sides_of_the_denser_sample(ks, orc, C, D, K, bf16):
     """Samples of one row in 16 (less than a chunk, one chunk, several workgroups' lists merged, more blocks than compute units)
-    and of one in 32, on either side of the lines between them (C * D = 50, 15 and 30 million): with clustered rows and exact twins."""
+    and of one in 32, on either side of the lines between them (C * D = 50, 15 and 30 million, 96,000 rows with K > 8): with
+    clustered rows and exact twins.  The sample is the one that was asked for.  No row of bf16 goes to the exhaustive search,
+    which finds the right list whatever the thresholds were; of fp32 rows, whose error bound is that of their rounding, at most a few do."""
     import torch
     print(f"[depths] sample C={C} D={D} K={K}", flush=True)
     rng = np.random.default_rng(C)
@@ -410,10 +413,21 @@ def test_graph_on_both_sides_of_the_denser_sample(ks, orc, C, D, K, bf16):
     W[C - 1] = W[C // 3]
     W = synth.bf16_round(W) if bf16 else W.astype(np.float32)
     rows = np.unique(np.concatenate([rng.integers(0, C, 60), [0, C // 3, C - 1]])).astype(np.int32)
-    g, s = ks.knn_graph_build(dev(W, bf16), K, want_sims=True)
+    ws = torch.zeros(ks.knn_graph_build_workspace(C, D, K, 0 if bf16 else 1), dtype=torch.uint8, device="cuda")
+    Wd = dev(W, bf16)
+    g, s = ks.knn_graph_build(Wd, K, want_sims=True, ws=ws)
     torch.cuda.synchronize()
     eg, es = orc.graph_bruteforce(W, K, rows)
     assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
+    if bf16:
+        assert _exhaustive_rows(ws, C, float(Wd.double().norm(dim=1).max()), 1) == 0
+        most = 50e6 if D <= 256 else 30e6 if D == 512 and K > 16 else 15e6
+        symmetric = D in (128, 256, 512) and C * D >= 15e6
+        long = not symmetric and K > 8 and (D == 64 or D >= 128) and C > 96_000
+        assert _searched_sample(ws, C, 1, Wd) == (16 if K <= 24 and C * D <= most and not long else 32)
+    else:
+        at = 2 * C * D + (4 * C + 255) // 256 * 256 + 4096 + 256   # (the copy in bf16 comes first)
+        assert int(ws[at:at + 4].view(torch.int32)) <= 8
 
 
 @pytest.mark.parametrize("C_loc,C_vis,D,K", [(40, 7_000, 64, 8), (600, 30_000, 256, 33)])
