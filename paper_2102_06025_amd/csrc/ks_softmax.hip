@@ -1070,15 +1070,19 @@ struct DwCells {
 // trip -- so with few rows the smallest tiles that still fit the chip in one round are the fastest; tall tiles load the X panel
 // and a wide tile the dZ8 panel less often, which counts once every compute unit has a tile.  Estimated time = rounds x cost
 // of a lone tile x (1 + share of the compute units at work: the memory is shared); the smallest wins, ties to the larger tile.
-// The costs are those that reproduce the order of the five shapes at sixteen sizes.  us, 256 x 256, 192 x 256, 128 x 256,
-// 128 x 128, 64 x 128 (dW and update, list of A classes): D = 128, B = 64, A = 600: 16.3, 11.2, 8.4, 5.9, 5.1; D = 320,
-// B = 333, A = 3,001: 21.3, 16.6, 12.4, 9.0, 7.8; D = 512, B = 1,024, A = 4,725: 36.5, 29.1, 24.0, 21.6, 25.2;
-// A = 17,425: 48.9, 40.0, 51.0, 51.6, 58.7; A = 32,374: 54.0, 58.8, 57.8, 67.3, 91.0.  (64 x 256: never ahead of 128 x 128.)
+// The costs are fitted to whole calls with each shape forced, at 1,700 sizes of D = 64 to 512, B = 33 to 2,048, A = 600 to
+// 110,000: the call with the shape chosen is 0.2 % slower than with the best one on average, 8 % at most (the batch makes no
+// difference to the choice, and near ties may go either way).  us, 256 x 256, 192 x 256, 128 x 256, 128 x 128, 64 x 128: dW and
+// update, list of A classes: D = 128, B = 64, A = 600: 16.3, 11.2, 8.4, 5.9, 5.1; D = 320, B = 333, A = 3,001: 21.3, 16.6, 12.4,
+// 9.0, 7.8; D = 512, B = 1,024, A = 4,725: 36.5, 29.1, 24.0, 21.6, 25.2; A = 17,425: 48.9, 40.0, 51.0, 51.6, 58.7; A = 32,374:
+// 54.0, 58.8, 57.8, 67.3, 91.0.  Whole calls: D = 512, B = 2,048, A = 6,529: 123.5, 109.3, 100.8, 90.7, 109.4; D = 256, B = 1,024,
+// A = 6,529: 72.5, 62.2, 57.2, 52.1, 47.5; D = 512, B = 64, A = 15,391: 44.1, 40.4, 43.8, 45.1, 44.0.  (64 x 256: never ahead of
+// 128 x 128.)
 enum { DW_KINDS = 5 };
 __device__ __forceinline__ int dw_tile_kind(int n_active, int D, int n_cu, int tiles_max) {
     const int rows[DW_KINDS] = {TileDw::BM, TileDw192::BM, TileDw128::BM, TileDw128n::BM, TileDw64n::BM};
     const int cols[DW_KINDS] = {TileDw::BN, TileDw192::BN, TileDw128::BN, TileDw128n::BN, TileDw64n::BN};
-    const float cost[DW_KINDS] = {33.5f, 24.4f, 17.7f, 13.8f, 10.8f};
+    const float cost[DW_KINDS] = {31.5f, 21.24f, 18.0f, 13.78f, 10.57f};
     const float per_cu = 1.f / (float)n_cu;
     int best = 0;
     float best_t = INFINITY;
@@ -1086,7 +1090,7 @@ __device__ __forceinline__ int dw_tile_kind(int n_active, int D, int n_cu, int t
     for (int k = 0; k < DW_KINDS; ++k) {
         const int tiles = ((D + cols[k] - 1) / cols[k]) * ((n_active + rows[k] - 1) / rows[k]);
         const float share = (float)tiles * per_cu;
-        const float t = ceilf(share) * cost[k] * (1.f + fminf(share, 1.f));
+        const float t = ceilf(share) * cost[k] * (1.f + 0.98f * fminf(share, 1.f));
         if (t < best_t && tiles <= tiles_max) { best_t = t; best = k; }
     }
     return best;

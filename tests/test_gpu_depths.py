@@ -348,25 +348,44 @@ def test_candidate_counts_of_many_rows_fit(ks):
 
 @pytest.mark.parametrize("D,A,B", [
     (64, 2, 1), (128, 63, 33), (320, 65, 64), (128, 4097, 65),       # tiles of 64 x 128: two rows, one short, one over, many
-    (512, 4737, 40), (320, 5000, 33),                                # 128 x 128
-    (512, 6529, 33), (512, 6527, 129),                               # 128 x 256
+    (512, 4737, 40), (320, 5000, 33), (512, 6529, 33), (512, 6527, 129),   # 128 x 128
+    (512, 8200, 33), (512, 11_999, 129),                             # 128 x 256
     (2048, 4225, 40), (2048, 6209, 33)])                             # 192 x 256, 256 x 256
 def test_gradient_rows_and_update_in_every_tile_shape(ks, orc, D, A, B):
     """The dW launch picks its tile from the active count: lists that end inside a tile of each shape, depths that end inside
     one.  Gradient rows against the oracle, rows beyond the list untouched, the update bit for bit the stand-alone one."""
+    _gradient_rows_and_update(ks, orc, D, A, B, False)
+
+
+@pytest.mark.parametrize("D,A,B", [
+    (128, 401, 333), (128, 4097, 333), (256, 6529, 129),             # 64 x 128
+    (512, 4737, 333), (128, 20_001, 200), (256, 13_000, 65),         # 128 x 128
+    (512, 8200, 333), (256, 18_001, 130),                            # 128 x 256
+    (512, 17_425, 333), (128, 33_001, 64), (256, 33_000, 127),       # 192 x 256
+    (512, 32_374, 130)])                                             # 256 x 256
+def test_target_entries_in_every_tile_shape(ks, orc, D, A, B):
+    """Unit rows: the samples' own entries are put into the tiles in LDS, in every shape, over more k-tiles than have their entries
+    there at a time, with batches that end inside one and classes that several samples share."""
+    _gradient_rows_and_update(ks, orc, D, A, B, True)
+
+
+def _gradient_rows_and_update(ks, orc, D, A, B, unit):
     import torch
     from gradcheck import check_rows, grad_floors
-    print(f"[depths] dW tiles D={D} A={A} B={B}", flush=True)
+    print(f"[depths] dW tiles D={D} A={A} B={B} unit={unit}", flush=True)
     C, M, scale, gs, alpha = A + 77, A + 13, 20.0, 4.0, -0.5
     W, X = synth.unit_rows(41, synth.TID_W, C, D, bf16=True), synth.unit_rows(41, synth.TID_X, B, D, bf16=True)
     active = np.sort(synth.class_permutation(41, C)[:A]).astype(np.int32)
     tpos = ((np.arange(B) * 7919 + A - 1) % A).astype(np.int32)
+    if unit:
+        tpos[B // 2:] = tpos[:B - B // 2]
     act = np.full(M, -1, np.int32)
     act[:A] = active
     Wm, Wb, n = dev(W), dev(W, True), dev(np.array([A], np.int32))
     out = dict(loss_per_sample=torch.empty(B, device="cuda"), loss_mean=torch.empty(1, device="cuda"),
                dX=torch.empty((B, D), device="cuda"), dW_active=torch.full((M, D), 123.0, device="cuda"))
-    ks.knn_softmax_fwd_bwd_update_selected(Wm, Wb, dev(X, True), dev(act), n, dev(tpos), scale, gs, alpha, out=out, want_dW=True)
+    ks.knn_softmax_fwd_bwd_update_selected(Wm, Wb, dev(X, True), dev(act), n, dev(tpos), scale, gs, alpha, out=out, want_dW=True,
+                                           unit_rows=unit)
     Wm2, Wb2 = dev(W), dev(W, True)
     ks.apply_weight_grad(Wm2, Wb2, dev(act), n, out["dW_active"], alpha, idx_sorted_unique=True)
     torch.cuda.synchronize()
