@@ -445,7 +445,7 @@ __host__ __device__ __forceinline__ int sm_slab_rows(int n64, int slabs) {
 // a 32 x 32 block hold them: four pieces of 64 lanes x 16 bytes.  In 16-byte pieces: the first of class block cb, sample block sb.
 __device__ __forceinline__ int64_t sm_kept_at(int cb, int sb, int Bp, int lane) { return ((int64_t)cb * (Bp >> 5) + sb) * 256 + lane; }
 
-template <class CFG>
+template <class CFG, bool KEEP>
 __global__ void __launch_bounds__(512)
 sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ W, const int32_t *__restrict__ active_idx,
                     const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, int B, int Bp, int D, int M,
@@ -470,7 +470,7 @@ sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     // l = sum exp(scale * (acc - m)) = sum exp2(fma(acc, k1, -k1 * m)); one fused multiply-add per element
     const float k1 = scale * 1.4426950408889634f;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
-        if (kept) {
+        if (KEEP) {
             float4 *p = (float4 *)kept + sm_kept_at(c0 >> 5, i >> 5, Bp, lane);
 #pragma unroll
             for (int fm = 0; fm < CFG::FM; ++fm)
@@ -1100,11 +1100,12 @@ __device__ __forceinline__ int dw_tile_kind(int n_active, int D, int n_cu, int t
 #define DW_CELL_SLOTS 4 /* k-tiles whose cells lie in LDS */
 constexpr int DW_TILE_ELEMS = TileDw::LDS_ELEMS + 2 * (TileDw::BM + DW_CELL_SLOTS * 128);
 constexpr int DW_LDS_ELEMS = DW_TILE_ELEMS > 2 * SEL1_LDS_WORDS ? DW_TILE_ELEMS : 2 * SEL1_LDS_WORDS;
-template <class T>
+template <class T, bool CELLS>
 __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
                                         const DwUpdate &up, const DwCells &cells);
 
+template <bool CELLS>
 __global__ void __launch_bounds__(TileDw::NT)
 dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B, int Bp,
                 const int32_t *__restrict__ n_active_p, int D, int M, int64_t Mp, float scale, float *__restrict__ dW,
@@ -1149,7 +1150,7 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
     }
     const int n_active = sm_clamp_n(n_active_p, M);
     const int kind = dw_tile_kind(n_active, D, n_cu, tiles_max);
-#define DW_TILE(T) dw_tile<T>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up, cells)
+#define DW_TILE(T) dw_tile<T, CELLS>(bid, lds, dZ8, X, B, Bp, n_active, D, Mp, scale, dW, up, cells)
     if (kind == 0) DW_TILE(TileDw);
     else if (kind == 1) DW_TILE(TileDw192);
     else if (kind == 2) DW_TILE(TileDw128);
@@ -1158,7 +1159,7 @@ dw_async_kernel(const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X
 #undef DW_TILE
 }
 
-template <class T>
+template <class T, bool CELLS>
 __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *__restrict__ dZ8, const uint16_t *__restrict__ X, int B,
                                         int Bp, int n_active, int D, int64_t Mp, float scale, float *__restrict__ dW,
                                         const DwUpdate &up, const DwCells &cells) {
@@ -1194,7 +1195,6 @@ __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *
     };
     int pos_next = -1; // of the lane's sample in the next k-tile; as read (a wait for it would stand here otherwise)
     auto place = [&](int kt, uint16_t *st) __attribute__((always_inline)) {
-        if (!cells.pos) return;
         const int32_t *const here = s_cells + (kt & (DW_CELL_SLOTS - 1)) * 128 + lane;
         const int pos = (kt == 0 ? here[0] : pos_next) - m_first;
         pos_next = s_cells[((kt + 1) & (DW_CELL_SLOTS - 1)) * 128 + lane]; // (beyond the last k-tile: not used)
@@ -1205,12 +1205,14 @@ __device__ __forceinline__ void dw_tile(int bid, uint16_t *lds, const uint16_t *
         }
         cells_request(kt + 2);
     };
-    if (cells.pos) {
+    // (samples B .. of the last k-tile: zeros of dZ8 meet the last row of X)
+    if constexpr (CELLS) {
         cells_request(0);
         cells_request(1);
+        ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, nk, lds, acc, place);
+    } else {
+        ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, nk, lds, acc);
     }
-    // (samples B .. of the last k-tile: zeros of dZ8 meet the last row of X)
-    ks_a_mainloop_il<T, KS_M8, KS_KMAJ, 2>(ar, br, 0, nk, lds, acc, place);
     // epilogue, row-wise through LDS: gradient rows out (if wanted) and, if asked for, the update of the master
     // rows and of their 16-bit copy.  Up to four rows per thread are in flight at a time, the next ones requested before
     // the present ones are stored (and the first before the slab is staged): 192 x 256 tiles of 17,425 rows 43 -> 40 us,
@@ -1595,8 +1597,14 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             const bool keep = mode == SM_WHOLE && w.kept;
             if (mode != SM_IMPORT) {
 #define SM_STATS_LAUNCH(CFG)                                                                                              \
-    hipLaunchKernelGGL((sm_stats_soe_kernel<CFG>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, B, \
-                       w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt, keep ? w.kept : nullptr)
+    do {                                                                                                                  \
+        if (keep)                                                                                                         \
+            hipLaunchKernelGGL((sm_stats_soe_kernel<CFG, true>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, \
+                               B, w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt, w.kept);                                 \
+        else                                                                                                              \
+            hipLaunchKernelGGL((sm_stats_soe_kernel<CFG, false>), dim3(grid), dim3(512), 0, st, X, W, active_idx, n_active, target_pos, \
+                               B, w.Bp, D, Mi, tiles_s, scale, w.pm, w.pl, w.zt, w.kept);                                 \
+    } while (0)
                 SM_FOR_DEPTH(SM_STATS_LAUNCH);
 #undef SM_STATS_LAUNCH
                 mark(2);
@@ -1673,9 +1681,13 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             job.dX = dX;
             job.loss_i = loss_per_sample;
             job.loss_mean = loss_mean;
-            hipLaunchKernelGGL(dw_async_kernel, dim3(next.nsel + tiles + DW_REDUCE_BLOCKS), dim3(T::NT), 0, st, w.dZ8,
-                               fused ? w.X2 : X, B, w.Bp, n_active, D, Mi, w.Mp, fused ? scale * g : scale, dW_active, tiles,
-                               n_cu, job, up, fused ? DwCells{w.cell_pos, w.cell} : DwCells(), next);
+            const dim3 grid(next.nsel + tiles + DW_REDUCE_BLOCKS);
+            if (fused)
+                hipLaunchKernelGGL(dw_async_kernel<true>, grid, dim3(T::NT), 0, st, w.dZ8, w.X2, B, w.Bp, n_active, D, Mi, w.Mp,
+                                   scale * g, dW_active, tiles, n_cu, job, up, DwCells{w.cell_pos, w.cell}, next);
+            else
+                hipLaunchKernelGGL(dw_async_kernel<false>, grid, dim3(T::NT), 0, st, w.dZ8, X, B, w.Bp, n_active, D, Mi, w.Mp, scale,
+                                   dW_active, tiles, n_cu, job, up, DwCells(), next);
         }
         mark(7);
         KS_LAUNCH_CHECK();
