@@ -1575,15 +1575,22 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
             comb.dev_status = dev_status;
             comb.mode = mode;
             comb.io = io;
-            // Beside narrow dX tiles, two to a compute unit, all workgroups should run at once: few samples each if there is
-            // room, or else many, and a twelfth less shares for the tiles if that does it.  (B = 1,024, D = 512: combine and dX
-            // 37.0 us one after the other; 33.8 with 16 shares beside 128 workgroups, 32.1 with 15 beside 32.)
+            // Narrow dX tiles are two to a compute unit.  Where the tiles and workgroups of few samples are more than that, and
+            // workgroups of many samples fit beside them, with a twelfth less shares for the tiles if that does it, all run at once.
+            // Where they do not, or where the shares are short, the long chain of many samples only delays the launch's end.
+            // Whole calls, us, few -> many: D = 512, B = 1,024: A = 2,000: 44.4 -> 46.4; 9,000: 69.6 -> 69.3; 17,425: 97.5 -> 96.2 (15
+            // shares instead of 16); D = 512, B = 512: 2,000: 39.8 -> 42.6; 17,425: 69.4 -> 68.4 (31 for 32); D = 256, B = 777: 2,000:
+            // 37.1 -> 39.2; 4,737: 40.2 -> 39.8; 17,425: 65.5 -> 63.6; D = 128, B = 1,536: 4,737: 48.3 -> 46.9; and where they do not fit:
+            // D = 512, B = 2,048: 4,737: 77.4 -> 84.0; 17,425: 153.9 -> 156.5; D = 256, B = 2,048: 9,000: 75.0 -> 77.8; D = 512, B = 777:
+            // 17,425: 95.6 -> 97.2; B = 1,536: 139.6 -> 141.3.
             const bool wide = sm_dx_wide(B, D, M);
             const int tiles = (int)(ks_ceil_div(B, TileDx::BM) * ks_ceil_div(D, TileDx::BN)), slots = 2 * 256;
-            comb.many = mode != SM_EXPORT && (wide || tiles * S + ks_ceil_div(B, SM_CF_FEW) > slots);
-            comb.blocks = (int)ks_ceil_div(B, comb.many ? SM_CF_MANY : SM_CF_FEW);
-            const int fit = (slots - comb.blocks) / tiles; // shares that leave room
-            if (!wide && tiles * S <= slots && fit < S && fit >= S - S / 12 && (int64_t)fit * DxIdx<TileDx>::CAP >= M) S = fit;
+            const int few = (int)ks_ceil_div(B, SM_CF_FEW), many = (int)ks_ceil_div(B, SM_CF_MANY);
+            const int room = tiles * S <= slots ? (slots - many) / tiles : 0, fit = room < S ? room : S; // shares that leave room
+            comb.many = mode != SM_EXPORT && (wide || (tiles * S + few > slots && fit > 0 && fit >= S - S / 12 && M >= 128 * (int64_t)S &&
+                                                       (int64_t)fit * DxIdx<TileDx>::CAP >= M));
+            comb.blocks = comb.many ? many : few;
+            if (!wide && comb.many) S = fit;
             comb.extra = w.part + (int64_t)S * B * D;
             if (mode == SM_EXPORT) {
                 hipLaunchKernelGGL(sm_combine_fused_kernel, dim3((unsigned)comb.blocks), dim3(SM_CF_NT), 0, st, comb, n_active, Mi, B,
