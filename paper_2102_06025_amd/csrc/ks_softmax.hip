@@ -470,7 +470,7 @@ sm_stats_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     // l = sum exp(scale * (acc - m)) = sum exp2(fma(acc, k1, -k1 * m)); one fused multiply-add per element
     const float k1 = scale * 1.4426950408889634f;
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
-        if (KEEP) {
+        if (KEEP && (i & ~31) < ((B + 63) & ~63)) { // (blocks of padding samples beyond what dW reads: nowhere)
             float4 *p = (float4 *)kept + sm_kept_at(c0 >> 5, i >> 5, Bp, lane);
 #pragma unroll
             for (int fm = 0; fm < CFG::FM; ++fm)
@@ -606,7 +606,8 @@ sm_grad_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__ 
 // Small problems (sm_kept_bytes): the second sweep and the merge of the slabs' statistics before it as one pass over the products, which the
 // first sweep has kept (fp32, as they stood in its accumulators: the same gradient bit for bit but for the order of the merge).
 // A workgroup has 32 samples and takes every gridDim.y-th group of four class blocks; it merges its samples' statistics itself,
-// while its first block is on the way.  (2,297 classes x 320, batch 333: merge and sweep 3.9 + 9.2 us, this 6.3.)
+// while its first block is on the way.  Blocks of padding samples are left out but for the one that completes dW's k-tile of 64
+// (12,000 classes x 512, batch 33: 47.9 -> 44.3 us; 8,192 x 320: 39.3 -> 35.4).  (2,297 classes x 320, batch 333: merge and sweep 3.9 + 9.2 us, this 6.3.)
 __global__ void __launch_bounds__(SM_NT)
 sm_grad_kept_kernel(const float *__restrict__ kept, const float *__restrict__ pm, const float *__restrict__ pl, const float *__restrict__ zt,
                     const int32_t *__restrict__ n_active_p, const int32_t *__restrict__ target_pos, int B, int Bp, int M, int slabs,
@@ -1624,7 +1625,7 @@ static int sm_run(const uint16_t *W, const uint16_t *X, int D, int B, int64_t M,
                                    loss_per_sample);
             }
             if (keep) {
-                const int sbs = w.Bp / 32, groups = (int)ks_ceil_div(M, 128); // class blocks in fours
+                const int sbs = (B + 63) / 64 * 2, groups = (int)ks_ceil_div(M, 128); // class blocks in fours
                 const int gy = (int)ks_ceil_div(1024, sbs);
                 hipLaunchKernelGGL(sm_grad_kept_kernel, dim3(sbs, gy < groups ? gy : groups), dim3(SM_NT), 0, st, w.kept, w.pm, w.pl,
                                    w.zt, n_active, target_pos, B, w.Bp, Mi, slabs, scale, g, loss_per_sample, w.dZ8);
