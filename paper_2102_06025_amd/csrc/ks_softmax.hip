@@ -640,13 +640,13 @@ sm_grad_kept_kernel(const float *__restrict__ kept, const float *__restrict__ pm
                 tm[u] = in ? pm[(int64_t)t * Bp + i] : -INFINITY;
                 tl[u] = in ? pl[(int64_t)t * Bp + i] : 0.f;
             }
+            float mm = m;
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (tm[u] != -INFINITY) {
-                    const float mm = fmaxf(m, tm[u]);
-                    l = l * __expf(m - mm) + tl[u] * __expf(tm[u] - mm); // (m = -inf, l = 0 at the start)
-                    m = mm;
-                }
+            for (int u = 0; u < 8; ++u) mm = fmaxf(mm, tm[u]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) tl[u] = tm[u] != -INFINITY ? tl[u] * __expf(tm[u] - mm) : 0.f;
+            if (mm != -INFINITY) l = l * __expf(m - mm) + (((tl[0] + tl[1]) + (tl[2] + tl[3])) + ((tl[4] + tl[5]) + (tl[6] + tl[7])));
+            m = mm; // (m = -inf, l = 0 at the start)
         }
         s_m[part][j] = m;
         s_l[part][j] = l;
@@ -657,9 +657,14 @@ sm_grad_kept_kernel(const float *__restrict__ kept, const float *__restrict__ pm
     float m = -INFINITY, l = 0.f;
 #pragma unroll
     for (int p = 0; p < PARTS; ++p) m = fmaxf(m, s_m[p][lane & 31]);
+    float lp[PARTS];
 #pragma unroll
-    for (int p = 0; p < PARTS; ++p) // a fixed order
-        if (s_m[p][lane & 31] != -INFINITY) l += s_l[p][lane & 31] * __expf(s_m[p][lane & 31] - m);
+    for (int p = 0; p < PARTS; ++p) lp[p] = s_m[p][lane & 31] != -INFINITY ? s_l[p][lane & 31] * __expf(s_m[p][lane & 31] - m) : 0.f;
+#pragma unroll
+    for (int o = PARTS / 2; o > 0; o >>= 1) // a tree: as close to the exact sum as the merge by a wavefront
+#pragma unroll
+        for (int p = 0; p < o; ++p) lp[p] += lp[p + o];
+    l = lp[0];
     const float lse = m + __logf(l);
     const int tp = ok ? target_pos[i] : -1;
     if (blockIdx.y == 0 && threadIdx.x < 32 && ok) loss_i[i] = lse - zt[i];
@@ -1445,9 +1450,12 @@ static int sm_splits(int B, int D, int64_t M, bool fast) {
 }
 
 // Whether the two-sweep softmax keeps its products instead of forming them again.  It spares a launch (the merge, 4 us) and the
-// second sweep's set-up, and costs 10 bytes of traffic per product against 2 D operations.  Whole calls, us, sweep -> kept: 900
-// classes x 64, batch 64: 34.5 -> 31.3; 3,001 x 320, 333: 54.9 -> 51.8; 4,000 x 512, 128: 56.6 -> 50.4; 8,300 x 512, 500: 78.1 -> 75.7;
-// 7,000 x 192, 300: 57.6 -> 60.6; 25,000 x 384, 600: 130 -> 135; 32,319 x 512, 1,024: 212 -> 216.
+// second sweep's set-up, and costs 10 bytes of traffic per product against 2 D operations: it pays up to a million products or
+// 32 D^2, whichever is more.  Whole calls, us, sweep -> kept, inside: 900 classes x 64, batch 256: 26.7 -> 23.3; 4,096 x 64, 256:
+// 28.5 -> 26.4; 2,000 x 128, 512: 33.3 -> 30.6; 8,192 x 256, 180: 38.1 -> 37.1; 3,000 x 320, 400: 43.9 -> 37.8; 16,384 x 384, 256: 55.8 ->
+// 56.0; 4,096 x 512, 128: 41.8 -> 34.6; 24,000 x 512, 256: 74.3 -> 73.0; 16,384 x 512, 512: 82.6 -> 76.0; beyond: 4,096 x 64, 512: 31.3 ->
+// 32.1; 8,192 x 128, 256: 32.1 -> 34.5; 12,000 x 256, 512: 46.0 -> 48.3; 24,000 x 320, 256: 61.5 -> 64.1; 24,000 x 384, 256: 64.3 -> 66.3;
+// 32,319 x 512, 1,024: 212 -> 216.  (By the cap M: the active count is known to the device only, and with fewer both get faster.)
 // Bytes of the array (0: not kept), at most 34 MB.
 static size_t sm_kept_bytes(int B, int D, int64_t M) {
     const int64_t n = (int64_t)ks_align_up((size_t)B, KS_BP_ALIGN) * sm_mp(M);
