@@ -24,9 +24,9 @@ def dev(a, bf16=False):
 
 
 def _guarded(nbytes):
-    """A workspace of exactly nbytes, and the bytes behind it."""
+    """A workspace of exactly nbytes, and the bytes behind it: all NaN, as bf16 and as fp32."""
     import torch
-    whole = torch.full((nbytes + 4096,), 0xAB, dtype=torch.uint8, device="cuda")
+    whole = torch.full((nbytes + 4096,), 0xFF, dtype=torch.uint8, device="cuda")
     return whole[:nbytes], whole[nbytes:]
 
 
@@ -75,7 +75,7 @@ def test_workspace_of_the_full_batch_serves_the_last_one(ks, call, D, M, large, 
     for o in (got, want):
         o["dW_active"] = o["dW_active"][:n]
     _same(got, want, call)
-    assert bool((guard == 0xAB).all()) and bool((own_guard == 0xAB).all())
+    assert bool((guard == 0xFF).all()) and bool((own_guard == 0xFF).all())
 
 
 def test_workspace_of_all_classes_serves_fewer(ks):
@@ -86,4 +86,4 @@ def test_workspace_of_all_classes_serves_fewer(ks):
     y = dev(synth.labels_uniform(82, B, small))
     ws, guard = _guarded(ks.full_softmax_workspace(large, D, B))
     _same(ks.full_softmax_fwd_bwd(W, X, y, scale, gs, ws=ws), ks.full_softmax_fwd_bwd(W, X, y, scale, gs), "full")
-    assert bool((guard == 0xAB).all())
+    assert bool((guard == 0xFF).all())
