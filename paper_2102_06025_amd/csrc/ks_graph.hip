@@ -3,7 +3,7 @@
 //
 //   prepare   bf16 copy of W when the input is fp32; row norms and their maximum (for the error bound); the sampled rows
 //   threshold (K <= 64, D <= 512) per row the 8th, 10th or 12th largest similarity to a sample of one in 32 (or 16) of the searched rows: what lies below
-//             it is not recalled.  Some 256 to 384 rows lie above it, whatever the data (an order statistic).
+//             it is not recalled.  Some 256 to 384 rows (one in 16: 128 to 192) lie above it, whatever the data (an order statistic).
 //   recall    each workgroup keeps a block of 256 rows resident and streams rows of W by them: bf16 MFMA tiles of
 //             similarities; an element above its row's threshold is appended to one of the row's candidate segments.
 //             The C x C similarities are never stored.  Small problems cut the streamed rows into parts so that every

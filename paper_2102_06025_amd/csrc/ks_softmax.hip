@@ -695,10 +695,12 @@ sm_grad_kept_kernel(const float *__restrict__ kept, const float *__restrict__ pm
 // One-sweep variant for rows of norm <= 1 (the paper normalises W and X, section 3.2): every logit
 // lies in [-scale, scale], so the softmax can be evaluated against the fixed reference `scale` and no
 // statistics pass is needed.  The sweep writes E[a][i] = exp(z_ia - scale) (bf16, transposed, zero in the
-// padding) and per-slab sums of the stored (rounded) E; sm_combine_fused_kernel then forms sum_i = sum_a E_ia,
-// the loss, and turns column i into (P_ia - [a = target_i]) * sum_i by replacing the target entry.  The
-// factor g / sum_i that is still missing is applied where it is cheap: on the rows of dX after the
-// contraction over classes, and on the rows of X (X2 = X / sum_i, bf16) before the contraction over samples.
+// padding and at the sample's own class) and per-slab sums of the stored (rounded) E; sm_combine then forms
+// sum_i = sum_a E_ia and the loss.  Column i of the gradient, (P_ia - [a = target_i]) * sum_i, is the stored column
+// and one entry more, E_t - sum_i at the own class, which never goes into the stored array: its term of dX is
+// a partial product of its own, and dW puts it into its tile in LDS.  The factor g / sum_i that is still missing is
+// applied where it is cheap: on the rows of dX after the contraction over classes, and on the rows of X
+// (X2 = X / sum_i, bf16) before the contraction over samples.
 // The reference only shifts the exponent range: results are the same function of the inputs as long as no
 // exponential overflows and not all of a sample's vanish, which the combine kernel checks.
 // ------------------------------------------------------------------------------------------------
@@ -729,8 +731,8 @@ sm_fused_soe_kernel(const uint16_t *__restrict__ X, const uint16_t *__restrict__
     // For the loss: this lane's sum of the UNROUNDED exponentials of its sample over its rows, the sample's own class
     // left out (the combine step adds that one from an fp32 dot product).  The sums of the stored, rounded values
     // (`pl`) are what the gradient columns must add up to; for the loss of a confident sample they would carry the
-    // bf16 rounding of its strongest competitor, 2^-9 relative.  The own class is left out of those too, and stored as 0:
-    // the combine step writes its place.
+    // bf16 rounding of its strongest competitor, 2^-9 relative.  The own class is left out of those too, and stored as 0,
+    // which it stays (see sm_combine).
     float others = 0.f;
     f32x4_t rounded = {0.f, 0.f, 0.f, 0.f}; // every element: the sum of the values that this lane has stored
     auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
