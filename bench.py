@@ -125,10 +125,12 @@ def phase_model(cfg, A, unit_rows, fused_update=False):
         # unit rows: the only sweep (logits -> exponentials stored transposed + their sums); otherwise
         # logits + per-slab softmax statistics, nothing stored
         "logits_gemm": dict(bound="mfma", flops=gemm),
-        "row_stats": dict(bound="latency"),                  # merge of the per-slab sums, loss, loss mean
-        # logits again -> logit gradient (stored transposed); no such sweep with unit rows
+        # general rows: merge of the per-slab statistics, loss; with unit rows that is part of the dX launch and nothing is
+        # launched here (what stands between the two events is their own time)
+        "row_stats": dict(bound="latency"),
+        # general rows: logits again -> logit gradient (stored transposed); nothing is launched with unit rows
         "logit_grad": dict(bound="latency") if unit_rows else dict(bound="mfma", flops=gemm),
-        "dx_gemm": dict(bound="mfma", flops=gemm),
+        "dx_gemm": dict(bound="mfma", flops=gemm),           # (with unit rows: beside it the combine step, sums and loss)
         "dx_reduce": dict(bound="latency"),                  # nothing launched here: the reduction rides with dw_gemm
         "dw_gemm": dict(bound="mfma", flops=gemm),
         # the stand-alone update; nothing is launched here when the update runs inside the dW kernel
@@ -397,6 +399,9 @@ def main():
             e["gbs"] = round(m["bytes"] / (dur[p] * 1e-6) / 1e9, 1)
             e.update(fracs(e["gbs"], PEAK_HBM_GBS, copy_peak))
         phases[p] = e
+    if unit_rows:
+        phases["row_stats"]["note"] = phases["logit_grad"]["note"] = "nothing is launched here with unit rows: the time of two events"
+        phases["dx_gemm"]["note"] = "with the combine step (sums, loss) in workgroups beside the tiles"
     if next_inside:
         phases["select"]["note"] = ("stage times are those of the one-call step; in the headline loop the selection (of the next "
                                     "batch) runs inside the dx_gemm and dw_gemm launches and adds nothing to the step")
