@@ -1242,7 +1242,9 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // segments): the keys are read once, and the row's own data and the other lanes' entries come through scalar registers
 // (the ranking by shuffles cost three LDS permutes and 24 instructions per entry, now three lane reads and 6).
 // SHORT: lists of at most 256 candidates have a copy of the search of their own, taken for K <= 24 (beyond, too few rows have
-// so few).  For K <= 32 the kernel of K > 24 does without the copy, which alone costs it 1 %.  For K > 32 and bf16 rows the
+// so few).  For K <= 32 the kernel of K > 24 does without the copy, which alone costs it 1 %; so does that of K <= 24 where few rows
+// gain by it, those of fp32 builds and of hops (one row in 32 sampled), and the rows are one round of the chip (2,000 x 256, K = 16,
+// fp32: 64.3 -> 63.3 us; 5,000 x 512, K = 16, fp32, with it: 134 -> 130).  For K > 32 and bf16 rows the
 // compiler needs 83 registers with it and 123 without: five wavefronts to a SIMD instead of four, but the longer chain of one.
 // So it has the copy where the rows need more than one round of the chip at four (GR_RANK_AT_ONCE).  Builds, us, without -> with:
 // 2,000 x 512, K = 64: 87.3 -> 88.6; 4,000 x 320, K = 33: 92.2 -> 93.0; 5,000 x 512, K = 64: 162.9 -> 149.4; 20,000 x 64, K = 64: 319 -> 301.
@@ -2003,7 +2005,7 @@ static void gr_launch_rank(const IN *W, int64_t C, int D, int K, const GrFixPlan
     hipLaunchKernelGGL((gr_rank_kernel<IN, KP, false, SHORT>), grid, dim3(GR_NT), 0, st, W, C, W, C, D, K, f.seg, w.cand,               \
                        w.cnt_res, w.cnt_str, w.tbits, w.norms, w.maxnorm, gamma, (int64_t)0, graph, (void *)sims, w.second_count, \
                        w.second_rows)
-    if (K <= 24) GR_RANK_LAUNCH(1, true);
+    if (K <= 24 && (sizeof(IN) == 2 || C > GR_RANK_AT_ONCE)) GR_RANK_LAUNCH(1, true);
     else if (K <= 32) GR_RANK_LAUNCH(1, false);
     else if (sizeof(IN) == 2 && C > GR_RANK_AT_ONCE) GR_RANK_LAUNCH(2, true);
     else GR_RANK_LAUNCH(2, false);
@@ -2333,7 +2335,7 @@ static void gr_up_exact(const IN *Wl, int64_t C_loc, const IN *Wv, int64_t C_vis
     hipLaunchKernelGGL((gr_rank_kernel<IN, KP, true, SHORT>), grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, f->seg,             \
                        w.cand, w.cnt_res, (const int32_t *)nullptr, w.tbits, w.norms_l, w.maxnorm_v, gamma, vo, graph, (void *)sims, \
                        w.fb_count, w.fb_rows)
-    if (f && K <= 24) GR_HOP_RANK_LAUNCH(1, true);
+    if (f && K <= 24 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(1, true);
     else if (f && K <= 32) GR_HOP_RANK_LAUNCH(1, false);
     else if (f && sizeof(IN) == 2 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(2, true);
     else if (f) GR_HOP_RANK_LAUNCH(2, false);
