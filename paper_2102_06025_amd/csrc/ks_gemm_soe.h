@@ -29,6 +29,7 @@
 // loads in flight with the MFMAs (it did in the two-sweep softmax and in the graph's symmetric sweep).
 #pragma once
 #include <type_traits>
+#include <utility>
 #include "ks_gemm_async.h"
 
 // RAGGED: the depth is 64 * KT - 32 (D an odd multiple of 32).  The second half of the last k-tile is then no data: the
@@ -75,6 +76,54 @@ __device__ __forceinline__ int ks_soe_col() { return (threadIdx.x >> 6) * 32 + (
 struct KsSoeNoSide {
     __device__ __forceinline__ void operator()(int, int) const {}
 };
+
+// The MFMA fragments of the resident block: staged through LDS (coalesced row loads), then kept in registers.
+template <class CFG>
+__device__ __forceinline__ void ks_soe_resident(const uint16_t *__restrict__ R, int64_t ldr, int r_row0, int r_limit, uint16_t *lds,
+                                                bf16x8_t (&bres)[CFG::KT * 4]) {
+    constexpr int KT = CFG::KT;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    static_assert(CFG::LDS_ELEMS >= 2 * CFG::RES * 64, "the stream stages double as staging for the resident block");
+    KsARows<CFG::RES, CFG::NW> rr;
+    rr.init(R, ldr, nullptr, r_row0, r_limit);
+    // the last k-tile of a ragged depth: chunks 4..7 of its rows are redirected to chunks 0..3
+    auto res_issue = [&](int kt, uint16_t *dst) __attribute__((always_inline)) {
+        if (CFG::RAGGED && kt == KT - 1) {
+#pragma unroll
+            for (int j = 0; j < KsARows<CFG::RES, CFG::NW>::NI; ++j) {
+                const int row = (j * CFG::NW + wave) * 8 + (lane >> 3);
+                if (((lane & 7) ^ ((row >> 1) & 7)) >= 4) rr.ptr[j] -= 32;
+            }
+        }
+        rr.issue(kt * 64, dst);
+    };
+    const int r31 = lane & 31, khalf = lane >> 5, swz = (lane >> 1) & 7;
+    // up to four k-tiles in flight (the stream stages hold that many 256-row tiles): one memory round trip for the
+    // first four instead of one per k-tile
+    constexpr int NS = CFG::LDS_ELEMS / (CFG::RES * 64) >= 4 ? 4 : 2;
+    constexpr int RNI = KsARows<CFG::RES, CFG::NW>::NI;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < KT) res_issue(s, lds + s * CFG::RES * 64);
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+        const int issued_tiles = (NS + (kt > 0 ? kt - 1 : 0)) < KT ? (NS + (kt > 0 ? kt - 1 : 0)) : KT;
+        const int later = issued_tiles - (kt + 1); // k-tiles issued after this one (compile-time: the loop is unrolled)
+        if (later >= 3) ks_wait_vmcnt<3 * RNI>();
+        else if (later == 2) ks_wait_vmcnt<2 * RNI>();
+        else if (later == 1) ks_wait_vmcnt<1 * RNI>();
+        else ks_wait_vmcnt<0>();
+        __builtin_amdgcn_s_waitcnt(0xC07F); // the fragment reads of k-tile kt-1 have returned: its slot may be reused
+        ks_barrier_nofence();               // k-tile kt is in LDS
+        if (kt > 0 && kt - 1 + NS < KT) res_issue(kt - 1 + NS, lds + ((kt - 1) % NS) * CFG::RES * 64);
+        const uint16_t *st = lds + (kt % NS) * CFG::RES * 64;
+#pragma unroll
+        for (int kk = 0; kk < (CFG::RAGGED && kt == KT - 1 ? 2 : 4); ++kk)
+            bres[kt * 4 + kk] = *(const bf16x8_t *)(st + (wave * 32 + r31) * 64 + (((kk * 2 + khalf) ^ swz) * 8));
+    }
+}
+
 template <class CFG, int NSTORE = 0, class Epi, class Side = KsSoeNoSide>
 __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int64_t ldr, int r_row0, int r_limit,
                                               const uint16_t *__restrict__ S, int64_t lds_ld, const int32_t *__restrict__ gidx,
@@ -98,48 +147,8 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
         }
     }
 
-    // ---- resident fragments: staged through LDS (coalesced row loads), then kept in registers ----------------
     bf16x8_t bres[KT * 4];
-    {
-        static_assert(CFG::LDS_ELEMS >= 2 * CFG::RES * 64, "the stream stages double as staging for the resident block");
-        KsARows<CFG::RES, CFG::NW> rr;
-        rr.init(R, ldr, nullptr, r_row0, r_limit);
-        // the last k-tile of a ragged depth: chunks 4..7 of its rows are redirected to chunks 0..3
-        auto res_issue = [&](int kt, uint16_t *dst) __attribute__((always_inline)) {
-            if (CFG::RAGGED && kt == KT - 1) {
-#pragma unroll
-                for (int j = 0; j < KsARows<CFG::RES, CFG::NW>::NI; ++j) {
-                    const int row = (j * CFG::NW + wave) * 8 + (lane >> 3);
-                    if (((lane & 7) ^ ((row >> 1) & 7)) >= 4) rr.ptr[j] -= 32;
-                }
-            }
-            rr.issue(kt * 64, dst);
-        };
-        const int r31 = lane & 31, khalf = lane >> 5, swz = (lane >> 1) & 7;
-        // up to four k-tiles in flight (the stream stages hold that many 256-row tiles): one memory round trip for the
-        // first four instead of one per k-tile
-        constexpr int NS = CFG::LDS_ELEMS / (CFG::RES * 64) >= 4 ? 4 : 2;
-        constexpr int RNI = KsARows<CFG::RES, CFG::NW>::NI;
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-            if (s < KT) res_issue(s, lds + s * CFG::RES * 64);
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
-            const int issued_tiles = (NS + (kt > 0 ? kt - 1 : 0)) < KT ? (NS + (kt > 0 ? kt - 1 : 0)) : KT;
-            const int later = issued_tiles - (kt + 1); // k-tiles issued after this one (compile-time: the loop is unrolled)
-            if (later >= 3) ks_wait_vmcnt<3 * RNI>();
-            else if (later == 2) ks_wait_vmcnt<2 * RNI>();
-            else if (later == 1) ks_wait_vmcnt<1 * RNI>();
-            else ks_wait_vmcnt<0>();
-            __builtin_amdgcn_s_waitcnt(0xC07F); // the fragment reads of k-tile kt-1 have returned: its slot may be reused
-            ks_barrier_nofence();               // k-tile kt is in LDS
-            if (kt > 0 && kt - 1 + NS < KT) res_issue(kt - 1 + NS, lds + ((kt - 1) % NS) * CFG::RES * 64);
-            const uint16_t *st = lds + (kt % NS) * CFG::RES * 64;
-#pragma unroll
-            for (int kk = 0; kk < (CFG::RAGGED && kt == KT - 1 ? 2 : 4); ++kk)
-                bres[kt * 4 + kk] = *(const bf16x8_t *)(st + (wave * 32 + r31) * 64 + (((kk * 2 + khalf) ^ swz) * 8));
-        }
-    }
+    ks_soe_resident<CFG>(R, ldr, r_row0, r_limit, lds, bres);
 
     // ---- stream state ---------------------------------------------------------------------------------------
     auto chunk_first = [&](int c) __attribute__((always_inline)) { return ctab ? ctab[c].x : s_begin + c * CFG::CH; };
@@ -294,5 +303,182 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
         else chunk(std::false_type());
         epi(ctab ? ct.x : chunk_first(c), rows_here, acc);
     }
+    ks_barrier_nofence();
+}
+
+// ------------------------------------------------------------------------------------------------
+// The sweep with the two halves of the workgroup in turn ("ping-pong"): while wavefronts 0..3 (one per SIMD) multiply a stage,
+// wavefronts 4..7 run a part of their epilogue for the chunk before, and the other way round, so that the element-wise work
+// of one half hides behind the other half's MFMAs.  In the sweep above both wavefronts of a SIMD reach their epilogues
+// together and the matrix pipe idles meanwhile.  What it takes: two sets of accumulators (the chunk being multiplied and the
+// one before it, 32 FM registers), an epilogue cut into pieces, one per 32-row block, that run in different stages, and two
+// barriers per stage.  All wavefronts run the same program; wavefronts 4..7 are one barrier behind, half a stage.
+//
+// FM: 32-row blocks per chunk (chunk = 32 FM rows).  P = KT / KSUB stages per chunk; block f's epilogue runs in stage f P / FM of
+// the next chunk.  PF: k-steps whose fragments are requested ahead -- a lone wavefront per SIMD has no partner whose MFMAs
+// would cover the round trip to LDS; the first PF of a stage are requested before its barrier, which is why a stage has to land one
+// barrier earlier than in the sweep above.
+// f(integral_constant 0), f(1), ..., f(N - 1)
+template <class F, int... I> __device__ __forceinline__ void ks_each_of(F &f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F> __device__ __forceinline__ void ks_each(F &f) { ks_each_of(f, std::make_integer_sequence<int, N>()); }
+
+template <int KT_, int FM_, int KSUB_, int STAGES_, int PF_, bool RAGGED_ = false> struct KsPp {
+    static constexpr int KT = KT_, FM = FM_, KSUB = KSUB_, STAGES = STAGES_, PF = PF_;
+    static constexpr bool RAGGED = RAGGED_;
+    static constexpr int P = KT / KSUB;
+    static constexpr int NW = 8, NT = 512, CH = 32 * FM, RES = 256;
+    static constexpr int LW = 4, NI = CH / 32;
+    static constexpr int STAGE_ELEMS = KSUB * CH * 64;
+    static constexpr int LDS_ELEMS = STAGES * STAGE_ELEMS;
+    static constexpr int AHEAD = (STAGES - 1 + P - 1) / P + 3; // chunks from the one whose loads begin back to the epilogue's
+    static_assert(KT >= 1 && KT <= 8 && KT % KSUB == 0 && STAGES >= 3 && (STAGES - 2) * NI * KSUB <= 63, "sweep shape");
+    static_assert(LDS_ELEMS >= 2 * RES * 64, "the stream stages double as staging for the resident block");
+    static constexpr int ksteps(int stage_in_chunk) { // k-steps of a stage: four per k-tile, two in the last one of a ragged depth
+        return 4 * KSUB - (RAGGED && stage_in_chunk == P - 1 ? 2 : 0);
+    }
+};
+
+// Rows, resident block, table of chunks and side as for ks_soe_sweep.  A chunk that has fewer rows than CH is multiplied in
+// full (rows beyond s_clamp repeat the last one).  epi(f, chunk_first_row, rows_in_chunk, acc) is called for the blocks f = 0 ..
+// FM - 1 of every chunk in turn (f a std::integral_constant); no barriers inside, and no access to the stream stages.
+template <class CFG, class Epi, class Side = KsSoeNoSide>
+__device__ __forceinline__ void ks_soe_pp_sweep(const uint16_t *__restrict__ R, int64_t ldr, int r_row0, int r_limit,
+                                                const uint16_t *__restrict__ S, int64_t lds_ld, int s_begin, int s_end, int s_clamp,
+                                                uint16_t *lds, Epi &epi, const int2 *__restrict__ ctab = nullptr, int ctab_n = 0,
+                                                Side side = Side()) {
+    constexpr int KT = CFG::KT, ST = CFG::STAGES, NI = CFG::NI, FM = CFG::FM, P = CFG::P, PF = CFG::PF;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_chunks = ctab ? ctab_n : (s_end - s_begin + CFG::CH - 1) / CFG::CH;
+    bf16x8_t bres[KT * 4];
+    ks_soe_resident<CFG>(R, ldr, r_row0, r_limit, lds, bres);
+    if (n_chunks <= 0) return; // the same for all wavefronts
+
+    // ---- stream state (as above) ---------------------------------------------------------------------------------
+    const int n_tiles = n_chunks * P;
+    __builtin_amdgcn_s_waitcnt(0xC07F); // the fragment reads have returned before the stages are reused
+    __syncthreads();
+    const bool loader = wave < CFG::LW;
+    const int tail_back = (CFG::RAGGED && ((lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7)) >= 4) ? 32 : 0;
+    const uint16_t *ptr[NI];
+    int ahead_first = ctab ? ctab[0].x : 0;
+    auto chunk_ptrs = [&](int c) __attribute__((always_inline)) {
+        const int first = ctab ? ahead_first : s_begin + c * CFG::CH;
+        if (ctab) ahead_first = ctab[c + 1 < n_chunks ? c + 1 : c].x;
+        if (wave == 0) side(first, c);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int row = (j * CFG::LW + wave) * 8 + (lane >> 3);
+            int g = first + row;
+            if (g >= s_clamp) g = s_clamp - 1;
+            ptr[j] = S + (int64_t)g * lds_ld + (((lane & 7) ^ ((row >> 1) & 7)) * 8);
+        }
+    };
+    int is_c = 0, is_kt = 0, is_stage = 0, issued = 0;
+    auto issue_one = [&]() __attribute__((always_inline)) {
+        uint16_t *st = lds + is_stage * CFG::STAGE_ELEMS;
+        if (loader) {
+#pragma unroll
+            for (int u = 0; u < CFG::KSUB; ++u) {
+                int koff = (is_kt + u) * 64;
+                if (CFG::RAGGED && is_kt + u == KT - 1) koff -= tail_back;
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    __builtin_amdgcn_global_load_lds(KS_GPTR(ptr[j] + koff),
+                                                     KS_LPTR(st + u * CFG::CH * 64 + (j * CFG::LW + wave) * 8 * 64), 16, 0, 0);
+            }
+        }
+        ++issued;
+        if (++is_stage == ST) is_stage = 0;
+        is_kt += CFG::KSUB;
+        if (is_kt == KT) {
+            is_kt = 0;
+            ++is_c;
+            if (is_c < n_chunks && loader) chunk_ptrs(is_c);
+        }
+    };
+    if (loader) chunk_ptrs(0);
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s)
+        if (issued < n_tiles) issue_one();
+    if (issued < ST - 1) ks_wait_vmcnt<0>();
+    else ks_wait_vmcnt<(ST - 2) * NI * CFG::KSUB>();
+    ks_barrier_nofence(); // stage 0 is in LDS
+
+    // ---- sweep -------------------------------------------------------------------------------------------
+    const int r31 = lane & 31, khalf = lane >> 5, swz = (lane >> 1) & 7;
+    bf16x8_t frag[PF][FM];
+    int stage = 0, done = 0;
+    auto fetch = [&](int s, int ks, bf16x8_t(&to)[FM]) __attribute__((always_inline)) { // the fragments of one k-step of stage slot s
+        const uint16_t *st = lds + s * CFG::STAGE_ELEMS + (ks >> 2) * CFG::CH * 64;
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+            to[fm] = *(const bf16x8_t *)(st + (fm * 32 + r31) * 64 + ((((ks & 3) * 2 + khalf) ^ swz) * 8));
+    };
+    auto fetch_first = [&](int s, int ksteps) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < PF; ++ks)
+            if (ks < ksteps) fetch(s, ks, frag[ks]);
+    };
+    fetch_first(0, CFG::ksteps(0));
+    f32x16_t acc[FM], before[FM];
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) before[fm][r] = 0.f;
+    int before_first = 0, before_rows = 0;
+    auto pieces = [&](auto phase) __attribute__((always_inline)) {
+        constexpr int p = decltype(phase)::value;
+        auto piece = [&](auto block) __attribute__((always_inline)) {
+            constexpr int f = decltype(block)::value;
+            if constexpr (f * P / FM == p) epi(block, before_first, before_rows, before[f]);
+        };
+        ks_each<FM>(piece);
+    };
+    int2 ct_next = ctab ? ctab[0] : make_int2(0, 0);
+    for (int c = 0; c < n_chunks; ++c) {
+        const int2 ct = ct_next;
+        if (ctab) ct_next = ctab[c + 1 < n_chunks ? c + 1 : c];
+        auto one_stage = [&](auto phase) __attribute__((always_inline)) {
+            constexpr int p = decltype(phase)::value, NK = CFG::ksteps(p);
+            if (loader) {
+                if (issued - done - 2 < ST - 3) ks_wait_vmcnt<0>();
+                else ks_wait_vmcnt<(ST - 3) * NI * CFG::KSUB>();
+                ks_barrier_nofence();
+            }
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) {
+                const int kstep = p * CFG::KSUB * 4 + ks;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int fm = 0; fm < FM; ++fm) {
+                    const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    acc[fm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[ks % PF][fm], bres[kstep], kstep == 0 ? zero : acc[fm], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (ks + PF < NK) fetch(stage, ks + PF, frag[ks % PF]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+            ++done;
+            if (++stage == ST) stage = 0;
+            if (!loader) ks_barrier_nofence();
+            // the slot of the stage before this one: the other half has left it too
+            if (issued < n_tiles) issue_one();
+            if (c > 0) pieces(phase);
+            if (p == P - 1) {
+#pragma unroll
+                for (int fm = 0; fm < FM; ++fm) before[fm] = acc[fm];
+                before_first = ctab ? ct.x : s_begin + c * CFG::CH;
+                before_rows = ctab ? ct.y : (s_end - before_first < CFG::CH ? s_end - before_first : CFG::CH);
+            }
+            fetch_first(stage, CFG::ksteps(p + 1 == P ? 0 : p + 1)); // (after the last stage: not used)
+        };
+        ks_each<P>(one_stage);
+    }
+    ks_each<P>(pieces);
     ks_barrier_nofence();
 }

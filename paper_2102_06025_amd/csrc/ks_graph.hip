@@ -592,9 +592,44 @@ __device__ __forceinline__ bool gr_segments(const GrSegs &seg, const int32_t *__
     if (overflow) c = 0;
     return overflow;
 }
-// stage shape of the sweeps for a depth of KT k-tiles: twelve k-tiles in flight, two per stage where KT is even (a barrier
-// per stage); a single k-tile per chunk (KT = 1): six, so that at most seven chunks are in flight
+// Shape of the sweeps (ks_soe_pp_sweep) for a depth of KT k-tiles: as many rows per chunk as two sets of accumulators beside the resident fragments
+// allow, and as few stages per chunk as the LDS allows with three in flight: a stage is a barrier, at which the wavefront with
+// the most hits keeps the others waiting.  (100,000 x 256: one stage per chunk 4.40 ms, two 4.51, four 4.77; 100,000 x 128:
+// one 3.76, two 3.81; 390,625 x 512: two 81.0 ms, four 82.9.)  Whole builds, plain sweep -> in turns: 390,625 x 512, K = 32: 82.8 ->
+// 80.1 ms; 300,000 x 128: 26.1 -> 22.7; 200,000 x 256: 19.5 -> 17.2; 100,000 x 256: 5.01 -> 4.32; 60,000 x 320: 2.89 -> 2.58; 70,000 x 192:
+// 2.97 -> 2.48; 40,000 x 448: 1.73 -> 1.57; 20,000 x 96: 257 -> 242 us; 10,000 x 128 fp32: 123 -> 118.  (The pass over every similarity once
+// spills 6 registers at KT = 8 and 16 at KT = 2; smaller chunks or fewer k-steps ahead spill nothing and are slower: 150,000 x 128 7.51 ->
+// 7.76 ms, 390,625 x 512 80.1 -> 80.6.)
+template <int KT, bool RAGGED> struct GrPpOf;
+#define GR_PP(KT, ...) \
+    template <bool RAGGED> struct GrPpOf<KT, RAGGED> { typedef KsPp<KT, __VA_ARGS__, RAGGED> T; };
+GR_PP(1, 4, 1, 5, 2)
+GR_PP(2, 4, 2, 4, 2)
+GR_PP(3, 3, 3, 4, 2)
+GR_PP(4, 3, 4, 3, 2)
+GR_PP(5, 2, 5, 3, 4)
+GR_PP(6, 2, 6, 3, 2)
+GR_PP(7, 1, 7, 4, 4)
+GR_PP(8, 2, 4, 4, 3)
+#undef GR_PP
+template <int KT, bool RAGGED> using GrPp = typename GrPpOf<KT, RAGGED>::T;
+// The thresholds' sorted lists take 24 registers more, hence chunks of 32 or 64 rows; small problems (several workgroups per block of
+// rows) have a chunk or two per workgroup, with nothing to take turns in, and stay on the plain sweep (10,000 x 128: 11.6 us, in
+// turns 17).
+template <int KT, bool RAGGED> using GrThrPp = KsPp<KT, KT >= 7 ? 1 : 2, KT == 8 ? 4 : KT, KT == 1 ? 8 : KT == 2 ? 5 : KT == 8 ? 8 : KT == 7 ? 4 : 3, KT >= 7 ? 4 : 2, RAGGED>;
 template <int KT, bool RAGGED> using GrSoe = KsSoe<KT, 96, (KT % 2 == 0 || KT == 1) ? 6 : 12, KT % 2 == 0 ? 2 : 1, RAGGED>;
+static int gr_chunk(int D) { // streamed rows per chunk of the recall passes
+    switch ((D + 63) / 64) {
+    case 1: return GrPp<1, false>::CH;
+    case 2: return GrPp<2, false>::CH;
+    case 3: return GrPp<3, false>::CH;
+    case 4: return GrPp<4, false>::CH;
+    case 5: return GrPp<5, false>::CH;
+    case 6: return GrPp<6, false>::CH;
+    case 7: return GrPp<7, false>::CH;
+    default: return GrPp<8, false>::CH;
+    }
+}
 
 // One hop of the distributed build: a row whose list is full needs no visiting row whose similarity cannot reach the
 // list's last entry: its threshold is at least that entry's similarity, lowered by more than twice the recall's error
@@ -654,11 +689,12 @@ struct GrSample {
 // median-of-three per place.  (The first version appended to candidate buffers in memory and cut them back: every cut is
 // 32 rows in turn per wavefront, 199 us for 10,000 rows of 128 against a sample of 312.)
 // PARTS: whether smp.parts > 1.
-template <class CFG, bool PARTS>
+template <int KT, bool RAGGED, bool PARTS>
 __global__ void __launch_bounds__(512)
 gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *__restrict__ Ws, int n_sample, int D,
                     GrSample smp, const float *__restrict__ blockmax, int n_blockmax, float *maxnorm, GrHop hop, float *__restrict__ thf,
                     uint32_t *__restrict__ tbits) {
+    typedef typename std::conditional<PARTS, GrSoe<KT, RAGGED>, GrThrPp<KT, RAGGED>>::type CFG;
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
     const int id = PARTS ? ks_xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x, nb = PARTS ? gridDim.x / smp.parts : gridDim.x;
     const int part = PARTS ? id / nb : 0;
@@ -667,28 +703,33 @@ gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *
     float top[GR_RANK]; // descending
 #pragma unroll
     for (int k = 0; k < GR_RANK; ++k) top[k] = -INFINITY;
-    auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
-        (void)c0;
+    auto epi = [&](auto block, int, int rows_here, const f32x16_t &acc) __attribute__((always_inline)) {
         const int lane = threadIdx.x & 63;
 #pragma unroll
-        for (int fm = 0; fm < CFG::FM; ++fm)
+        for (int q = 0; q < 4; ++q) {
+            float v[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float v[4];
+            for (int e = 0; e < 4; ++e) v[e] = acc[4 * q + e];
+            if (rows_here < CFG::CH) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[fm][4 * q + e];
-                if (rows_here < CFG::CH) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (ks_soe_row(fm, 4 * q + e, lane) >= rows_here) v[e] = -INFINITY;
-                }
-                if (fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > top[GR_RANK - 1]) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) gr_insert(top, v[e]);
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (ks_soe_row(decltype(block)::value, 4 * q + e, lane) >= rows_here) v[e] = -INFINITY;
             }
+            if (fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > top[GR_RANK - 1]) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) gr_insert(top, v[e]);
+            }
+        }
     };
-    ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, s0, s1, n_sample, lds, epi);
+    if constexpr (PARTS) {
+        auto chunk = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) __attribute__((always_inline)) {
+            auto one = [&](auto block) __attribute__((always_inline)) { epi(block, c0, rows_here, acc[decltype(block)::value]); };
+            ks_each<CFG::FM>(one);
+        };
+        ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, s0, s1, n_sample, lds, chunk);
+    } else {
+        ks_soe_pp_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, s0, s1, n_sample, lds, epi);
+    }
     gr_merge_halves(top); // the two lanes of a row hold disjoint sampled rows
     const float mx = (!PARTS && hop.graph) || id == 0 ? gr_max_norm(blockmax, n_blockmax) : 0.f;
     if (id == 0 && threadIdx.x == 0) *maxnorm = mx;
@@ -789,10 +830,11 @@ __device__ __forceinline__ uint32_t gr_hit_mask(float t, const f32x16_t &a) {
 // counts in a register: an append is a store and an increment.  In the problems that come here one value in 30 to 1,000
 // passes, so that of 64 lanes x 16 values nearly always some do: the hits of a lane become a bit mask and are taken one by
 // one (testing value by value costs a branch around the append for each of them).
-template <class CFG, class MERGE>
+template <int KT, bool RAGGED, class MERGE>
 __global__ void __launch_bounds__(512)
 gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE merge, const float *__restrict__ thf_row,
                      uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res) {
+    typedef GrPp<KT, RAGGED> CFG;
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
     const int id = ks_xcd_remap(blockIdx.x, gridDim.x); // the workgroups of an XCD stream the same parts
     const int part = id / nb;
@@ -814,32 +856,32 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE 
     const int down = (threadIdx.x & 32) ? -1 : 0;
     const uint32_t my_base = (uint32_t)(ks_soe_col() * cap + 2 * part * seg.q + (down ? last + 1 : 0));
     int my_cnt = 0;
-    auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
-        const int lane = threadIdx.x & 63;
-        // (a lane finds half of a chunk's rows at most; one that may run out of slots here stores nothing any more, and its
+    auto epi = [&](auto block, int c0, int rows_here, const f32x16_t &acc) __attribute__((always_inline)) {
+        // (a lane finds half of a block's rows at most; one that may run out of slots here stores nothing any more, and its
         // count, which no segment holds, marks the row as overflowed)
-        const bool full = my_cnt > last + 1 - CFG::CH / 2;
-        if (full) my_cnt = 1 << 20;
-        const bool special = rows_here < CFG::CH || ((int64_t)c0 < self0 + CFG::RES && (int64_t)c0 + CFG::CH > self0);
+        if (my_cnt > last + 1 - 16) my_cnt = 1 << 20;
+        uint32_t hm = gr_hit_mask(my_cnt >= 1 << 20 ? INFINITY : thf, acc);
+        int first = c0 + 32 * decltype(block)::value + 4 * ((threadIdx.x >> 5) & 1);
+        asm volatile("" : "+v"(first));
+        if (rows_here < CFG::CH || ((int64_t)c0 < self0 + CFG::RES && (int64_t)c0 + CFG::CH > self0)) {
+            // rows beyond the part's last, and the row itself: no hits
 #pragma unroll
-        for (int fm = 0; fm < CFG::FM; ++fm) {
-            uint32_t hm = full ? 0u : gr_hit_mask(thf, acc[fm]);
-            while (__ballot(hm != 0u) != 0ull) { // as often as the lane with the most hits has some
-                if (hm != 0u) {
-                    const int r = 15 - __builtin_ctz(hm);
-                    hm &= hm - 1u;
-                    const float v = gr_sym_pick16(acc[fm], r);
-                    const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), j = c0 + lr;
-                    if (!special || (lr < rows_here && (int64_t)j != (int64_t)row0 + ks_soe_col() + pr.self)) {
-                        wg_cand[my_base + (uint32_t)(my_cnt ^ down)] =
-                            ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
-                        ++my_cnt;
-                    }
-                }
+            for (int r = 0; r < 16; ++r) {
+                const int j = first + 8 * (r >> 2) + (r & 3);
+                if (j >= c0 + rows_here || (int64_t)j == (int64_t)row0 + ks_soe_col() + pr.self) hm &= ~(0x8000u >> r);
             }
         }
+        while (__ballot(hm != 0u) != 0ull) { // as often as the lane with the most hits has some
+            const int r = 15 - (__ffs(hm) - 1);
+            const float v = gr_sym_pick16(acc, r);
+            const int j = first + r + (r & 12);
+            if (hm != 0u)
+                wg_cand[my_base + (uint32_t)(my_cnt ^ down)] = ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
+            my_cnt += hm != 0u ? 1 : 0;
+            hm &= hm - 1u;
+        }
     };
-    ks_soe_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, nullptr, s0, s1, (int)pr.Cs, lds, epi);
+    ks_soe_pp_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, s0, s1, (int)pr.Cs, lds, epi);
     const int i = row0 + ks_soe_col();
     if (i < Cr) cnt_res[(int64_t)i * 2 * seg.parts + 2 * part + ((threadIdx.x & 63) >> 5)] = my_cnt;
 }
@@ -853,7 +895,7 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE 
 // share of the work, which halves the MFMA work of the pass.  What it takes beyond the fixed thresholds:
 //
 //  * who takes which pair.  Rows are cut into blocks of 256 (a share's resident rows), super-blocks of 768 rows
-//    (three blocks = eight 96-row chunks, so that every streamed range starts on a chunk boundary) and groups of up
+//    (three blocks, and whole chunks of every size, so that every streamed range starts on a chunk boundary) and groups of up
 //    to 10 super-blocks.  On each level the members form a ring and a member takes the following half of the ring
 //    (gr_sym_succ): a share streams its own super-block (its own block for the resident side only, the blocks it
 //    takes there for both sides), then the super-blocks it takes inside its group, then all rows of the groups its
@@ -929,7 +971,7 @@ __host__ __device__ inline GrSymRanges gr_sym_ranges(int block, int C, int GS) {
     return out;
 }
 __global__ void __launch_bounds__(GR_NT)
-gr_sym_plan_kernel(int C, int GS, int32_t *__restrict__ plan, int2 *__restrict__ chunks, int chunks_stride) {
+gr_sym_plan_kernel(int C, int GS, int ch, int32_t *__restrict__ plan, int2 *__restrict__ chunks, int chunks_stride) {
     const int wg = blockIdx.x;
     int32_t *out = plan + (int64_t)wg * GR_SYM_PLAN;
     int2 *tab = chunks + (int64_t)wg * chunks_stride;
@@ -937,10 +979,10 @@ gr_sym_plan_kernel(int C, int GS, int32_t *__restrict__ plan, int2 *__restrict__
     int n_chunks = 0;
     for (int part = 0; part < 5; ++part) {
         if (r.end[part] <= r.first[part]) continue;
-        const int n = (r.end[part] - r.first[part] + 95) / 96;
+        const int n = (r.end[part] - r.first[part] + ch - 1) / ch;
         for (int c = threadIdx.x; c < n; c += GR_NT) {
-            const int first = r.first[part] + c * 96;
-            if (n_chunks + c < chunks_stride) tab[n_chunks + c] = make_int2(first, r.end[part] - first < 96 ? r.end[part] - first : 96);
+            const int first = r.first[part] + c * ch;
+            if (n_chunks + c < chunks_stride) tab[n_chunks + c] = make_int2(first, r.end[part] - first < ch ? r.end[part] - first : ch);
         }
         n_chunks += n;
     }
@@ -964,7 +1006,7 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
                      const int2 *__restrict__ chunks, int chunks_stride, int split_parts, int split_log_rows,
                      const float *__restrict__ thf_row, uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res,
                      uint2 *__restrict__ log, int32_t *logcnt) {
-    typedef GrSoe<KT, false> CFG;
+    typedef GrPp<KT, false> CFG;
     constexpr int Q = GR_SYM_Q, SB = GR_SYM_SB;
     const int parts = SPLIT ? split_parts : 1, log_rows = SPLIT ? split_log_rows : SB;
     static_assert(SB % CFG::CH == 0 && SB % CFG::RES == 0 && CFG::RES == 256, "super-blocks are whole chunks and whole blocks");
@@ -1018,25 +1060,26 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
     // The thresholds of a chunk's rows travel to LDS beside its rows: requested by wavefront 0 when the chunk's loads begin.
     // The loads run up to STAGES - 1 pipeline stages ahead of the MFMAs and a chunk of D = 128 is a single stage, so up to
     // seven chunks lie between the request and the epilogue that reads it: eight slots.
-    static_assert((CFG::STAGES - 1) * CFG::KSUB / KT + 2 <= 8, "slots for the chunks in flight");
+    static_assert(CFG::AHEAD <= 8, "slots for the chunks in flight");
     auto side = [&](int first, int c) __attribute__((always_inline)) {
-        static_assert(CFG::CH == 96, "64 + 32 lanes");
-        __builtin_amdgcn_global_load_lds(KS_GPTR(thf_row + first + lane), KS_LPTR(&s_thr[c & 7][0]), 4, 0, 0);
-        if (lane < 32) __builtin_amdgcn_global_load_lds(KS_GPTR(thf_row + first + 64 + lane), KS_LPTR(&s_thr[c & 7][64]), 4, 0, 0);
+#pragma unroll
+        for (int u = 0; u < CFG::CH; u += 64)
+            if (u + 64 <= CFG::CH || lane < CFG::CH - u)
+                __builtin_amdgcn_global_load_lds(KS_GPTR(thf_row + first + u + lane), KS_LPTR(&s_thr[c & 7][u]), 4, 0, 0);
     };
     int epi_chunk = 0; // chunks seen by the epilogue: the slot of their thresholds
-    auto epi = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) {
+    auto epi = [&](auto block32, int c0, int rows_here, const f32x16_t &acc) __attribute__((always_inline)) {
+        constexpr int fm = decltype(block32)::value;
         const float *thr_chunk = s_thr[epi_chunk & 7];
-        ++epi_chunk;
+        if (fm == CFG::FM - 1) ++epi_chunk;
         const int sb = c0 / SB; // uniform; a chunk lies in one super-block and in one log
-        if (c0 < cur_log * log_rows || c0 >= (cur_log + 1) * log_rows) { flush(); cur_log = c0 / log_rows; }
+        if (fm == 0 && (c0 < cur_log * log_rows || c0 >= (cur_log + 1) * log_rows)) { flush(); cur_log = c0 / log_rows; }
         // Which sides are wanted is the same for 32 streamed rows at a time (block boundaries are multiples of 32 rows):
         // both, except in the workgroup's own super-block, where its own block is searched for the resident side only and
         // the other blocks as the ring says.
         const bool own_sb = sb == sb_own, ragged = rows_here < CFG::CH; // (ragged: the last chunk of W)
         const bool real_row = row0 + ks_soe_col() < C;
-#pragma unroll
-        for (int fm = 0; fm < CFG::FM; ++fm) {
+        {
             bool res_side = true, str_side = true, diag = false;
             if (own_sb) {
                 const int kb = ring & 15, n_b = (ring >> 4) & 15, succ_b = ring >> 8;
@@ -1049,24 +1092,30 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
             if (res_side) {
                 const bool check = diag || ragged;
                 if (SPLIT) {
-                    uint32_t hr = gr_hit_mask(thf, acc[fm]);
-                    while (__ballot(hr != 0u) != 0ull) {
-                        if (hr != 0u) {
-                            const int r = 15 - __builtin_ctz(hr);
-                            hr &= hr - 1u;
-                            const float v = gr_sym_pick16(acc[fm], r);
-                            const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                            if (!check || (lr < rows_here && c0 + lr != row0 + ks_soe_col())) append_res(c0 + lr, v);
+                    uint32_t hr = gr_hit_mask(thf, acc);
+                    int first = c0 + fm * 32 + 4 * (lane >> 5);
+                    asm volatile("" : "+v"(first));
+                    if (check) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int j = first + 8 * (r >> 2) + (r & 3);
+                            if (j >= c0 + rows_here || j == row0 + ks_soe_col()) hr &= ~(0x8000u >> r);
                         }
+                    }
+                    while (__ballot(hr != 0u) != 0ull) {
+                        const int r = 15 - (__ffs(hr) - 1);
+                        const float v = gr_sym_pick16(acc, r);
+                        if (hr != 0u) append_res(first + r + (r & 12), v);
+                        hr &= hr - 1u;
                     }
                 } else {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) { // four values at a time: most groups have none that passes
-                        const float a0 = acc[fm][4 * q], a1 = acc[fm][4 * q + 1], a2 = acc[fm][4 * q + 2], a3 = acc[fm][4 * q + 3];
+                        const float a0 = acc[4 * q], a1 = acc[4 * q + 1], a2 = acc[4 * q + 2], a3 = acc[4 * q + 3];
                         if (fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)) > thf) {
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const float v = acc[fm][4 * q + e];
+                                const float v = acc[4 * q + e];
                                 if (v > thf) {
                                     const int lr = ks_soe_row(fm, 4 * q + e, lane);
                                     if (!check || (lr < rows_here && c0 + lr != row0 + ks_soe_col())) append_res(c0 + lr, v);
@@ -1092,29 +1141,28 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x4_t t4 = *(const f32x4_t *)(thr_chunk + fm * 32 + 8 * q + 4 * (lane >> 5));
-                    hm = gr_hit_mask4(hm, t4[0], t4[1], t4[2], t4[3], acc[fm][4 * q], acc[fm][4 * q + 1], acc[fm][4 * q + 2],
-                                      acc[fm][4 * q + 3]);
+                    hm = gr_hit_mask4(hm, t4[0], t4[1], t4[2], t4[3], acc[4 * q], acc[4 * q + 1], acc[4 * q + 2],
+                                      acc[4 * q + 3]);
                 }
                 if (!real_row) hm = 0u; // (streamed rows beyond W have a threshold that nothing exceeds)
                 uint64_t any = __ballot(hm != 0u);
                 while (any != 0ull) {
                     const int n = __popcll(any);
                     if (staged + n > GR_SYM_STAGE) flush();
-                    if (hm != 0u) {
-                        const int r = 15 - __builtin_ctz(hm);
-                        hm &= hm - 1u;
-                        const float v = gr_sym_pick16(acc[fm], r);
-                        const int lr = fm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                        my_stage()[staged + __popcll(any & ((1ull << lane) - 1ull))] = gr_sym_record(c0 - cur_log * log_rows + lr, row0 + ks_soe_col(), v);
-                    }
+                    const int r = 15 - (__ffs(hm) - 1);
+                    const float v = gr_sym_pick16(acc, r);
+                    const int lr = fm * 32 + 4 * (lane >> 5) + r + (r & 12);
+                    if (hm != 0u)
+                        my_stage()[staged + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(any >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)any, 0u))] =
+                            gr_sym_record(c0 - cur_log * log_rows + lr, row0 + ks_soe_col(), v);
+                    hm &= hm - 1u;
                     staged = __builtin_amdgcn_readfirstlane(staged + n);
                     any = __ballot(hm != 0u);
                 }
             }
         }
     };
-    ks_soe_sweep<CFG>(W, D, row0, C, W, D, nullptr, 0, 0, C, lds, epi, nullptr, 0,
-                      chunks + (int64_t)share * chunks_stride + chunk0, chunk1 - chunk0, side);
+    ks_soe_pp_sweep<CFG>(W, D, row0, C, W, D, 0, 0, C, lds, epi, chunks + (int64_t)share * chunks_stride + chunk0, chunk1 - chunk0, side);
     flush();
     if (row0 + ks_soe_col() < C)
         cnt_res[(int64_t)(row0 + ks_soe_col()) * 2 * parts + 2 * part + (lane >> 5)] = my_cnt;
@@ -1636,9 +1684,9 @@ gr_second_kernel(const IN *__restrict__ W, int64_t C, int D, int K, GrSegs seg, 
 // host side
 // ------------------------------------------------------------------------------------------------
 static unsigned gr_sym_shares(int64_t C) { return (unsigned)ks_ceil_div(C, 256); } // a share per block of resident rows
-static int gr_sym_chunks_stride(int64_t C) { // chunks of a share at most: half of all groups, half of its own, a spare
+static int gr_sym_chunks_stride(int64_t C, int D) { // chunks of a share at most: half of all groups, half of its own, a spare
     const int64_t nsb = ks_ceil_div(C, GR_SYM_SB), GS = gr_sym_group_sbs(C), NG = ks_ceil_div(nsb, GS);
-    return (int)(((NG / 2) * GS + GS / 2 + 2) * (GR_SYM_SB / 96));
+    return (int)(((NG / 2) * GS + GS / 2 + 2) * (GR_SYM_SB / gr_chunk(D)));
 }
 // Fixed thresholds serve K <= 64 (a row with few candidates keeps them all and is certified against its fixed threshold).
 // The resident rows' fragments of a depth beyond
@@ -1659,7 +1707,7 @@ static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && 
 // chip's compute units (rounds of workgroups x (set-up + chunks of a part); set-up 6 us and a chunk of 96 rows 1.2 us,
 // 0.5 and 0.4 us more per k-tile: measured on the sweeps).  Bounded by memory: a part costs every row two segments.
 static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
-    const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 1.2 + 0.4 * kt;
+    const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = (1.2 + 0.4 * kt) * gr_chunk(D) / 96;
     int64_t most = ((int64_t)1 << 19) / C; // 4.5 to 5.5 GiB of segments
     if (most > GR_MAX_PARTS) most = GR_MAX_PARTS;
     if (most > chunks) most = chunks;
@@ -1737,11 +1785,11 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bo
     GrFixPlan f;
     f.every = gr_every(Cs, D, K, dtype, hop);
     f.smp = gr_sample_plan(Cr, Cs, f.every, D, gr_rank_of(K, f.every), sym);
-    const int64_t nb = ks_ceil_div(Cr, 256), chunks = ks_ceil_div(Cs, 96);
+    const int64_t nb = ks_ceil_div(Cr, 256), ch = gr_chunk(D), chunks = ks_ceil_div(Cs, ch);
     f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
     f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K, 32) + 10) + 24; // (with the denser sample: room for ties)
     f.seg.stream = sym ? GR_SYM_SCAP : 0;
-    f.part_rows = (int)ks_ceil_div(chunks, f.seg.parts) * 96;
+    f.part_rows = (int)(ks_ceil_div(chunks, f.seg.parts) * ch);
     if (!sym) f.seg.parts = (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
     if (!sym && f.seg.q > f.part_rows / 2) f.seg.q = f.part_rows / 2;
     f.log_rows = GR_SYM_SB;
@@ -1795,7 +1843,7 @@ static GrWs gr_carve(void *ws, int64_t C, int D, int K, int dtype, size_t *total
         w.thr = ar.take<uint32_t>((size_t)C);
     } else {
         const GrFixPlan f = gr_fix_plan(C, C, D, K, dtype, sym, false);
-        const int64_t Cpad = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
+        const int64_t Cpad = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 128;
         w.cand = ar.take<uint64_t>((size_t)C * f.seg.cap());
         KsArena over(w.scratch); // see gr_sample_plan
         w.Ws = over.take<uint16_t>((size_t)(C / f.every) * D);
@@ -1809,7 +1857,7 @@ static GrWs gr_carve(void *ws, int64_t C, int D, int K, int dtype, size_t *total
             w.cnt_str = ar.take<int32_t>((size_t)C);
             w.logcnt = ar.take<int32_t>((size_t)f.logs);
             w.plan = ar.take<int32_t>((size_t)gr_sym_shares(C) * GR_SYM_PLAN);
-            w.chunks = ar.take<int2>((size_t)gr_sym_shares(C) * gr_sym_chunks_stride(C));
+            w.chunks = ar.take<int2>((size_t)gr_sym_shares(C) * gr_sym_chunks_stride(C, D));
             w.log = ar.take<uint2>((size_t)f.logs * f.log_rows * GR_SYM_LOG_PER_ROW);
         }
     }
@@ -1879,34 +1927,31 @@ static void gr_launch_prepare(const GrPrepJob &j0, const GrPrepJob &j1, int D, i
     else hipLaunchKernelGGL(gr_prepare_kernel<uint16_t>, grid, dim3(GR_NT), 0, st, j0, j1, D, clr);
 }
 
-// Sweeps of a depth of KT k-tiles (D <= 512, D % 32 == 0): F(CFG) is instantiated for the depth's stage shape
+// Sweeps of a depth of KT k-tiles (D <= 512, D % 32 == 0): F(KT, RAGGED) is instantiated
 #define GR_FOR_DEPTH(F)                                                                                     \
     do {                                                                                                    \
         const int kt = (D + 63) / 64;                                                                       \
         if (D % 64 == 0) {                                                                                  \
-            if (kt == 1) F(GrSoe<1 COMMA false>); else if (kt == 2) F(GrSoe<2 COMMA false>);                \
-            else if (kt == 3) F(GrSoe<3 COMMA false>); else if (kt == 4) F(GrSoe<4 COMMA false>);           \
-            else if (kt == 5) F(GrSoe<5 COMMA false>); else if (kt == 6) F(GrSoe<6 COMMA false>);           \
-            else if (kt == 7) F(GrSoe<7 COMMA false>); else F(GrSoe<8 COMMA false>);                        \
+            if (kt == 1) F(1, false); else if (kt == 2) F(2, false); else if (kt == 3) F(3, false);         \
+            else if (kt == 4) F(4, false); else if (kt == 5) F(5, false); else if (kt == 6) F(6, false);    \
+            else if (kt == 7) F(7, false); else F(8, false);                                                \
         } else {                                                                                            \
-            if (kt == 1) F(GrSoe<1 COMMA true>); else if (kt == 2) F(GrSoe<2 COMMA true>);                  \
-            else if (kt == 3) F(GrSoe<3 COMMA true>); else if (kt == 4) F(GrSoe<4 COMMA true>);             \
-            else if (kt == 5) F(GrSoe<5 COMMA true>); else if (kt == 6) F(GrSoe<6 COMMA true>);             \
-            else if (kt == 7) F(GrSoe<7 COMMA true>); else F(GrSoe<8 COMMA true>);                          \
+            if (kt == 1) F(1, true); else if (kt == 2) F(2, true); else if (kt == 3) F(3, true);            \
+            else if (kt == 4) F(4, true); else if (kt == 5) F(5, true); else if (kt == 6) F(6, true);       \
+            else if (kt == 7) F(7, true); else F(8, true);                                                  \
         }                                                                                                   \
     } while (0)
-#define COMMA ,
 
 static void gr_launch_threshold(const uint16_t *R, int64_t Cr, const uint16_t *Ws, int64_t n_sample, int D, const GrSample &smp, const float *blockmax,
                                 int n_blockmax, float *maxnorm, const GrHop &hop, float *thf, uint32_t *tbits, hipStream_t st) {
     const dim3 grid((unsigned)(ks_ceil_div(Cr, 256) * smp.parts));
-#define GR_THR_LAUNCH(CFG)                                                                                                    \
+#define GR_THR_LAUNCH(KT, RAGGED)                                                                                                    \
     do {                                                                                                                      \
         if (smp.parts > 1)                                                                                                    \
-            hipLaunchKernelGGL((gr_threshold_kernel<CFG, true>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
+            hipLaunchKernelGGL((gr_threshold_kernel<KT, RAGGED, true>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
                                n_blockmax, maxnorm, hop, thf, tbits);                                                         \
         else                                                                                                                  \
-            hipLaunchKernelGGL((gr_threshold_kernel<CFG, false>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
+            hipLaunchKernelGGL((gr_threshold_kernel<KT, RAGGED, false>), grid, dim3(512), 0, st, R, Cr, Ws, (int)n_sample, D, smp, blockmax, \
                                n_blockmax, maxnorm, hop, thf, tbits);                                                         \
     } while (0)
     GR_FOR_DEPTH(GR_THR_LAUNCH);
@@ -1917,13 +1962,13 @@ static void gr_launch_recall_fix(const GrPair &pr, int D, const GrFixPlan &f, co
     const int nb = (int)ks_ceil_div(pr.Cr, 256);
     const dim3 grid((unsigned)(nb * f.seg.parts));
     const GrMerge merge{smp, hop, maxnorm, tbits};
-#define GR_FIX_LAUNCH(CFG)                                                                                                          \
+#define GR_FIX_LAUNCH(KT, RAGGED)                                                                                                          \
     do {                                                                                                                            \
         if (smp.parts > 1)                                                                                                          \
-            hipLaunchKernelGGL((gr_recall_fix_kernel<CFG, GrMerge>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, merge, thf, \
+            hipLaunchKernelGGL((gr_recall_fix_kernel<KT, RAGGED, GrMerge>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, merge, thf, \
                                cand, cnt_res);                                                                                      \
         else                                                                                                                        \
-            hipLaunchKernelGGL((gr_recall_fix_kernel<CFG, GrReady>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, GrReady(), \
+            hipLaunchKernelGGL((gr_recall_fix_kernel<KT, RAGGED, GrReady>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, GrReady(), \
                                thf, cand, cnt_res);                                                                                 \
     } while (0)
     GR_FOR_DEPTH(GR_FIX_LAUNCH);
@@ -1967,8 +2012,8 @@ static void gr_launch_recall(const GrPair &pr, int D, const GrParams &p, uint64_
 // W searched in W with every similarity computed once: the sweep, the stream side's records to their rows
 static void gr_launch_recall_sym(const uint16_t *Wb, int64_t C, int D, const GrFixPlan &f, const GrWs &w, hipStream_t st) {
     const unsigned shares = gr_sym_shares(C), grid = shares * (unsigned)f.seg.parts;
-    const int stride = gr_sym_chunks_stride(C);
-    hipLaunchKernelGGL(gr_sym_plan_kernel, dim3(shares), dim3(GR_NT), 0, st, (int)C, gr_sym_group_sbs(C), w.plan, w.chunks, stride);
+    const int stride = gr_sym_chunks_stride(C, D);
+    hipLaunchKernelGGL(gr_sym_plan_kernel, dim3(shares), dim3(GR_NT), 0, st, (int)C, gr_sym_group_sbs(C), gr_chunk(D), w.plan, w.chunks, stride);
     const bool split = f.seg.parts > 1 || f.log_rows != GR_SYM_SB;
 #define GR_SYM_LAUNCH2(KT, SPLIT)                                                                                              \
     hipLaunchKernelGGL((gr_recall_sym_kernel<KT, SPLIT>), dim3(grid), dim3(512), 0, st, Wb, (int)C, D, w.plan, w.chunks, stride, \
@@ -2035,7 +2080,7 @@ extern "C" int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K
         clr.nlog = f.logs;
         clr.thf = w.thf;
         clr.pad0 = C;
-        clr.pad1 = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 96;
+        clr.pad1 = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 128;
     }
     const GrPrepJob job = gr_prep_job(W, C, D, dtype, w.Wb, w.norms, w.blockmax, fixed ? w.Ws : nullptr, f.every);
     gr_launch_prepare(job, GrPrepJob(), D, dtype, clr, st);

@@ -480,3 +480,42 @@ def test_two_sweeps_and_one_with_kept_products(ks, orc, D, over):
     y = synth.labels_uniform(71, B, C)
     G = ((np.arange(C)[:, None] * 7 + 1 + np.arange(K)[None, :] * 13) % C).astype(np.int32)
     run_and_compare(ks, orc, W, X, y, G, C, M, scale=20.0, grad_scale=4.0, tag=f"D={D}", modes=(False,))
+
+
+@pytest.mark.parametrize("D", [32, 64, 96, 128, 192, 256, 320, 384, 448, 480, 512])
+@pytest.mark.parametrize("over", [-1, 0, 1])
+def test_hop_of_one_to_five_chunks(ks, orc, D, over):
+    """The sweep in turns with fewer chunks than stages, whole last chunks and ones of a single row: every chunk size divides 384, and a
+    hop of few rows against 128 to 640 has one to five chunks in one part.  The rows' lists are those of all visiting rows."""
+    import torch
+    K = 8
+    for blocks in (1, 2, 3, 5):
+        n = 128 * blocks + over
+        print(f"[depths] hop of chunks D={D} visiting {n}", flush=True)
+        W = synth.unit_rows(61 + blocks, synth.TID_W, n + 70, D, bf16=True)
+        Wl, Wv = dev(W[n:], True), dev(W[:n], True)
+        graph = torch.full((70, K), -1, dtype=torch.int32, device="cuda")
+        sims = torch.full((70, K), -np.inf, dtype=torch.float64, device="cuda")
+        ks.knn_graph_update(Wl, Wv, n, 0, graph, sims)
+        torch.cuda.synchronize()
+        S = W[n:].astype(np.float64) @ W[:n].astype(np.float64).T
+        expect = np.argsort(-S, axis=1, kind="stable")[:, :K]
+        got = graph.cpu().numpy()
+        # (sums in another order: neighbours closer than the rounding of fp64 sums may change places)
+        for i in range(70):
+            assert (got[i] == expect[i]).all() or np.allclose(S[i, got[i]], S[i, expect[i]], rtol=0, atol=1e-14)
+
+
+@pytest.mark.parametrize("D", [64, 96, 192, 256, 320, 416, 448, 480])
+def test_thresholds_of_many_blocks(ks, orc, D):
+    """Enough rows for one workgroup per block in the sample's search (the sweep in turns there too), at depths without the pass that
+    computes every similarity once, whole and ragged."""
+    import torch
+    C, K = 66_000, 12
+    print(f"[depths] thresholds D={D}", flush=True)
+    W = torch.nn.functional.normalize(torch.randn((C, D), generator=torch.Generator().manual_seed(D))).to(torch.bfloat16)
+    g, s = ks.knn_graph_build(W.cuda(), K, want_sims=True)
+    torch.cuda.synchronize()
+    rows = np.array([0, 1, 255, 256, 31_999, 65_535, 65_536, C - 1], dtype=np.int32)
+    eg, es = orc.graph_bruteforce(W.float().numpy(), K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
