@@ -323,6 +323,13 @@ template <class F, int... I> __device__ __forceinline__ void ks_each_of(F &f, st
     (f(std::integral_constant<int, I>()), ...);
 }
 template <int N, class F> __device__ __forceinline__ void ks_each(F &f) { ks_each_of(f, std::make_integer_sequence<int, N>()); }
+// the epilogue of ks_soe_sweep, chunk by chunk, from one that takes 32-row blocks (as for ks_soe_pp_sweep)
+template <class CFG, class Epi> __device__ __forceinline__ auto ks_soe_blocks(Epi &epi) {
+    return [&epi](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) __attribute__((always_inline)) {
+        auto one = [&](auto block) __attribute__((always_inline)) { epi(block, c0, rows_here, acc[decltype(block)::value]); };
+        ks_each<CFG::FM>(one);
+    };
+}
 
 template <int KT_, int FM_, int KSUB_, int STAGES_, int PF_, bool RAGGED_ = false> struct KsPp {
     static constexpr int KT = KT_, FM = FM_, KSUB = KSUB_, STAGES = STAGES_, PF = PF_;

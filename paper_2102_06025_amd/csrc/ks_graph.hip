@@ -722,10 +722,7 @@ gr_threshold_kernel(const uint16_t *__restrict__ R, int64_t Cr, const uint16_t *
         }
     };
     if constexpr (PARTS) {
-        auto chunk = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) __attribute__((always_inline)) {
-            auto one = [&](auto block) __attribute__((always_inline)) { epi(block, c0, rows_here, acc[decltype(block)::value]); };
-            ks_each<CFG::FM>(one);
-        };
+        auto chunk = ks_soe_blocks<CFG>(epi);
         ks_soe_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, nullptr, s0, s1, n_sample, lds, chunk);
     } else {
         ks_soe_pp_sweep<CFG>(R, D, (int)row0, (int)Cr, Ws, D, s0, s1, n_sample, lds, epi);
@@ -830,11 +827,12 @@ __device__ __forceinline__ uint32_t gr_hit_mask(float t, const f32x16_t &a) {
 // counts in a register: an append is a store and an increment.  In the problems that come here one value in 30 to 1,000
 // passes, so that of 64 lanes x 16 values nearly always some do: the hits of a lane become a bit mask and are taken one by
 // one (testing value by value costs a branch around the append for each of them).
-template <int KT, bool RAGGED, class MERGE>
+// TURNS: whether the halves of the workgroup take turns (ks_soe_pp_sweep).
+template <int KT, bool RAGGED, class MERGE, bool TURNS>
 __global__ void __launch_bounds__(512)
 gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE merge, const float *__restrict__ thf_row,
                      uint64_t *__restrict__ cand, int32_t *__restrict__ cnt_res) {
-    typedef GrPp<KT, RAGGED> CFG;
+    typedef typename std::conditional<TURNS, GrPp<KT, RAGGED>, GrSoe<KT, RAGGED>>::type CFG;
     __shared__ __attribute__((aligned(16))) uint16_t lds[CFG::LDS_ELEMS];
     const int id = ks_xcd_remap(blockIdx.x, gridDim.x); // the workgroups of an XCD stream the same parts
     const int part = id / nb;
@@ -881,7 +879,12 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE 
             hm &= hm - 1u;
         }
     };
-    ks_soe_pp_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, s0, s1, (int)pr.Cs, lds, epi);
+    if constexpr (TURNS) {
+        ks_soe_pp_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, s0, s1, (int)pr.Cs, lds, epi);
+    } else {
+        auto chunk = ks_soe_blocks<CFG>(epi);
+        ks_soe_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, nullptr, s0, s1, (int)pr.Cs, lds, chunk);
+    }
     const int i = row0 + ks_soe_col();
     if (i < Cr) cnt_res[(int64_t)i * 2 * seg.parts + 2 * part + ((threadIdx.x & 63) >> 5)] = my_cnt;
 }
@@ -1707,7 +1710,7 @@ static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && 
 // chip's compute units (rounds of workgroups x (set-up + chunks of a part); set-up 6 us and a chunk of 96 rows 1.2 us,
 // 0.5 and 0.4 us more per k-tile: measured on the sweeps).  Bounded by memory: a part costs every row two segments.
 static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
-    const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = (1.2 + 0.4 * kt) * gr_chunk(D) / 96;
+    const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 1.2 + 0.4 * kt;
     int64_t most = ((int64_t)1 << 19) / C; // 4.5 to 5.5 GiB of segments
     if (most > GR_MAX_PARTS) most = GR_MAX_PARTS;
     if (most > chunks) most = chunks;
@@ -1776,6 +1779,8 @@ static GrSample gr_sample_plan(int64_t Cr, int64_t Cs, int every, int D, int r, 
 // how a pass with fixed thresholds divides its work and a row's segments
 struct GrFixPlan {
     GrSegs seg;
+    int room_parts, room; // what a row has room for in the workspace: parts, slots
+    bool turns;           // parts: sweep in turns
     int part_rows;        // streamed rows per part (not the symmetric sweep)
     int log_rows, logs;   // symmetric sweep: rows per log, number of logs
     int every;            // searched rows per sampled row
@@ -1785,13 +1790,30 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bo
     GrFixPlan f;
     f.every = gr_every(Cs, D, K, dtype, hop);
     f.smp = gr_sample_plan(Cr, Cs, f.every, D, gr_rank_of(K, f.every), sym);
-    const int64_t nb = ks_ceil_div(Cr, 256), ch = gr_chunk(D), chunks = ks_ceil_div(Cs, ch);
+    const int64_t nb = ks_ceil_div(Cr, 256), ch = gr_chunk(D), chunks = ks_ceil_div(Cs, 96);
     f.seg.parts = gr_parts(Cr, nb, sym ? chunks / 2 + 8 : chunks, D);
-    f.seg.q = sym ? GR_SYM_Q : 32 * (gr_rank_of(K, 32) + 10) + 24; // (with the denser sample: room for ties)
+    const int q_most = sym ? GR_SYM_Q : 32 * (gr_rank_of(K, 32) + 10) + 24; // (with the denser sample: room for ties)
+    f.seg.q = q_most;
     f.seg.stream = sym ? GR_SYM_SCAP : 0;
-    f.part_rows = (int)(ks_ceil_div(chunks, f.seg.parts) * ch);
-    if (!sym) f.seg.parts = (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
+    f.part_rows = (int)(ks_ceil_div(chunks, f.seg.parts) * 96);
+    f.room_parts = sym ? f.seg.parts : (int)ks_ceil_div(Cs, f.part_rows); // (rounding up may leave the last parts without rows)
+    f.turns = false;
     if (!sym && f.seg.q > f.part_rows / 2) f.seg.q = f.part_rows / 2;
+    f.room = 2 * f.room_parts * f.seg.q + f.seg.stream;
+    if (!sym) {
+        // The room is planned in chunks of 96 rows whatever the sweep's are: a workspace serves what it always did.  The parts are whole
+        // chunks of the sweep where those fit in it; otherwise (a few thousand searched rows at most) the last chunk of
+        // each is a ragged one.
+        // In turns from seven chunks of 96 rows on: with fewer there is little to take turns in, and larger chunks fit the parts less
+        // well (2,000 x 64, one chunk a part: 41.5 us, in turns 42.4; 2,345 x 128: 58.2, 59.8; 5,500 x 256, six: 76.5, 77.1; 8,000 x
+        // 320, eleven: 129.5, 119.2; 10,000 x 128: 124.0, 119.2).
+        f.seg.parts = f.room_parts;
+        f.turns = f.part_rows >= 672;
+        const int rows = (int)(ks_ceil_div(ks_ceil_div(Cs, ch), f.room_parts) * ch), parts = (int)ks_ceil_div(Cs, rows);
+        const int64_t half = Cs < 32 ? 16 : ((rows < Cs ? rows : Cs) + 1) / 2; // (a lane looks for room for a block's 16 hits)
+        const int q = half < q_most ? (int)half : q_most;
+        if (f.turns && 2 * parts * q <= f.room) { f.part_rows = rows; f.seg.parts = parts; f.seg.q = q; }
+    }
     f.log_rows = GR_SYM_SB;
     f.logs = 0;
     if (sym) {
@@ -1844,13 +1866,13 @@ static GrWs gr_carve(void *ws, int64_t C, int D, int K, int dtype, size_t *total
     } else {
         const GrFixPlan f = gr_fix_plan(C, C, D, K, dtype, sym, false);
         const int64_t Cpad = ks_ceil_div(C, GR_SYM_SB) * GR_SYM_SB + 128;
-        w.cand = ar.take<uint64_t>((size_t)C * f.seg.cap());
+        w.cand = ar.take<uint64_t>((size_t)C * f.room);
         KsArena over(w.scratch); // see gr_sample_plan
         w.Ws = over.take<uint16_t>((size_t)(C / f.every) * D);
         w.tops = f.smp.parts > 1 ? over.take<float>((size_t)f.smp.parts * GR_RANK * C) : nullptr;
         w.thf = ar.take<float>((size_t)Cpad);
         w.tbits = ar.take<uint32_t>((size_t)C);
-        w.cnt_res = ar.take<int32_t>((size_t)C * 2 * f.seg.parts);
+        w.cnt_res = ar.take<int32_t>((size_t)C * 2 * f.room_parts);
         w.second_count = ar.take<int32_t>(1);
         w.second_rows = ar.take<int32_t>((size_t)C);
         if (sym) {
@@ -1962,17 +1984,23 @@ static void gr_launch_recall_fix(const GrPair &pr, int D, const GrFixPlan &f, co
     const int nb = (int)ks_ceil_div(pr.Cr, 256);
     const dim3 grid((unsigned)(nb * f.seg.parts));
     const GrMerge merge{smp, hop, maxnorm, tbits};
-#define GR_FIX_LAUNCH(KT, RAGGED)                                                                                                          \
+#define GR_FIX_LAUNCH2(KT, RAGGED, TURNS)                                                                                             \
     do {                                                                                                                            \
         if (smp.parts > 1)                                                                                                          \
-            hipLaunchKernelGGL((gr_recall_fix_kernel<KT, RAGGED, GrMerge>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, merge, thf, \
-                               cand, cnt_res);                                                                                      \
+            hipLaunchKernelGGL((gr_recall_fix_kernel<KT, RAGGED, GrMerge, TURNS>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, \
+                               merge, thf, cand, cnt_res);                                                                          \
         else                                                                                                                        \
-            hipLaunchKernelGGL((gr_recall_fix_kernel<KT, RAGGED, GrReady>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, GrReady(), \
-                               thf, cand, cnt_res);                                                                                 \
+            hipLaunchKernelGGL((gr_recall_fix_kernel<KT, RAGGED, GrReady, TURNS>), grid, dim3(512), 0, st, pr, D, nb, f.part_rows, f.seg, \
+                               GrReady(), thf, cand, cnt_res);                                                                      \
+    } while (0)
+#define GR_FIX_LAUNCH(KT, RAGGED)                          \
+    do {                                                   \
+        if (f.turns) GR_FIX_LAUNCH2(KT, RAGGED, true);     \
+        else GR_FIX_LAUNCH2(KT, RAGGED, false);            \
     } while (0)
     GR_FOR_DEPTH(GR_FIX_LAUNCH);
 #undef GR_FIX_LAUNCH
+#undef GR_FIX_LAUNCH2
 }
 
 // thr_init (optional, honoured by the sweep kernel only, may be `thr`): per row the value bits of a similarity at or below
@@ -2342,13 +2370,13 @@ static GrUpWs gr_up_carve(void *ws, int64_t C_loc, int64_t C_vis, int D, int K, 
     w.scratch = ar.take<double>((size_t)GR_FB_BLOCKS * C_vis);
     if (gr_use_fixed(C_loc, C_vis, D, K)) {
         const GrFixPlan f = gr_fix_plan(C_loc, C_vis, D, K, dtype, false, true);
-        w.cand = ar.take<uint64_t>((size_t)C_loc * f.seg.cap());
+        w.cand = ar.take<uint64_t>((size_t)C_loc * f.room);
         KsArena over(w.scratch);
         w.Ws = over.take<uint16_t>((size_t)(C_vis / f.every) * D);
         w.tops = f.smp.parts > 1 ? over.take<float>((size_t)f.smp.parts * GR_RANK * C_loc) : nullptr;
         w.thf = ar.take<float>((size_t)C_loc);
         w.tbits = ar.take<uint32_t>((size_t)C_loc);
-        w.cnt_res = ar.take<int32_t>((size_t)C_loc * 2 * f.seg.parts);
+        w.cnt_res = ar.take<int32_t>((size_t)C_loc * 2 * f.room_parts);
     } else {
         w.cand = ar.take<uint64_t>((size_t)C_loc * p.cap);
         w.cnt = ar.take<int32_t>((size_t)C_loc);

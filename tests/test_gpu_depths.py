@@ -485,12 +485,11 @@ def test_two_sweeps_and_one_with_kept_products(ks, orc, D, over):
 @pytest.mark.parametrize("D", [32, 64, 96, 128, 192, 256, 320, 384, 448, 480, 512])
 @pytest.mark.parametrize("over", [-1, 0, 1])
 def test_hop_of_one_to_five_chunks(ks, orc, D, over):
-    """The sweep in turns with fewer chunks than stages, whole last chunks and ones of a single row: every chunk size divides 384, and a
-    hop of few rows against 128 to 640 has one to five chunks in one part.  The rows' lists are those of all visiting rows."""
+    """The sweep in turns with fewer chunks than stages, whole last chunks and ones of a single row, visiting shards of a few rows
+    among them.  The rows' lists are those of all visiting rows."""
     import torch
     K = 8
-    for blocks in (1, 2, 3, 5):
-        n = 128 * blocks + over
+    for blocks, n in ((0, 10 + over), (0, 32 + over), (1, 96 + over), (1, 128 + over), (2, 256 + over), (3, 384 + over), (5, 640 + over)):
         print(f"[depths] hop of chunks D={D} visiting {n}", flush=True)
         W = synth.unit_rows(61 + blocks, synth.TID_W, n + 70, D, bf16=True)
         Wl, Wv = dev(W[n:], True), dev(W[:n], True)
