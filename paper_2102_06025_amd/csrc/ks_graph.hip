@@ -1292,6 +1292,11 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // One kernel does what were three passes over the candidates (cut, re-rank, and before them a gather of the
 // segments): the keys are read once, and the row's own data and the other lanes' entries come through scalar registers
 // (the ranking by shuffles cost three LDS permutes and 24 instructions per entry, now three lane reads and 6).
+// The kernel is bound by the instructions it issues.  Where a key lies in the segments comes from a running sum over LDS (before, a
+// loop over the segments for every register of keys), and for K <= 32 the K-th key is first bounded by the lanes' largest values, one
+// compare a round, and then searched among the at most 64 keys above the bound (before, 4 or 8 compares a round).  Builds, us:
+// 2,000 x 64, K = 16: 41.2 -> 33.1; 10,000 x 128, K = 8, fp32: 119.0 -> 113.8; 8,000 x 320, K = 24: 119 -> 114; two hops of 15,000 x 15,000
+// x 256, K = 32: 500 -> 491.
 // SHORT: lists of at most 256 candidates have a copy of the search of their own, taken for K <= 24 (beyond, too few rows have
 // so few).  For K <= 32 the kernel of K > 24 does without the copy, which alone costs it 1 %; so does that of K <= 24 where few rows
 // gain by it, those of fp32 builds and of hops (one row in 32 sampled), and the rows are one round of the chip (2,000 x 256, K = 16,
@@ -1309,6 +1314,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                int64_t visit_offset, int32_t *__restrict__ graph, void *__restrict__ sims_, int32_t *list_count,
                int32_t *__restrict__ list_rows) {
     __shared__ uint64_t s_key[GR_NT / 64][KP * 64];
+    __shared__ int s_grow[GR_NT / 64][512];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t i = (int64_t)blockIdx.x * (GR_NT / 64) + wave;
     if (i >= C) return;
@@ -1330,20 +1336,57 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
     auto select = [&](auto e_) __attribute__((always_inline)) {
         constexpr int E = decltype(e_)::value;
         uint64_t val[E];
+        // (an index counts through the segments laid end to end: what has to be added to it to find its place grows at the first index
+        // of every segment)
+        if (E <= 8 && nseg > 4) {
+            int *const grow = s_grow[wave];
 #pragma unroll
-        for (int r = 0; r < E; ++r) {
-            val[r] = 0ull; // below every real key
-            if (r * 64 < n) {
-                const int idx = r * 64 + lane;
-                int adj = 0; // (the first segment begins at 0)
-                for (int sg = 1; sg < nseg; ++sg) {
-                    const int st = __builtin_amdgcn_readlane(excl, sg);
-                    const int sh = __builtin_amdgcn_readlane(shift, sg);
-                    if (idx >= st) adj = sh;
+            for (int r = 0; r < E; ++r) grow[r * 64 + lane] = 0;
+            asm volatile("" ::: "memory");
+            const int before = __shfl_up(shift, 1, 64);
+            if (lane > 0 && lane < nseg && excl < n) atomicAdd(&grow[excl], shift - before);
+            asm volatile("" ::: "memory"); // (a wavefront's LDS instructions are carried out in order)
+            int carry = 0; // (the first segment begins at 0)
+#pragma unroll
+            for (int r = 0; r < E; ++r) {
+                val[r] = 0ull; // below every real key
+                if (r * 64 < n) {
+                    const int adj = ks_wave_iscan(grow[r * 64 + lane]) + carry;
+                    carry = __builtin_amdgcn_readlane(adj, 63);
+                    if (r * 64 + lane < n) val[r] = row[r * 64 + lane + adj];
                 }
-                if (idx < n) val[r] = row[idx + adj];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < E; ++r) {
+                val[r] = 0ull;
+                if (r * 64 < n) {
+                    const int idx = r * 64 + lane;
+                    int adj = 0;
+                    for (int sg = 1; sg < nseg; ++sg) {
+                        const int st = __builtin_amdgcn_readlane(excl, sg);
+                        const int sh = __builtin_amdgcn_readlane(shift, sg);
+                        if (idx >= st) adj = sh;
+                    }
+                    if (idx < n) val[r] = row[idx + adj];
+                }
             }
         }
+        // the keys for which keep(value) holds go to the front of LDS; returns how many (64 KP at most are stored)
+        auto compact = [&](auto keep) __attribute__((always_inline)) {
+            int base = 0;
+#pragma unroll
+            for (int r = 0; r < E; ++r) {
+                if (r * 64 < n) {
+                    const bool k = r * 64 + lane < n && keep(val[r]);
+                    const uint64_t m = __ballot(k);
+                    const int q = base + __popcll(m & ((1ull << lane) - 1ull));
+                    if (k && q < KP * 64) s_key[wave][q] = val[r];
+                    base += __popcll(m);
+                }
+            }
+            return base;
+        };
         uint64_t t = 1ull; // keeps every real key
         if (n > K) {
             auto count_hi = [&](uint32_t v) __attribute__((always_inline)) {
@@ -1353,9 +1396,10 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                     if (E <= 8 || r * 64 < n) k += __popcll(__ballot((uint32_t)(val[r] >> 32) >= v));
                 return k;
             };
-            uint32_t mx = 0u;
+            uint32_t mine = 0u; // the largest value of the lane
 #pragma unroll
-            for (int r = 0; r < E; ++r) mx = (uint32_t)(val[r] >> 32) > mx ? (uint32_t)(val[r] >> 32) : mx;
+            for (int r = 0; r < E; ++r) mine = (uint32_t)(val[r] >> 32) > mine ? (uint32_t)(val[r] >> 32) : mine;
+            uint32_t mx = mine;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) {
                 const uint32_t other = (uint32_t)__shfl_xor((int)mx, o, 64);
@@ -1364,21 +1408,43 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
             mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)mx);
             const int top_bit = mx > tb ? 31 - __builtin_clz(mx ^ tb) : -1; // (always above: only such keys are appended)
             const uint32_t prefix = top_bit >= 31 ? 0u : (top_bit < 0 ? mx : mx >> (top_bit + 1) << (top_bit + 1));
-            auto search = [&](int m, bool &exact) __attribute__((always_inline)) {
+            auto search_by = [&](int m, bool &exact, auto count) __attribute__((always_inline)) {
                 uint32_t v = prefix;
                 exact = false;
                 for (int bit = top_bit; bit >= 0 && !exact; --bit) {
-                    const int k = count_hi(v | (1u << bit));
+                    const int k = count(v | (1u << bit));
                     if (k >= m) v |= 1u << bit;
                     exact = k == m;
                 }
                 return v;
             };
+            auto search = [&](int m, bool &exact) __attribute__((always_inline)) { return search_by(m, exact, count_hi); };
+            auto below = [&](uint32_t v) __attribute__((always_inline)) { // 2.5 error bounds lower
+                const double low = (double)gr_unorder(v) - 2.5 * eps;
+                float f = (float)low;
+                if ((double)f > low) f = nextafterf(f, -INFINITY); // rounded down
+                return f == f ? gr_orderable(f) : 0u;
+            };
             bool exact;
-            const double low = (double)gr_unorder(search(K, exact)) - 2.5 * eps;
-            float f = (float)low;
-            if ((double)f > low) f = nextafterf(f, -INFINITY); // rounded down
-            uint32_t cut = f == f ? gr_orderable(f) : 0u;
+            if (KP == 1) {
+                // The K-th largest of the lanes' largest values is a bound that K keys reach, found with one compare a round instead of E;
+                // what lies above it (less 2.5 error bounds) is a key per lane, and the search goes on among those.
+                const uint32_t bound = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(mine >= v)); }));
+                const int few = bound > tb ? count_hi(bound) : 65;
+                if (few <= 64) {
+                    compact([&](uint64_t v) __attribute__((always_inline)) { return (uint32_t)(v >> 32) >= bound; });
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    const uint64_t key = lane < few ? s_key[wave][lane] : 0ull;
+                    const uint32_t hi = (uint32_t)(key >> 32);
+                    thr = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(hi >= v)); }));
+                    const uint64_t m = __ballot(hi >= thr); // (above the bound: what was left out is below this)
+                    asm volatile("" ::: "memory");
+                    if (hi >= thr) s_key[wave][__popcll(m & ((1ull << lane) - 1ull))] = key;
+                    kept = __popcll(m);
+                    return;
+                }
+            }
+            uint32_t cut = below(search(K, exact));
             if (cut > tb) {
                 kept = count_hi(cut);
                 t = (uint64_t)cut << 32;
@@ -1407,17 +1473,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                 kept = KP * 64;
             }
         }
-        int base = 0;
-#pragma unroll
-        for (int r = 0; r < E; ++r) {
-            if (r * 64 < n) {
-                const bool keep = r * 64 + lane < n && val[r] >= t;
-                const uint64_t m = __ballot(keep);
-                const int q = base + __popcll(m & ((1ull << lane) - 1ull));
-                if (keep && q < KP * 64) s_key[wave][q] = val[r]; // (q < kept always)
-                base += __popcll(m);
-            }
-        }
+        compact([&](uint64_t v) __attribute__((always_inline)) { return v >= t; }); // (kept of them)
     };
     if (SHORT && K <= 24 && n <= 256) select(std::integral_constant<int, 4>());
     else if (n <= 512) select(std::integral_constant<int, 8>());

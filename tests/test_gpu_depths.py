@@ -518,3 +518,25 @@ def test_thresholds_of_many_blocks(ks, orc, D):
     rows = np.array([0, 1, 255, 256, 31_999, 65_535, 65_536, C - 1], dtype=np.int32)
     eg, es = orc.graph_bruteforce(W.float().numpy(), K, rows)
     assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("C,K,D,bf16", [(3000, 1, 64, False), (3000, 8, 64, True), (2600, 16, 128, False), (7000, 32, 128, True), (9000, 24, 64, False),
+                                        (3000, 40, 64, False), (118_000, 16, 128, True)])
+@pytest.mark.parametrize("noise", [0.0, 0.01, 0.3])
+def test_ranking_of_candidates_that_lie_close(ks, orc, C, K, D, bf16, noise):
+    """Clusters of 100 rows: more than 64 candidates within the error bound of the K-th (exact copies, and rows closer than the bound of
+    rounding fp32 rows), where the search goes through all keys, and rows apart, where it goes through those above the lanes'
+    bound; with many segments per row and with three."""
+    import torch
+    print(f"[depths] close candidates C={C} K={K} D={D} bf16={bf16} noise={noise}", flush=True)
+    rng = np.random.default_rng(C + K)
+    n = max(C // 100, 1)
+    centre = rng.standard_normal((n, D)) / np.sqrt(D)
+    W = (centre[np.arange(C) % n] + noise * rng.standard_normal((C, D)) / np.sqrt(D)).astype(np.float32)
+    if bf16:
+        W = synth.bf16_round(W)
+    g, s = ks.knn_graph_build(dev(W, bf16), K, want_sims=True)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([rng.integers(0, C, 40), [0, C - 1]])).astype(np.int32)
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
