@@ -306,18 +306,6 @@ __device__ __forceinline__ void ks_soe_sweep(const uint16_t *__restrict__ R, int
     ks_barrier_nofence();
 }
 
-// ------------------------------------------------------------------------------------------------
-// The sweep with the two halves of the workgroup in turn ("ping-pong"): while wavefronts 0..3 (one per SIMD) multiply a stage,
-// wavefronts 4..7 run a part of their epilogue for the chunk before, and the other way round, so that the element-wise work
-// of one half hides behind the other half's MFMAs.  In the sweep above both wavefronts of a SIMD reach their epilogues
-// together and the matrix pipe idles meanwhile.  What it takes: two sets of accumulators (the chunk being multiplied and the
-// one before it, 32 FM registers), an epilogue cut into pieces, one per 32-row block, that run in different stages, and two
-// barriers per stage.  All wavefronts run the same program; wavefronts 4..7 are one barrier behind, half a stage.
-//
-// FM: 32-row blocks per chunk (chunk = 32 FM rows).  P = KT / KSUB stages per chunk; block f's epilogue runs in stage f P / FM of
-// the next chunk.  PF: k-steps whose fragments are requested ahead -- a lone wavefront per SIMD has no partner whose MFMAs
-// would cover the round trip to LDS; the first PF of a stage are requested before its barrier, which is why a stage has to land one
-// barrier earlier than in the sweep above.
 // f(integral_constant 0), f(1), ..., f(N - 1)
 template <class F, int... I> __device__ __forceinline__ void ks_each_of(F &f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>()), ...);
@@ -331,6 +319,21 @@ template <class CFG, class Epi> __device__ __forceinline__ auto ks_soe_blocks(Ep
     };
 }
 
+// ------------------------------------------------------------------------------------------------
+// The sweep with the two halves of the workgroup in turn ("ping-pong"): while wavefronts 0..3 (one per SIMD) multiply a stage,
+// wavefronts 4..7 run a part of their epilogue for the chunk before, and the other way round, so that the element-wise work
+// of one half hides behind the other half's MFMAs.  In the sweep above both wavefronts of a SIMD reach their epilogues
+// together and the matrix pipe idles meanwhile.  What it takes: two sets of accumulators (the chunk being multiplied and the
+// one before it, 32 FM registers), an epilogue cut into pieces, one per 32-row block, that run in different stages.  There is
+// one barrier per stage: all wavefronts run the same program, but wavefronts 0..3 meet the stage's barrier before their MFMAs and
+// wavefronts 4..7 behind theirs.  (Two barriers, so that the halves alternate strictly, make every turn as long as the longest
+// epilogue of four wavefronts: the graph's recall 84 -> 94 to 108 ms.)  Wavefronts 0..3 load, like above: with all eight, whose
+// loads then wait behind their epilogues' stores, the hops gain 1 to 3 % and the pass over every similarity once loses 3 to 5 %.
+//
+// FM: 32-row blocks per chunk (chunk = 32 FM rows).  P = KT / KSUB stages per chunk; block f's epilogue runs in stage f P / FM of
+// the next chunk.  PF: k-steps whose fragments are requested ahead -- a lone wavefront per SIMD has no partner whose MFMAs
+// would cover the round trip to LDS; the first PF of a stage are requested before its barrier, which is why a stage has to land one
+// barrier earlier than in the sweep above.
 template <int KT_, int FM_, int KSUB_, int STAGES_, int PF_, bool RAGGED_ = false> struct KsPp {
     static constexpr int KT = KT_, FM = FM_, KSUB = KSUB_, STAGES = STAGES_, PF = PF_;
     static constexpr bool RAGGED = RAGGED_;
@@ -450,6 +453,8 @@ __device__ __forceinline__ void ks_soe_pp_sweep(const uint16_t *__restrict__ R, 
         if (ctab) ct_next = ctab[c + 1 < n_chunks ? c + 1 : c];
         auto one_stage = [&](auto phase) __attribute__((always_inline)) {
             constexpr int p = decltype(phase)::value, NK = CFG::ksteps(p);
+            // Behind this barrier wavefronts 4..7, which have multiplied this stage, go on to the next one, and 0..3 read that one's first
+            // fragments ahead: its loads must have landed.
             if (loader) {
                 if (issued - done - 2 < ST - 3) ks_wait_vmcnt<0>();
                 else ks_wait_vmcnt<(ST - 3) * NI * CFG::KSUB>();
@@ -473,7 +478,7 @@ __device__ __forceinline__ void ks_soe_pp_sweep(const uint16_t *__restrict__ R, 
             ++done;
             if (++stage == ST) stage = 0;
             if (!loader) ks_barrier_nofence();
-            // the slot of the stage before this one: the other half has left it too
+            // (into the slot of the stage before this one, which both halves have left)
             if (issued < n_tiles) issue_one();
             if (c > 0) pieces(phase);
             if (p == P - 1) {

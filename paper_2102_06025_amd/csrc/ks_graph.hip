@@ -2139,7 +2139,8 @@ static void gr_launch_rank(const IN *W, int64_t C, int D, int K, const GrFixPlan
     else if (sizeof(IN) == 2 && C > GR_RANK_AT_ONCE) GR_RANK_LAUNCH(2, true);
     else GR_RANK_LAUNCH(2, false);
 #undef GR_RANK_LAUNCH
-    hipLaunchKernelGGL(gr_second_kernel<IN>, dim3(1024), dim3(GR_NT), 0, st, W, C, D, K, f.seg, w.cand, w.cnt_res, w.cnt_str, w.tbits,
+    // (as many workgroups as run at once, by their LDS: nearly always there is nothing to do, and four rounds of that take 1 to 2 us more)
+    hipLaunchKernelGGL(gr_second_kernel<IN>, dim3(GR_CUS), dim3(GR_NT), 0, st, W, C, D, K, f.seg, w.cand, w.cnt_res, w.cnt_str, w.tbits,
                        w.norms, w.maxnorm, gamma, w.second_count, w.second_rows, graph, sims, w.fb_count, w.fb_rows);
 }
 
