@@ -88,8 +88,8 @@ int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K, int32_t *
 
 /* knn_graph_build_plan -- how knn_graph_build divides the linear search of Section 3.2.2 when it computes every
  * similarity once and uses it for both rows of the pair (C >= 6,144; D = 128, 256 or 512; K <= 64).  Host-only, no GPU
- * work; for tests and tools.  (Problems of less than 15 million elements of W have such a division too, but the build
- * passes all rows by all blocks there, which is faster; a large share may be carried out by several workgroups.)
+ * work; for tests and tools.  (Problems of less than 11 million elements of W, or 15 million at D = 128, have such a
+ * division too, but the build passes all rows by all blocks there, which is faster; a large share may be carried out by several workgroups.)
  *   n_workgroups [1]   out (host): shares of that pass, 0 when this problem has no such division
  *   out          [12]  out (host), may be NULL: for `workgroup` in [0, *n_workgroups):
  *                      [0] its block of 256 resident rows (rows 256 b .. 256 b + 255), or -1: none;

@@ -1754,14 +1754,17 @@ static int gr_sym_chunks_stride(int64_t C, int D) { // chunks of a share at most
 static bool gr_use_fixed(int64_t Cr, int64_t Cs, int D, int K) {
     return K <= 64 && D <= 512 && Cr <= ((int64_t)1 << 22) && Cs <= ((int64_t)1 << 22);
 }
-// The division of the symmetric sweep exists from 6,144 rows on; it is used from C * D = 15 million on.  Below, the passes
-// over both halves of the pairs (gr_recall_fix_kernel) are faster: the matrix cores idle anyway, and what costs is the
-// epilogue's work per hit, of which the stream side's is the dearer one (10,000 x 128: 148 against 170 us; 30,000 x 512:
-// 1.17 against 1.03 ms; 65,000 x 256: 2.47 against 2.43; 100,000 x 128: 4.13 against 4.29).
+// The division of the symmetric sweep exists from 6,144 rows on; it is used from C * D = 11 million on, at D = 128 from 15 million.
+// Below, the passes over both halves of the pairs (gr_recall_fix_kernel) are faster: the matrix cores idle anyway, and what
+// costs is the epilogue's work per hit, of which the stream side's is the dearer one.  Whole builds, us, parts -> symmetric, D = 512:
+// 12,000, K = 8: 238, 259; 15,000, K = 32: 358, 387; 18,000: K = 16 447, 426, K = 64 573, 596; 22,000, K = 32: 653, 598; 28,000, K = 8: 913,
+// 762; 40,000, K = 64: 1,994, 1,686; D = 256: 22,000, K = 16: 392, 408; 34,000: K = 8 773, 702, K = 64 928, 957; 45,000, K = 16: 1,232, 1,085;
+// 57,000: 1,841, 1,530; D = 128: 68,000, K = 16: 1,977, 2,024; 100,000: K = 16 3,738, 3,564, K = 32 3,844, 3,814; 130,000, K = 32: 5,873,
+// 6,206; 160,000, K = 16: 8,671, 7,695.
 static bool gr_has_sym(int64_t C, int D, int K) {
     return (D == 128 || D == 256 || D == 512) && gr_use_fixed(C, C, D, K) && C >= 6144;
 }
-static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && C * D >= 15000000; }
+static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && C * D >= (D == 128 ? 15000000 : 11000000); }
 // Parts that the streamed chunks of each of nb blocks are cut into: the number with the least estimated time on the
 // chip's compute units (rounds of workgroups x (set-up + chunks of a part); set-up 6 us and a chunk of 96 rows 1.2 us,
 // 0.5 and 0.4 us more per k-tile: measured on the sweeps).  Bounded by memory: a part costs every row two segments.

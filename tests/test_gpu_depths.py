@@ -540,3 +540,20 @@ def test_ranking_of_candidates_that_lie_close(ks, orc, C, K, D, bf16, noise):
     rows = np.unique(np.concatenate([rng.integers(0, C, 40), [0, C - 1]])).astype(np.int32)
     eg, es = orc.graph_bruteforce(W, K, rows)
     assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("C,D,K,bf16", [(21_484, 512, 32, True), (21_485, 512, 16, True), (21_600, 512, 64, False), (42_968, 256, 24, True), (42_969, 256, 8, True),
+                                        (43_008, 256, 33, True)])
+def test_graph_around_the_smallest_symmetric_pass(ks, orc, C, D, K, bf16):
+    """The last sizes before and the first of the pass that computes every similarity once (C * D = 11 million beyond D = 128)."""
+    import torch
+    print(f"[depths] symmetric from C={C} D={D} K={K} bf16={bf16}", flush=True)
+    W = torch.nn.functional.normalize(torch.randn((C, D), generator=torch.Generator().manual_seed(C))).numpy()
+    if bf16:
+        W = synth.bf16_round(W)
+    W[C - 1] = W[C // 3]                                          # an exact twin
+    rows = np.unique(np.concatenate([synth.class_permutation(21, C)[:60], [0, C // 3, C - 2, C - 1]])).astype(np.int32)
+    g, s = ks.knn_graph_build(dev(W, bf16), K, want_sims=True)
+    torch.cuda.synchronize()
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
