@@ -1297,6 +1297,8 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // compare a round, and then searched among the at most 64 keys above the bound (before, 4 or 8 compares a round).  Builds, us:
 // 2,000 x 64, K = 16: 41.2 -> 33.1; 10,000 x 128, K = 8, fp32: 119.0 -> 113.8; 8,000 x 320, K = 24: 119 -> 114; two hops of 15,000 x 15,000
 // x 256, K = 32: 500 -> 491.
+// (Not for K > 32, where rows are few wavefronts and the chain of LDS accesses counts: 2,600 x 512, K = 64, fp32: 146 -> 153.  Five
+// wavefronts to a SIMD for K <= 32, at four spilled registers in one form: 5,000 x 320, K = 32, fp32: 128 with four, 122.5.)
 // SHORT: lists of at most 256 candidates have a copy of the search of their own, taken for K <= 24 (beyond, too few rows have
 // so few).  For K <= 32 the kernel of K > 24 does without the copy, which alone costs it 1 %; so does that of K <= 24 where few rows
 // gain by it, those of fp32 builds and of hops (one row in 32 sampled), and the rows are one round of the chip (2,000 x 256, K = 16,
@@ -1307,7 +1309,7 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // ------------------------------------------------------------------------------------------------
 #define GR_RANK_AT_ONCE 4096 /* 256 compute units x 4 workgroups x 4 rows */
 template <typename IN, int KP, bool HOP, bool SHORT>
-__global__ void __launch_bounds__(GR_NT)
+__global__ void __launch_bounds__(GR_NT, KP == 1 ? 5 : 4)
 gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, int64_t Cv, int D, int K, GrSegs seg,
                const uint64_t *__restrict__ cand, const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str,
                const uint32_t *__restrict__ tbits, const float *__restrict__ norms, const float *__restrict__ maxnorm, float gamma,
@@ -1338,7 +1340,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
         uint64_t val[E];
         // (an index counts through the segments laid end to end: what has to be added to it to find its place grows at the first index
         // of every segment)
-        if (E <= 8 && nseg > 4) {
+        if (KP == 1 && E <= 8 && nseg > 4) {
             int *const grow = s_grow[wave];
 #pragma unroll
             for (int r = 0; r < E; ++r) grow[r * 64 + lane] = 0;
