@@ -101,6 +101,15 @@ int knn_graph_build(const void *W, int dtype, int64_t C, int D, int K, int32_t *
  * with every row.  Returns KS_OK, or KS_INVALID_ARG / KS_UNSUPPORTED as knn_graph_build would. */
 int knn_graph_build_plan(int64_t C, int D, int K, int dtype, int workgroup, int32_t *n_workgroups, int32_t *out);
 
+/* knn_graph_recall_plan -- which recall pass knn_graph_build (C_vis = 0) or knn_graph_update (C_loc own, C_vis visiting rows)
+ * takes, and how it divides the searched rows.  Host-only, no GPU work; for tests and tools.
+ *   out [5]  out (host): [0] 0: running thresholds, 1: fixed thresholds, all rows by all searched rows, 2: every similarity once;
+ *            and for 1: [1] parts of the searched rows, one workgroup each per 256 rows; [2] searched rows per part (the
+ *            last may have fewer); [3] searched rows that a workgroup multiplies at a time; [4] 1 when the two halves of a
+ *            workgroup take turns, else 0
+ * Returns KS_OK, or KS_INVALID_ARG / KS_UNSUPPORTED as the call itself would for these sizes. */
+int knn_graph_recall_plan(int64_t C_loc, int64_t C_vis, int D, int K, int dtype, int32_t *out);
+
 /* ------------------------------------------------------------------------------------------------------
  * knn_select_active -- Algorithm 1 without its random fill-up branch: the de-duplicated union of the
  * labels' neighbour lists, each list headed by the label itself; when more than M classes remain, the M

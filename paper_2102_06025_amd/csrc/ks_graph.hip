@@ -2482,6 +2482,25 @@ static void gr_up_exact(const IN *Wl, int64_t C_loc, const IN *Wv, int64_t C_vis
                        w.fb_count, w.fb_rows, w.scratch, graph, sims);
 }
 
+extern "C" int knn_graph_recall_plan(int64_t C_loc, int64_t C_vis, int D, int K, int dtype, int32_t *out) {
+    if (!out) return KS_INVALID_ARG;
+    const bool hop = C_vis != 0;
+    const int rc = hop ? gr_up_check(C_loc, C_vis, D, K, dtype, 0, 0) : gr_check(C_loc, D, K, dtype);
+    if (rc != KS_OK) return rc;
+    const int64_t Cs = hop ? C_vis : C_loc;
+    const bool sym = !hop && gr_use_sym(C_loc, D, K);
+    for (int q = 0; q < 5; ++q) out[q] = 0;
+    if (!gr_use_fixed(C_loc, Cs, D, K)) return KS_OK;
+    out[0] = sym ? 2 : 1;
+    if (sym) return KS_OK;
+    const GrFixPlan f = gr_fix_plan(C_loc, Cs, D, K, dtype, false, hop);
+    out[1] = f.seg.parts;
+    out[2] = f.part_rows;
+    out[3] = f.turns ? gr_chunk(D) : 96;
+    out[4] = f.turns ? 1 : 0;
+    return KS_OK;
+}
+
 extern "C" int knn_graph_update(const void *W_local, const void *W_visit, int dtype, int64_t C_loc, int64_t C_vis, int D, int K,
                                 int64_t local_offset, int64_t visit_offset, int32_t *graph, double *sims, void *ws,
                                 size_t ws_bytes, int32_t *dev_status, void *stream) {

@@ -406,6 +406,20 @@ def test_graph_plan_is_absent_for_small_problems(ks):
         ks.knn_graph_build_plan(390_625, 512, 32, 0, workgroup=10_000_000)
 
 
+def test_recall_plan(ks):
+    """Which recall pass a build or a hop takes; the parts cover the searched rows, the last one with at least one of them."""
+    assert ks.knn_graph_recall_plan(390_625, 0, 512, 32, 0)["kind"] == 2
+    for C, D, K in [(390_625, 512, 65), (5_000_000, 128, 8)]:
+        assert ks.knn_graph_recall_plan(C, 0, D, K, 0)["kind"] == 0
+    for C, V, D, K in [(10_000, 0, 128, 8), (2, 0, 32, 1), (100_000, 0, 192, 16), (25_000, 25_000, 256, 16), (70, 1, 64, 4), (1, 300_000, 512, 64)]:
+        p, n = ks.knn_graph_recall_plan(C, V, D, K, 0), V or C
+        assert p["kind"] == 1 and p["chunk"] % 32 == 0 and (p["parts"] - 1) * p["part_rows"] < n <= p["parts"] * p["part_rows"]
+        assert p["turns"] == 0 or p["part_rows"] >= 672
+    for bad in [(1, 0, 128, 8, 0), (0, 5, 128, 8, 0), (100, -1, 128, 8, 0), (100, 0, 100, 8, 0), (100, 0, 128, 100, 0), (100, 0, 128, 8, 7)]:
+        with pytest.raises(ks.KsError):
+            ks.knn_graph_recall_plan(*bad)
+
+
 def test_topk_argument_errors(ks):
     assert _plan(ks, [10], [0])[0] == -ks.KS_INVALID_ARG          # k < 1
     assert _plan(ks, [10], [11])[0] == -ks.KS_INVALID_ARG         # k > n

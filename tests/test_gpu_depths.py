@@ -18,6 +18,18 @@ def ks():
     return ks
 
 
+def size_with_last_part(ks, n_loc, D, K, last):
+    """The least number of visiting rows from 4,000 on for which the halves of a workgroup take turns and the last part is as wanted (None:
+    not below 60,000)."""
+    for n in range(4000, 60_000):
+        p = ks.knn_graph_recall_plan(n_loc, n, D, K, 0)
+        rows, whole = n - (p["parts"] - 1) * p["part_rows"], p["part_rows"] % p["chunk"] == 0
+        if p["turns"] and {"one row": whole and rows == 1, "one chunk": whole and rows == p["chunk"], "no whole chunks": not whole,
+                           "a chunk and some": whole and p["chunk"] < rows < 2 * p["chunk"]}[last]:
+            return n
+    return None
+
+
 def dev(a, bf16=False):
     import torch
     t = torch.from_numpy(np.ascontiguousarray(a)).cuda()
@@ -30,7 +42,8 @@ def dev(a, bf16=False):
     (29_296, 512, 32, True), (29_297, 512, 16, True), (58_594, 256, 8, True), (117_188, 128, 32, True)])
 def test_graph_at_every_depth_and_around_the_symmetric_pass(ks, orc, C, D, K, bf16):
     """Fixed-threshold recall: depths of 1 to 8 k-tiles, whole and ragged; fewer rows than one sample, than one chunk, than one
-    block; the last sizes before and the first sizes of the pass that computes every similarity once (C * D = 15 million)."""
+    block; sizes of the pass that computes every similarity once (29,296 rows and more; its first sizes are in
+    test_graph_around_the_smallest_symmetric_pass)."""
     import torch
     print(f"[depths] graph C={C} D={D} K={K} bf16={bf16}", flush=True)
     W = synth.unit_rows(21, synth.TID_W, C, D, bf16=bf16)
@@ -485,8 +498,9 @@ def test_two_sweeps_and_one_with_kept_products(ks, orc, D, over):
 @pytest.mark.parametrize("D", [32, 64, 96, 128, 192, 256, 320, 384, 448, 480, 512])
 @pytest.mark.parametrize("over", [-1, 0, 1])
 def test_hop_of_one_to_five_chunks(ks, orc, D, over):
-    """The sweep in turns with fewer chunks than stages, whole last chunks and ones of a single row, visiting shards of a few rows
-    among them.  The rows' lists are those of all visiting rows."""
+    """Visiting shards of a few rows to a few chunks, whole last chunks and ones of a single row.  (Their parts are too short for
+    the halves of a workgroup to take turns: the plain sweep, and for their samples the one in turns with a chunk at most.)  The rows' lists
+    are those of all visiting rows."""
     import torch
     K = 8
     for blocks, n in ((0, 10 + over), (0, 32 + over), (1, 96 + over), (1, 128 + over), (2, 256 + over), (3, 384 + over), (5, 640 + over)):
@@ -503,6 +517,37 @@ def test_hop_of_one_to_five_chunks(ks, orc, D, over):
         # (sums in another order: neighbours closer than the rounding of fp64 sums may change places)
         for i in range(70):
             assert (got[i] == expect[i]).all() or np.allclose(S[i, got[i]], S[i, expect[i]], rtol=0, atol=1e-14)
+
+
+@pytest.mark.parametrize("D", [32, 64, 96, 128, 192, 256, 288, 320, 384, 448, 480, 512])
+@pytest.mark.parametrize("last", ["one row", "one chunk", "a chunk and some", "no whole chunks"])
+def test_hop_in_turns_with_short_last_parts(ks, orc, D, last):
+    """The sweep in turns where the last part has fewer chunks than the pipeline has stages (one of a single row, a whole one, one and
+    a piece of the next), and where the parts themselves are no whole number of chunks.  The sizes come from the plan, which says
+    that the halves take turns there."""
+    import torch
+    n_loc, K = 70, 8
+    n = size_with_last_part(ks, n_loc, D, K, last)
+    if n is None:
+        assert last == "no whole chunks" and 96 % ks.knn_graph_recall_plan(n_loc, 20_000, D, K, 0)["chunk"] == 0
+        return
+    print(f"[depths] hop in turns D={D} visiting {n}: {last}", flush=True)
+    gen = torch.Generator().manual_seed(D + n)
+    W = torch.nn.functional.normalize(torch.randn((n + n_loc, D), generator=gen)).to(torch.bfloat16)
+    W[n:n + 8] = W[n - 8:n]                                       # neighbours among the last part's last rows
+    W[n - 1] = W[0]                                               # and a tie: the last row and the first one
+    W[n + 8] = W[0]
+    graph = torch.full((n_loc, K), -1, dtype=torch.int32, device="cuda")
+    sims = torch.full((n_loc, K), -np.inf, dtype=torch.float64, device="cuda")
+    ks.knn_graph_update(W[n:].cuda(), W[:n].cuda(), n, 0, graph, sims)
+    torch.cuda.synchronize()
+    S = (W[n:].double() @ W[:n].double().T).numpy()
+    expect = np.argsort(-S, axis=1, kind="stable")[:, :K]
+    got = graph.cpu().numpy()
+    assert (got[8, :2] == [0, n - 1]).all()
+    # (sums in another order: neighbours closer than the rounding of fp64 sums may change places)
+    for i in range(n_loc):
+        assert (got[i] == expect[i]).all() or np.allclose(S[i, got[i]], S[i, expect[i]], rtol=0, atol=1e-14)
 
 
 @pytest.mark.parametrize("D", [64, 96, 192, 256, 320, 416, 448, 480])
@@ -548,6 +593,7 @@ def test_graph_around_the_smallest_symmetric_pass(ks, orc, C, D, K, bf16):
     """The last sizes before and the first of the pass that computes every similarity once (C * D = 11 million beyond D = 128)."""
     import torch
     print(f"[depths] symmetric from C={C} D={D} K={K} bf16={bf16}", flush=True)
+    assert ks.knn_graph_recall_plan(C, 0, D, K, 0 if bf16 else 1)["kind"] == (2 if C * D >= 11_000_000 else 1)
     W = torch.nn.functional.normalize(torch.randn((C, D), generator=torch.Generator().manual_seed(C))).numpy()
     if bf16:
         W = synth.bf16_round(W)

@@ -464,7 +464,7 @@ def _sampled_rows(C, n_rows):
                                              (6400, 128, 32, True, "integers"), (9000, 256, 64, True, "unit"),
                                              (12_345, 128, 40, False, "clustered"), (7000, 512, 64, True, "integers")])
 def test_graph_recall_with_fixed_thresholds(ks, orc, C, D, K, bf16, kind):
-    """Thresholds from a sample, all rows past all blocks (C * D below 15 million): block counts that are odd, even and
+    """Thresholds from a sample, all rows past all blocks (C * D below 11 million): block counts that are odd, even and
     ragged, all three ranks of the sample, clustered rows, and rows with so many equal similarities that their segments
     overflow and the rows go to the exhaustive pass."""
     _check_graph(ks, orc, _rows_of_kind(kind, C, D, bf16), K, bf16, rows=_sampled_rows(C, 400 if C <= 10_000 else 160),
@@ -472,7 +472,7 @@ def test_graph_recall_with_fixed_thresholds(ks, orc, C, D, K, bf16, kind):
 
 
 def _takes_the_symmetric_sweep(ks, C, D, K, bf16):
-    """For C * D from 15 million on: its segments are the same for every K, those of the pass of all rows by all blocks grow
+    """For C * D from 11 million on (D = 128: 15 million): its segments are the same for every K, those of the pass of all rows by all blocks grow
     with the rank of the sample."""
     of_k = [ks.knn_graph_build_workspace(C, D, k, 0 if bf16 else 1) for k in (K, 8, 20, 64)]
     return K <= 64 and min(of_k) == max(of_k) > 24_000 * C
@@ -484,7 +484,7 @@ def _takes_the_symmetric_sweep(ks, C, D, K, bf16):
                                              (58_700, 256, 64, False, "unit"), (117_300, 128, 32, True, "clustered"),
                                              (118_000, 128, 64, True, "copies")])
 def test_graph_every_similarity_computed_once(ks, orc, C, D, K, bf16, kind):
-    """The recall pass that uses the symmetry of the similarities (D = 128, 256, 512, K <= 64, C * D from 15 million on), with
+    """The recall pass that uses the symmetry of the similarities (D = 128, 256, 512, K <= 64, C * D from 15 million on here), with
     shares cut into parts and logs of half a super-block (D = 512) and without: last super-blocks of one, two and three
     blocks, all three ranks of the sample, fp32 rows, clustered rows, many equal similarities, and so many equal rows that
     segments and logs overflow and the rows go to the exhaustive pass."""
