@@ -854,35 +854,63 @@ gr_recall_fix_kernel(GrPair pr, int D, int nb, int part_rows, GrSegs seg, MERGE 
     const int down = (threadIdx.x & 32) ? -1 : 0;
     const uint32_t my_base = (uint32_t)(ks_soe_col() * cap + 2 * part * seg.q + (down ? last + 1 : 0));
     int my_cnt = 0;
-    auto epi = [&](auto block, int c0, int rows_here, const f32x16_t &acc) __attribute__((always_inline)) {
-        // (a lane finds half of a block's rows at most; one that may run out of slots here stores nothing any more, and its
-        // count, which no segment holds, marks the row as overflowed)
-        if (my_cnt > last + 1 - 16) my_cnt = 1 << 20;
-        uint32_t hm = gr_hit_mask(my_cnt >= 1 << 20 ? INFINITY : thf, acc);
-        int first = c0 + 32 * decltype(block)::value + 4 * ((threadIdx.x >> 5) & 1);
-        asm volatile("" : "+v"(first));
-        if (rows_here < CFG::CH || ((int64_t)c0 < self0 + CFG::RES && (int64_t)c0 + CFG::CH > self0)) {
-            // rows beyond the part's last, and the row itself: no hits
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = first + 8 * (r >> 2) + (r & 3);
-                if (j >= c0 + rows_here || (int64_t)j == (int64_t)row0 + ks_soe_col() + pr.self) hm &= ~(0x8000u >> r);
-            }
-        }
-        while (__ballot(hm != 0u) != 0ull) { // as often as the lane with the most hits has some
-            const int r = 15 - (__ffs(hm) - 1);
-            const float v = gr_sym_pick16(acc, r);
-            const int j = first + r + (r & 12);
-            if (hm != 0u)
-                wg_cand[my_base + (uint32_t)(my_cnt ^ down)] = ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j);
-            my_cnt += hm != 0u ? 1 : 0;
-            hm &= hm - 1u;
-        }
+    // A lane finds half of the rows at most; one that may run out of slots here stores nothing any more, and its count, which
+    // no segment holds, marks the row as overflowed.
+    auto threshold_with_room = [&](int rows) __attribute__((always_inline)) {
+        if (my_cnt > last + 1 - rows / 2) my_cnt = 1 << 20;
+        return my_cnt >= 1 << 20 ? INFINITY : thf;
     };
+    auto special = [&](int c0, int rows_here) __attribute__((always_inline)) { // a chunk with rows beyond the part's last, or own rows
+        return rows_here < CFG::CH || ((int64_t)c0 < self0 + CFG::RES && (int64_t)c0 + CFG::CH > self0);
+    };
+    auto no_hits = [&](int first, int end, uint32_t hm) __attribute__((always_inline)) { // without rows from `end` on and the row itself
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int j = first + 8 * (r >> 2) + (r & 3);
+            if (j >= end || (int64_t)j == (int64_t)row0 + ks_soe_col() + pr.self) hm &= ~(0x8000u >> r);
+        }
+        return hm;
+    };
+    auto key = [&](float v, int j) __attribute__((always_inline)) { return ((uint64_t)gr_orderable(v) << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)j); };
     if constexpr (TURNS) {
+        auto epi = [&](auto block, int c0, int rows_here, const f32x16_t &acc) __attribute__((always_inline)) {
+            uint32_t hm = gr_hit_mask(threshold_with_room(32), acc);
+            int first = c0 + 32 * decltype(block)::value + 4 * ((threadIdx.x >> 5) & 1);
+            asm volatile("" : "+v"(first));
+            if (special(c0, rows_here)) hm = no_hits(first, c0 + rows_here, hm);
+            while (__ballot(hm != 0u) != 0ull) { // as often as the lane with the most hits has some
+                const int r = 15 - (__ffs(hm) - 1);
+                const float v = gr_sym_pick16(acc, r);
+                const int j = first + r + (r & 12);
+                if (hm != 0u) wg_cand[my_base + (uint32_t)(my_cnt ^ down)] = key(v, j);
+                my_cnt += hm != 0u ? 1 : 0;
+                hm &= hm - 1u;
+            }
+        };
         ks_soe_pp_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, s0, s1, (int)pr.Cs, lds, epi);
     } else {
-        auto chunk = ks_soe_blocks<CFG>(epi);
+        // (Here a whole chunk's values are at hand, and what is the same for all of them is worked out once; with the loop above,
+        // block by block: 150,000 x 64, K = 32: 5.18 ms -> 5.57.)
+        auto chunk = [&](int c0, int rows_here, f32x16_t (&acc)[CFG::FM]) __attribute__((always_inline)) {
+            const float t = threshold_with_room(CFG::CH);
+            const bool check = special(c0, rows_here);
+            auto one = [&](auto block) __attribute__((always_inline)) {
+                constexpr int f = decltype(block)::value;
+                uint32_t hm = gr_hit_mask(t, acc[f]);
+                const int first = c0 + 32 * f + 4 * ((threadIdx.x >> 5) & 1);
+                if (check) hm = no_hits(first, c0 + rows_here, hm);
+                while (__ballot(hm != 0u) != 0ull) {
+                    if (hm != 0u) {
+                        const int r = 15 - __builtin_ctz(hm);
+                        hm &= hm - 1u;
+                        const float v = gr_sym_pick16(acc[f], r);
+                        wg_cand[my_base + (uint32_t)(my_cnt ^ down)] = key(v, first + r + (r & 12));
+                        ++my_cnt;
+                    }
+                }
+            };
+            ks_each<CFG::FM>(one);
+        };
         ks_soe_sweep<CFG>(pr.R, D, row0, Cr, pr.S, D, nullptr, s0, s1, (int)pr.Cs, lds, chunk);
     }
     const int i = row0 + ks_soe_col();
@@ -1869,7 +1897,11 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bo
         // well (2,000 x 64, one chunk a part: 41.5 us, in turns 42.4; 2,345 x 128: 58.2, 59.8; 5,500 x 256, six: 76.5, 77.1; 8,000 x
         // 320, eleven: 129.5, 119.2; 10,000 x 128: 124.0, 119.2).
         f.seg.parts = f.room_parts;
-        f.turns = f.part_rows >= 672;
+        // At D = 32 and 64 a compute unit has room for two workgroups of the plain sweep (120 registers, 72 KiB of LDS; in turns 214), which
+        // cover each other's epilogues better than two halves do: there in turns only where no two workgroups meet.  Plain, in turns:
+        // x 64, K = 32: 20,000 (237 workgroups) 253 us, 238; 26,000 280, 339; 50,000 780, 953; 150,000 5,170, 6,914; x 32, K = 8: 20,000 201,
+        // 189; 50,000 649, 868; 150,000 4,264, 5,930; a hop of 50,000 x 20,000 x 64, K = 16: 444, 533.
+        f.turns = f.part_rows >= 672 && (D > 64 || nb * f.room_parts <= GR_CUS);
         const int rows = (int)(ks_ceil_div(ks_ceil_div(Cs, ch), f.room_parts) * ch), parts = (int)ks_ceil_div(Cs, rows);
         const int64_t half = Cs < 32 ? 16 : ((rows < Cs ? rows : Cs) + 1) / 2; // (a lane looks for room for a block's 16 hits)
         const int q = half < q_most ? (int)half : q_most;
