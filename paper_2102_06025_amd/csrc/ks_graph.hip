@@ -1466,8 +1466,11 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     const uint64_t key = lane < few ? s_key[wave][lane] : 0ull;
                     const uint32_t hi = (uint32_t)(key >> 32);
-                    thr = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(hi >= v)); }));
-                    const uint64_t m = __ballot(hi >= thr); // (above the bound: what was left out is below this)
+                    const uint32_t cut = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(hi >= v)); }));
+                    // What was left out is below this.  (With K keys above the bound the search ends at the first prefix that all of them
+                    // reach, which may lie below the bound and so below keys that are not here.)
+                    thr = cut > bound ? cut : bound;
+                    const uint64_t m = __ballot(hi >= thr);
                     asm volatile("" ::: "memory");
                     if (hi >= thr) s_key[wave][__popcll(m & ((1ull << lane) - 1ull))] = key;
                     kept = __popcll(m);

@@ -587,6 +587,26 @@ def test_ranking_of_candidates_that_lie_close(ks, orc, C, K, D, bf16, noise):
     assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
 
 
+@pytest.mark.parametrize("C,K,D,bf16", [(3000, 1, 64, True), (3006, 8, 128, False), (4012, 16, 64, True), (3003, 32, 128, True), (3003, 32, 64, False)])
+@pytest.mark.parametrize("noise", [0.0, 0.05])
+def test_ranking_of_exactly_k_close_candidates(ks, orc, C, K, D, bf16, noise):
+    """Clusters of K + 1 rows: exactly K candidates above the lanes' bound, all others far below.  (The search among the K ends far below
+    the bound then; what the certificate tests against must not.)"""
+    import torch
+    print(f"[depths] K close candidates C={C} K={K} D={D} bf16={bf16} noise={noise}", flush=True)
+    rng = np.random.default_rng(C + K)
+    n = C // (K + 1)
+    W = rng.standard_normal((n, D))[np.arange(C) % n] + noise * rng.standard_normal((C, D))
+    W = (W / np.linalg.norm(W, axis=1, keepdims=True)).astype(np.float32)
+    if bf16:
+        W = synth.bf16_round(W)
+    g, s = ks.knn_graph_build(dev(W, bf16), K, want_sims=True)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([rng.integers(0, C, 200), [0, C - 1]])).astype(np.int32)
+    eg, es = orc.graph_bruteforce(W, K, rows)
+    assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
+
+
 @pytest.mark.parametrize("C,D,K,bf16", [(21_484, 512, 32, True), (21_485, 512, 16, True), (21_600, 512, 64, False), (42_968, 256, 24, True), (42_969, 256, 8, True),
                                         (43_008, 256, 33, True)])
 def test_graph_around_the_smallest_symmetric_pass(ks, orc, C, D, K, bf16):
