@@ -1325,6 +1325,11 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // compare a round, and then searched among the at most 64 keys above the bound (before, 4 or 8 compares a round).  Builds, us:
 // 2,000 x 64, K = 16: 41.2 -> 33.1; 10,000 x 128, K = 8, fp32: 119.0 -> 113.8; 8,000 x 320, K = 24: 119 -> 114; two hops of 15,000 x 15,000
 // x 256, K = 32: 500 -> 491.
+// Not for fp32 rows with K > 29 and D > 128: the K-th of 64 largest values is nearly their median, similarities of longer rows lie closer
+// together while the error bound is that of rounding the rows, and more than 64 keys are above the bound so often that the first
+// search is wasted.  K = 32, plain, by lanes: 2,600 x 320 83.5 us, 85.5; 4,500 x 320 120, 125; 4,900 x 256 106, 109; 20,000 x 256 423, 431;
+// but 5,800 x 512 187, 182; 4,200 x 64 70.2, 63.6; K = 29: 900 x 320 58.2, 52.0; a hop of 120 x 2,909 x 192
+// 67.2, 61.9.
 // (Not for K > 32, where rows are few wavefronts and the chain of LDS accesses counts: 2,600 x 512, K = 64, fp32: 146 -> 153.  Five
 // wavefronts to a SIMD for K <= 32, at four spilled registers in one form: 5,000 x 320, K = 32, fp32: 128 with four, 122.5.)
 // SHORT: lists of at most 256 candidates have a copy of the search of their own, taken for K <= 24 (beyond, too few rows have
@@ -1360,6 +1365,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
     const double eps = (double)gamma * (double)norms[i] * (double)*maxnorm; // error bound of the 16-bit similarities
     uint32_t thr = tb; // nothing above this value (as a key) was dropped
     int kept = n;
+    const bool by_lanes = KP == 1 && (sizeof(IN) == 2 || K <= 29 || D <= 128); // (see above)
     // The keys to rank to LDS.  E: registers for the keys.  The m-th largest value by a bitwise search ("how many keys are
     // >= this prefix": a compare, a ballot and a population count per register and round) below the bits that threshold
     // and largest key share; it ends as soon as exactly m keys are left (a bound below the m-th and above the next).
@@ -1368,7 +1374,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
         uint64_t val[E];
         // (an index counts through the segments laid end to end: what has to be added to it to find its place grows at the first index
         // of every segment)
-        if (KP == 1 && E <= 8 && nseg > 4) {
+        if (by_lanes && E <= 8 && nseg > 4) {
             int *const grow = s_grow[wave];
 #pragma unroll
             for (int r = 0; r < E; ++r) grow[r * 64 + lane] = 0;
@@ -1456,7 +1462,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                 return f == f ? gr_orderable(f) : 0u;
             };
             bool exact;
-            if (KP == 1) {
+            if (by_lanes) {
                 // The K-th largest of the lanes' largest values is a bound that K keys reach, found with one compare a round instead of E;
                 // what lies above it (less 2.5 error bounds) is a key per lane, and the search goes on among those.
                 const uint32_t bound = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(mine >= v)); }));

@@ -566,7 +566,8 @@ def test_thresholds_of_many_blocks(ks, orc, D):
 
 
 @pytest.mark.parametrize("C,K,D,bf16", [(3000, 1, 64, False), (3000, 8, 64, True), (2600, 16, 128, False), (7000, 32, 128, True), (9000, 24, 64, False),
-                                        (3000, 40, 64, False), (118_000, 16, 128, True)])
+                                        (3000, 40, 64, False), (2600, 29, 320, False), (2600, 32, 320, False),
+                                        (118_000, 16, 128, True)])
 @pytest.mark.parametrize("noise", [0.0, 0.01, 0.3])
 def test_ranking_of_candidates_that_lie_close(ks, orc, C, K, D, bf16, noise):
     """Clusters of 100 rows: more than 64 candidates within the error bound of the K-th (exact copies, and rows closer than the bound of
@@ -587,7 +588,8 @@ def test_ranking_of_candidates_that_lie_close(ks, orc, C, K, D, bf16, noise):
     assert (g.cpu().numpy()[rows] == eg).all() and (s.cpu().numpy()[rows] == es.astype(np.float32)).all()
 
 
-@pytest.mark.parametrize("C,K,D,bf16", [(3000, 1, 64, True), (3006, 8, 128, False), (4012, 16, 64, True), (3003, 32, 128, True), (3003, 32, 64, False)])
+@pytest.mark.parametrize("C,K,D,bf16", [(3000, 1, 64, True), (3006, 8, 128, False), (4012, 16, 64, True), (3003, 32, 128, True), (3003, 32, 64, False),
+                                        (2000, 30, 160, False), (2013, 32, 320, False)])
 @pytest.mark.parametrize("noise", [0.0, 0.05])
 def test_ranking_of_exactly_k_close_candidates(ks, orc, C, K, D, bf16, noise):
     """Clusters of K + 1 rows: exactly K candidates above the lanes' bound, all others far below.  (The search among the K ends far below
