@@ -1325,13 +1325,13 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // compare a round, and then searched among the at most 64 keys above the bound (before, 4 or 8 compares a round).  Builds, us:
 // 2,000 x 64, K = 16: 41.2 -> 33.1; 10,000 x 128, K = 8, fp32: 119.0 -> 113.8; 8,000 x 320, K = 24: 119 -> 114; two hops of 15,000 x 15,000
 // x 256, K = 32: 500 -> 491.
-// Not for fp32 rows with K > 29 and D > 128: the K-th of 64 largest values is nearly their median, similarities of longer rows lie closer
-// together while the error bound is that of rounding the rows, and more than 64 keys are above the bound so often that the first
-// search is wasted.  K = 32, plain, by lanes: 2,600 x 320 83.5 us, 85.5; 4,500 x 320 120, 125; 4,900 x 256 106, 109; 20,000 x 256 423, 431;
-// but 5,800 x 512 187, 182; 4,200 x 64 70.2, 63.6; K = 29: 900 x 320 58.2, 52.0; a hop of 120 x 2,909 x 192
-// 67.2, 61.9.
 // (Not for K > 32, where rows are few wavefronts and the chain of LDS accesses counts: 2,600 x 512, K = 64, fp32: 146 -> 153.  Five
-// wavefronts to a SIMD for K <= 32, at four spilled registers in one form: 5,000 x 320, K = 32, fp32: 128 with four, 122.5.)
+// wavefronts to a SIMD for K <= 32: 5,000 x 320, K = 32, fp32: 128 with four, 122.5.)
+// LANES: with that bound and the running sum.  Not for fp32 rows with K > 29 and D > 128: the K-th of 64 largest values is nearly their
+// median, similarities of longer rows lie closer together while the error bound is that of rounding the rows, and more than 64
+// keys are above the bound so often that the first search is wasted.  K = 32, plain, by lanes: 2,600 x 320 83.5 us, 85.5; 4,500 x
+// 320 120, 125; 4,900 x 256 106, 109; 20,000 x 256 423, 431; but 5,800 x 512 187, 182; 4,200 x 64 70.2, 63.6; K = 29: 900 x 320 58.2, 52.0;
+// a hop of 120 x 2,909 x 192 67.2, 61.9.
 // SHORT: lists of at most 256 candidates have a copy of the search of their own, taken for K <= 24 (beyond, too few rows have
 // so few).  For K <= 32 the kernel of K > 24 does without the copy, which alone costs it 1 %; so does that of K <= 24 where few rows
 // gain by it, those of fp32 builds and of hops (one row in 32 sampled), and the rows are one round of the chip (2,000 x 256, K = 16,
@@ -1341,7 +1341,7 @@ __device__ __forceinline__ void gr_count_before(double s2, int32_t id2, int n, c
 // 2,000 x 512, K = 64: 87.3 -> 88.6; 4,000 x 320, K = 33: 92.2 -> 93.0; 5,000 x 512, K = 64: 162.9 -> 149.4; 20,000 x 64, K = 64: 319 -> 301.
 // ------------------------------------------------------------------------------------------------
 #define GR_RANK_AT_ONCE 4096 /* 256 compute units x 4 workgroups x 4 rows */
-template <typename IN, int KP, bool HOP, bool SHORT>
+template <typename IN, int KP, bool HOP, bool SHORT, bool LANES>
 __global__ void __launch_bounds__(GR_NT, KP == 1 ? 5 : 4)
 gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, int64_t Cv, int D, int K, GrSegs seg,
                const uint64_t *__restrict__ cand, const int32_t *__restrict__ cnt_res, const int32_t *__restrict__ cnt_str,
@@ -1365,7 +1365,6 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
     const double eps = (double)gamma * (double)norms[i] * (double)*maxnorm; // error bound of the 16-bit similarities
     uint32_t thr = tb; // nothing above this value (as a key) was dropped
     int kept = n;
-    const bool by_lanes = KP == 1 && (sizeof(IN) == 2 || K <= 29 || D <= 128); // (see above)
     // The keys to rank to LDS.  E: registers for the keys.  The m-th largest value by a bitwise search ("how many keys are
     // >= this prefix": a compare, a ballot and a population count per register and round) below the bits that threshold
     // and largest key share; it ends as soon as exactly m keys are left (a bound below the m-th and above the next).
@@ -1374,7 +1373,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
         uint64_t val[E];
         // (an index counts through the segments laid end to end: what has to be added to it to find its place grows at the first index
         // of every segment)
-        if (by_lanes && E <= 8 && nseg > 4) {
+        if (LANES && E <= 8 && nseg > 4) {
             int *const grow = s_grow[wave];
 #pragma unroll
             for (int r = 0; r < E; ++r) grow[r * 64 + lane] = 0;
@@ -1462,7 +1461,7 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                 return f == f ? gr_orderable(f) : 0u;
             };
             bool exact;
-            if (by_lanes) {
+            if (LANES) {
                 // The K-th largest of the lanes' largest values is a bound that K keys reach, found with one compare a round instead of E;
                 // what lies above it (less 2.5 error bounds) is a key per lane, and the search goes on among those.
                 const uint32_t bound = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(mine >= v)); }));
@@ -1474,8 +1473,9 @@ gr_rank_kernel(const IN *__restrict__ Wl, int64_t C, const IN *__restrict__ Wv, 
                     const uint32_t hi = (uint32_t)(key >> 32);
                     const uint32_t cut = below(search_by(K, exact, [&](uint32_t v) __attribute__((always_inline)) { return __popcll(__ballot(hi >= v)); }));
                     // What was left out is below this.  (With K keys above the bound the search ends at the first prefix that all of them
-                    // reach, which may lie below the bound and so below keys that are not here.)
-                    thr = cut > bound ? cut : bound;
+                    // reach, which may lie below the bound and so below keys that are not here.  As a scalar: kept in a vector register, small fp32
+                    // builds take 2 to 4 % longer, 2,000 x 320, K = 24: 61.3 us, 63.1.)
+                    thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)(cut > bound ? cut : bound));
                     const uint64_t m = __ballot(hi >= thr);
                     asm volatile("" ::: "memory");
                     if (hi >= thr) s_key[wave][__popcll(m & ((1ull << lane) - 1ull))] = key;
@@ -2176,14 +2176,15 @@ template <typename IN>
 static void gr_launch_rank(const IN *W, int64_t C, int D, int K, const GrFixPlan &f, const GrWs &w, float gamma,
                            int32_t *graph, float *sims, hipStream_t st) {
     const dim3 grid((unsigned)ks_ceil_div(C, GR_NT / 64));
-#define GR_RANK_LAUNCH(KP, SHORT)                                                                                              \
-    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, false, SHORT>), grid, dim3(GR_NT), 0, st, W, C, W, C, D, K, f.seg, w.cand,               \
+#define GR_RANK_LAUNCH(KP, SHORT, LANES)                                                                                       \
+    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, false, SHORT, LANES>), grid, dim3(GR_NT), 0, st, W, C, W, C, D, K, f.seg, w.cand,        \
                        w.cnt_res, w.cnt_str, w.tbits, w.norms, w.maxnorm, gamma, (int64_t)0, graph, (void *)sims, w.second_count, \
                        w.second_rows)
-    if (K <= 24 && (sizeof(IN) == 2 || C > GR_RANK_AT_ONCE)) GR_RANK_LAUNCH(1, true);
-    else if (K <= 32) GR_RANK_LAUNCH(1, false);
-    else if (sizeof(IN) == 2 && C > GR_RANK_AT_ONCE) GR_RANK_LAUNCH(2, true);
-    else GR_RANK_LAUNCH(2, false);
+    if (K <= 24 && (sizeof(IN) == 2 || C > GR_RANK_AT_ONCE)) GR_RANK_LAUNCH(1, true, true);
+    else if (K <= 29 || (K <= 32 && D <= 128)) GR_RANK_LAUNCH(1, false, true);
+    else if (K <= 32) GR_RANK_LAUNCH(1, false, sizeof(IN) == 2);
+    else if (sizeof(IN) == 2 && C > GR_RANK_AT_ONCE) GR_RANK_LAUNCH(2, true, false);
+    else GR_RANK_LAUNCH(2, false, false);
 #undef GR_RANK_LAUNCH
     // (as many workgroups as run at once, by their LDS: nearly always there is nothing to do, and four rounds of that take 1 to 2 us more)
     hipLaunchKernelGGL(gr_second_kernel<IN>, dim3(GR_CUS), dim3(GR_NT), 0, st, W, C, D, K, f.seg, w.cand, w.cnt_res, w.cnt_str, w.tbits,
@@ -2507,14 +2508,15 @@ template <typename IN>
 static void gr_up_exact(const IN *Wl, int64_t C_loc, const IN *Wv, int64_t C_vis, int D, int K, const GrParams &p, const GrFixPlan *f,
                         const GrUpWs &w, float gamma, int64_t lo, int64_t vo, int32_t *graph, double *sims, hipStream_t st) {
     const dim3 grid((unsigned)ks_ceil_div(C_loc, GR_NT / 64));
-#define GR_HOP_RANK_LAUNCH(KP, SHORT)                                                                                          \
-    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, true, SHORT>), grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, f->seg,             \
+#define GR_HOP_RANK_LAUNCH(KP, SHORT, LANES)                                                                                   \
+    hipLaunchKernelGGL((gr_rank_kernel<IN, KP, true, SHORT, LANES>), grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, f->seg,      \
                        w.cand, w.cnt_res, (const int32_t *)nullptr, w.tbits, w.norms_l, w.maxnorm_v, gamma, vo, graph, (void *)sims, \
                        w.fb_count, w.fb_rows)
-    if (f && K <= 24 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(1, true);
-    else if (f && K <= 32) GR_HOP_RANK_LAUNCH(1, false);
-    else if (f && sizeof(IN) == 2 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(2, true);
-    else if (f) GR_HOP_RANK_LAUNCH(2, false);
+    if (f && K <= 24 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(1, true, true);
+    else if (f && (K <= 29 || (K <= 32 && D <= 128))) GR_HOP_RANK_LAUNCH(1, false, true);
+    else if (f && K <= 32) GR_HOP_RANK_LAUNCH(1, false, sizeof(IN) == 2);
+    else if (f && sizeof(IN) == 2 && C_loc > GR_RANK_AT_ONCE) GR_HOP_RANK_LAUNCH(2, true, false);
+    else if (f) GR_HOP_RANK_LAUNCH(2, false, false);
     else
         hipLaunchKernelGGL(gr_merge_kernel<IN>, grid, dim3(GR_NT), 0, st, Wl, C_loc, Wv, C_vis, D, K, p.cap, w.cand, w.cnt, w.thr,
                            w.norms_l, w.maxnorm_v, gamma, lo, vo, graph, sims, w.fb_count, w.fb_rows);
