@@ -566,7 +566,7 @@ gr_recall_soe_kernel(GrPair pr, int D, int kprime, uint64_t *__restrict__ cand, 
 // Symmetric sweep: a lane has its q slots.  Passes with parts (no stream segment): the two lanes of a part share 2 q slots and
 // fill them from both ends, so that however a row's hits fall on lanes and parts, all of them fit: a lane sees the streamed
 // rows whose id has bit 2 clear, or set, and neighbours with ids of one residue modulo 8 are all one lane's.  2 q = 64 (r + 10),
-// and what a lane can find in one chunk, before which it looks whether it has room.
+// and what a lane can find in one chunk of 96 rows, before which it looks whether it has room (in turns: in a block of 32).
 // (With 512 slots for each lane, four rows in 100,000 of K > 32 overflowed even with hits that fall evenly, and a row in the
 // exhaustive search costs 4 to 30 ms: 60,000 x 128, K = 64: 5.6 ms instead of 2.0; a hop of 65,000 rows of 512 against
 // a million 194 ms instead of 57.)
@@ -613,10 +613,25 @@ GR_PP(7, 1, 7, 4, 4)
 GR_PP(8, 2, 4, 4, 3)
 #undef GR_PP
 template <int KT, bool RAGGED> using GrPp = typename GrPpOf<KT, RAGGED>::T;
-// The thresholds' sorted lists take 24 registers more, hence chunks of 32 or 64 rows; small problems (several workgroups per block of
-// rows) have a chunk or two per workgroup, with nothing to take turns in, and stay on the plain sweep (10,000 x 128: 11.6 us, in
-// turns 17).
-template <int KT, bool RAGGED> using GrThrPp = KsPp<KT, KT >= 7 ? 1 : 2, KT == 8 ? 4 : KT, KT == 1 ? 8 : KT == 2 ? 5 : KT == 8 ? 8 : KT == 7 ? 4 : 3, KT >= 7 ? 4 : 2, RAGGED>;
+// The thresholds' sorted lists take 24 registers more, hence chunks of 32 or 64 rows.  gr_threshold_kernel, plain, in turns (on one card,
+// us): 150,000 x 64 409, 416; x 96 435, 438; x 128 522, 521; x 192 570, 557; x 256 676, 608; 100,000 x 320 347, 333; x 384 367, 353; x 448
+// 417, 403; x 512 453, 428; 390,625 x 512 4,995, 4,822.  Small problems (several workgroups per block of rows) have a chunk or two per
+// workgroup, with nothing to take turns in, and stay on the plain sweep (10,000 x 128: 11.6 us, in turns 17).
+template <int KT, bool RAGGED> struct GrThrPpOf;
+#define GR_THR_PP(KT, ...) \
+    template <bool RAGGED> struct GrThrPpOf<KT, RAGGED> { typedef KsPp<KT, __VA_ARGS__, RAGGED> T; };
+GR_THR_PP(1, 2, 1, 8, 2)
+GR_THR_PP(2, 2, 2, 5, 2)
+GR_THR_PP(3, 2, 3, 3, 2)
+GR_THR_PP(4, 2, 4, 3, 2)
+GR_THR_PP(5, 2, 5, 3, 2)
+GR_THR_PP(6, 2, 6, 3, 2)
+GR_THR_PP(7, 1, 7, 4, 4)
+GR_THR_PP(8, 1, 4, 8, 4)
+#undef GR_THR_PP
+template <int KT, bool RAGGED> using GrThrPp = typename GrThrPpOf<KT, RAGGED>::T;
+// Stage shape of the plain sweep: twelve k-tiles in flight, two per stage where KT is even (a barrier per stage); a single k-tile per
+// chunk (KT = 1): six, which leaves LDS for a second workgroup.
 template <int KT, bool RAGGED> using GrSoe = KsSoe<KT, 96, (KT % 2 == 0 || KT == 1) ? 6 : 12, KT % 2 == 0 ? 2 : 1, RAGGED>;
 static int gr_chunk(int D) { // streamed rows per chunk of the recall passes
     switch ((D + 63) / 64) {
@@ -1041,6 +1056,7 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
     constexpr int Q = GR_SYM_Q, SB = GR_SYM_SB;
     const int parts = SPLIT ? split_parts : 1, log_rows = SPLIT ? split_log_rows : SB;
     static_assert(SB % CFG::CH == 0 && SB % CFG::RES == 0 && CFG::RES == 256, "super-blocks are whole chunks and whole blocks");
+    static_assert(SB / 2 % CFG::CH == 0, "a log of half a super-block is whole chunks");
     // one LDS array (see ks_gemm_soe.h): the stream stages, the streamed rows' thresholds of the chunks in flight, the
     // records that the wavefronts collect
     constexpr int THR_ELEMS = 2 * 8 * CFG::CH, STAGE_ELEMS = 4 * GR_SYM_STAGE;
@@ -1089,8 +1105,8 @@ gr_recall_sym_kernel(const uint16_t *__restrict__ W, int C, int D, const int32_t
         ++my_cnt;
     };
     // The thresholds of a chunk's rows travel to LDS beside its rows: requested by wavefront 0 when the chunk's loads begin.
-    // The loads run up to STAGES - 1 pipeline stages ahead of the MFMAs and a chunk of D = 128 is a single stage, so up to
-    // seven chunks lie between the request and the epilogue that reads it: eight slots.
+    // The loads run up to STAGES - 1 pipeline stages ahead of the MFMAs and the epilogue a chunk behind them: AHEAD chunks at most (six at
+    // D = 128, where a chunk is a single stage) from the request to the epilogue that reads it, and eight slots.
     static_assert(CFG::AHEAD <= 8, "slots for the chunks in flight");
     auto side = [&](int first, int c) __attribute__((always_inline)) {
 #pragma unroll
@@ -1795,18 +1811,24 @@ static bool gr_use_fixed(int64_t Cr, int64_t Cs, int D, int K) {
 }
 // The division of the symmetric sweep exists from 6,144 rows on; it is used from C * D = 11 million on, at D = 128 from 15 million.
 // Below, the passes over both halves of the pairs (gr_recall_fix_kernel) are faster: the matrix cores idle anyway, and what
-// costs is the epilogue's work per hit, of which the stream side's is the dearer one.  Whole builds, us, parts -> symmetric, D = 512:
-// 12,000, K = 8: 238, 259; 15,000, K = 32: 358, 387; 18,000: K = 16 447, 426, K = 64 573, 596; 22,000, K = 32: 653, 598; 28,000, K = 8: 913,
-// 762; 40,000, K = 64: 1,994, 1,686; D = 256: 22,000, K = 16: 392, 408; 34,000: K = 8 773, 702, K = 64 928, 957; 45,000, K = 16: 1,232, 1,085;
-// 57,000: 1,841, 1,530; D = 128: 68,000, K = 16: 1,977, 2,024; 100,000: K = 16 3,738, 3,564, K = 32 3,844, 3,814; 130,000, K = 32: 5,873,
-// 6,206; 160,000, K = 16: 8,671, 7,695.
+// costs is the epilogue's work per hit, of which the stream side's is the dearer one.  Whole builds of bf16 rows, us, parts -> symmetric:
+// D = 512: 12,000, K = 8: 238, 259; 15,000, K = 32: 358, 387; 18,000: K = 16 447, 426, K = 64 573, 596; 21,500: K = 8 573, 491, K = 32 593, 539, K =
+// 64 717, 686; 26,000: K = 8 814, 633, K = 64 992, 864.  D = 256: 22,000, K = 16: 392, 408; 34,000: K = 8 773, 702, K = 64 928, 957; 43,000: K = 8
+// 1,094, 908, K = 32 1,142, 1,034, K = 64 1,277, 1,226; 52,000: K = 16 1,586, 1,315, K = 64 1,787, 1,723.
+// At D = 128 neither is the faster one on one side of a size: the parts' time goes up in steps of 256 blocks (65,536 and 131,072 rows),
+// the symmetric pass has steps of its own, and where one row in 32 is sampled (K > 24, fp32) its records cost more.  72,000: K = 16 2,099,
+// 2,073, K = 64 2,355, 2,460; 86,000: K = 16 2,748, 2,777, K = 32 2,795, 3,009; 100,000: K = 16 3,804, 3,531, K = 32 3,884, 3,780; 105,000, K = 32:
+// 4,157, 4,390; 115,000: K = 16 5,216, 5,013, K = 32 5,308, 5,768; 117,500: K = 16 5,335, 5,049, K = 32 5,448, 5,765; 126,000: K = 16 5,740, 5,493,
+// K = 32 5,840, 6,260, K = 64 6,152, 6,784; 136,000: K = 16 7,376, 6,727, K = 32 7,545, 7,043; 150,000, K = 32: 7,851, 7,713.  So from 15 million on the
+// symmetric pass is right for K <= 24, and for larger K (and fp32) only from 16.8 million, 131,072 rows, on: between the two lines they
+// take 4 to 18 % longer than in parts, and less than before the sweep in turns all the same.
 static bool gr_has_sym(int64_t C, int D, int K) {
     return (D == 128 || D == 256 || D == 512) && gr_use_fixed(C, C, D, K) && C >= 6144;
 }
 static bool gr_use_sym(int64_t C, int D, int K) { return gr_has_sym(C, D, K) && C * D >= (D == 128 ? 15000000 : 11000000); }
 // Parts that the streamed chunks of each of nb blocks are cut into: the number with the least estimated time on the
 // chip's compute units (rounds of workgroups x (set-up + chunks of a part); set-up 6 us and a chunk of 96 rows 1.2 us,
-// 0.5 and 0.4 us more per k-tile: measured on the sweeps).  Bounded by memory: a part costs every row two segments.
+// 0.5 and 0.4 us more per k-tile: measured on the plain sweep).  Bounded by memory: a part costs every row two segments.
 static int gr_parts(int64_t C, int64_t nb, int64_t chunks, int D) {
     const double kt = (D + 63) / 64, setup = 6.0 + 0.5 * kt, per_chunk = 1.2 + 0.4 * kt;
     int64_t most = ((int64_t)1 << 19) / C; // 4.5 to 5.5 GiB of segments
@@ -1900,8 +1922,8 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bo
     f.room = 2 * f.room_parts * f.seg.q + f.seg.stream;
     if (!sym) {
         // The room is planned in chunks of 96 rows whatever the sweep's are: a workspace serves what it always did.  The parts are whole
-        // chunks of the sweep where those fit in it; otherwise (a few thousand searched rows at most) the last chunk of
-        // each is a ragged one.
+        // chunks of the sweep where those fit in it; otherwise (builds of up to 12,000 rows, hops of few rows to 35,000 visiting ones) the last
+        // chunk of each is a ragged one.
         // In turns from seven chunks of 96 rows on: with fewer there is little to take turns in, and larger chunks fit the parts less
         // well (2,000 x 64, one chunk a part: 41.5 us, in turns 42.4; 2,345 x 128: 58.2, 59.8; 5,500 x 256, six: 76.5, 77.1; 8,000 x
         // 320, eleven: 129.5, 119.2; 10,000 x 128: 124.0, 119.2).
@@ -1912,15 +1934,16 @@ static GrFixPlan gr_fix_plan(int64_t Cr, int64_t Cs, int D, int K, int dtype, bo
         // 189; 50,000 649, 868; 150,000 4,264, 5,930; a hop of 50,000 x 20,000 x 64, K = 16: 444, 533.
         f.turns = f.part_rows >= 672 && (D > 64 || nb * f.room_parts <= GR_CUS);
         const int rows = (int)(ks_ceil_div(ks_ceil_div(Cs, ch), f.room_parts) * ch), parts = (int)ks_ceil_div(Cs, rows);
-        const int64_t half = Cs < 32 ? 16 : ((rows < Cs ? rows : Cs) + 1) / 2; // (a lane looks for room for a block's 16 hits)
+        const int64_t half = ((rows < Cs ? rows : Cs) + 1) / 2; // (in turns some 300 at least: a lane looks for room for a block's 16 hits)
         const int q = half < q_most ? (int)half : q_most;
         if (f.turns && 2 * parts * q <= f.room) { f.part_rows = rows; f.seg.parts = parts; f.seg.q = q; }
     }
     f.log_rows = GR_SYM_SB;
     f.logs = 0;
     if (sym) {
-        // A wavefront finds about 96 * 32 * 384 / C stream-side hits per chunk.  Logs of half a super-block where four chunks
-        // still give it half a batch (C <= 49,152): the scatter kernel then has 77 workgroups or more instead of 39.
+        // A wavefront finds about 32 * 384 / C stream-side hits per streamed row.  Logs of half a super-block where its 384 rows (six
+        // chunks at D = 512, three at 128) still give it half a batch (C <= 49,152): the scatter kernel then has 77 workgroups or more
+        // instead of 39.
         if ((double)(GR_SYM_SB / 2) * 32.0 * 384.0 / (double)Cs >= 96.0) f.log_rows = GR_SYM_SB / 2;
         f.logs = (int)ks_ceil_div(Cr, f.log_rows);
     }
